@@ -353,7 +353,7 @@ def exact(case, seed):
     n = sum(s.numel for s in specs)
     if c["op"] == "transcode":
         return None
-    if n * (c["R"] + 2) > 12e9:          # the selections of all workers in plain torch take too long
+    if n * (c["R"] + 2) > 20e9:          # the selections of all workers in plain torch take too long
         return None
     t = _inputs(c, specs, seed)
     beta = float(torch.tensor(BETA, dtype=torch.float32))
