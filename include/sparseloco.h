@@ -27,8 +27,7 @@
  *     kernels are enqueued on it and the call returns without synchronising;
  *   - the caller owns every buffer it passes; the library owns only sl_plan.
  *   - results are deterministic: the same inputs give the same bytes;
- *   - no environment variable is read; the one tuning knob is a field of the plan
- *     (sl_plan_set_codes_wave_below).
+ *   - no environment variable is read.
  */
 #ifndef SPARSELOCO_H
 #define SPARSELOCO_H
@@ -90,10 +89,8 @@ typedef struct sl_plan sl_plan; /* opaque: chunk work list and per-tensor tables
  * elements), NOMEM, HIP. */
 int sl_plan_create(const sl_tensor *tensors, int n_tensors, int k, sl_plan **out);
 int sl_plan_destroy(sl_plan *plan);
-/* Tuning knob of the code kernel of sl_compress* (Section 4 set-up: the 2-bit codes): lists of
- * fewer than `n_chunks` chunks give a chunk to a wavefront instead of a lane at any k (a lane
- * per chunk leaves most of the chip idle on a short list).  Default 32768.  The bytes written are
- * the same either way; takes effect at the next call on the plan. */
+/* Accepted and without effect: it chose between two forms of the code kernel of sl_compress* by the
+ * length of the list; one form now serves every length.  n_chunks < 0 is still INVALID_ARG. */
 int sl_plan_set_codes_wave_below(sl_plan *plan, int64_t n_chunks);
 
 /* sl_plan_create for another value width (the ablation "Effect of quantization

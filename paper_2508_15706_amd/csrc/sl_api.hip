@@ -175,7 +175,6 @@ int sl_plan_create_bits(const sl_tensor *tensors, int n_tensors, int k, int valu
     p->ws_tstat = off;  off = align_up(off + (size_t)n_tensors * sizeof(SlTensorStat), 256);
     p->ws_bytes = off ? off : 256;
     p->n_groups = (int64_t)groups.size();
-    p->codes_wave_below = 32768;
     {
         // the coded format's sizes, its upper bound and the scratch its writers need
         SlCodedGeom &g = p->cg;
@@ -385,7 +384,6 @@ int sl_compress_coded(sl_plan *p, float *e, const float *delta, float beta, int 
 int sl_plan_set_codes_wave_below(sl_plan *p, int64_t n_chunks)
 {
     if (!p || n_chunks < 0) return SL_ERR_INVALID_ARG;
-    p->codes_wave_below = n_chunks;
     return SL_OK;
 }
 

@@ -83,8 +83,10 @@ SL_DEV int sl_uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
 #define SL_DPP_XOR2 0x4E
 #define SL_DPP_HALF_MIRROR 0x141
 #define SL_DPP_MIRROR 0x140
+// (every lane has a source lane, so there is no old value to keep: the move needs no copy of v first and
+// can become an operand of the instruction that uses it)
 template <int CTRL>
-SL_DEV int sl_dpp(int v) { return __builtin_amdgcn_update_dpp(v, v, CTRL, 0xF, 0xF, false); }
+SL_DEV int sl_dpp(int v) { return __builtin_amdgcn_mov_dpp(v, CTRL, 0xF, 0xF, true); }
 template <int CTRL>
 SL_DEV double sl_dpp(double v)
 {

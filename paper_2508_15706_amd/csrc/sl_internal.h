@@ -114,7 +114,6 @@ struct sl_plan {
     // workspace sections of the coded path: per-chunk bit vectors (cg.ua words each) and quotient
     // sums, per-group run lengths and offsets (words), per-tensor section offsets (words)
     size_t ws_uvec, ws_qsum, ws_gwords, ws_goff, ws_twords;
-    long long codes_wave_below; // list length below which the code kernel gives a chunk to a wave at any k
     // host copies
     SlTensorDev *h_tensors;
     // optional per-kernel timing (sl_profile_begin / sl_profile_end)

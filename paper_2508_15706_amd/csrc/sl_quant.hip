@@ -122,269 +122,55 @@ struct CodeArgs {
     // coded wire format next to the plain record (null: not wanted): the value fields of a chunk are
     // the same bytes in both, in the coded buffer they follow the chunk's remainder fields
     unsigned char *coded;
-    const SlTensorDev *tensors;
-    int cfix, rem_bytes;
-    int park;               // k_codes_b: the codes of the first pass are kept in LDS for the later ones
+    const SlCodedDesc *cdesc;
+    int rem_bytes;
+    int passes;             // passes of 512 entries over a chunk (1 up to k = 512)
 };
 
-// Where a chunk's value fields go in the coded buffer (null when none is written).
-SL_DEV unsigned char *coded_values(const CodeArgs &A, const SlChunkDesc &d)
+// Value of lane i ^ (1 << L), exactly (sl_partner's mirrors only do where the lanes of a quad hold the
+// same value): inside a row of 16 lanes as DPP moves, across rows as a shuffle.
+template <int L>
+SL_DEV int xor_lane(int v)
 {
-    if (!A.coded) return nullptr;
-    return A.coded + A.tensors[d.tensor].cfix_off + (long long)d.local_chunk * A.cfix + A.rem_bytes;
+    if constexpr (L == 0) return sl_dpp<SL_DPP_XOR1>(v);
+    else if constexpr (L == 1) return sl_dpp<SL_DPP_XOR2>(v);
+    else if constexpr (L == 2) return sl_dpp<SL_DPP_HALF_MIRROR>(sl_dpp<0x1B>(v));     // i ^ 3, then ^ 7
+    else if constexpr (L == 3) return sl_dpp<0x128>(v);     // a rotation by eight inside the row
+    else return __shfl_xor(v, 1 << L);
+}
+template <int L>
+SL_DEV double xor_lane(double v)
+{
+    return __hiloint2double(xor_lane<L>(__double2hiint(v)), xor_lane<L>(__double2loint(v)));
 }
 
-template <int LV>
-struct BinStacksT {      // one binary-counter stack of partial tree sums per bin, LV levels (k <= 2^(LV-1))
-    double a[LV], b[LV], c[LV], d[LV];
-};
-using BinStacks = BinStacksT<13>;
-
-// Folds entry m (values v0..v3 for the four bins) into the stacks: while bit L
-// of m is set the partial sum of level L is the left sibling and is added; the
-// first clear bit is where the new partial sum is parked.
-template <int L, int LV>
-SL_DEV void stack_push(BinStacksT<LV> &s, int m, double v0, double v1, double v2, double v3)
+// Levels L .. LOG_LPC-1 of the adjacent-pair trees of N bins over groups of 2^LOG_LPC lanes.  While a
+// lane still holds several bins, a level halves them: the lanes of a pair exchange the bins they give
+// up, so that N bins cost N/2 + N/4 + ... exchanges instead of N per level.  (a + b = b + a bit for
+// bit, so it does not matter which lane of a pair adds.)  Afterwards r[0 .. max(1, N >> LOG_LPC)) of a
+// lane are the bins from bin_of_lane on.
+template <int N, int L, int LOG_LPC, int NB>
+SL_DEV void reduce_bins(double (&r)[NB], int lane)
 {
-    if constexpr (L < LV) {
-        if ((m >> L) & 1) {
-            stack_push<L + 1>(s, m, s.a[L] + v0, s.b[L] + v1, s.c[L] + v2, s.d[L] + v3);
-        } else {
-            s.a[L] = v0, s.b[L] = v1, s.c[L] = v2, s.d[L] = v3;
-        }
-    }
-}
-
-constexpr int CODE_WAVES = 2;        // waves per workgroup
-#ifndef SL_CODES_WAVE_FROM
-#define SL_CODES_WAVE_FROM 129        // k from which a wave, not a lane, owns a chunk in kernel C
-#endif
-// (... and at any k on a list of fewer chunks than the plan's codes_wave_below, 32768 unless set: with a lane per
-// chunk such a list leaves most of the chip without a wave)
-
-// One LANE per chunk, 64 consecutive chunks per wave.  The selected values of
-// the 64 chunks are read with coalesced 16-byte loads, 64 entries per chunk at a
-// time, and transposed through LDS so that every lane walks its own chunk's
-// values in ascending index.  A lane then needs no cross-lane traffic at all:
-// the code is two fp64 compares, and the per-bin fixed-tree sums are kept in a
-// binary-counter stack (entry m is folded into the partial sums of the aligned
-// subtrees that end at m, which reproduces the adjacent-pair tree exactly).
-// The entry index is uniform over the wave, so the stack walk is scalar control flow.
-// LV: levels of the stacks (k <= 2^(LV-1)); TC: entries per chunk that are transposed at a
-// time.  Few levels and a small tile (the paper's densities: k <= 256) leave room for four
-// waves per SIMD, which this latency- and VALU-bound kernel needs.
-template <int LV, int TC, int WAVES_PER_EU>
-__global__ void __launch_bounds__(64 * CODE_WAVES, WAVES_PER_EU) k_codes(CodeArgs A)
-{
-    constexpr int PITCH = TC + 1;            // conflict-free column reads
-    __shared__ float tile_all[CODE_WAVES][64 * PITCH];
-    const int lane = threadIdx.x & 63, k = A.k;
-    const int wave = sl_uniform((int)(threadIdx.x >> 6));
-    const long long c0 = ((long long)blockIdx.x * CODE_WAVES + wave) * 64;
-    if (c0 >= A.n_chunks) return;
-    float *tile = tile_all[wave];
-    const long long c = c0 + lane;
-    const bool live = c < A.n_chunks;
-
-    double mu = 0.0, T = 0.0;
-    unsigned char *codes_out = nullptr, *codes_out2 = nullptr;
-    if (live) {
-        const SlChunkDesc d = A.desc[c];
-        mu = A.tstat[d.tensor].mu;
-        T = 9.0 * A.tstat[d.tensor].var;      // squared distance of the outer edges (3 sigma)
-        codes_out = A.payload + d.rec_off + 3 * k / 2;
-        codes_out2 = coded_values(A, d);
-    }
-
-    BinStacksT<LV> st;
+    if constexpr (L < LOG_LPC) {
+        if constexpr (N > 1) {
+            const bool up = (lane >> L) & 1;
 #pragma unroll
-    for (int l = 0; l < LV; ++l) st.a[l] = st.b[l] = st.c[l] = st.d[l] = 0.0;
-    unsigned n_b[4] = {0u, 0u, 0u, 0u};
-    unsigned word = 0;
-
-    constexpr int LPR = TC / 4;              // lanes that load one row of the tile
-    const int lr = lane / LPR, lc = (lane % LPR) * 4;
-    for (int s0 = 0; s0 < k; s0 += TC) {
-        const int ncol = min(TC, k - s0);          // multiple of 4
-        sl_wave_sync();
-#pragma unroll
-        for (int i = 0; i < LPR; ++i) {
-            const int row = (64 / LPR) * i + lr;
-            if (c0 + row < A.n_chunks && lc < ncol) {
-                const float4 v = *reinterpret_cast<const float4 *>(A.vals + (c0 + row) * k + s0 + lc);
-                float *t = tile + row * PITCH + lc;
-                t[0] = v.x, t[1] = v.y, t[2] = v.z, t[3] = v.w;
+            for (int i = 0; i < N / 2; ++i) {
+                const double lo = r[i], hi = r[i + N / 2], keep = up ? hi : lo, give = up ? lo : hi;
+                r[i] = keep + xor_lane<L>(give);
             }
+            reduce_bins<N / 2, L + 1, LOG_LPC>(r, lane);
+        } else {
+            r[0] = r[0] + xor_lane<L>(r[0]);
+            reduce_bins<1, L + 1, LOG_LPC>(r, lane);
         }
-        sl_wave_sync();
-        for (int col = 0; col < ncol; ++col) {
-            const int m = s0 + col;
-            const float xf = tile[lane * PITCH + col];
-            const double x = (double)xf;
-            const double dlt = x - mu;
-            const double dd = dlt * dlt;
-            const int code = dlt < 0.0 ? (dd > T ? 0 : 1) : (dd >= T ? 3 : 2);
-            n_b[0] += code == 0, n_b[1] += code == 1, n_b[2] += code == 2, n_b[3] += code == 3;
-            stack_push<0>(st, m, code == 0 ? x : 0.0, code == 1 ? x : 0.0, code == 2 ? x : 0.0, code == 3 ? x : 0.0);
-            word |= (unsigned)code << (2 * (m & 15));
-            if ((k & 15) == 0) {
-                if ((m & 15) == 15) {
-                    if (live) reinterpret_cast<unsigned *>(codes_out)[m >> 4] = word;
-                    if (codes_out2) reinterpret_cast<unsigned *>(codes_out2)[m >> 4] = word;
-                    word = 0;
-                }
-            } else if ((m & 3) == 3) {
-                if (live) codes_out[m >> 2] = (unsigned char)(word >> (2 * (m & 12)));
-                if (codes_out2) codes_out2[m >> 2] = (unsigned char)(word >> (2 * (m & 12)));
-                if ((m & 15) == 15) word = 0;
-            }
-        }
-    }
-    // pad with +0.0 up to the next power of two; the root is then at level log2(P)
-    int P = 1, top = 0;
-    while (P < k) P <<= 1, ++top;
-    for (int m = k; m < P; ++m) stack_push<0>(st, m, 0.0, 0.0, 0.0, 0.0);
-    if (live) {
-        double r0 = st.a[0], r1 = st.b[0], r2 = st.c[0], r3 = st.d[0];
-#pragma unroll
-        for (int l = 1; l < LV; ++l)
-            if (top == l) r0 = st.a[l], r1 = st.b[l], r2 = st.c[l], r3 = st.d[l];
-        A.leafC[0 * A.n_chunks + c] = r0;
-        A.leafC[1 * A.n_chunks + c] = r1;
-        A.leafC[2 * A.n_chunks + c] = r2;
-        A.leafC[3 * A.n_chunks + c] = r3;
-#pragma unroll
-        for (int b = 0; b < 4; ++b) A.cnt[b * A.n_chunks + c] = n_b[b];
     }
 }
 
-// ------------------------------------------------------------------ kernel C at high densities
-// Above k = 128 a lane per chunk has too long a walk (and too deep a stack), and on a short list
-// it leaves most of the chip idle.  Here one WAVE owns
-// a chunk: lane l takes the E = pow2ceil(k)/64 consecutive entries E*l .., folds them through
-// the same binary-counter stacks (log2(E) levels, resolved at compile time), and the upper
-// levels of the adjacent-pair tree are a butterfly over the lanes (a + b = b + a bit for bit,
-// so it does not matter which of a pair of lanes is the left one).  Entries from k on are the
-// +0.0 padding of the tree.  Same codes, counts and per-bin roots as k_codes.
-template <int E>
-__global__ void __launch_bounds__(256) k_codes_wave(CodeArgs A)
-{
-    constexpr int LV = (E == 1 ? 0 : E == 2 ? 1 : E == 4 ? 2 : E == 8 ? 3 : E == 16 ? 4 : E == 32 ? 5 : 6) + 1;
-    const int lane = threadIdx.x & 63, k = A.k;
-    const int wave = sl_uniform((int)(threadIdx.x >> 6));
-    const long long c = (long long)blockIdx.x * (blockDim.x >> 6) + wave;
-    if (c >= A.n_chunks) return;
-    const SlChunkDesc d = A.desc[c];
-    const double mu = A.tstat[d.tensor].mu;
-    const double T = 9.0 * A.tstat[d.tensor].var;      // squared distance of the outer edges (3 sigma)
-    unsigned char *const record_codes = A.payload + d.rec_off + 3 * k / 2;
-    const float *vin = A.vals + c * k;
-    const int m0 = E * lane;
-
-    BinStacksT<LV> st;
-#pragma unroll
-    for (int l = 0; l < LV; ++l) st.a[l] = st.b[l] = st.c[l] = st.d[l] = 0.0;
-    unsigned long long counts = 0;           // four 16-bit counters, bin b in bits 16b..
-    unsigned words[E / 16 > 0 ? E / 16 : 1];
-#pragma unroll
-    for (int w = 0; w < (E / 16 > 0 ? E / 16 : 1); ++w) words[w] = 0u;
-    auto entry = [&](int j, float xf) {      // entry j of this lane (j a compile-time constant after unrolling)
-        const bool valid = m0 + j < k;
-        const double x = (double)xf;
-        const double dlt = x - mu;
-        const double dd = dlt * dlt;
-        const int code = dlt < 0.0 ? (dd > T ? 0 : 1) : (dd >= T ? 3 : 2);
-        counts += valid ? 1ull << (16 * code) : 0ull;
-        stack_push<0>(st, j, valid && code == 0 ? x : 0.0, valid && code == 1 ? x : 0.0,
-                      valid && code == 2 ? x : 0.0, valid && code == 3 ? x : 0.0);
-        words[j / 16] |= (valid ? (unsigned)code : 0u) << (2 * (j & 15));
-    };
-    if constexpr (E == 1) {
-        entry(0, m0 < k ? vin[m0] : 0.f);
-    } else if constexpr (E == 2) {
-        float2 v2 = make_float2(0.f, 0.f);
-        if (m0 < k) v2 = *reinterpret_cast<const float2 *>(vin + m0);              // k is a multiple of 4
-        entry(0, v2.x);
-        entry(1, v2.y);
-    } else {
-#pragma unroll
-        for (int j4 = 0; j4 < E; j4 += 4) {
-            float4 v4 = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (m0 + j4 < k) v4 = *reinterpret_cast<const float4 *>(vin + m0 + j4);
-            entry(j4 + 0, v4.x);
-            entry(j4 + 1, v4.y);
-            entry(j4 + 2, v4.z);
-            entry(j4 + 3, v4.w);
-        }
-    }
-    // the lane's subtree roots, then the levels above them across the lanes: log2(pow2ceil(k) / E)
-    // of them (six, except at E = 1, where the padded sequence may be shorter than the wave)
-    int levels = 6;
-    if constexpr (E == 1) {
-        levels = 0;
-        while ((1 << levels) < k) ++levels;
-    }
-    double r0 = st.a[LV - 1], r1 = st.b[LV - 1], r2 = st.c[LV - 1], r3 = st.d[LV - 1];
-    r0 = sl_wave_tree(r0, levels), r1 = sl_wave_tree(r1, levels), r2 = sl_wave_tree(r2, levels),
-    r3 = sl_wave_tree(r3, levels);
-#pragma unroll
-    for (int l = 0; l < 6; ++l) counts += sl_partner(counts, l);
-
-    // codes: E/4 bytes per lane at byte E/4 * lane of the code stream (whole bytes: k % 4 == 0)
-    const int nbytes = min(E / 4, max(0, (k - m0) / 4));
-    auto store_codes = [&](unsigned char *codes_out) __attribute__((always_inline)) {
-    if constexpr (E < 4) {
-        // 4 / E lanes share a byte, 16 / E lanes a word: OR the lanes' bits together inside the row
-        constexpr int LW = 16 / E;                           // lanes per word
-        unsigned w = words[0] << (2 * E * (lane & (LW - 1)));
-        w |= (unsigned)sl_dpp<SL_DPP_XOR1>((int)w);
-        w |= (unsigned)sl_dpp<SL_DPP_XOR2>((int)w);
-        w |= (unsigned)sl_dpp<SL_DPP_HALF_MIRROR>((int)w);
-        if constexpr (E == 1) w |= (unsigned)sl_dpp<SL_DPP_MIRROR>((int)w);
-        if ((k & 15) == 0) {
-            if ((lane & (LW - 1)) == 0 && m0 < k) reinterpret_cast<unsigned *>(codes_out)[lane / LW] = w;
-        } else {
-            constexpr int LB = 4 / E;                        // lanes per byte
-            if ((lane & (LB - 1)) == 0 && m0 < k)
-                codes_out[lane / LB] = (unsigned char)(w >> (8 * ((lane & (LW - 1)) / LB)));
-        }
-    } else if ((k & 15) == 0 && nbytes == E / 4) {   // records of whole words: aligned stores
-        if constexpr (E == 4) {
-            codes_out[lane] = (unsigned char)words[0];
-        } else if constexpr (E == 8) {
-            reinterpret_cast<unsigned short *>(codes_out)[lane] = (unsigned short)words[0];
-        } else {
-#pragma unroll
-            for (int w = 0; w < E / 16; ++w) reinterpret_cast<unsigned *>(codes_out)[(E / 16) * lane + w] = words[w];
-        }
-    } else {
-#pragma unroll
-        for (int b = 0; b < E / 4; ++b)
-            if (b < nbytes) codes_out[(E / 4) * lane + b] = (unsigned char)(words[b / 4] >> (8 * (b & 3)));
-    }
-    };
-    store_codes(record_codes);
-    if (unsigned char *second = coded_values(A, d)) store_codes(second);
-    if (lane == 0) {
-        A.leafC[0 * A.n_chunks + c] = r0;
-        A.leafC[1 * A.n_chunks + c] = r1;
-        A.leafC[2 * A.n_chunks + c] = r2;
-        A.leafC[3 * A.n_chunks + c] = r3;
-#pragma unroll
-        for (int b = 0; b < 4; ++b) A.cnt[b * A.n_chunks + c] = (unsigned)(counts >> (16 * b)) & 0xFFFFu;
-    }
-}
-
-// ------------------------------------------------------------------ kernel C, other widths
-// The same quantizer with 2^BITS uniform bins over [-6 sigma, 6 sigma] (the
-// paper's quantization ablation: 1, 3 and 4 bits).  Bin q is
-// [c_q, c_(q+1)) sigma around the mean with c_j = 12 j / 2^BITS - 6, the end
-// bins open-ended; the code is the number of inner edges the value has
-// reached, each edge decided on squares against (c_j * c_j) * var.  The bins
-// are handled four at a time (one pass over the chunk's values per group of
-// four), so that the per-bin tree stacks stay in registers.
-// Is the value at distance dlt from the mean at or beyond inner edge j (1 <= j < 2^BITS)?  The edge
-// sits at c_j sigma, c_j = 12 j / 2^BITS - 6 (exact in fp64); decided on squares against (c_j c_j) var.
+// Is the value at distance dlt from the mean at or beyond inner edge j (1 <= j < 2^BITS) of the
+// 2^BITS uniform bins over [-6 sigma, 6 sigma]?  The edge sits at c_j sigma, c_j = 12 j / 2^BITS - 6
+// (exact in fp64); decided on squares against (c_j c_j) var.
 template <int BITS>
 SL_DEV bool edge_reached(int j, double dlt, double dd, double var)
 {
@@ -409,122 +195,220 @@ SL_DEV int code_of(double dlt, double var)
     return code;
 }
 
-// One lane per chunk as in k_codes.  The codes are found in the first pass and parked in LDS (a
-// word per eight entries); every pass sums NBP bins.
-template <int BITS, int LV, int NBP, int WAVES_PER_EU>
-__global__ void __launch_bounds__(64 * CODE_WAVES, WAVES_PER_EU) k_codes_b(CodeArgs A)
+// The bins of eight consecutive values.  With two bits a bin is the side of the mean and whether the
+// value lies beyond 3 sigma, decided by compares against T = 9 var; both stay lane masks, and so do
+// the tests for a bin that follow from them.
+template <int BITS>
+struct Bins {
+    int code[8];
+    SL_DEV void find(const float *x, double mu, double var)
+    {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) code[j] = code_of<BITS>((double)x[j] - mu, var);
+    }
+    SL_DEV bool in(int j, int bin) const { return code[j] == bin; }
+    SL_DEV unsigned of(int j) const { return (unsigned)code[j]; }
+};
+template <>
+struct Bins<2> {
+    bool neg[8], far[8];
+    SL_DEV void find(const float *x, double mu, double var)
+    {
+        const double T = 9.0 * var;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const double dlt = (double)x[j] - mu, dd = dlt * dlt;
+            neg[j] = dlt < 0.0;
+            far[j] = neg[j] ? dd > T : dd >= T;
+        }
+    }
+    SL_DEV bool in(int j, int bin) const
+    {
+        return bin == 0 ? neg[j] && far[j] : bin == 1 ? neg[j] && !far[j] : bin == 2 ? !neg[j] && !far[j] : !neg[j] && far[j];
+    }
+    SL_DEV unsigned of(int j) const { return (neg[j] ? 0u : 2u) + (unsigned)(neg[j] != far[j]); }
+};
+
+// Adjacent-pair tree over entries j .. j+N-1 of a lane's eight, entries of other bins counting as +0.0.
+template <int N, int BITS>
+SL_DEV double lane_tree(const float *x, const Bins<BITS> &B, int j, int bin)
 {
-    constexpr int NB = 1 << BITS;
-    constexpr int PASSES = (NB + NBP - 1) / NBP;
-    constexpr int TC = 32, PITCH = TC + 1;
-    extern __shared__ __align__(16) unsigned char codes_lds[];
+    if constexpr (N == 1) return B.in(j, bin) ? (double)x[j] : 0.0;
+    else return lane_tree<N / 2>(x, B, j, bin) + lane_tree<N / 2>(x, B, j + N / 2, bin);
+}
+
+// 2^LOG_LPC lanes per chunk, eight consecutive entries per lane: 8 << LOG_LPC = pow2ceil(k), at
+// least 8, up to 512 (entries from k on are the +0.0 padding of the tree); above, the wave takes the
+// chunk's entries in 2, 4 or 8 passes of 512.  A lane finds its entries' codes and sums them bin by
+// bin (a subtree of the fixed tree); the lanes of a chunk finish the trees of all bins together
+// (reduce_bins).
+// What bounds it: on long lists reading the values, at the rate any kernel this short reads
+// memory that was written before the last gigabyte was (113 MB in 54 us at 443,569 chunks of k = 64,
+// 506 MB in 143 us at 123,505 chunks of k = 1024; with the arithmetic taken out 41 and 145 us); on
+// short lists the latency of one chain descriptor - statistics - arithmetic.  Eight entries per lane
+// need no transposition through LDS and no deep stacks of partial sums in registers, and the
+// cross-lane levels are shared by 64 / 2^LOG_LPC chunks.  A lane per chunk with such stacks, which
+// this replaces up to k = 128 and at 1, 3 and 4 bits, took 88 us at k = 64, 2 bits, and, four bins
+// per pass, 176 us for 46,537 chunks of k = 128 at 4 bits (here 30) and 1900 us for 300 chunks of
+// k = 1024 (here 25), where it left most of the chip without a wave.  Waves that stay for
+// several steps and fetch ahead are slower: the registers cost more waves than the overlap gains.
+template <int BITS, int LOG_LPC>
+__global__ void __launch_bounds__(256) k_codes(CodeArgs A)
+{
+    constexpr int E = 8, LPC = 1 << LOG_LPC, CPW = 64 / LPC, NB = 1 << BITS, LEFT = NB >> LOG_LPC > 0 ? NB >> LOG_LPC : 1;
+    constexpr bool WIDE = E * LPC > 128;     // a bin's count needs more than 8 bits
     const int lane = threadIdx.x & 63, k = A.k;
     const int wave = sl_uniform((int)(threadIdx.x >> 6));
-    const long long c0 = ((long long)blockIdx.x * CODE_WAVES + wave) * 64;
-    if (c0 >= A.n_chunks) return;
-    // per wave: the value tile, then the parked codes (k / 8 words per lane, word w of lane l at [w * 64 + l])
-    const bool park = PASSES > 1 && A.park;
-    const size_t per_wave = sizeof(float) * 64 * PITCH + (park ? sizeof(unsigned) * 64 * (size_t)(k >> 3) : 0);
-    float *tile = reinterpret_cast<float *>(codes_lds + (size_t)wave * per_wave);
-    unsigned *parked = reinterpret_cast<unsigned *>(tile + 64 * PITCH);
-    const long long c = c0 + lane;
+    const long long cw = ((long long)blockIdx.x * (blockDim.x >> 6) + wave) * CPW;
+    if (cw >= A.n_chunks) return;
+    const int sub = lane & (LPC - 1);
+    const long long c = cw + (lane >> LOG_LPC);
     const bool live = c < A.n_chunks;
+    const long long cl = live ? c : cw;          // (a lane without a chunk reads the wave's first one and writes nothing)
+    const int mine = live ? k : 0;
 
-    double mu = 0.0, var = 0.0;
-    unsigned char *codes_out = nullptr, *codes_out2 = nullptr;
-    if (live) {
-        const SlChunkDesc d = A.desc[c];
-        mu = A.tstat[d.tensor].mu;
-        var = A.tstat[d.tensor].var;
-        codes_out = A.payload + d.rec_off + 3 * k / 2;
-        codes_out2 = coded_values(A, d);
-    }
-    int P = 1, top = 0;
-    while (P < k) P <<= 1, ++top;
-    constexpr int LPR = TC / 4;              // lanes that load one row of the tile
-    const int lr = lane / LPR, lc = (lane % LPR) * 4;
+    const float *vin = A.vals + cl * k;
+    const SlChunkDesc d = A.desc[cl];
+    const double mu = A.tstat[d.tensor].mu, var = A.tstat[d.tensor].var;
+    unsigned char *const out1 = A.payload + d.rec_off + 3 * k / 2;
+    unsigned char *const out2 = A.coded ? A.coded + A.cdesc[cl].fix_off + A.rem_bytes : nullptr;
 
-    for (int pass = 0; pass < PASSES; ++pass) {
-        const int q0 = NBP * pass;
-        // (four bins to a set of stacks, as in k_codes; NBP = 8: two sets)
-        BinStacksT<LV> st, st2;
-#pragma unroll
-        for (int l = 0; l < LV; ++l) {
-            st.a[l] = st.b[l] = st.c[l] = st.d[l] = 0.0;
-            st2.a[l] = st2.b[l] = st2.c[l] = st2.d[l] = 0.0;
+    constexpr int BY = NB >= 8 ? NB / 4 : 1;
+    unsigned by[BY];                             // entries per bin, bytes (two bits: one word; more: word 2h + p
+#pragma unroll                                   // holds bins 8h + p, + 2, + 4, + 6; one bit: 16-bit fields)
+    for (unsigned &q : by) q = 0;
+    double r[NB], left1 = 0.0, left2 = 0.0, left4 = 0.0;     // (left*: roots of 512, 1024 and 2048 entries, above k = 512)
+    struct Values {
+        sl_f4 a, b;
+    };
+    auto values_at = [&](int m0) -> Values {     // entries m0 .. m0+7 of the chunk, +0.0f from entry k on
+        Values v;
+        v.a = v.b = sl_f4{0.f, 0.f, 0.f, 0.f};
+        if (m0 < mine) v.a = sl_load_stream(vin + m0);
+        if (m0 + 4 < mine) v.b = sl_load_stream(vin + m0 + 4);
+        return v;
+    };
+    Values next = values_at(E * sub);
+#pragma unroll 1
+    for (int p = 0, m0 = E * sub; p == 0 || (LOG_LPC == 6 && p < A.passes); ++p, m0 += E * LPC) {
+        const int n = min(max(mine - m0, 0), E);             // entries of this lane: a multiple of 4
+        const Values now = next;
+        if constexpr (LOG_LPC == 6) {
+            if (p + 1 < A.passes) next = values_at(m0 + E * LPC);
         }
-        unsigned n_b[NBP];
+        const float x[E] = {now.a.x, now.a.y, now.a.z, now.a.w, now.b.x, now.b.y, now.b.z, now.b.w};
+        Bins<BITS> B;
+        B.find(x, mu, var);
+        // ---- the code fields: eight entries are BITS whole bytes
+        unsigned w = 0;
 #pragma unroll
-        for (int q = 0; q < NBP; ++q) n_b[q] = 0u;
-        unsigned bitbuf = 0;                    // codes of 8 entries = BITS bytes
-        for (int s0 = 0; s0 < k; s0 += TC) {
-            const int ncol = min(TC, k - s0);   // a multiple of 8
-            sl_wave_sync();
+        for (int j = 0; j < 8; ++j) w |= B.of(j) << (BITS * j);
+        auto store_codes = [&](unsigned char *out) __attribute__((always_inline)) {
+            unsigned char *o = out + (m0 >> 3) * BITS;
+            if (n == E) {
+                if constexpr (BITS == 4) {                   // 4-byte aligned: k is a multiple of 8
+                    *reinterpret_cast<unsigned *>(o) = w;
+                } else if (BITS == 2 && (k & 7) == 0) {      // 2-byte aligned
+                    *reinterpret_cast<unsigned short *>(o) = (unsigned short)w;
+                } else {
 #pragma unroll
-            for (int i = 0; i < LPR; ++i) {
-                const int row = (64 / LPR) * i + lr;
-                if (c0 + row < A.n_chunks && lc < ncol) {
-                    const float4 v = *reinterpret_cast<const float4 *>(A.vals + (c0 + row) * k + s0 + lc);
-                    float *t = tile + row * PITCH + lc;
-                    t[0] = v.x, t[1] = v.y, t[2] = v.z, t[3] = v.w;
+                    for (int q = 0; q < BITS; ++q) o[q] = (unsigned char)(w >> (8 * q));
                 }
+            } else if (BITS == 2 && n == 4) {
+                o[0] = (unsigned char)w;
             }
-            sl_wave_sync();
-            for (int col = 0; col < ncol; ++col) {
-                const int m = s0 + col;
-                const double x = (double)tile[lane * PITCH + col];
-                int code;
-                if (pass == 0 || !park) {
-                    code = code_of<BITS>(x - mu, var);
-                }
-                if (pass == 0) {
-                    bitbuf |= (unsigned)code << (BITS * (m & 7));
-                    if ((m & 7) == 7) {         // k is a multiple of 8
-                        if (live) {
+        };
+        store_codes(out1);
+        if (A.coded) store_codes(out2);
+        // ---- entries per bin
+        if constexpr (NB <= 4) {                 // from the packed fields
+            const unsigned v = w & ((1u << (BITS * n)) - 1u);
+            if constexpr (NB == 2) {
+                const unsigned ones = (unsigned)__builtin_popcount(v);
+                by[0] += (unsigned)n - ones + (ones << 16);
+            } else {
+                const unsigned lo = v & 0x5555u, hi = (v >> 1) & 0x5555u, both = lo & hi;
+                const unsigned n3 = (unsigned)__builtin_popcount(both), n1 = (unsigned)__builtin_popcount(lo ^ both),
+                               n2 = (unsigned)__builtin_popcount(hi ^ both);
+                by[0] += (unsigned)n - n1 - n2 - n3 + (n1 << 8) + (n2 << 16) + (n3 << 24);
+            }
+        } else {
+            unsigned long long nib = 0;          // four bits per bin hold the counts of eight entries
 #pragma unroll
-                            for (int q = 0; q < BITS; ++q)
-                                codes_out[(m >> 3) * BITS + q] = (unsigned char)(bitbuf >> (8 * q));
-                        }
-                        if (codes_out2) {
+            for (int j = 0; j < 8; ++j) nib += j < n ? 1ull << (4 * B.of(j)) : 0ull;
 #pragma unroll
-                            for (int q = 0; q < BITS; ++q)
-                                codes_out2[(m >> 3) * BITS + q] = (unsigned char)(bitbuf >> (8 * q));
-                        }
-                        if (park) parked[(m >> 3) * 64 + lane] = bitbuf;
-                        bitbuf = 0;
-                    }
-                } else if (park) {
-                    if ((m & 7) == 0) bitbuf = parked[(m >> 3) * 64 + lane];
-                    code = (int)((bitbuf >> (BITS * (m & 7))) & (unsigned)(NB - 1));
-                }
-                const int rel = code - q0;
-#pragma unroll
-                for (int q = 0; q < NBP; ++q) n_b[q] += rel == q;
-                stack_push<0>(st, m, rel == 0 ? x : 0.0, rel == 1 ? x : 0.0, rel == 2 ? x : 0.0, rel == 3 ? x : 0.0);
-                if constexpr (NBP > 4)
-                    stack_push<0>(st2, m, rel == 4 ? x : 0.0, rel == 5 ? x : 0.0, rel == 6 ? x : 0.0, rel == 7 ? x : 0.0);
+            for (int h = 0; h < NB / 8; ++h) {
+                const unsigned v = (unsigned)(nib >> (32 * h));
+                by[2 * h] += v & 0x0F0F0F0Fu;
+                by[2 * h + 1] += (v >> 4) & 0x0F0F0F0Fu;
             }
         }
-        for (int m = k; m < P; ++m) {
-            stack_push<0>(st, m, 0.0, 0.0, 0.0, 0.0);
-            if constexpr (NBP > 4) stack_push<0>(st2, m, 0.0, 0.0, 0.0, 0.0);
-        }
-        if (live) {
-            double r[8] = {st.a[0], st.b[0], st.c[0], st.d[0], st2.a[0], st2.b[0], st2.c[0], st2.d[0]};
+        // ---- sums per bin
 #pragma unroll
-            for (int l = 1; l < LV; ++l)
-                if (top == l) {
-                    r[0] = st.a[l], r[1] = st.b[l], r[2] = st.c[l], r[3] = st.d[l];
-                    r[4] = st2.a[l], r[5] = st2.b[l], r[6] = st2.c[l], r[7] = st2.d[l];
+        for (int b = 0; b < NB; ++b) r[b] = lane_tree<8>(x, B, 0, b);
+        reduce_bins<NB, 0, LOG_LPC>(r, lane);
+        if constexpr (LOG_LPC == 6) {            // passes pair up like any other neighbours of the tree
+            if (p & 1) {
+                r[0] = left1 + r[0];
+                if (p & 2) {
+                    r[0] = left2 + r[0];
+                    if (p & 4) r[0] = left4 + r[0];
+                    else left4 = r[0];
+                } else {
+                    left2 = r[0];
                 }
-#pragma unroll
-            for (int q = 0; q < NBP; ++q)
-                if (q0 + q < NB) {
-                    A.leafC[(long long)(q0 + q) * A.n_chunks + c] = r[q];
-                    A.cnt[(long long)(q0 + q) * A.n_chunks + c] = n_b[q];
-                }
+            } else {
+                left1 = r[0];
+            }
         }
     }
+
+    // ---- the counts of the chunk: all its lanes end up with the sums
+    constexpr int CW = (NB >= 8 ? NB / 4 : 1) * (WIDE && NB > 2 ? 2 : 1);
+    unsigned cnt[CW];
+    if constexpr (CW == BY) {
+#pragma unroll
+        for (int w = 0; w < CW; ++w) cnt[w] = by[w];
+    } else {                                     // 16 bits: word 2w + s holds bytes s and s + 2 of word w
+#pragma unroll
+        for (int w = 0; w < BY; ++w) cnt[2 * w] = by[w] & 0x00FF00FFu, cnt[2 * w + 1] = (by[w] >> 8) & 0x00FF00FFu;
+    }
+#pragma unroll
+    for (int w = 0; w < CW; ++w)
+#pragma unroll
+        for (int l = 0; l < LOG_LPC; ++l) cnt[w] += (unsigned)sl_partner((int)cnt[w], l);
+    auto count_of = [&](int bin) -> unsigned {
+        if constexpr (NB == 2) return (cnt[0] >> (16 * bin)) & 0xFFFFu;
+        const int byte = NB == 4 ? bin : (bin >> 1) & 3, word = NB == 4 ? 0 : 2 * (bin >> 3) + (bin & 1);
+        const int at = WIDE ? 2 * word + (byte & 1) : word;
+        // (masks instead of a choice: the compiler turns a choice among array elements into an indexed
+        // read of a copy of the array in memory)
+        unsigned v = 0;
+#pragma unroll
+        for (int w = 0; w < CW; ++w) v |= cnt[w] & (CW == 1 || at == w ? 0xFFFFFFFFu : 0u);
+        return WIDE ? (v >> (16 * (byte >> 1))) & 0xFFFFu : (v >> (8 * byte)) & 0xFFu;
+    };
+
+    int bin0 = 0;                                // first bin that this lane ended up with
+#pragma unroll
+    for (int l = 0; l < BITS && l < LOG_LPC; ++l) bin0 += ((lane >> l) & 1) * (NB >> (l + 1));
+    if (live && (sub >> BITS) == 0) {
+#pragma unroll
+        for (int i = 0; i < LEFT; ++i) {
+            A.leafC[(long long)(bin0 + i) * A.n_chunks + c] = r[i];
+            A.cnt[(long long)(bin0 + i) * A.n_chunks + c] = count_of(bin0 + i);
+        }
+    }
+}
+
+typedef void (*codes_kernel)(CodeArgs);
+
+template <int BITS>
+codes_kernel codes_for(int log_lpc)
+{
+    static const codes_kernel table[7] = {k_codes<BITS, 0>, k_codes<BITS, 1>, k_codes<BITS, 2>, k_codes<BITS, 3>,
+                                          k_codes<BITS, 4>, k_codes<BITS, 5>, k_codes<BITS, 6>};
+    return table[log_lpc];
 }
 
 // ------------------------------------------------------------------ kernel D
@@ -689,62 +573,17 @@ int slk_quantize(const sl_plan *p, float *e, int skip_residual, unsigned char *p
     C.n_chunks = p->n_chunks;
     C.k = k;
     C.coded = coded;
-    C.tensors = p->d_tensors;
-    C.cfix = p->cg.cfix;
+    C.cdesc = p->d_cdesc;
     C.rem_bytes = p->cg.rem_bytes;
-    C.park = 0;
-    const long long per_block = 64ll * CODE_WAVES;
-    const unsigned nblk = (unsigned)((p->n_chunks + per_block - 1) / per_block);
-    // (the list length is a field of the plan, sl_plan_set_codes_wave_below: both kernels write the same bytes)
-    const bool by_wave = k >= SL_CODES_WAVE_FROM || p->n_chunks < p->codes_wave_below;
-    switch (p->bits) {
-        case 1:
-        case 3:
-        case 4: {
-            // stack depth by k as in k_codes; bins per pass: as many as the registers hold next to it
-            const int depth = k <= 64 ? 7 : k <= 256 ? 9 : 13;
-            const int nbp = p->bits == 1 ? 2 : 4;     // (eight at a time is no faster: the pushes per bin are the cost)
-            const int passes = ((1 << p->bits) + nbp - 1) / nbp;
-            C.park = passes > 1 && k <= 512;          // 32 KB of LDS per workgroup at most
-            const size_t lds = CODE_WAVES * (sizeof(float) * 64 * 33 + (C.park ? sizeof(unsigned) * 64 * (size_t)(k >> 3) : 0));
-            const dim3 g(nblk), b(64 * CODE_WAVES);
-#define SL_CODES_B(BITS, LV, NBP, WPE) hipLaunchKernelGGL((k_codes_b<BITS, LV, NBP, WPE>), g, b, lds, st, C)
-            if (p->bits == 1) {
-                if (depth == 7) SL_CODES_B(1, 7, 2, 4);
-                else if (depth == 9) SL_CODES_B(1, 9, 2, 4);
-                else SL_CODES_B(1, 13, 2, 2);
-            } else if (p->bits == 3) {
-                if (depth == 7) SL_CODES_B(3, 7, 4, 4);
-                else if (depth == 9) SL_CODES_B(3, 9, 4, 3);
-                else SL_CODES_B(3, 13, 4, 2);
-            } else {
-                if (depth == 7) SL_CODES_B(4, 7, 4, 4);
-                else if (depth == 9) SL_CODES_B(4, 9, 4, 3);
-                else SL_CODES_B(4, 13, 4, 2);
-            }
-#undef SL_CODES_B
-            break;
-        }
-        default:
-            if (k <= 64 && !by_wave) {
-                hipLaunchKernelGGL((k_codes<7, 32, 4>), dim3(nblk), dim3(64 * CODE_WAVES), 0, st, C);
-            } else if (k <= 256 && !by_wave) {
-                hipLaunchKernelGGL((k_codes<9, 32, 4>), dim3(nblk), dim3(64 * CODE_WAVES), 0, st, C);
-            } else if (!by_wave) {
-                hipLaunchKernelGGL((k_codes<13, 64, 2>), dim3(nblk), dim3(64 * CODE_WAVES), 0, st, C);
-            } else {
-                // a wave per chunk, E = pow2ceil(k) / 64 entries per lane
-                const dim3 wgrid((unsigned)((p->n_chunks + 3) / 4)), wblock(256);
-                if (k <= 64) hipLaunchKernelGGL(k_codes_wave<1>, wgrid, wblock, 0, st, C);
-                else if (k <= 128) hipLaunchKernelGGL(k_codes_wave<2>, wgrid, wblock, 0, st, C);
-                else if (k <= 256) hipLaunchKernelGGL(k_codes_wave<4>, wgrid, wblock, 0, st, C);
-                else if (k <= 512) hipLaunchKernelGGL(k_codes_wave<8>, wgrid, wblock, 0, st, C);
-                else if (k <= 1024) hipLaunchKernelGGL(k_codes_wave<16>, wgrid, wblock, 0, st, C);
-                else if (k <= 2048) hipLaunchKernelGGL(k_codes_wave<32>, wgrid, wblock, 0, st, C);
-                else hipLaunchKernelGGL(k_codes_wave<64>, wgrid, wblock, 0, st, C);
-            }
-            break;
-    }
+    int log_lpc = 0;
+    while (log_lpc < 6 && (8 << log_lpc) < k) ++log_lpc;
+    C.passes = 1;
+    while (512 * C.passes < k) C.passes <<= 1;
+    const codes_kernel fn = p->bits == 1 ? codes_for<1>(log_lpc) : p->bits == 2 ? codes_for<2>(log_lpc)
+                            : p->bits == 3 ? codes_for<3>(log_lpc) : codes_for<4>(log_lpc);
+    const long long per_wave = 64 >> log_lpc;
+    const long long per_block = 4ll * per_wave;
+    hipLaunchKernelGGL(fn, dim3((unsigned)((p->n_chunks + per_block - 1) / per_block)), dim3(256), 0, st, C);
     if ((rc = check_launch())) return rc;
     sl_prof_mark(p, SL_PROF_CODES, st);
 
