@@ -344,11 +344,9 @@ int sl_compress_impl(sl_plan *p, float *e, const float *delta, const float *thet
                         pay, static_cast<unsigned char *>(coded), ws, st);
     if (rc) return rc;
     sl_prof_mark(p, SL_PROF_SELECT, st);
-    rc = slk_quantize(p, e, frozen || defer, pay, static_cast<unsigned char *>(coded), ws, st);
-    if (rc || !coded) return rc;
-    rc = slk_coded_finish(p, static_cast<unsigned char *>(coded), ws, st);
-    sl_prof_mark(p, SL_PROF_INDEX, st);
-    return rc;
+    if (p->n_chunks == 0)
+        return coded ? slk_coded_finish(p, static_cast<unsigned char *>(coded), ws, st) : SL_OK;
+    return slk_quantize(p, e, frozen || defer, pay, static_cast<unsigned char *>(coded), ws, st);
 }
 
 extern "C" {

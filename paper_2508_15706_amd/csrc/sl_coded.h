@@ -181,3 +181,166 @@ SL_DEV SlVecPlace sl_coded_dir_entry(const SlCodedGeom &G, sl_gbytes entry, int 
     const SlDirWords W = sl_coded_dir_load(G, entry);
     return sl_coded_dir_parse(G, W.run_word, W.lo, W.hi, pos);
 }
+
+// ---------------------------------------------------------------------------------- placement
+// The variable-length part of a buffer.  The writers leave each chunk's bit vector and quotient sum
+// in the workspace; then, each step reading what the one before wrote:
+//   sl_coded_scan_tensor   one workgroup per tensor: words of each group's run, their exclusive
+//                          prefix inside the tensor, the tensor's total;
+//   sl_coded_scan_list     one wave: prefix over the tensors, total size, buffer header;
+//   sl_coded_place         one wave per group: the 16 vectors shifted into one run, the run and
+//                          the directory entry written.
+// The compressor runs them as extra workgroups of the quantizer's launches (sl_quant.hip), the
+// transcoder as launches of their own (sl_coded.hip).
+struct SlCodedArgs {
+    SlCodedGeom G;
+    const SlTensorDev *tensors;
+    const SlGroup *groups;
+    long long n_groups;
+    int n_tensors;
+    int ua_log2;                    // log2 of a power of two >= G.ua
+    const unsigned *uvec;           // [n_chunks][G.ua] bit vectors as the writers left them
+    const unsigned short *qsum;     // [n_chunks]
+    unsigned *gwords;               // [n_groups] words of each group's run
+    unsigned *goff;                 // [n_groups] word offset of the run inside its tensor's part of the section
+    unsigned long long *twords;     // [n_tensors + 1] words of each tensor's part, then (after the list scan) its offset
+    unsigned char *out;             // the coded buffer
+};
+
+inline SlCodedArgs sl_coded_args(const sl_plan *p, unsigned char *out, unsigned char *ws)
+{
+    SlCodedArgs A;
+    A.G = p->cg;
+    A.tensors = p->d_tensors;
+    A.groups = p->d_groups;
+    A.n_groups = p->n_groups;
+    A.n_tensors = p->n_tensors;
+    A.ua_log2 = 0;
+    while ((1 << A.ua_log2) < p->cg.ua) ++A.ua_log2;
+    A.uvec = reinterpret_cast<const unsigned *>(ws + p->ws_uvec);
+    A.qsum = reinterpret_cast<const unsigned short *>(ws + p->ws_qsum);
+    A.gwords = reinterpret_cast<unsigned *>(ws + p->ws_gwords);
+    A.goff = reinterpret_cast<unsigned *>(ws + p->ws_goff);
+    A.twords = reinterpret_cast<unsigned long long *>(ws + p->ws_twords);
+    A.out = out;
+    return A;
+}
+
+// Tensor `t`; called by all threads of a workgroup of THREADS; `wsum` (LDS) THREADS / 64 words.
+template <int THREADS>
+SL_DEV void sl_coded_scan_tensor(const SlCodedArgs &A, int t, unsigned *wsum)
+{
+    const SlTensorDev td = A.tensors[t];
+    const long long ng = (td.n_chunks + SL_RICE_GROUP - 1) / SL_RICE_GROUP;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    unsigned long long carry = 0;                // words of the groups before this tile
+    for (long long base = 0; base < ng; base += THREADS) {
+        const long long i = base + tid, c0 = i * SL_RICE_GROUP;
+        const int nc = i < ng ? (int)min((long long)SL_RICE_GROUP, td.n_chunks - c0) : 0;
+        unsigned bits = 0;
+#pragma unroll
+        for (int q = 0; q < SL_RICE_GROUP; ++q)
+            if (q < nc) bits += (unsigned)A.G.k + A.qsum[td.chunk0 + c0 + q];
+        const unsigned v = (bits + 31u) >> 5;
+        const unsigned incl = (unsigned)sl_wave_iscan((int)v);     // a tile's total stays far below 2^31
+        if (lane == 63) wsum[wave] = incl;
+        __syncthreads();
+        unsigned long long before = carry;
+        for (int q = 0; q < THREADS / 64; ++q) {
+            before += q < wave ? wsum[q] : 0u;
+            carry += wsum[q];
+        }
+        if (i < ng) {
+            A.gwords[td.group0 + i] = v;
+            A.goff[td.group0 + i] = (unsigned)(before + incl - v);
+        }
+        __syncthreads();
+    }
+    if (tid == 0) A.twords[t] = carry;
+}
+
+// Prefix over the tensors (twords[t] becomes the tensor's offset in the section, in words), the
+// buffer header, and the zero padding that rounds the buffer up to 16 bytes.  One wave.
+SL_DEV void sl_coded_scan_list(unsigned long long *twords, int n_tensors, long long section, unsigned char *out)
+{
+    const int lane = threadIdx.x & 63;
+    unsigned long long pos = 0;
+    for (int base = 0; base < n_tensors; base += 64) {
+        const int t = base + lane;
+        const unsigned long long v = t < n_tensors ? twords[t] : 0ull;
+        unsigned long long incl = v;
+#pragma unroll
+        for (int s = 1; s < 64; s <<= 1) {
+            const unsigned long long up = __shfl_up(incl, s);
+            if (lane >= s) incl += up;
+        }
+        if (t < n_tensors) twords[t] = pos + incl - v;
+        pos += __shfl(incl, 63);
+    }
+    const unsigned long long end = (unsigned long long)section + 4ull * pos;
+    const unsigned long long total = (end + 15ull) & ~15ull;
+    if (lane == 0) {
+        unsigned long long *h = reinterpret_cast<unsigned long long *>(out);
+        h[0] = 0x3230454349524C53ull;                      // "SLRICE02", little endian
+        h[1] = total;
+        twords[n_tensors] = pos;
+    }
+    if (end + 4ull * lane < total) *reinterpret_cast<unsigned *>(out + end + 4ull * lane) = 0u;
+}
+
+// Words of LDS that sl_coded_place needs per wave.
+inline size_t sl_coded_place_words(const SlCodedGeom &G) { return (size_t)SL_RICE_GROUP * G.ua + 1; }
+
+// Group gi (one wave; `run`: its LDS): the chunks' vectors, as the writers left them (G.ua words each,
+// bits beyond k + Q undefined), are shifted to their bit offsets inside the run in LDS; the run and
+// the directory entry go to the buffer.  A lane takes one (chunk, word) pair per turn, so that the
+// loads of several chunks are under way together (a chunk per turn left most lanes idle and waited
+// for memory sixteen times in a row: 33 us for 443,569 chunks of k = 64).
+SL_DEV void sl_coded_place(const SlCodedArgs &A, long long gi, unsigned *run)
+{
+    const int lane = threadIdx.x & 63;
+    const SlCodedGeom &G = A.G;
+    const SlGroup g = A.groups[gi];
+    const SlTensorDev td = A.tensors[g.tensor];
+    const long long c0 = td.chunk0 + (long long)g.local_group * SL_RICE_GROUP;
+    const int nc = (int)min((long long)SL_RICE_GROUP, td.n_chunks - (long long)g.local_group * SL_RICE_GROUP);
+    const unsigned nw = A.gwords[gi];
+    const unsigned long long base = A.twords[g.tensor] + A.goff[gi];    // below 2^32 by the plan's check
+
+    const int q = lane < nc ? (int)A.qsum[c0 + lane] : 0;
+    const int nbits = lane < nc ? G.k + q : 0;
+    const int start = sl_wave_iscan(nbits) - nbits;                      // lanes 0..15 matter
+    for (unsigned w = lane; w < nw + 1u; w += 64) run[w] = 0u;
+    sl_wave_sync();
+    const int slots = nc << A.ua_log2;
+    constexpr int U = 2;                         // turns whose loads are issued together
+    for (int s0 = 0; s0 < slots; s0 += 64 * U) {
+        unsigned v[U];
+        int at[U];                               // first bit of the word inside the run, or -1
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int slot = s0 + 64 * u + lane, i = min(slot >> A.ua_log2, SL_RICE_GROUP - 1), j = slot & ((1 << A.ua_log2) - 1);
+            const int n = sl_lane_read(nbits, i), left = n - 32 * j;     // bits of this word that belong to the vector
+            const int first = sl_lane_read(start, i);
+            at[u] = slot < slots && left > 0 ? first + 32 * j : -1;
+            v[u] = at[u] >= 0 ? A.uvec[(size_t)(c0 + i) * G.ua + j] & (left < 32 ? (1u << left) - 1u : 0xFFFFFFFFu) : 0u;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (at[u] >= 0) {
+                const int sh = at[u] & 31;
+                sl_lds_or(&run[at[u] >> 5], v[u] << sh);
+                if (sh) sl_lds_or(&run[(at[u] >> 5) + 1], v[u] >> (32 - sh));
+            }
+        }
+    }
+    sl_wave_sync();
+    unsigned *dst = reinterpret_cast<unsigned *>(A.out + G.section) + base;
+    for (unsigned w = lane; w < nw; w += 64) dst[w] = run[w];
+    unsigned char *entry = A.out + td.cdir_off + (long long)g.local_group * G.dent;
+    if (lane == 0) *reinterpret_cast<unsigned *>(entry) = (unsigned)base;
+    if (lane < SL_RICE_GROUP) {
+        if (G.qf == 1) entry[4 + lane] = (unsigned char)q;
+        else reinterpret_cast<unsigned short *>(entry + 4)[lane] = (unsigned short)q;
+    }
+}

@@ -6,12 +6,7 @@
 // The writers of a coded buffer (kernel A of sl_compress_coded, or k_rice_chunks below for a
 // payload that already exists) put everything whose place follows from the tensor list - table
 // headers, remainder and value fields - straight into the buffer, and leave each chunk's bit
-// vector and quotient sum Q in the workspace.  Then
-//   k_coded_scan_tensor   one workgroup per tensor: words of each group's run, their exclusive
-//                         prefix inside the tensor, the tensor's total;
-//   k_coded_scan_list     one wave: prefix over the tensors, total size, buffer header;
-//   k_coded_place         one wave per group: the 16 vectors shifted into one run, the run and
-//                         the directory entry written.
+// vector and quotient sum Q in the workspace, from where the placement steps of sl_coded.h take them.
 #include "sl_coded.h"
 
 int sl_rice_param(int k)
@@ -24,133 +19,26 @@ int sl_rice_param(int k)
 
 namespace {
 
-struct CodedArgs {
-    SlCodedGeom G;
-    const SlChunkDesc *desc;
-    const SlTensorDev *tensors;
-    const SlGroup *groups;
-    long long n_groups, n_chunks;
-    int n_tensors;
-    const unsigned *uvec;           // [n_chunks][G.ua] bit vectors as the writers left them
-    const unsigned short *qsum;     // [n_chunks]
-    unsigned *gwords;               // [n_groups] words of each group's run
-    unsigned *goff;                 // [n_groups] word offset of the run inside its tensor's part of the section
-    unsigned long long *twords;     // [n_tensors + 1] words of each tensor's part, then (after the list scan) its offset
-    unsigned char *out;             // the coded buffer
-};
+constexpr int SCAN_THREADS = 1024;
 
-// Words of the run of the group that starts at chunk c0 of a tensor with n_chunks chunks.
-SL_DEV unsigned group_words(const CodedArgs &A, const SlTensorDev &td, long long g)
+__global__ void __launch_bounds__(SCAN_THREADS) k_coded_scan_tensor(SlCodedArgs A)
 {
-    const long long c0 = g * SL_RICE_GROUP;
-    const int nc = (int)min((long long)SL_RICE_GROUP, td.n_chunks - c0);
-    unsigned bits = 0;
-    for (int i = 0; i < nc; ++i) bits += (unsigned)A.G.k + A.qsum[td.chunk0 + c0 + i];
-    return (bits + 31u) >> 5;
+    __shared__ unsigned wsum[SCAN_THREADS / 64];
+    sl_coded_scan_tensor<SCAN_THREADS>(A, (int)blockIdx.x, wsum);
 }
 
-__global__ void __launch_bounds__(256) k_coded_scan_tensor(CodedArgs A)
+__global__ void __launch_bounds__(64) k_coded_scan_list(SlCodedArgs A)
 {
-    __shared__ unsigned long long wsum[4];
-    __shared__ unsigned long long carry;
-    const SlTensorDev td = A.tensors[blockIdx.x];
-    const long long ng = (td.n_chunks + SL_RICE_GROUP - 1) / SL_RICE_GROUP;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    if (tid == 0) carry = 0ull;
-    __syncthreads();
-    for (long long base = 0; base < ng; base += 256) {
-        const long long i = base + tid;
-        const unsigned v = i < ng ? group_words(A, td, i) : 0u;
-        const unsigned incl = (unsigned)sl_wave_iscan((int)v);     // a tile's total stays far below 2^31
-        if (lane == 63) wsum[wave] = incl;
-        __syncthreads();
-        unsigned long long before = carry;
-        for (int q = 0; q < wave; ++q) before += wsum[q];
-        if (i < ng) {
-            A.gwords[td.group0 + i] = v;
-            A.goff[td.group0 + i] = (unsigned)(before + incl - v);
-        }
-        __syncthreads();
-        if (tid == 255) carry = before + incl;
-        __syncthreads();
-    }
-    if (tid == 0) A.twords[blockIdx.x] = carry;
+    sl_coded_scan_list(A.twords, A.n_tensors, A.G.section, A.out);
 }
 
-// Prefix over the tensors (twords[t] becomes the tensor's offset in the section, in words), the
-// buffer header, and the zero padding that rounds the buffer up to 16 bytes.
-__global__ void __launch_bounds__(64) k_coded_scan_list(CodedArgs A)
-{
-    const int lane = threadIdx.x;
-    unsigned long long pos = 0;
-    for (int base = 0; base < A.n_tensors; base += 64) {
-        const int t = base + lane;
-        const unsigned long long v = t < A.n_tensors ? A.twords[t] : 0ull;
-        unsigned long long incl = v;
-#pragma unroll
-        for (int s = 1; s < 64; s <<= 1) {
-            const unsigned long long up = __shfl_up(incl, s);
-            if (lane >= s) incl += up;
-        }
-        if (t < A.n_tensors) A.twords[t] = pos + incl - v;
-        pos += __shfl(incl, 63);
-    }
-    const unsigned long long end = (unsigned long long)A.G.section + 4ull * pos;
-    const unsigned long long total = (end + 15ull) & ~15ull;
-    if (lane == 0) {
-        unsigned long long *h = reinterpret_cast<unsigned long long *>(A.out);
-        h[0] = 0x3230454349524C53ull;                      // "SLRICE02", little endian
-        h[1] = total;
-        A.twords[A.n_tensors] = pos;
-    }
-    if (end + 4ull * lane < total) *reinterpret_cast<unsigned *>(A.out + end + 4ull * lane) = 0u;
-}
-
-// One wave per group: its chunks' vectors, as the writers left them in the workspace (G.ua
-// words each, bits beyond k + Q undefined), are shifted to their bit offsets inside the run
-// in LDS; the run and the directory entry go to the buffer.
-__global__ void __launch_bounds__(256) k_coded_place(CodedArgs A)
+__global__ void __launch_bounds__(256) k_coded_place(SlCodedArgs A)
 {
     extern __shared__ __align__(16) unsigned place_lds[];
-    const int lane = threadIdx.x & 63;
     const int wave = sl_uniform((int)(threadIdx.x >> 6));
     const long long gi = (long long)blockIdx.x * (blockDim.x >> 6) + wave;
     if (gi >= A.n_groups) return;
-    const SlCodedGeom &G = A.G;
-    unsigned *run = place_lds + (size_t)wave * (SL_RICE_GROUP * G.ua + 1);
-    const SlGroup g = A.groups[gi];
-    const SlTensorDev td = A.tensors[g.tensor];
-    const long long c0 = td.chunk0 + (long long)g.local_group * SL_RICE_GROUP;
-    const int nc = (int)min((long long)SL_RICE_GROUP, td.n_chunks - (long long)g.local_group * SL_RICE_GROUP);
-    const unsigned nw = A.gwords[gi];
-    const unsigned long long base = A.twords[g.tensor] + A.goff[gi];    // below 2^32 by the plan's check
-
-    const int q = lane < nc ? (int)A.qsum[c0 + lane] : 0;
-    const int nbits = lane < nc ? G.k + q : 0;
-    const int start = sl_wave_iscan(nbits) - nbits;                      // lanes 0..15 matter
-    for (unsigned w = lane; w < nw + 1u; w += 64) run[w] = 0u;
-    sl_wave_sync();
-    for (int i = 0; i < nc; ++i) {
-        const int s = __builtin_amdgcn_readlane(start, i), n = __builtin_amdgcn_readlane(nbits, i);
-        const unsigned *src = A.uvec + (size_t)(c0 + i) * G.ua;
-        const int words = (n + 31) >> 5, sh = s & 31;
-        for (int j = lane; j < words; j += 64) {
-            unsigned w = src[j];
-            const int left = n - 32 * j;                                  // bits of this word that belong to the vector
-            if (left < 32) w &= (1u << left) - 1u;
-            sl_lds_or(&run[(s >> 5) + j], w << sh);
-            if (sh) sl_lds_or(&run[(s >> 5) + j + 1], w >> (32 - sh));
-        }
-    }
-    sl_wave_sync();
-    unsigned *dst = reinterpret_cast<unsigned *>(A.out + G.section) + base;
-    for (unsigned w = lane; w < nw; w += 64) dst[w] = run[w];
-    unsigned char *entry = A.out + td.cdir_off + (long long)g.local_group * G.dent;
-    if (lane == 0) *reinterpret_cast<unsigned *>(entry) = (unsigned)base;
-    if (lane < SL_RICE_GROUP) {
-        if (G.qf == 1) entry[4 + lane] = (unsigned char)q;
-        else reinterpret_cast<unsigned short *>(entry + 4)[lane] = (unsigned short)q;
-    }
+    sl_coded_place(A, gi, place_lds + (size_t)wave * (SL_RICE_GROUP * A.G.ua + 1));
 }
 
 // ------------------------------------------------------------------ transcoder, plain -> coded
@@ -223,39 +111,30 @@ int launched()
 
 }  // namespace
 
-// The passes that finish a coded buffer once its writers have run (see the top of this file).
+int slk_coded_scan(const sl_plan *p, unsigned char *out, unsigned char *ws, hipStream_t st)
+{
+    hipLaunchKernelGGL(k_coded_scan_tensor, dim3(p->n_tensors), dim3(SCAN_THREADS), 0, st, sl_coded_args(p, out, ws));
+    return launched();
+}
+
+int slk_coded_place(const sl_plan *p, unsigned char *out, unsigned char *ws, hipStream_t st)
+{
+    int wpb = 4;
+    const size_t per_wave = sl_coded_place_words(p->cg) * sizeof(unsigned);
+    while (wpb > 1 && per_wave * wpb > 65536) wpb >>= 1;
+    hipLaunchKernelGGL(k_coded_place, dim3((unsigned)((p->n_groups + wpb - 1) / wpb)), dim3(64 * wpb), per_wave * wpb, st,
+                       sl_coded_args(p, out, ws));
+    return launched();
+}
+
+// The steps that finish a coded buffer once its writers have run, as launches of their own.
 int slk_coded_finish(const sl_plan *p, unsigned char *out, unsigned char *ws, hipStream_t st)
 {
-    CodedArgs A;
-    A.G = p->cg;
-    A.desc = p->d_desc;
-    A.tensors = p->d_tensors;
-    A.groups = p->d_groups;
-    A.n_groups = p->n_groups;
-    A.n_chunks = p->n_chunks;
-    A.n_tensors = p->n_tensors;
-    A.uvec = reinterpret_cast<const unsigned *>(ws + p->ws_uvec);
-    A.qsum = reinterpret_cast<const unsigned short *>(ws + p->ws_qsum);
-    A.gwords = reinterpret_cast<unsigned *>(ws + p->ws_gwords);
-    A.goff = reinterpret_cast<unsigned *>(ws + p->ws_goff);
-    A.twords = reinterpret_cast<unsigned long long *>(ws + p->ws_twords);
-    A.out = out;
     int rc;
-    if (p->n_groups > 0) {
-        hipLaunchKernelGGL(k_coded_scan_tensor, dim3(p->n_tensors), dim3(256), 0, st, A);
-        if ((rc = launched())) return rc;
-    }
-    hipLaunchKernelGGL(k_coded_scan_list, dim3(1), dim3(64), 0, st, A);
+    if (p->n_groups > 0 && (rc = slk_coded_scan(p, out, ws, st))) return rc;
+    hipLaunchKernelGGL(k_coded_scan_list, dim3(1), dim3(64), 0, st, sl_coded_args(p, out, ws));
     if ((rc = launched())) return rc;
-    if (p->n_groups > 0) {
-        int wpb = 4;
-        const size_t per_wave = ((size_t)SL_RICE_GROUP * p->cg.ua + 1) * sizeof(unsigned);
-        while (wpb > 1 && per_wave * wpb > 65536) wpb >>= 1;
-        hipLaunchKernelGGL(k_coded_place, dim3((unsigned)((p->n_groups + wpb - 1) / wpb)), dim3(64 * wpb),
-                           per_wave * wpb, st, A);
-        if ((rc = launched())) return rc;
-    }
-    return SL_OK;
+    return p->n_groups > 0 ? slk_coded_place(p, out, ws, st) : SL_OK;
 }
 
 int slk_rice_encode(const sl_plan *p, const unsigned char *payload, unsigned char *out,

@@ -146,7 +146,7 @@ int slk_select(const sl_plan *p, float *e, const float *delta, const float *thet
 int slk_select_random(const sl_plan *p, float *e, const float *delta, float beta, int frozen,
                       const unsigned char *pending, unsigned char *payload, unsigned char *ws, unsigned seed,
                       hipStream_t st);
-// B, C, D and (unless skip_residual) E
+// B, C, D and (unless skip_residual) E; with `coded` also the placement steps of the coded buffer
 int slk_quantize(const sl_plan *p, float *e, int skip_residual, unsigned char *payload, unsigned char *coded,
                  unsigned char *ws, hipStream_t st);
 // E on its own: e[idx] -= LUT[code] for the entries of `payload`
@@ -166,8 +166,11 @@ int slk_pack_bits(const uint16_t *idx, const uint8_t *codes, const float *values
                   int bits, unsigned char *out, hipStream_t st);
 int slk_rice_encode(const sl_plan *p, const unsigned char *payload, unsigned char *out,
                     unsigned char *ws, hipStream_t st);
-// coded wire format: the passes that place the quotient bit vectors once a buffer's writers have run
+// coded wire format: the steps that place the quotient bit vectors once a buffer's writers have run (all of
+// them; the first; the last)
 int slk_coded_finish(const sl_plan *p, unsigned char *out, unsigned char *ws, hipStream_t st);
+int slk_coded_scan(const sl_plan *p, unsigned char *out, unsigned char *ws, hipStream_t st);
+int slk_coded_place(const sl_plan *p, unsigned char *out, unsigned char *ws, hipStream_t st);
 // mode 0: theta update from R coded payloads; 1: with the global momentum `mom`; 2: payloads[0] decoded into `plain`
 int slk_apply_coded(const sl_plan *p, int mode, float *theta, float *mom, float mu, unsigned char *plain,
                     const void *const *payloads, const size_t *bytes, int R, float lr, hipStream_t st);

@@ -14,93 +14,133 @@
 // leaves, produced by kernels A and C) and a tree over the chunk leaves in
 // chunk order.  Both trees pad with +0.0 to a power of two and add adjacent
 // pairs, so the result does not depend on scheduling.
-#include "sl_device.h"
-#include "sl_internal.h"
+#include <algorithm>
+
+#include "sl_coded.h"
 
 namespace {
 
-constexpr int RED_THREADS = 1024;
-constexpr int RED_TILE = 4 * RED_THREADS;   // leaves reduced per block iteration
+constexpr int RED_THREADS = 1024, RED_WAVES = RED_THREADS / 64;
+constexpr int RED_TILE = 4 * RED_THREADS;   // leaves that the block's threads read at a time
+constexpr int RED_TILES = 16;               // tiles whose partial sums are kept before they are summed in turn
+
+typedef double red_d2 __attribute__((ext_vector_type(2), aligned(8)));   // one 16-byte access, 8-byte aligned
 
 struct RedShared {
-    double wsum[RED_THREADS / 64];
-    double stack[40];
-    double result;
-    unsigned long long cnt[4];
+    double part[2][RED_TILES * RED_WAVES];  // sums of 256 consecutive leaves
+    double stack[2][40];
+    double result[2];
+    unsigned long long cnt;
 };
 
-// Adjacent-pair tree over leaf[0..n) padded with +0.0 (to a multiple of 4096 and
-// then to a power of two; extra +0.0 leaves do not change a sum).  Called by all
-// RED_THREADS threads of the block; returns the sum to every thread.
-__device__ double block_tree_sum(const double *leaf, long long n, RedShared &sh)
+// Adjacent-pair trees over leaf[s][0 .. n), s < NS, padded with +0.0 to a power of two (of at least
+// 65536; extra +0.0 leaves do not change a sum).  Called by all RED_THREADS threads of the block;
+// the sums come back to every thread.
+// What bounds it: latency, one block per tensor and bin; with hundreds of small tensors the number of
+// instructions of a block.  The waves read all tiles of 4096 leaves without waiting for each other,
+// four loads of 32 bytes per lane under way together, and meet once per 65536 leaves (with a barrier
+// pair per tile and one sum after the other the statistics of a 25,152-chunk tensor took 17.7 us, the
+// centroids 21); a wave without leaves only writes its zero.
+template <int NS>
+__device__ void block_tree_sums(const double *const (&leaf)[NS], long long n, RedShared &sh, double (&sum)[NS])
 {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const long long tiles = n > 0 ? (n + RED_TILE - 1) / RED_TILE : 1;
-    long long pushed = 0;
-    for (long long tile = 0; tile < tiles; ++tile) {
-        const long long b = tile * RED_TILE + 4ll * tid;
-        const double x0 = b + 0 < n ? leaf[b + 0] : 0.0;
-        const double x1 = b + 1 < n ? leaf[b + 1] : 0.0;
-        const double x2 = b + 2 < n ? leaf[b + 2] : 0.0;
-        const double x3 = b + 3 < n ? leaf[b + 3] : 0.0;
-        double v = (x0 + x1) + (x2 + x3);
-        v = sl_wave_tree(v, 6);
-        if (lane == 0) sh.wsum[wave] = v;
-        __syncthreads();
-        if (wave == 0) {
-            double w = lane < RED_THREADS / 64 ? sh.wsum[lane] : 0.0;
-            w = sl_wave_tree(w, 4);
-            if (lane == 0) {
-                // binary-counter stack: combines equal-sized aligned subtrees
-                long long idx = pushed;
-                int lvl = 0;
-                while (idx & 1) {
-                    w = sh.stack[lvl] + w;
-                    idx >>= 1;
-                    ++lvl;
+    constexpr long long SUPER = (long long)RED_TILE * RED_TILES;
+    const long long supers = n > SUPER ? (n + SUPER - 1) / SUPER : 1;
+    auto push = [&](int s, long long idx, double w) {          // binary-counter stack over the supers
+        int lvl = 0;
+        while (idx & 1) {
+            w = sh.stack[s][lvl] + w;
+            idx >>= 1;
+            ++lvl;
+        }
+        sh.stack[s][lvl] = w;
+    };
+    for (long long su = 0; su < supers; ++su) {
+        const long long rest = n - su * SUPER;
+        const int tiles = (int)min((long long)RED_TILES, (rest + RED_TILE - 1) / RED_TILE);
+        constexpr int U = 4 / NS;
+        for (int t0 = 0; t0 < tiles; t0 += U) {
+            const long long first = su * SUPER + (long long)t0 * RED_TILE + 256ll * wave;     // this wave's first leaf
+            if (first >= n) {                                      // (then the later tiles of the wave are empty too)
+                if (lane < U)
+#pragma unroll
+                    for (int s = 0; s < NS; ++s) sh.part[s][(t0 + lane) * RED_WAVES + wave] = 0.0;
+                continue;
+            }
+            double x[U][NS][4];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const long long b = first + (long long)u * RED_TILE + 4ll * lane;
+#pragma unroll
+                for (int s = 0; s < NS; ++s) {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) x[u][s][q] = 0.0;
+                    if (b + 3 < n) {
+                        const red_d2 lo = *reinterpret_cast<const red_d2 *>(leaf[s] + b), hi = *reinterpret_cast<const red_d2 *>(leaf[s] + b + 2);
+                        x[u][s][0] = lo.x, x[u][s][1] = lo.y, x[u][s][2] = hi.x, x[u][s][3] = hi.y;
+                    } else if (b < n) {
+                        x[u][s][0] = leaf[s][b];
+                        if (b + 1 < n) x[u][s][1] = leaf[s][b + 1];
+                        if (b + 2 < n) x[u][s][2] = leaf[s][b + 2];
+                    }
                 }
-                sh.stack[lvl] = w;
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (t0 + u < tiles) {
+#pragma unroll
+                    for (int s = 0; s < NS; ++s) {
+                        const double v = sl_wave_tree((x[u][s][0] + x[u][s][1]) + (x[u][s][2] + x[u][s][3]), 6);
+                        if (lane == 0) sh.part[s][(t0 + u) * RED_WAVES + wave] = v;
+                    }
+                }
+        }
+        __syncthreads();
+        if (wave < NS) {
+            const int have = tiles * RED_WAVES;
+            double p[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) p[q] = 4 * lane + q < have ? sh.part[wave][4 * lane + q] : 0.0;
+            const double w = sl_wave_tree((p[0] + p[1]) + (p[2] + p[3]), 6);
+            if (lane == 0) {
+                push(wave, su, w);
+                if (su == supers - 1) {
+                    long long P = 1;
+                    int top = 0;
+                    while (P < supers) P <<= 1, ++top;
+                    for (long long i = supers; i < P; ++i) push(wave, i, 0.0);      // +0.0 padding
+                    sh.result[wave] = sh.stack[wave][top];
+                }
             }
         }
-        ++pushed;
         __syncthreads();
     }
-    if (tid == 0) {
-        long long P = 1;
-        int top = 0;
-        while (P < tiles) P <<= 1, ++top;
-        for (; pushed < P; ++pushed) {          // +0.0 padding tiles
-            double w = 0.0;
-            long long idx = pushed;
-            int lvl = 0;
-            while (idx & 1) {
-                w = sh.stack[lvl] + w;
-                idx >>= 1;
-                ++lvl;
-            }
-            sh.stack[lvl] = w;
-        }
-        sh.result = sh.stack[top];
-    }
-    __syncthreads();
-    const double r = sh.result;
-    __syncthreads();
-    return r;
+#pragma unroll
+    for (int s = 0; s < NS; ++s) sum[s] = sh.result[s];
 }
 
 // ------------------------------------------------------------------ kernel B
-__global__ void __launch_bounds__(RED_THREADS)
+// One workgroup per tensor: its statistics.  With the coded format a second row of workgroups takes
+// the first placement step (independent of the statistics, and a launch of its own would cost more
+// than its work).
+__global__ void __launch_bounds__(RED_THREADS, 8)
 k_tensor_stats(const SlTensorDev *tensors, const double *leafA, long long n_chunks_total, int k,
-               SlTensorStat *tstat)
+               SlTensorStat *tstat, SlCodedArgs C)
 {
     __shared__ RedShared sh;
+    if (blockIdx.y == 1) {
+        sl_coded_scan_tensor<RED_THREADS>(C, (int)blockIdx.x, reinterpret_cast<unsigned *>(sh.part[0]));
+        return;
+    }
     const SlTensorDev td = tensors[blockIdx.x];
-    const double S1 = block_tree_sum(leafA + td.chunk0, td.n_chunks, sh);
-    const double S2 = block_tree_sum(leafA + n_chunks_total + td.chunk0, td.n_chunks, sh);
+    const double *const leaf[2] = {leafA + td.chunk0, leafA + n_chunks_total + td.chunk0};
+    double S[2];
+    block_tree_sums<2>(leaf, td.n_chunks, sh, S);
     if (threadIdx.x == 0) {
         const double M = (double)(td.n_chunks * (long long)k);
-        const double mu = S1 / M;
-        const double q = S2 / M;
+        const double mu = S[0] / M;
+        const double q = S[1] / M;
         const double p = mu * mu;
         double var = q - p;
         if (var < 0.0) var = 0.0;
@@ -125,6 +165,10 @@ struct CodeArgs {
     const SlCodedDesc *cdesc;
     int rem_bytes;
     int passes;             // passes of 512 entries over a chunk (1 up to k = 512)
+    unsigned code_blocks;   // workgroups with chunks; with the coded format one more takes the list scan
+    unsigned long long *twords;
+    int n_tensors;
+    long long section;
 };
 
 // Value of lane i ^ (1 << L), exactly (sl_partner's mirrors only do where the lanes of a quad hold the
@@ -259,6 +303,10 @@ __global__ void __launch_bounds__(256) k_codes(CodeArgs A)
     constexpr bool WIDE = E * LPC > 128;     // a bin's count needs more than 8 bits
     const int lane = threadIdx.x & 63, k = A.k;
     const int wave = sl_uniform((int)(threadIdx.x >> 6));
+    if (blockIdx.x == A.code_blocks) {
+        if (wave == 0) sl_coded_scan_list(A.twords, A.n_tensors, A.section, A.coded);
+        return;
+    }
     const long long cw = ((long long)blockIdx.x * (blockDim.x >> 6) + wave) * CPW;
     if (cw >= A.n_chunks) return;
     const int sub = lane & (LPC - 1);
@@ -412,29 +460,43 @@ codes_kernel codes_for(int log_lpc)
 }
 
 // ------------------------------------------------------------------ kernel D
-// One workgroup per (tensor, bin): fixed-tree sum of the bin's leaves, integer
-// count, centroid -> LUT[b] in the tensor block's header.
-__global__ void __launch_bounds__(RED_THREADS)
-k_tensor_lut(const SlTensorDev *tensors, const double *leafC, const unsigned *cnt,
+// One workgroup per (tensor, bin): fixed-tree sum of the bin's leaves, integer count, centroid ->
+// LUT[b] in the tensor block's header.  With the coded format further workgroups take the last
+// placement step, `place_waves` groups each.
+template <bool PLACE>
+__global__ void __launch_bounds__(RED_THREADS, 8)
+k_tensor_lut(const SlTensorDev *tensors, int n_tensors, const double *leafC, const unsigned *cnt,
              long long n_chunks_total, int hdr_bytes, int rec_bytes, int nbins, unsigned char *payload,
-             unsigned char *coded, int cfix)
+             unsigned char *coded, int cfix, SlCodedArgs C, int place_waves)
 {
     __shared__ RedShared sh;
-    const SlTensorDev td = tensors[blockIdx.x];
-    const int b = blockIdx.y;
+    extern __shared__ __align__(16) unsigned place_lds[];
     const int tid = threadIdx.x;
-    if (tid == 0) sh.cnt[0] = 0ull;
+    const int b = blockIdx.y;
+    if (PLACE && (int)blockIdx.x >= n_tensors) {
+        const int wave = sl_uniform(tid >> 6);
+        const long long gi = ((long long)((int)blockIdx.x - n_tensors) * nbins + b) * place_waves + wave;
+        if (wave < place_waves && gi < C.n_groups)
+            sl_coded_place(C, gi, place_lds + (size_t)wave * (SL_RICE_GROUP * C.G.ua + 1));
+        return;
+    }
+    const SlTensorDev td = tensors[blockIdx.x];
+    if (tid == 0) sh.cnt = 0ull;
     __syncthreads();
     unsigned long long part = 0;
-    for (long long i = tid; i < td.n_chunks; i += RED_THREADS)
-        part += cnt[b * n_chunks_total + td.chunk0 + i];
+    const unsigned *cb = cnt + b * n_chunks_total + td.chunk0;
+    for (long long i = tid; i < td.n_chunks; i += RED_THREADS) part += cb[i];
+    if (64 * (tid >> 6) < td.n_chunks) {                        // (a wave without chunks has nothing to add)
 #pragma unroll
-    for (int s = 32; s >= 1; s >>= 1) part += __shfl_xor(part, s);
-    if ((tid & 63) == 0 && part) atomicAdd(&sh.cnt[0], part);   // integer: order-free
-    __syncthreads();
-    const double Sb = block_tree_sum(leafC + b * n_chunks_total + td.chunk0, td.n_chunks, sh);
+        for (int l = 0; l < 6; ++l) part += sl_partner(part, l);
+    }
+    if ((tid & 63) == 0 && part) atomicAdd(&sh.cnt, part);      // integer: order-free
+    const double *const leaf[1] = {leafC + b * n_chunks_total + td.chunk0};
+    double S[1];
+    block_tree_sums<1>(leaf, td.n_chunks, sh, S);               // (its barriers are behind the additions above)
+    const double Sb = S[0];
     if (tid == 0) {
-        const unsigned long long nb = sh.cnt[0];
+        const unsigned long long nb = sh.cnt;
         float cen = nb ? (float)(Sb / (double)nb) : 0.0f;
         if (cen == 0.0f) cen = 0.0f;        // never -0.0f on the wire
         reinterpret_cast<float *>(payload + td.pay_off)[b] = cen;
@@ -452,10 +514,16 @@ k_tensor_lut(const SlTensorDev *tensors, const double *leafC, const unsigned *cn
     if (coded && b == 0 && tid < td.cblk_bytes - cused) coded[td.cblk_off + cused + tid] = 0;
 }
 
-// Unquantized values: there is no table, only the block padding is left to write.
+// Unquantized values: there is no table, only the block padding is left to write; with the coded
+// format one more workgroup takes the list scan.
 __global__ void __launch_bounds__(64)
-k_pad_blocks(const SlTensorDev *tensors, int rec_bytes, unsigned char *payload, unsigned char *coded, int cfix)
+k_pad_blocks(const SlTensorDev *tensors, int n_tensors, int rec_bytes, unsigned char *payload, unsigned char *coded,
+             int cfix, SlCodedArgs C)
 {
+    if ((int)blockIdx.x == n_tensors) {
+        sl_coded_scan_list(C.twords, C.n_tensors, C.G.section, C.out);
+        return;
+    }
     const SlTensorDev td = tensors[blockIdx.x];
     const long long used = td.n_chunks * (long long)rec_bytes;
     if ((long long)threadIdx.x < td.block_bytes - used) payload[td.pay_off + used + threadIdx.x] = 0;
@@ -538,6 +606,7 @@ int slk_quantize(const sl_plan *p, float *e, int skip_residual, unsigned char *p
 {
     if (p->n_chunks == 0) return SL_OK;
     const int k = p->k;
+    const SlCodedArgs placing = sl_coded_args(p, coded, ws);     // (used only with `coded`)
     const float *vals = reinterpret_cast<const float *>(ws + p->ws_vals);
     double *leafA = reinterpret_cast<double *>(ws + p->ws_leafA);
     double *leafC = reinterpret_cast<double *>(ws + p->ws_leafC);
@@ -547,19 +616,24 @@ int slk_quantize(const sl_plan *p, float *e, int skip_residual, unsigned char *p
 
     if (p->bits == 32) {
         // nothing to quantize: kernel A wrote the values into the records
-        hipLaunchKernelGGL(k_pad_blocks, dim3(p->n_tensors), dim3(64), 0, st, p->d_tensors, p->rec_bytes,
-                           payload, coded, p->cg.cfix);
+        if (coded && (rc = slk_coded_scan(p, coded, ws, st))) return rc;
+        hipLaunchKernelGGL(k_pad_blocks, dim3(p->n_tensors + (coded ? 1 : 0)), dim3(64), 0, st, p->d_tensors,
+                           p->n_tensors, p->rec_bytes, payload, coded, p->cg.cfix, placing);
         if ((rc = check_launch())) return rc;
         sl_prof_mark(p, SL_PROF_LUT, st);
         if (!skip_residual) {
             if ((rc = launch_residual(p, e, vals, payload, st))) return rc;
             sl_prof_mark(p, SL_PROF_RESIDUAL, st);
         }
+        if (coded) {
+            if ((rc = slk_coded_place(p, coded, ws, st))) return rc;
+            sl_prof_mark(p, SL_PROF_INDEX, st);
+        }
         return SL_OK;
     }
 
-    hipLaunchKernelGGL(k_tensor_stats, dim3(p->n_tensors), dim3(RED_THREADS), 0, st, p->d_tensors,
-                       leafA, (long long)p->n_chunks, k, tstat);
+    hipLaunchKernelGGL(k_tensor_stats, dim3(p->n_tensors, coded ? 2 : 1), dim3(RED_THREADS), 0, st, p->d_tensors,
+                       leafA, (long long)p->n_chunks, k, tstat, placing);
     if ((rc = check_launch())) return rc;
     sl_prof_mark(p, SL_PROF_STATS, st);
 
@@ -583,13 +657,22 @@ int slk_quantize(const sl_plan *p, float *e, int skip_residual, unsigned char *p
                             : p->bits == 3 ? codes_for<3>(log_lpc) : codes_for<4>(log_lpc);
     const long long per_wave = 64 >> log_lpc;
     const long long per_block = 4ll * per_wave;
-    hipLaunchKernelGGL(fn, dim3((unsigned)((p->n_chunks + per_block - 1) / per_block)), dim3(256), 0, st, C);
+    C.code_blocks = (unsigned)((p->n_chunks + per_block - 1) / per_block);
+    C.twords = placing.twords;
+    C.n_tensors = p->n_tensors;
+    C.section = p->cg.section;
+    hipLaunchKernelGGL(fn, dim3(C.code_blocks + (coded ? 1 : 0)), dim3(256), 0, st, C);
     if ((rc = check_launch())) return rc;
     sl_prof_mark(p, SL_PROF_CODES, st);
 
-    hipLaunchKernelGGL(k_tensor_lut, dim3(p->n_tensors, 1 << p->bits), dim3(RED_THREADS), 0, st,
-                       p->d_tensors, leafC, cnt, (long long)p->n_chunks, p->hdr_bytes, p->rec_bytes,
-                       1 << p->bits, payload, coded, p->cg.cfix);
+    const int nbins = 1 << p->bits;
+    const size_t per_wave_lds = sl_coded_place_words(p->cg) * sizeof(unsigned);
+    const int place_waves = coded ? (int)std::max<size_t>(1, std::min<size_t>(RED_WAVES, 49152 / per_wave_lds)) : 0;
+    const long long per_column = (long long)place_waves * nbins;      // groups that one column of workgroups takes
+    const long long place_columns = coded ? (p->n_groups + per_column - 1) / per_column : 0;
+    hipLaunchKernelGGL(coded ? k_tensor_lut<true> : k_tensor_lut<false>, dim3((unsigned)(p->n_tensors + place_columns), nbins), dim3(RED_THREADS),
+                       place_waves * per_wave_lds, st, p->d_tensors, p->n_tensors, leafC, cnt, (long long)p->n_chunks,
+                       p->hdr_bytes, p->rec_bytes, nbins, payload, coded, p->cg.cfix, placing, place_waves);
     if ((rc = check_launch())) return rc;
     sl_prof_mark(p, SL_PROF_LUT, st);
 
