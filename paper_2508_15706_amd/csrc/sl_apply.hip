@@ -10,6 +10,8 @@
 // conflicts, workers are added in the order r = 0..R-1, and theta streams
 // through registers once (8 bytes per element of HBM traffic plus R*7k/4 bytes
 // per chunk).
+#include <algorithm>
+
 #include "sl_device.h"
 #include "sl_internal.h"
 
@@ -28,11 +30,13 @@ namespace {
 #ifndef SL_APPLY_OCTETS_FROM
 #define SL_APPLY_OCTETS_FROM 256   // k from which a lane decodes eight entries at a time
 #endif
-#ifndef SL_APPLY_QUADS_FROM
-#define SL_APPLY_QUADS_FROM 136    // ... or four (2-bit records with many entries to decode per chunk)
-#endif
-#ifndef SL_APPLY_QUADS_ENTRIES
-#define SL_APPLY_QUADS_ENTRIES 2048     // ... R * k from which that holds below k = 256
+// The direct route of 2-bit records below that: where a chunk has so many entries to decode (R * k).
+// From k = 136 a worker's lanes fill half the wave or more; below, up to four workers share it and add
+// one after the other, which pays later (24,000 chunks, the other routes / direct: k = 136, R = 16
+// 199 / 179 us, k = 200, R = 32 421 / 285; k = 128, R = 16 169 / 173, k = 96, R = 32 339 / 195,
+// k = 128, R = 32 355 / 198, k = 64, R = 32 181 / 193, k = 64, R = 64 419 / 286).
+#ifndef SL_APPLY_DIRECT_ENTRIES
+#define SL_APPLY_DIRECT_ENTRIES(k) ((k) >= 136 ? 2048 : 3072)
 #endif
 #ifndef SL_APPLY_PF1
 #define SL_APPLY_PF1 16     // words per lane fetched ahead of the theta loads on the entry-by-entry route (2-bit codes)
@@ -62,8 +66,9 @@ struct ApplyArgs {
     int R, k;
     int bits, hdr_bytes, rec_bytes;   // value width and the sizes that follow from it
     int batch;               // records staged per round
-    int quads;               // eight-entry route, 2-bit format: four entries per lane instead (up to k = 256: a
-                             // worker's record then spans up to 64 lanes instead of 32, in one round)
+    // direct route: lanes of one worker's record (k / 8), workers side by side in the wave, steps per worker
+    int dl, dw, dp;
+    unsigned magic_dl;       // floor(2^32 / dl) + 1
     // x / d for the staging loops without a division: __umulhi(x, floor(2^32 / d) + 1) is
     // exact while x * d < 2^32 (x < 16384 here); d = words per (table + record padded to whole words)
     unsigned magic_src;
@@ -81,12 +86,17 @@ struct ApplyArgs {
 // ROUTE: how a staged record's entries reach the accumulators.
 //   0 (k <= 128, one pass): the entries of several workers are decoded ahead of the additions;
 //   1: entry by entry, one worker at a time;
-//   2 (k >= 256, a multiple of 8): a lane decodes eight consecutive entries from whole words.
+//   2 (k >= 256, a multiple of 8): a lane decodes eight consecutive entries from whole words; with 2-bit
+//      codes ("direct", also below k = 256 with many workers) it loads those words from the payload itself, a
+//      batch of eight steps ahead, and no record passes through LDS.  Bound by instruction issue and, at two
+//      waves per SIMD, by what one wave has in flight: staging the records 4 KB at a time cost a dozen
+//      instructions per word and a trip to memory per batch (123,505 chunks, k = 1024, R = 8: 1363 us, direct
+//      1024; 24,000 chunks, k = 512, R = 16: 289 and 223).
 // The routes are separate instantiations, so that none pays for another's registers.
 template <bool TWO_BIT, bool NESTEROV, int NH, int ROUTE>
 __global__ void __launch_bounds__(256) k_apply(ApplyArgs A)
 {
-    constexpr bool SMALLK = ROUTE == 0, OCTETS = ROUTE == 2;
+    constexpr bool SMALLK = ROUTE == 0, OCTETS = ROUTE == 2, DIRECT = OCTETS && TWO_BIT;
     static_assert(ROUTE == 1 || NH == 1, "two halves go entry by entry");
     constexpr int ACC_FLOATS = SL_CHUNK / NH, ROWS4 = 16 / NH;   // accumulators, 16-byte accesses per lane
     extern __shared__ __align__(16) unsigned char smem_all[];
@@ -157,10 +167,52 @@ __global__ void __launch_bounds__(256) k_apply(ApplyArgs A)
     // (wider records at other widths: 3 KB; many workers at small k, the entry-by-entry route, and
     // the eight-entry route: 4 KB, which is all that is staged at a time there)
     constexpr int PF = ROUTE == 2 ? 16 : !TWO_BIT ? 12 : ROUTE == 1 ? SL_APPLY_PF1 : 8;
-    unsigned pf[PF];
+    unsigned pf[DIRECT ? 1 : PF];
     const int nb0 = min(A.batch, A.R);
+    if constexpr (!DIRECT) {
 #pragma unroll
-    for (int u = 0; u < PF; ++u) pf[u] = src_word(0, lane + 64 * u, nb0 * wpr);
+        for (int u = 0; u < PF; ++u) pf[u] = src_word(0, lane + 64 * u, nb0 * wpr);
+    }
+    // Direct route.  Step s of a chunk: lane (i, o) of the wave loads entries 8o .. 8o+7 (64 lanes further on
+    // in each of the dp steps of a worker when its record has more) of worker (s / dp) dw + i: three words
+    // of indices - four, when the record starts in the middle of a word - and 16 bits of codes.  A batch is
+    // DS steps; the first one is under way before the theta loads, each step of a later one is loaded
+    // as soon as the step before it in the same registers has been added.
+    constexpr int DS = DIRECT ? 8 : 1;
+    unsigned dx[DS][4];
+    float dlut = 0.f;
+    const int di = DIRECT ? (A.dl <= 64 ? (A.dl == 1 ? lane : (int)__umulhi((unsigned)lane, A.magic_dl)) : 0) : 0;
+    const int steps = DIRECT ? ((A.R + A.dw - 1) / A.dw) * A.dp : 0;
+    const int per_batch = DIRECT ? min(DS / A.dp, 16 / A.dw) * A.dw : 0;      // workers of a batch: 16 tables at most
+    auto direct_load = [&](int st, unsigned (&x)[4]) __attribute__((always_inline)) {
+        const int g = A.dp == 1 ? st : A.dp == 2 ? st >> 1 : A.dp == 4 ? st >> 2 : st >> 3;
+        const int w = g * A.dw + di, o = A.dl <= 64 ? lane - di * A.dl : 64 * (st - g * A.dp) + lane;
+        const bool live = st < steps && di < A.dw && w < A.R && o < A.dl;
+        const sl_gbytes p = payload_of(live ? w : 0) + rec_off;
+        if (live) {
+            const sl_gwords q = reinterpret_cast<sl_gwords>(p - sh) + 3 * o;
+            x[0] = q[0], x[1] = q[1], x[2] = q[2];
+            // (the codes of the record follow its indices: the fourth word still holds bytes of the record)
+            x[3] = *reinterpret_cast<const unsigned short __attribute__((address_space(1))) *>(p + 3 * k / 2 + 2 * o);
+            if (sh != 0u) {
+                const unsigned w3 = q[3];
+                x[0] = __builtin_amdgcn_alignbyte(x[1], x[0], sh);
+                x[1] = __builtin_amdgcn_alignbyte(x[2], x[1], sh);
+                x[2] = __builtin_amdgcn_alignbyte(w3, x[2], sh);
+            }
+        }
+    };
+    auto direct_table = [&](int w0) -> float {       // entry lane % 4 of the table of worker w0 + lane / 4
+        const int w = w0 + (lane >> 2);
+        const bool live = (lane >> 2) < per_batch && w < A.R;
+        const sl_gbytes p = payload_of(live ? w : 0) + lut_off;
+        return live ? reinterpret_cast<const float __attribute__((address_space(1))) *>(p)[lane & 3] : 0.f;
+    };
+    if constexpr (DIRECT) {
+        dlut = direct_table(0);
+#pragma unroll
+        for (int u = 0; u < DS; ++u) direct_load(u, dx[u]);
+    }
 
     sl_f4 th[16], mo[NESTEROV ? 16 : 1];
     float *mc = NESTEROV ? A.mom + d.base : nullptr;
@@ -204,7 +256,63 @@ __global__ void __launch_bounds__(256) k_apply(ApplyArgs A)
         for (int i = 0; i < ROWS4; ++i)
             reinterpret_cast<float4 *>(acc)[i * 64 + lane] = make_float4(0.f, 0.f, 0.f, 0.f);
 
-        for (int r0 = 0; r0 < A.R; r0 += A.batch) {
+        if constexpr (DIRECT) {
+            // (LDS behind the accumulators: the values of two consecutive codes by their four bits, 16 pairs
+            // per worker of the batch; in front of them the tables they are put together from)
+            float *tabs = reinterpret_cast<float *>(stage);
+            float2 *pairs = reinterpret_cast<float2 *>(stage + 256);
+            const int db = per_batch / A.dw * A.dp;  // steps of a batch: whole workers
+            for (int s0 = 0; s0 < steps; s0 += db) {
+                const int w0 = s0 / A.dp * A.dw, nw = min(per_batch, A.R - w0);
+                sl_wave_sync();
+                tabs[lane] = dlut;
+                sl_wave_sync();
+                for (int q = lane; q < 16 * nw; q += 64) {
+                    const float *t = tabs + 4 * (q >> 4);
+                    pairs[q] = make_float2(t[q & 3], t[(q >> 2) & 3]);
+                }
+                if (s0 + db < steps) dlut = direct_table(w0 + per_batch);
+                sl_wave_sync();
+#pragma unroll
+                for (int u = 0; u < DS; ++u) {
+                    if (u < db && s0 + u < steps) {
+                        const int g = A.dp == 1 ? u : A.dp == 2 ? u >> 1 : A.dp == 4 ? u >> 2 : u >> 3;
+                        const int wi = g * A.dw + di, o = A.dl <= 64 ? lane - di * A.dl : 64 * (u - g * A.dp) + lane;
+                        const bool live = di < A.dw && w0 + wi < A.R && o < A.dl;
+                        const unsigned x0 = dx[u][0], x1 = dx[u][1], x2 = dx[u][2], cw = dx[u][3];
+                        unsigned j[8];               // byte offsets of the entries' accumulators
+                        j[0] = (x0 << 2) & 0x3FFCu;
+                        j[1] = (x0 >> 10) & 0x3FFCu;
+                        j[2] = (__builtin_amdgcn_alignbit(x1, x0, 24) << 2) & 0x3FFCu;
+                        j[3] = (x1 >> 2) & 0x3FFCu;
+                        j[4] = (x1 >> 14) & 0x3FFCu;
+                        j[5] = (__builtin_amdgcn_alignbit(x2, x1, 28) << 2) & 0x3FFCu;
+                        j[6] = (x2 >> 6) & 0x3FFCu;
+                        j[7] = (x2 >> 18) & 0x3FFCu;
+                        float v[8];
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            const float2 q2 = pairs[16 * (live ? wi : 0) + ((cw >> (4 * e)) & 15u)];
+                            v[2 * e] = q2.x, v[2 * e + 1] = q2.y;
+                        }
+                        char *ab = reinterpret_cast<char *>(acc);
+                        for (int i = 0; i < A.dw; ++i) {
+                            // the positions of one record are distinct: the reads, then the writes, are issued together
+                            if (live && di == i) {
+                                float t[8];
+#pragma unroll
+                                for (int e = 0; e < 8; ++e) t[e] = *reinterpret_cast<float *>(ab + j[e]);
+#pragma unroll
+                                for (int e = 0; e < 8; ++e) *reinterpret_cast<float *>(ab + j[e]) = t[e] + v[e];
+                            }
+                            sl_wave_sync();          // worker r is complete before worker r+1 is added
+                        }
+                        direct_load(s0 + db + u, dx[u]);
+                    }
+                }
+            }
+        }
+        for (int r0 = 0; !DIRECT && r0 < A.R; r0 += A.batch) {
             const int nb = min(A.batch, A.R - r0);
             sl_wave_sync();
             if (h == 0 || !single) {
@@ -212,7 +320,7 @@ __global__ void __launch_bounds__(256) k_apply(ApplyArgs A)
                 int wb = 0;                       // wave-uniform: word wb + lane is this lane's next
                 if (r0 == 0 && h == 0) {
 #pragma unroll
-                    for (int u = 0; u < PF; ++u) {
+                    for (int u = 0; u < (DIRECT ? 0 : PF); ++u) {
                         const int w = lane + 64 * u;
                         // (the staging pitch is wpr words: word w lands at w)
                         if (w < nw) reinterpret_cast<unsigned *>(stage)[w] = pf[u];
@@ -274,7 +382,7 @@ __global__ void __launch_bounds__(256) k_apply(ApplyArgs A)
                         }
                     }
                 }
-            } else if constexpr (OCTETS) {
+            } else if constexpr (OCTETS && !TWO_BIT) {
                 // Eight consecutive entries per lane: their indices are three aligned words
                 // of the record and their codes `bits` bytes, so a lane decodes them with 4
                 // LDS reads instead of 24 and a fraction of the arithmetic.  The positions
@@ -285,35 +393,6 @@ __global__ void __launch_bounds__(256) k_apply(ApplyArgs A)
                     const float *lutp = reinterpret_cast<const float *>(base);
                     const unsigned *iw = reinterpret_cast<const unsigned *>(base + hdr);
                     const unsigned char *codes = base + hdr + 3 * k / 2;
-                    float l0 = 0.f, l1 = 0.f, l2 = 0.f, l3 = 0.f;
-                    if (TWO_BIT) l0 = lutp[0], l1 = lutp[1], l2 = lutp[2], l3 = lutp[3];
-                    if (TWO_BIT && A.quads) {
-                        // four consecutive entries = 48 bits that start at bit 0 or 16 of a word
-                        for (int q = lane; q < (k >> 2); q += 64) {
-                            const int wi = (3 * q) >> 1;
-                            const unsigned wa = iw[wi], wb = iw[wi + 1], sh = 16u * (q & 1);
-                            const unsigned lo = __builtin_amdgcn_alignbit(wb, wa, sh), hi = wb >> sh;
-                            unsigned jq[4];
-                            jq[0] = lo & 0xFFFu;
-                            jq[1] = (lo >> 12) & 0xFFFu;
-                            jq[2] = (lo >> 24) | ((hi & 0xFu) << 8);
-                            jq[3] = (hi >> 4) & 0xFFFu;
-                            const unsigned cw = codes[q];
-                            float qv[4], tq[4];
-#pragma unroll
-                            for (int e = 0; e < 4; ++e) {
-                                const unsigned cde = cw >> (2 * e);
-                                const float lo_v = (cde & 1u) ? l1 : l0, hi_v = (cde & 1u) ? l3 : l2;
-                                qv[e] = (cde & 2u) ? hi_v : lo_v;
-                            }
-#pragma unroll
-                            for (int e = 0; e < 4; ++e) tq[e] = acc[jq[e] & (ACC_FLOATS - 1)];
-#pragma unroll
-                            for (int e = 0; e < 4; ++e) acc[jq[e] & (ACC_FLOATS - 1)] = tq[e] + qv[e];
-                        }
-                        sl_wave_sync();       // worker r is complete before worker r+1 is added
-                        continue;
-                    }
                     for (int o = lane; o < (k >> 3); o += 64) {
                         const unsigned w0 = iw[3 * o], w1 = iw[3 * o + 1], w2 = iw[3 * o + 2];
                         unsigned jj[8];
@@ -326,15 +405,7 @@ __global__ void __launch_bounds__(256) k_apply(ApplyArgs A)
                         jj[6] = (w2 >> 8) & 0xFFFu;
                         jj[7] = w2 >> 20;
                         float qq[8];
-                        if (TWO_BIT) {
-                            const unsigned cw = reinterpret_cast<const unsigned short *>(codes)[o];
-#pragma unroll
-                            for (int e = 0; e < 8; ++e) {
-                                const unsigned cde = cw >> (2 * e);
-                                const float lo = (cde & 1u) ? l1 : l0, hi = (cde & 1u) ? l3 : l2;
-                                qq[e] = (cde & 2u) ? hi : lo;
-                            }
-                        } else if (bits == 32) {
+                        if (bits == 32) {
 #pragma unroll
                             for (int e = 0; e < 8; ++e) qq[e] = reinterpret_cast<const float *>(codes)[8 * o + e];
                         } else {
@@ -634,22 +705,22 @@ int slk_apply(const sl_plan *p, float *theta, float *mom, float mu, const void *
     A.rec_bytes = p->rec_bytes;
     const int rec_pad = ((p->rec_bytes + 3) & ~3) + p->hdr_bytes;
     // at most 16 KB of staged records; 4 KB on the eight-entry route (measured against 2, 8 and 16 KB:
-    // more waves per compute unit outweigh the extra staging rounds), and whenever a record alone is large
-    // ... and, four entries per lane, 2-bit records from k = 136 when there is much to decode (measured at
-    // 16 workers: k = 160 0.90 -> 0.83 ms, k = 192 1.31 -> 0.86 ms; below 2048 entries per chunk the two-halves
-    // route is as fast or faster)
+    // more waves per compute unit outweigh the extra staging rounds), and whenever a record alone is large.
+    // 2-bit records take the direct route from k = 256, and below when there is much to decode.
     const bool octets = (p->k & 7) == 0 &&
                         (p->k >= SL_APPLY_OCTETS_FROM ||
-                         (p->bits == 2 && p->k >= SL_APPLY_QUADS_FROM && (long long)R * p->k >= SL_APPLY_QUADS_ENTRIES));
+                         (p->bits == 2 && (long long)R * p->k >= SL_APPLY_DIRECT_ENTRIES(p->k)));
+    const bool direct = octets && p->bits == 2;
+    A.dl = p->k >> 3;
+    A.dw = std::max(1, std::min(4, 64 / std::max(1, A.dl)));
+    A.dp = 1;
+    while (64 * A.dp < A.dl) A.dp <<= 1;
+    A.magic_dl = A.dl > 1 ? (unsigned)(0x100000000ull / (unsigned)A.dl + 1) : 0u;
     int batch = (rec_pad > 1024 || octets ? SL_APPLY_BIG_STAGE : 16384) / rec_pad;
     if (batch < 1) batch = 1;
     if (batch > R) batch = R;
     A.batch = batch;
     A.magic_src = (unsigned)(0x100000000ull / (unsigned)(rec_pad >> 2) + 1);
-#ifndef SL_APPLY_QUADS_BELOW
-#define SL_APPLY_QUADS_BELOW 257
-#endif
-    A.quads = octets && p->bits == 2 && p->k < SL_APPLY_QUADS_BELOW;
     for (int r = 0; r < SL_MAX_WORKERS; ++r)
         A.payload[r] = r < R ? static_cast<const unsigned char *>(payloads[r]) : nullptr;
     A.n_chunks = p->n_chunks;
@@ -657,13 +728,15 @@ int slk_apply(const sl_plan *p, float *theta, float *mom, float mu, const void *
     // (not on the eight-entry route: with 4 KB staged at a time the halves would fetch every record twice)
     const bool halves = (long long)R * p->k >= SL_APPLY_HALVES_FROM && (size_t)batch * rec_pad <= 8192 && !octets;
     const size_t acc_bytes = SL_CHUNK * sizeof(float) / (halves ? 2 : 1);
-    A.lds_per_wave = (int)((acc_bytes + (size_t)batch * rec_pad + 15) & ~(size_t)15);
+    // (direct: 16 tables of 16 bytes, 128 bytes of value pairs per worker of a batch)
+    const size_t stage_bytes = direct ? 256 + 128 * (size_t)std::min(R, std::min(8 / A.dp, 16 / A.dw) * A.dw) : (size_t)batch * rec_pad;
+    A.lds_per_wave = (int)((acc_bytes + stage_bytes + 15) & ~(size_t)15);
     int wpb = 4;
     while (wpb > 1 && (size_t)A.lds_per_wave * wpb > (size_t)p->max_lds) wpb >>= 1;
     const size_t lds = (size_t)A.lds_per_wave * wpb;
     const bool two = p->bits == 2;
     typedef void (*kernel_t)(ApplyArgs);
-    const int route = (!halves && p->k <= 128) ? 0 : !octets ? 1 : 2;
+    const int route = octets ? 2 : (!halves && p->k <= 128) ? 0 : 1;
 #define SL_APPLY_ROUTES(TWO, NEST) \
     {k_apply<TWO, NEST, 1, 0>, k_apply<TWO, NEST, 1, 1>, k_apply<TWO, NEST, 1, 2>, k_apply<TWO, NEST, 2, 1>}
     static const kernel_t table[2][2][4] = {{SL_APPLY_ROUTES(false, false), SL_APPLY_ROUTES(false, true)},
