@@ -9,21 +9,35 @@
 //   1. lane r reads worker r's directory entry: where the chunk's quotient bit vector lies;
 //   2. the workers' fixed records (table, remainders, value fields) and bit vectors are staged
 //      in LDS with coalesced loads, the first of them fetched ahead of the theta loads;
-//   3. every lane takes one 32-bit word of some worker's vector and lists its zero bits: the
-//      i-th zero of a vector, at bit z, ends entry i, whose quotients so far sum to z - i
-//      (ranks from one prefix sum over the words' zero counts);
-//   4. every lane takes 8 consecutive entries of some worker: their remainders are b bytes of
-//      the record, a prefix sum over the lanes of a worker completes
-//      idx_i = i + ((z_i - i) << b) + r_0 + ... + r_i, written back as 16-bit indices;
-//   5. the additions, worker by worker, from those index lists.
+//   3. every lane takes one 32-bit word of some worker's vector, counts its zero bits and, from one
+//      prefix sum over the counts, writes down where every eighth zero of the vector lies (the byte,
+//      and how many zeros of that byte come before it);
+//   4. every lane takes 8 consecutive entries of some worker: it finds the first one's zero bit from that
+//      note, the others in the 64 bits behind it; the i-th zero of a vector, at bit z, ends entry i,
+//      whose quotients so far sum to z - i.  The entries' remainders are b bytes of the record, a prefix
+//      sum over the lanes of a worker completes idx_i = i + ((z_i - i) << b) + r_0 + ... + r_i;
+//   5. the same lanes add their entries, worker by worker.
+// With few entries per chunk (LISTS) step 3 lists every zero of the words instead, step 4 turns that
+// list into one of 16-bit indices and step 5 adds an entry per lane from it: more work, a shorter chain.
 // Steps 3 and 4 run for all workers of a batch at once, so their cost per chunk hardly grows
 // with R; only step 5 is a chain over the workers.
+// What bounds it: above R * k of about 1024 entries per chunk the number of instructions, two waves per
+// SIMD sharing the issue slots (LDS: 16 KB of accumulators per wave).  With lists everywhere, a lane per
+// word of the longest possible vector and as many turns as the fullest word has zeros, a chunk at k = 256,
+// R = 16 took 3500 vector and 1233 scalar instructions (1398 us for 123,505 chunks).
 #include "sl_coded.h"
 
 namespace {
 
 #ifndef SL_CAPPLY_STAGE
 #define SL_CAPPLY_STAGE 4096      // LDS bytes for one batch of staged workers
+#endif
+// Up to k = 128 with fewer than so many entries per chunk (R * k) the entries go through index lists in
+// LDS: the decode is short there and hidden behind the theta loads, what is left is the length of its
+// chain (24,000 chunks, lists / the other form: k = 64, R = 8 165 / 167 us; k = 128, R = 8 174 / 170;
+// k = 96, R = 16 243 / 178; k = 64, R = 32 245 / 214).
+#ifndef SL_CAPPLY_LISTS_BELOW
+#define SL_CAPPLY_LISTS_BELOW 1024
 #endif
 #ifndef SL_CAPPLY_PFF
 #define SL_CAPPLY_PFF 4           // words per lane fetched ahead of the theta loads: tables and fixed records,
@@ -48,7 +62,8 @@ struct CodedApplyArgs {
     unsigned magic_l;        // floor(2^32 / d) + 1 for d = lanes per worker in step 4
     int lpw_log2;            // staging: log2 of the lanes that fetch one worker's words (64 / lanes >= batch)
     int uwp_log2;            // log2 of the slots per worker in step 3 (a power of two >= G.ua)
-    int E;                   // entries per lane in step 4: 8, or 4 when k is not a multiple of 8
+    int E;                   // index lists: entries per lane in step 4, 8, or 4 when k is not a multiple of 8
+    int off_t, off_q, off_h; // a slot's table of every eighth zero, its value pairs, its index list (bytes)
     int rec_bytes;           // MODE 2: bytes of a plain record
     int lds_per_wave;
     long long n_chunks;
@@ -58,9 +73,24 @@ struct CodedApplyArgs {
 
 SL_DEV void acc_add(float *acc, unsigned j, float q) { acc[j] = acc[j] + q; }
 
+// Place of the set bit of byte x that has n set bits below it, by halving.
+SL_DEV int place_in_byte(unsigned x, int n)
+{
+    const int c4 = __builtin_popcount(x & 15u);
+    const bool up4 = n >= c4;
+    n -= up4 ? c4 : 0;
+    x = up4 ? x >> 4 : x;
+    const int c2 = __builtin_popcount(x & 3u);
+    const bool up2 = n >= c2;
+    n -= up2 ? c2 : 0;
+    x = up2 ? x >> 2 : x;
+    return (up4 ? 4 : 0) + (up2 ? 2 : 0) + (n >= (int)(x & 1u) ? 1 : 0);
+}
+
 // MODE 0: theta update; 1: with DiLoCo's global Nesterov momentum (Eq. (1)); 2: no update at
 // all - the one payload is decoded into a plain payload (R = 1).
-template <bool TWO_BIT, int MODE>
+// LISTS (few entries): steps 3 to 5 go through index lists in LDS, see the top of the file.
+template <bool TWO_BIT, int MODE, bool LISTS>
 __global__ void __launch_bounds__(256) k_apply_coded(CodedApplyArgs A)
 {
     constexpr bool NESTEROV = MODE == 1, DECODE = MODE == 2;
@@ -78,8 +108,9 @@ __global__ void __launch_bounds__(256) k_apply_coded(CodedApplyArgs A)
     const int bits = TWO_BIT ? 2 : G.bits;
     const int hdr = TWO_BIT ? 16 : G.hdr, hdrw = hdr >> 2;
     const int fwp = A.fwp, uraw = G.ua + 1;
-    // one staged worker: [table header][fixed record][uraw words of the bit vector][k 16-bit values]
-    const int off_u = 4 * fwp, off_h = (off_u + 4 * uraw + 15) & ~15;
+    // one staged worker: [table header][fixed record][uraw words of the bit vector][where every eighth zero
+    // lies, 16 bits each][step 5 by the lanes of step 4, 2-bit codes: the 16 pairs of values][else: indices]
+    const int off_u = 4 * fwp, off_t = A.off_t, off_q = A.off_q, off_h = A.off_h;
 
     float *tc = DECODE ? nullptr : A.theta + d.base;
     const int lr = lane >> 4, lc = (lane & 15) * 4;
@@ -208,7 +239,7 @@ __global__ void __launch_bounds__(256) k_apply_coded(CodedApplyArgs A)
             reinterpret_cast<float4 *>(acc)[i * 64 + lane] = make_float4(0.f, 0.f, 0.f, 0.f);
     }
 
-    const int E = A.E, L = k / E;                 // step 4: entries per lane, lanes per worker
+    const int L = (k + 7) >> 3;                   // step 4: lanes per worker, eight entries each (without lists)
     const int uwp = 1 << A.uwp_log2;
     // One batch of workers: staged, decoded, added.  The first batch is processed by straight-line code
     // of its own ahead of the loop over the others: inside a loop the wait in front of the staged words
@@ -332,7 +363,8 @@ __global__ void __launch_bounds__(256) k_apply_coded(CodedApplyArgs A)
             }
             return;
         }
-        // ---- step 3: the zero bits of the vectors -> running quotient sums, by entry
+        if constexpr (LISTS) {
+        // ---- step 3 with lists: the zero bits of the vectors -> running quotient sums, by entry
         {
             const int slots = nb << A.uwp_log2;
             int carry = 0;
@@ -402,8 +434,9 @@ __global__ void __launch_bounds__(256) k_apply_coded(CodedApplyArgs A)
             }
             sl_wave_sync();
         }
-        // ---- step 4: remainders, their prefix sums, the indices
+        // ---- step 4 with lists: remainders, their prefix sums, the indices
         {
+            const int L = k / A.E, E = A.E;             // lanes per worker, entries per lane
             const int wpp = L <= 64 ? 64 / L : 1;       // workers per pass
             const int ppw = (L + 63) >> 6;              // passes per worker (1 unless L > 64)
             const unsigned fmask = (1u << b) - 1u;
@@ -489,19 +522,229 @@ __global__ void __launch_bounds__(256) k_apply_coded(CodedApplyArgs A)
             }
             sl_wave_sync();
         }
-        if constexpr (DECODE) {
-            // ---- plain record: the 12-bit index stream, then the value fields byte for byte
-            const unsigned short *idx = reinterpret_cast<const unsigned short *>(stage + off_h);
-            unsigned char *rec = A.plain + d.rec_off;
-            const int nbytes = 3 * k / 2;
-            for (int q = lane; q < nbytes; q += 64) {
-                const int bit0 = 8 * q, m = bit0 / 12, sh = bit0 - 12 * m;     // 0, 4 or 8
-                unsigned v = (unsigned)idx[m] >> sh;
-                if (sh == 8 && m + 1 < k) v |= (unsigned)idx[m + 1] << 4;
-                rec[q] = (unsigned char)v;
+        } else {
+        // ---- step 3: where every eighth zero of the vectors lies
+        {
+            const int slots = nb << A.uwp_log2;
+            int carry = 0;
+            for (int s0 = 0; s0 < slots; s0 += 64) {
+                const int slot = s0 + lane;
+                const int r = slot >> A.uwp_log2, j = slot & (uwp - 1);
+                // (a lane without a word reads the first one of some worker and finds no zeros in it)
+                const int rr = r < nb ? r : 0, jj = j < G.ua ? j : 0;
+                const int meta = sl_lane_read(v_meta, r0 + rr);
+                const int sh = meta & 31;
+                unsigned char *base = stage + rr * A.slot_bytes;
+                const unsigned *raw = reinterpret_cast<const unsigned *>(base + off_u) + jj;
+                const int left = r < nb && j < G.ua ? (meta >> 5) - 32 * j : 0;
+                const unsigned mask = left >= 32 ? 0xFFFFFFFFu : left > 0 ? (1u << left) - 1u : 0u;
+                const unsigned zeros = ~__builtin_amdgcn_alignbit(raw[1], raw[0], (unsigned)sh) & mask;
+                const int nz = __builtin_popcount(zeros);
+                const int incl = sl_wave_iscan(nz);
+                int rank;
+                if (uwp <= 64) {
+                    const int seg = lane & ~(uwp - 1);                 // first lane of this worker's words
+                    const int before = sl_lane_read(incl, seg > 0 ? seg - 1 : 0);
+                    rank = incl - nz - (seg > 0 ? before : 0);
+                } else {
+                    if ((s0 & (uwp - 1)) == 0) carry = 0;              // a new worker starts with this pass
+                    rank = carry + incl - nz;
+                    carry += __builtin_amdgcn_readlane(incl, 63);
+                }
+                // zeros rank .. rank + nz - 1 of the vector lie in this word: each of its four bytes holds at
+                // most one whose number is a multiple of eight (a vector with more than k zeros is malformed:
+                // the rest is left out)
+                unsigned short *table = reinterpret_cast<unsigned short *>(base + off_t);
+                int from = rank;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int to = q < 3 ? rank + __builtin_popcount(zeros & ((1u << (8 * (q + 1))) - 1u)) : rank + nz;
+                    const int m = (from + 7) & ~7;
+                    // (no such zero: entry L of the table takes the write, nobody reads it)
+                    table[m < to && m < k ? m >> 3 : L] = (unsigned short)(((4 * j + q) << 3) | (m - from));
+                    from = to;
+                }
             }
+            sl_wave_sync();
+        }
+        // ---- steps 4 and 5
+        {
+            const int wpp = L <= 64 ? 64 / L : 1;       // workers per pass
+            const int ppw = (L + 63) >> 6;              // passes per worker (1 unless L > 64)
+            const unsigned fmask = (1u << b) - 1u;
+            if constexpr (TWO_BIT && !DECODE) {
+                // the values of two consecutive codes, by their four bits
+                for (int q = lane; q < 16 * nb; q += 64) {
+                    unsigned char *slot = stage + (q >> 4) * A.slot_bytes;
+                    const float *lutp = reinterpret_cast<const float *>(slot);
+                    reinterpret_cast<float2 *>(slot + off_q)[q & 15] = make_float2(lutp[q & 3], lutp[(q >> 2) & 3]);
+                }
+                sl_wave_sync();
+            }
+            for (int rb = 0; rb < nb; rb += wpp) {
+                int carry = 0;
+                for (int ps = 0; ps < ppw; ++ps) {
+                    // (lane / L; the multiplier does not exist for L = 1)
+                    const int rl = L == 1 ? lane : L <= 64 ? (int)__umulhi((unsigned)lane, A.magic_l) : 0;
+                    const int o = L <= 64 ? lane - rl * L : 64 * ps + lane;
+                    const int r = rb + rl;
+                    const bool live = rl < wpp && r < nb && o < L;
+                    unsigned char *slot = stage + (live ? r : 0) * A.slot_bytes;
+                    const int meta = sl_lane_read(v_meta, live ? r0 + r : 0);
+                    const int oo = live ? o : 0;         // (a lane without entries decodes some worker's first ones)
+                    int pre[8];                          // r_0 + ... + r_e, plus e - (e << b): what entry e's index holds
+                                                         // besides the lane's part and its zero's place
+                    int total;
+                    {
+                        // (the two words behind the one that holds the first field are read whether or not
+                        // the fields reach them: they lie inside the worker's slot)
+                        const unsigned *rem = reinterpret_cast<const unsigned *>(slot + 4 * hdrw);
+                        const int bit = oo * 8 * b, wi = bit >> 5;
+                        const unsigned w0 = rem[wi], w1 = rem[wi + 1], w2 = rem[wi + 2];
+                        const unsigned lo = __builtin_amdgcn_alignbit(w1, w0, (unsigned)(bit & 31));
+                        const unsigned hi = __builtin_amdgcn_alignbit(w2, w1, (unsigned)(bit & 31));
+                        // entries 0..2 from the window's low word, 3 from the word that starts at its field (b is
+                        // at most 9), 4..7 from the word that starts at field 4 (b = 9 is k = 4: no such entries)
+                        const unsigned lo3 = __builtin_amdgcn_alignbit(hi, lo, (unsigned)(3 * b));
+                        const unsigned lo4 = (unsigned)((((unsigned long long)hi << 32) | lo) >> (4 * b));
+                        const int step = 1 - (1 << b);
+                        int t = 0;
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) {
+                            const unsigned f = e < 3 ? __builtin_amdgcn_ubfe(lo, (unsigned)(e * b), (unsigned)b)
+                                               : e == 3 ? lo3 & fmask : __builtin_amdgcn_ubfe(lo4, (unsigned)((e - 4) * b), (unsigned)b);
+                            t = e ? t + (int)f + step : (int)f;
+                            pre[e] = t;
+                        }
+                        total = t - 7 * step;
+                    }
+                    const int incl = sl_wave_iscan(total);
+                    int excl;
+                    if (L <= 64) {
+                        const int seg = rl * L;
+                        const int before = sl_lane_read(incl, seg > 0 ? seg - 1 : 0);
+                        excl = incl - total - (seg > 0 ? before : 0);
+                    } else {
+                        excl = carry + incl - total;
+                        carry += __builtin_amdgcn_readlane(incl, 63);
+                    }
+                    // the eight zeros: the first from the table, the others in the 64 bits behind it (20 of them on
+                    // average, whatever k: the Rice parameter follows it; 32 would not do for one lane in a hundred)
+                    const unsigned *raw = reinterpret_cast<const unsigned *>(slot + off_u);
+                    int p[8];                            // places of the zeros, from the first one's on
+                    int start = 0;                       // place of the first in the vector
+                    unsigned z, zh;
+                    {
+                        const unsigned note = reinterpret_cast<const unsigned short *>(slot + off_t)[oo];
+                        const int byte = min((int)(note >> 3), 4 * G.ua - 1);      // (beyond: a vector with too few zeros)
+                        const int at = (meta & 31) + 8 * byte, wi = at >> 5;
+                        const unsigned w0 = raw[wi], w1 = raw[wi + 1], w2 = raw[wi + 2];
+                        const unsigned lo = ~__builtin_amdgcn_alignbit(w1, w0, (unsigned)(at & 31));
+                        const unsigned hi = ~__builtin_amdgcn_alignbit(w2, w1, (unsigned)(at & 31));
+                        const unsigned skip = (unsigned)place_in_byte(lo & 0xFFu, (int)(note & 7u));
+                        start = 8 * byte + (int)skip;
+                        z = __builtin_amdgcn_alignbit(hi, lo, skip);
+                        zh = hi >> skip;                 // (57 bits at least)
+                    }
+                    const int want = min(8, k - 8 * o);
+                    if (__builtin_amdgcn_ballot_w64(live && __builtin_popcount(z) + __builtin_popcount(zh) < want) == 0) {
+                        p[0] = 0;
+                        int off = 0;
+#pragma unroll
+                        for (int e = 1; e < 8; ++e) {
+                            if (e == 4) z = want == 8 && live ? z : 0x1Fu;       // (the last four of a lane that has four: any)
+                            if (e == 1) z = live ? z : 0x1Fu;
+                            z &= z - 1u;
+                            const bool next = z == 0u;                   // on to the upper word (once at most)
+                            z = next ? zh : z;
+                            off = next ? 32 : off;
+                            p[e] = __builtin_ctz(z) + off;
+                        }
+                    } else {
+                        // a lane's eight zeros reach further (clustered supports): word by word
+                        int q = start;
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) {
+                            for (int turn = 0; turn < 130; ++turn) {     // (at most 128 words: a malformed vector ends the search)
+                                const int at = (meta & 31) + q, wi = min(at >> 5, G.ua);
+                                const unsigned w = ~__builtin_amdgcn_alignbit(raw[wi + 1], raw[wi], (unsigned)(at & 31));
+                                if (w != 0u) {
+                                    q += __builtin_ctz(w);
+                                    break;
+                                }
+                                q += 32;
+                            }
+                            p[e] = q - start;
+                            ++q;
+                        }
+                    }
+                    const int base = excl + 8 * oo + ((start - 8 * oo) << b);
+                    // index of entry e, cut to 12 bits: a malformed payload stays inside the chunk (a valid one
+                    // never reaches bit 12)
+                    unsigned idx[8];
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) idx[e] = (unsigned)(base + (pre[e] + (p[e] << b))) & 0xFFFu;
+                    if constexpr (DECODE) {
+                        // the plain record's 12-bit index stream: eight entries are twelve bytes
+                        if (live) {
+                            unsigned char *rec = A.plain + d.rec_off + 12 * o;
+                            const unsigned w0 = idx[0] | (idx[1] << 12) | (idx[2] << 24);
+                            const unsigned w1 = (idx[2] >> 8) | (idx[3] << 4) | (idx[4] << 16) | (idx[5] << 28);
+                            const unsigned w2 = (idx[5] >> 4) | (idx[6] << 8) | (idx[7] << 20);
+                            if ((d.rec_off & 3) == 0 && want == 8) {
+                                reinterpret_cast<unsigned *>(rec)[0] = w0;
+                                reinterpret_cast<unsigned *>(rec)[1] = w1;
+                                reinterpret_cast<unsigned *>(rec)[2] = w2;
+                            } else {
+                                const unsigned w[3] = {w0, w1, w2};
+#pragma unroll
+                                for (int q = 0; q < 12; ++q)
+                                    if (q < 6 || want == 8) rec[q] = (unsigned char)(w[q >> 2] >> (8 * (q & 3)));
+                            }
+                        }
+                    } else {
+                        // ---- step 5: these lanes add their entries, worker after worker.  The positions of
+                        // one record are distinct: the reads, then the writes, are issued together.
+                        float v[8];
+                        const unsigned char *vals = slot + 4 * hdrw + G.rem_bytes;
+                        if constexpr (TWO_BIT) {
+                            const unsigned cw = reinterpret_cast<const unsigned short *>(vals)[oo];
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) {
+                                const float2 q2 = reinterpret_cast<const float2 *>(slot + off_q)[(cw >> (4 * e)) & 15u];
+                                v[2 * e] = q2.x, v[2 * e + 1] = q2.y;
+                            }
+                        } else {
+#pragma unroll
+                            for (int e = 0; e < 8; ++e) v[e] = e < want ? value_at(slot, min(8 * o + e, k - 1)) : 0.f;
+                        }
+                        for (int w = 0; w < wpp; ++w) {
+                            if (live && rl == w) {
+                                float t[8];
+#pragma unroll
+                                for (int e = 0; e < 8; ++e) t[e] = acc[idx[e]];
+#pragma unroll
+                                for (int e = 0; e < 8; ++e)
+                                    if (e < 4 || want == 8) acc[idx[e]] = t[e] + v[e];
+                            }
+                            sl_wave_sync();   // worker r is complete before worker r+1 is added
+                        }
+                    }
+                }
+            }
+            sl_wave_sync();
+        }
+        }
+        if constexpr (DECODE) {
+            // ---- the value fields as they stand, after the index stream
+            unsigned char *rec = A.plain + d.rec_off + 3 * k / 2;
             const unsigned char *vals = stage + 4 * hdrw + G.rem_bytes;
-            for (int q = lane; q < G.val_bytes; q += 64) rec[nbytes + q] = vals[q];
+            if ((d.rec_off & 3) == 0 && (k & 7) == 0 && (G.val_bytes & 3) == 0) {
+                for (int q = lane; 4 * q < G.val_bytes; q += 64)
+                    reinterpret_cast<unsigned *>(rec)[q] = reinterpret_cast<const unsigned *>(vals)[q];
+            } else {
+                for (int q = lane; q < G.val_bytes; q += 64) rec[q] = vals[q];
+            }
             if (d.local_chunk == 0 || d.local_chunk == A.tensors[d.tensor].n_chunks - 1) {
                 const SlTensorDev td = A.tensors[d.tensor];
                 if (d.local_chunk == 0)
@@ -511,52 +754,33 @@ __global__ void __launch_bounds__(256) k_apply_coded(CodedApplyArgs A)
                     for (long long q = hdr + td.n_chunks * (long long)A.rec_bytes + lane; q < td.block_bytes; q += 64)
                         A.plain[td.pay_off + q] = 0;
             }
-        } else {
-            // ---- step 5: the additions, worker by worker
-            if (k <= 128) {
-                // the entries of up to eight workers are fetched first (independent LDS reads),
-                // then added worker by worker: the additions form a chain of LDS round trips
-                for (int rb = 0; rb < nb; rb += 8) {
-                    unsigned jj[8][2];
-                    float qq[8][2];
+        } else if constexpr (LISTS) {
+            // ---- step 5 with lists: the entries of up to eight workers are fetched first (independent LDS
+            // reads), then added worker by worker: the additions form a chain of LDS round trips
+            for (int rb = 0; rb < nb; rb += 8) {
+                unsigned jj[8][2];
+                float qq[8][2];
 #pragma unroll
-                    for (int u = 0; u < 8; ++u)
+                for (int u = 0; u < 8; ++u)
 #pragma unroll
-                        for (int s2 = 0; s2 < 2; ++s2) {
-                            const int m = lane + 64 * s2;
-                            jj[u][s2] = 0xFFFFu;
-                            qq[u][s2] = 0.0f;
-                            if (rb + u < nb && m < k) {
-                                const unsigned char *slot = stage + (rb + u) * A.slot_bytes;
-                                jj[u][s2] = reinterpret_cast<const unsigned short *>(slot + off_h)[m];
-                                qq[u][s2] = value_at(slot, m);
-                            }
-                        }
-#pragma unroll
-                    for (int u = 0; u < 8; ++u) {
-                        if (rb + u < nb) {
-#pragma unroll
-                            for (int s2 = 0; s2 < 2; ++s2)
-                                if (jj[u][s2] != 0xFFFFu) acc_add(acc, jj[u][s2], qq[u][s2]);
-                            sl_wave_sync();   // worker r is complete before worker r+1 is added
+                    for (int s2 = 0; s2 < 2; ++s2) {
+                        const int m = lane + 64 * s2;
+                        jj[u][s2] = 0xFFFFu;
+                        qq[u][s2] = 0.0f;
+                        if (rb + u < nb && m < k) {
+                            const unsigned char *slot = stage + (rb + u) * A.slot_bytes;
+                            jj[u][s2] = reinterpret_cast<const unsigned short *>(slot + off_h)[m];
+                            qq[u][s2] = value_at(slot, m);
                         }
                     }
-                }
-            } else {
-                // four consecutive entries per lane: one 8-byte read of indices, the positions of one
-                // record are distinct, so the four reads and the four writes are issued together
-                for (int r = 0; r < nb; ++r) {
-                    const unsigned char *slot = stage + r * A.slot_bytes;
-                    const unsigned short *idx = reinterpret_cast<const unsigned short *>(slot + off_h);
-                    for (int q4 = lane; q4 < (k >> 2); q4 += 64) {
-                        const uint2 iw = *reinterpret_cast<const uint2 *>(idx + 4 * q4);
-                        const unsigned j0 = iw.x & 0xFFFFu, j1 = iw.x >> 16, j2 = iw.y & 0xFFFFu, j3 = iw.y >> 16;
-                        const float q0 = value_at(slot, 4 * q4), q1 = value_at(slot, 4 * q4 + 1),
-                                    q2 = value_at(slot, 4 * q4 + 2), q3 = value_at(slot, 4 * q4 + 3);
-                        const float t0 = acc[j0], t1 = acc[j1], t2 = acc[j2], t3 = acc[j3];
-                        acc[j0] = t0 + q0, acc[j1] = t1 + q1, acc[j2] = t2 + q2, acc[j3] = t3 + q3;
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    if (rb + u < nb) {
+#pragma unroll
+                        for (int s2 = 0; s2 < 2; ++s2)
+                            if (jj[u][s2] != 0xFFFFu) acc_add(acc, jj[u][s2], qq[u][s2]);
+                        sl_wave_sync();   // worker r is complete before worker r+1 is added
                     }
-                    sl_wave_sync();           // worker r is complete before worker r+1 is added
                 }
             }
         }
@@ -652,19 +876,32 @@ int slk_apply_coded(const sl_plan *p, int mode, float *theta, float *mom, float 
     A.R = R;
     const SlCodedGeom &G = p->cg;
     A.fwp = (G.hdr + G.cfix) >> 2;
-    A.E = (G.k & 7) ? 4 : 8;
     A.rec_bytes = p->rec_bytes;
-    A.slot_bytes = (int)(((((size_t)4 * A.fwp + 4 * ((size_t)G.ua + 1) + 15) & ~(size_t)15) + 2 * (size_t)G.k + 15) & ~(size_t)15);
+    const bool lists = mode != 2 && G.k <= 128 && (long long)R * G.k < SL_CAPPLY_LISTS_BELOW;
+    A.E = (G.k & 7) ? 4 : 8;
+    const int L = lists ? G.k / A.E : (G.k + 7) / 8;
+    auto up16 = [](int v) { return (v + 15) & ~15; };
+    A.off_t = A.off_q = A.off_h = up16(4 * A.fwp + 4 * (G.ua + 1));
+    if (lists) {
+        A.slot_bytes = up16(A.off_h + 2 * G.k);
+    } else {
+        A.off_q = up16(A.off_t + 2 * (L + 1));
+        A.slot_bytes = A.off_q + (mode != 2 && G.bits == 2 ? 128 : 0);
+    }
     A.uwp_log2 = pow2_log2_at_least(G.ua);
     int batch = SL_CAPPLY_STAGE / A.slot_bytes;
     // (a whole number of passes of step 3, where a pass holds several workers' vectors)
     const int per_pass = A.uwp_log2 < 6 ? 64 >> A.uwp_log2 : 1;
     if (batch > per_pass) batch -= batch % per_pass;
+    // (without lists no more workers than have all their words fetched ahead, SL_CAPPLY_PFF and _PFU words by
+    // each of a worker's 64 / batch lanes; below two workers per batch that cannot be had)
+    int lanes = 1;
+    while (lanes < 32 && (SL_CAPPLY_PFF * lanes < A.fwp || SL_CAPPLY_PFU * lanes < G.ua + 1)) lanes <<= 1;
+    if (!lists && batch > 64 / lanes) batch = 64 / lanes;
     if (batch < 1) batch = 1;
     if (batch > R) batch = R;
     A.batch = batch;
     A.lpw_log2 = 6 - pow2_log2_at_least(batch);
-    const int L = G.k / A.E;
     A.magic_l = L > 1 ? (unsigned)(0x100000000ull / (unsigned)L + 1) : 0u;
     A.n_chunks = p->n_chunks;
     for (int r = 0; r < SL_MAX_WORKERS; ++r) {
@@ -677,9 +914,12 @@ int slk_apply_coded(const sl_plan *p, int mode, float *theta, float *mom, float 
     while (wpb > 1 && (size_t)A.lds_per_wave * wpb > (size_t)p->max_lds) wpb >>= 1;
     const size_t lds = (size_t)A.lds_per_wave * wpb;
     typedef void (*kernel_t)(CodedApplyArgs);
-    static const kernel_t table[2][3] = {{k_apply_coded<false, 0>, k_apply_coded<false, 1>, k_apply_coded<false, 2>},
-                                         {k_apply_coded<true, 0>, k_apply_coded<true, 1>, k_apply_coded<true, 2>}};
-    const kernel_t fn = table[p->bits == 2 ? 1 : 0][mode];
+    static const kernel_t table[2][2][3] = {
+        {{k_apply_coded<false, 0, false>, k_apply_coded<false, 1, false>, k_apply_coded<false, 2, false>},
+         {k_apply_coded<false, 0, true>, k_apply_coded<false, 1, true>, nullptr}},
+        {{k_apply_coded<true, 0, false>, k_apply_coded<true, 1, false>, k_apply_coded<true, 2, false>},
+         {k_apply_coded<true, 0, true>, k_apply_coded<true, 1, true>, nullptr}}};
+    const kernel_t fn = table[p->bits == 2 ? 1 : 0][lists ? 1 : 0][mode];
     if (lds > 65536) {
         hipError_t aerr = hipFuncSetAttribute(reinterpret_cast<const void *>(fn),
                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
