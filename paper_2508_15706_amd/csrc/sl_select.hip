@@ -250,6 +250,42 @@ SL_DEV void select_general(int (&key)[64], const float (&a)[64], unsigned sg0, u
     }
 }
 
+// Lower bound L of the chunk's k-th largest magnitude key, and the largest key hi: the k-th largest of
+// the maxima of G groups per lane (group g = the lane's registers r with r % G == g), or a little less.
+// There are k distinct elements >= L as soon as k groups reach it.  A bound is all that is needed, so
+// only its leading bits are decided - a slightly longer candidate list for half the counting passes.
+template <int G>
+SL_DEV void prune_bound(const float (&a)[64], int k, int &L, int &hi)
+{
+    int gm[G];
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+        int m = key_of(a[g]);
+#pragma unroll
+        for (int r = g + G; r < 64; r += G) m = max(m, key_of(a[r]));
+        gm[g] = m;
+    }
+    int lmin = gm[0], lmax = gm[0];
+#pragma unroll
+    for (int g = 1; g < G; ++g) lmin = min(lmin, gm[g]), lmax = max(lmax, gm[g]);
+    hi = sl_wave_max(lmax);
+    const int lo = sl_wave_min(lmin);
+    L = bisect_kth(lo, hi, k, [&](int x) {
+        int n = 0;
+#pragma unroll
+        for (int g = 0; g < G; ++g) n += sl_popc(sl_ballot(gm[g] >= x));
+        return n;
+    }, SL_SELECT_BOUND_BITS);
+}
+
+// Groups per lane for a partial chunk, whatever k: only the lanes whose columns exist hold elements (a
+// tile with 8 columns: 8 of 64 lanes), and with one or two groups each there are fewer than k maxima -
+// the bound is then 0, the candidate list overflows and the chunk takes the general route (a list of
+// 1155 chunks, half of them such, k = 32: 44.7 us so, 29.2 with 16 groups).
+#ifndef SL_SELECT_PARTIAL_GROUPS
+#define SL_SELECT_PARTIAL_GROUPS 16
+#endif
+
 // 3 waves per SIMD (<= 168 VGPRs): measured faster than 2 (no spills) or 4 (heavy spills).
 #ifndef SL_SELECT_WAVES_PER_EU
 #define SL_SELECT_WAVES_PER_EU 3
@@ -592,31 +628,9 @@ __global__ void SL_SELECT_BOUNDS k_select(SelectArgs A)
     // overflows (it would hold all 4096 positions) and the general route, which knows the
     // outside positions, takes over.
     if constexpr (GPL > 0) {
-        constexpr int G = GPL;
-        // group g of a lane = its registers r with r % G == g
-        int gm[G];
-#pragma unroll
-        for (int g = 0; g < G; ++g) {
-            int m = key_of(a[g]);
-#pragma unroll
-            for (int r = g + G; r < 64; r += G) m = max(m, key_of(a[r]));
-            gm[g] = m;
-        }
-        int lmin = gm[0], lmax = gm[0];
-#pragma unroll
-        for (int g = 1; g < G; ++g) lmin = min(lmin, gm[g]), lmax = max(lmax, gm[g]);
-        const int hi = sl_wave_max(lmax);               // largest key of the chunk
-        const int lo = sl_wave_min(lmin);
-        // L = k-th largest group maximum, or a little less: a lower bound of T, because k
-        // distinct elements are >= L (64*G >= k groups).  A bound is all that is needed, so
-        // only its leading bits are decided - a slightly longer candidate list for half the
-        // counting passes.
-        const int L = bisect_kth(lo, hi, k, [&](int x) {
-            int n = 0;
-#pragma unroll
-            for (int g = 0; g < G; ++g) n += sl_popc(sl_ballot(gm[g] >= x));
-            return n;
-        }, SL_SELECT_BOUND_BITS);
+        int L, hi;
+        if (full) prune_bound<GPL>(a, k, L, hi);
+        else prune_bound<(GPL > SL_SELECT_PARTIAL_GROUPS ? GPL : SL_SELECT_PARTIAL_GROUPS)>(a, k, L, hi);
         // ordered compaction of the entries with key >= L
         int ncand = 0;
 #pragma unroll
