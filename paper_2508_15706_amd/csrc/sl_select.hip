@@ -25,9 +25,10 @@
 //   3. T is bisected over that short list, and a second compaction over the
 //      list emits the selected entries, still in ascending local index; ties
 //      at T go to the lowest indices.
-// Partial chunks, a candidate list that overflows (massive ties) and k > 512
-// take the general route: T bisected over the registers directly and one
-// ordered compaction over the registers - slower, same result.
+// A candidate list that overflows (massive ties; a partial chunk with too few
+// non-empty groups) and k > 512 take the general route: T bisected over the
+// registers directly and one ordered compaction over the registers - slower,
+// same result.
 #include "sl_coded.h"
 
 namespace {
@@ -278,13 +279,24 @@ SL_DEV void prune_bound(const float (&a)[64], int k, int &L, int &hi)
     }, SL_SELECT_BOUND_BITS);
 }
 
-// Groups per lane for a partial chunk, whatever k: only the lanes whose columns exist hold elements (a
+// Groups per lane for a narrow partial chunk, whatever k: only the lanes whose columns exist hold elements (a
 // tile with 8 columns: 8 of 64 lanes), and with one or two groups each there are fewer than k maxima -
 // the bound is then 0, the candidate list overflows and the chunk takes the general route (a list of
 // 1155 chunks, half of them such, k = 32: 44.7 us so, 29.2 with 16 groups).
 #ifndef SL_SELECT_PARTIAL_GROUPS
 #define SL_SELECT_PARTIAL_GROUPS 16
 #endif
+
+// Does a partial chunk need them?  Not where the lanes that hold elements give about k maxima with GPL
+// groups too (the bound is then as good and takes a fraction of the instructions: 5000 vectors of 4096 + 600
+// elements, fp32 values, k = 16: select and padding 58 us with 16 groups everywhere, 53 so), nor where each element is a group
+// of its own already, nor where 16 groups are fewer than k as well.
+template <int GPL>
+SL_DEV bool needs_more_groups(const SlChunkDesc &d, int k)
+{
+    const int lanes = min(d.rows, 4) * ((d.cols + 3) >> 2);      // four rows of 64 columns per register quad
+    return d.rows > GPL && 2 * lanes * GPL < 3 * k && lanes * SL_SELECT_PARTIAL_GROUPS >= k;
+}
 
 // 3 waves per SIMD (<= 168 VGPRs): measured faster than 2 (no spills) or 4 (heavy spills).
 #ifndef SL_SELECT_WAVES_PER_EU
@@ -629,7 +641,7 @@ __global__ void SL_SELECT_BOUNDS k_select(SelectArgs A)
     // outside positions, takes over.
     if constexpr (GPL > 0) {
         int L, hi;
-        if (full) prune_bound<GPL>(a, k, L, hi);
+        if (full || !needs_more_groups<GPL>(d, k)) prune_bound<GPL>(a, k, L, hi);
         else prune_bound<(GPL > SL_SELECT_PARTIAL_GROUPS ? GPL : SL_SELECT_PARTIAL_GROUPS)>(a, k, L, hi);
         // ordered compaction of the entries with key >= L
         int ncand = 0;

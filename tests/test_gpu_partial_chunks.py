@@ -76,3 +76,34 @@ def test_partial_chunks(oracle, k, zero):
     torch.cuda.synchronize()
     same(theta, want, "theta with momentum")
     same(mom, mom_ref, "momentum")
+
+
+@pytest.mark.parametrize("k", [4, 12, 32, 48, 64, 100, 128, 200, 256, 300, 512])
+def test_pruning_groups_of_partial_chunks(oracle, k):
+    """Widths and tail lengths on both sides of every place where the number of groups per lane of a partial
+    chunk changes: as many lanes with elements as give just under and just over 3k/2 maxima, one element per
+    group, fewer elements than 16 groups per lane can spread."""
+    from paper_2508_15706_amd import binding as sl
+    descs, off = [], 0
+    shapes = [(r, c, 1) for r in (64, 66, 67, 80, 96, 192) for c in (4, 8, 12, 20, 24, 28, 36, 44, 52, 60, 63, 100)]
+    shapes += [(1, 4096 + t, 0) for t in (64, 100, 128, 192, 255, 256, 300, 320, 512, 513, 600, 1024, 1100, 2048, 4000)]
+    for r, c, lay in shapes:
+        smallest = (r * c % 4096 or 4096) if lay == 0 else (r % 64 or 64) * (c % 64 or 64)
+        if smallest < k:
+            continue
+        descs.append((r, c, off, lay))
+        off += (r * c + 63) // 64 * 64
+    rng = np.random.default_rng(31 * k)
+    plan = sl.sl_plan_create(descs, k)
+    e0, d0 = rng.normal(0, 1e-3, off).astype(np.float32), (1e-3 * rng.standard_t(3, off)).astype(np.float32)
+    e, pay = torch.from_numpy(e0.copy()).cuda(), sl.alloc_payload(plan)
+    sl.sl_compress(plan, e, torch.from_numpy(d0).cuda(), 0.95, pay, sl.alloc_workspace(plan))
+    e_ref = e0.copy()
+    ref = oracle.compress(descs, k, e_ref, d0, 0.95)
+    m, m_ref = torch.from_numpy(d0.copy()).cuda(), d0.copy()
+    sl.sl_sub_topk(plan, m)
+    oracle.sub_topk(descs, k, m_ref)
+    torch.cuda.synchronize()
+    assert np.array_equal(pay[:plan.payload_bytes].cpu().numpy(), ref)
+    assert np.array_equal(e.cpu().numpy().view(np.uint32), e_ref.view(np.uint32))
+    assert np.array_equal(m.cpu().numpy().view(np.uint32), m_ref.view(np.uint32))
