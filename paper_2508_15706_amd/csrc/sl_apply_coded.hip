@@ -35,7 +35,9 @@ namespace {
 // Up to k = 128 with fewer than so many entries per chunk (R * k) the entries go through index lists in
 // LDS: the decode is short there and hidden behind the theta loads, what is left is the length of its
 // chain (24,000 chunks, lists / the other form: k = 64, R = 8 165 / 167 us; k = 128, R = 8 174 / 170;
-// k = 96, R = 16 243 / 178; k = 64, R = 32 245 / 214).
+// k = 96, R = 16 243 / 178; k = 64, R = 32 245 / 214).  Up to k = 16 at 2 bits that holds whatever R: two lanes
+// per worker add while the others wait (k = 16, R = 64 272 / 299; 1, 3, 4 and 32 bits 315, 341, 403 and 355 with
+// lists, 281, 295, 355 and 309 without).
 #ifndef SL_CAPPLY_LISTS_BELOW
 #define SL_CAPPLY_LISTS_BELOW 1024
 #endif
@@ -877,7 +879,8 @@ int slk_apply_coded(const sl_plan *p, int mode, float *theta, float *mom, float 
     const SlCodedGeom &G = p->cg;
     A.fwp = (G.hdr + G.cfix) >> 2;
     A.rec_bytes = p->rec_bytes;
-    const bool lists = mode != 2 && G.k <= 128 && (long long)R * G.k < SL_CAPPLY_LISTS_BELOW;
+    const bool few = (long long)R * G.k < SL_CAPPLY_LISTS_BELOW || (G.k <= 16 && G.bits == 2);
+    const bool lists = mode != 2 && G.k <= 128 && few;
     A.E = (G.k & 7) ? 4 : 8;
     const int L = lists ? G.k / A.E : (G.k + 7) / 8;
     auto up16 = [](int v) { return (v + 15) & ~15; };
@@ -893,11 +896,22 @@ int slk_apply_coded(const sl_plan *p, int mode, float *theta, float *mom, float 
     // (a whole number of passes of step 3, where a pass holds several workers' vectors)
     const int per_pass = A.uwp_log2 < 6 ? 64 >> A.uwp_log2 : 1;
     if (batch > per_pass) batch -= batch % per_pass;
-    // (without lists no more workers than have all their words fetched ahead, SL_CAPPLY_PFF and _PFU words by
-    // each of a worker's 64 / batch lanes; below two workers per batch that cannot be had)
-    int lanes = 1;
-    while (lanes < 32 && (SL_CAPPLY_PFF * lanes < A.fwp || SL_CAPPLY_PFU * lanes < G.ua + 1)) lanes <<= 1;
-    if (!lists && batch > 64 / lanes) batch = 64 / lanes;
+    // Without lists the batch follows two things more (24,000 chunks each).  `cap`: no more workers than have all
+    // their words fetched ahead (SL_CAPPLY_PFF and _PFU words by each of a worker's 64 / batch lanes; below two
+    // workers per batch that cannot be had) - but not where that leaves more than a third of step 4's lanes without
+    // a worker, i.e. with wide tables or values at small k (k = 64: at 4 bits, R = 64 660 us with the cap, 468
+    // without, 504 with lists; at 32 bits, R = 16 306, 219 and 238).  And workers left over after whole passes of
+    // step 4 cost a pass: they wait for the next batch where that makes passes and batches fewer (k = 72, R = 40:
+    // 380 us with eight at a time, 310 with seven at 1 bit, 300 and 266 at 2).
+    if (!lists) {
+        int lanes = 1;
+        while (lanes < 32 && (SL_CAPPLY_PFF * lanes < A.fwp || SL_CAPPLY_PFU * lanes < G.ua + 1)) lanes <<= 1;
+        const int cap = 64 / lanes, wpp = L <= 64 ? 64 / L : 1;
+        if (batch > cap && 2 * wpp <= 3 * cap) batch = cap;
+        auto turns = [&](int b) { return R / b * (1 + (b + wpp - 1) / wpp) + (R % b ? 1 + (R % b + wpp - 1) / wpp : 0); };
+        const int whole = batch - batch % wpp;
+        if (batch > wpp && turns(whole) < turns(batch)) batch = whole;
+    }
     if (batch < 1) batch = 1;
     if (batch > R) batch = R;
     A.batch = batch;

@@ -58,3 +58,39 @@ def test_aggregates_at_layout_edges(oracle, k, R):
         sl.sl_rice_decode(plan, wires[r], sizes[r], back)
         torch.cuda.synchronize()
         assert np.array_equal(back.cpu().numpy(), refs[r]), f"worker {r} decoded"
+
+
+@pytest.mark.parametrize("bits, k, R", [(b, k, R) for b in (1, 3, 4, 32) for k, R in ((16, 64), (24, 43), (32, 33), (64, 17), (72, 15), (72, 64),
+                                                                                      (80, 13), (96, 11), (128, 9), (168, 7), (256, 5))]
+                         + [(2, 16, 64), (2, 72, 15), (2, 72, 64), (2, 160, 7)])
+def test_coded_aggregate_batches(oracle, bits, k, R):
+    """The coded aggregate where the number of workers staged at a time is decided: fewer than a pass of the decode
+    holds, just as many, whole passes and a remainder that waits for the next batch; with and without momentum."""
+    from paper_2508_15706_amd import binding as sl
+    descs, off = [], 0
+    for r, c, lay in ((1, 2 * 4096, 0), (64, 64, 1), (127, 64, 1)):
+        descs.append((r, c, off, lay))
+        off += (r * c + 63) // 64 * 64
+    rng = np.random.default_rng(1000 * bits + 17 * k + R)
+    plan = sl.sl_plan_create_bits(descs, k, bits)
+    theta0, mom0 = rng.normal(0, 0.02, off).astype(np.float32), rng.normal(0, 1e-3, off).astype(np.float32)
+    refs, wires, sizes = [], [], []
+    for r in range(R):
+        d = supports(rng, off, k, ("spread", "ends", "block")[r % 3])
+        refs.append(oracle.compress_b(descs, k, bits, np.zeros(off, np.float32), d, 0.95))
+        wire = oracle.rice_encode_b(descs, k, bits, refs[-1])
+        wires.append(torch.from_numpy(wire).cuda())
+        sizes.append(wire.size)
+    want = theta0.copy()
+    oracle.decompress_avg_apply_b(descs, k, bits, want, refs, 0.8)
+    theta = torch.from_numpy(theta0.copy()).cuda()
+    sl.sl_decompress_avg_apply_coded(plan, theta, wires, sizes, 0.8)
+    torch.cuda.synchronize()
+    assert np.array_equal(theta.cpu().numpy().view(np.uint32), want.view(np.uint32))
+    want, mom_want = theta0.copy(), mom0.copy()
+    oracle.decompress_avg_apply_nesterov_b(descs, k, bits, want, mom_want, refs, 0.8, 0.9)
+    theta, mom = torch.from_numpy(theta0.copy()).cuda(), torch.from_numpy(mom0.copy()).cuda()
+    sl.sl_decompress_avg_apply_nesterov_coded(plan, theta, mom, wires, sizes, 0.8, 0.9)
+    torch.cuda.synchronize()
+    assert np.array_equal(theta.cpu().numpy().view(np.uint32), want.view(np.uint32)), "theta with momentum"
+    assert np.array_equal(mom.cpu().numpy().view(np.uint32), mom_want.view(np.uint32)), "momentum"
