@@ -295,7 +295,12 @@ inline size_t sl_coded_place_words(const SlCodedGeom &G) { return (size_t)SL_RIC
 // bits beyond k + Q undefined), are shifted to their bit offsets inside the run in LDS; the run and
 // the directory entry go to the buffer.  A lane takes one (chunk, word) pair per turn, so that the
 // loads of several chunks are under way together (a chunk per turn left most lanes idle and waited
-// for memory sixteen times in a row: 33 us for 443,569 chunks of k = 64).
+// for memory sixteen times in a row: 33 us for 443,569 chunks of k = 64).  From k = 356 (33 words and
+// more) a chunk's words fill the wave by themselves, and pairs spend a third of it on words beyond the
+// vectors: a chunk per turn (304 chunks, k = 1024, whole transcode: pairs 27.5 us, so 25.5; k = 512 19.5 and 19.0).
+#ifndef SL_PLACE_BY_CHUNK
+#define SL_PLACE_BY_CHUNK 6               // log2 of the words of the longest vector, rounded up
+#endif
 SL_DEV void sl_coded_place(const SlCodedArgs &A, long long gi, unsigned *run)
 {
     const int lane = threadIdx.x & 63;
@@ -312,7 +317,18 @@ SL_DEV void sl_coded_place(const SlCodedArgs &A, long long gi, unsigned *run)
     const int start = sl_wave_iscan(nbits) - nbits;                      // lanes 0..15 matter
     for (unsigned w = lane; w < nw + 1u; w += 64) run[w] = 0u;
     sl_wave_sync();
-    const int slots = nc << A.ua_log2;
+    const bool by_chunk = A.ua_log2 >= SL_PLACE_BY_CHUNK;
+    for (int i = 0; by_chunk && i < nc; ++i) {
+        const int s = __builtin_amdgcn_readlane(start, i), n = __builtin_amdgcn_readlane(nbits, i), sh = s & 31;
+        const unsigned *src = A.uvec + (size_t)(c0 + i) * G.ua;
+        for (int j = lane; 32 * j < n; j += 64) {
+            const int left = n - 32 * j;         // bits of this word that belong to the vector
+            const unsigned w = src[j] & (left < 32 ? (1u << left) - 1u : 0xFFFFFFFFu);
+            sl_lds_or(&run[(s >> 5) + j], w << sh);
+            if (sh) sl_lds_or(&run[(s >> 5) + j + 1], w >> (32 - sh));
+        }
+    }
+    const int slots = by_chunk ? 0 : nc << A.ua_log2;
     constexpr int U = 2;                         // turns whose loads are issued together
     for (int s0 = 0; s0 < slots; s0 += 64 * U) {
         unsigned v[U];

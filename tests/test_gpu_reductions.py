@@ -43,3 +43,32 @@ def test_more_than_65536_leaves(oracle):
     torch.cuda.synchronize()
     want = oracle.compress([(1, n, 0, sl.SL_LAYOUT_FLAT)], 4, np.zeros(n, np.float32), delta.cpu().numpy(), 0.95)
     assert np.array_equal(pay[:plan.payload_bytes].cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("k", [352, 356, 360, 512, 1024, 2048, 4096])
+def test_placement_of_long_vectors(oracle, k):
+    """Vectors of 32, 33 and more words: a group's vectors are placed by (chunk, word) pairs or a chunk per turn;
+    groups of 16, of 1 and of 13 chunks, supports spread and in one block (the shortest and longest vectors)."""
+    from paper_2508_15706_amd import binding as sl
+    descs, off = [], 0
+    for chunks in (16, 33, 13):
+        descs.append((1, 4096 * chunks, off, sl.SL_LAYOUT_FLAT))
+        off += 4096 * chunks
+    rng = np.random.default_rng(k)
+    d0 = rng.normal(0, 1e-3, off).astype(np.float32)
+    j = np.arange(off) % 4096
+    d0[(j >= 4096 - k) & (np.arange(off) // 4096 % 3 == 1)] += 1.0             # every third chunk: the last k positions
+    d0[(j < k) & (np.arange(off) // 4096 % 3 == 2)] += 1.0                       # ... and the first
+    plan = sl.sl_plan_create(descs, k)
+    pay, ws = sl.alloc_payload(plan), sl.alloc_workspace(plan)
+    coded, again = (torch.full((sl.sl_rice_max_bytes(plan),), 0xCD, dtype=torch.uint8, device="cuda") for _ in range(2))
+    e = torch.zeros(off, dtype=torch.float32, device="cuda")
+    sl.sl_compress_coded(plan, e, torch.from_numpy(d0).cuda(), 0.95, pay, coded, ws)
+    sl.sl_rice_encode(plan, pay, again, ws)
+    torch.cuda.synchronize()
+    want = oracle.compress(descs, k, np.zeros(off, np.float32), d0, 0.95)
+    assert np.array_equal(pay[:plan.payload_bytes].cpu().numpy(), want)
+    want = oracle.rice_encode(descs, k, want)
+    for what, buf in (("compress", coded), ("transcoder", again)):
+        size = sl.coded_size(buf)
+        assert size == want.size and np.array_equal(buf[:size].cpu().numpy(), want), what
