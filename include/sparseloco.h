@@ -366,9 +366,10 @@ enum { SL_PROF_SELECT = 0,  /* accumulate + chunk Top-k          (sl_compress)  
        SL_PROF_LUT = 3,     /* per-tensor centroids                              */
        SL_PROF_RESIDUAL = 4,/* e <- a - LUT[code] at the selected positions      */
        SL_PROF_APPLY = 5,   /* sl_decompress_avg_apply[_coded]                   */
-       SL_PROF_INDEX = 6,   /* coded format, unquantized values: placement of the
-                               quotient bit vectors (at other widths it shares the
-                               launches of STATS, CODES and LUT)                 */
+       SL_PROF_INDEX = 6,   /* coded format: placement of the quotient bit vectors,
+                               where it has launches of its own (unquantized values;
+                               lists of more than a few hundred tensors; else it
+                               shares those of STATS, CODES and LUT)             */
        SL_PROF_PHASES = 7 };
 int sl_profile_begin(sl_plan *plan, int max_calls);
 int sl_profile_end(sl_plan *plan, double *ms, int *calls);

@@ -190,8 +190,8 @@ SL_DEV SlVecPlace sl_coded_dir_entry(const SlCodedGeom &G, sl_gbytes entry, int 
 //   sl_coded_scan_list     one wave: prefix over the tensors, total size, buffer header;
 //   sl_coded_place         one wave per group: the 16 vectors shifted into one run, the run and
 //                          the directory entry written.
-// The compressor runs them as extra workgroups of the quantizer's launches (sl_quant.hip), the
-// transcoder as launches of their own (sl_coded.hip).
+// The compressor runs them as extra workgroups of the quantizer's launches (sl_quant.hip), on lists of
+// many tensors and in the transcoder they are launches of their own (sl_coded.hip).
 struct SlCodedArgs {
     SlCodedGeom G;
     const SlTensorDev *tensors;

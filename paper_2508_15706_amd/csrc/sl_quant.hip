@@ -121,9 +121,9 @@ __device__ void block_tree_sums(const double *const (&leaf)[NS], long long n, Re
 }
 
 // ------------------------------------------------------------------ kernel B
-// One workgroup per tensor: its statistics.  With the coded format a second row of workgroups takes
-// the first placement step (independent of the statistics, and a launch of its own would cost more
-// than its work).
+// One workgroup per tensor: its statistics.  With the coded format, up to SL_PLACE_SHARED_UPTO, a second
+// row of workgroups takes the first placement step (independent of the statistics, and a launch of its
+// own would cost more than its work).
 __global__ void __launch_bounds__(RED_THREADS, 8)
 k_tensor_stats(const SlTensorDev *tensors, const double *leafA, long long n_chunks_total, int k,
                SlTensorStat *tstat, SlCodedArgs C)
@@ -165,7 +165,7 @@ struct CodeArgs {
     const SlCodedDesc *cdesc;
     int rem_bytes;
     int passes;             // passes of 512 entries over a chunk (1 up to k = 512)
-    unsigned code_blocks;   // workgroups with chunks; with the coded format one more takes the list scan
+    unsigned code_blocks;   // workgroups with chunks; the placement steps in these launches: one more takes the list scan
     unsigned long long *twords;
     int n_tensors;
     long long section;
@@ -461,8 +461,8 @@ codes_kernel codes_for(int log_lpc)
 
 // ------------------------------------------------------------------ kernel D
 // One workgroup per (tensor, bin): fixed-tree sum of the bin's leaves, integer count, centroid ->
-// LUT[b] in the tensor block's header.  With the coded format further workgroups take the last
-// placement step, `place_waves` groups each.
+// LUT[b] in the tensor block's header.  With the placement steps in these launches (PLACE) further
+// workgroups take the last of them, `place_waves` groups each.
 template <bool PLACE>
 __global__ void __launch_bounds__(RED_THREADS, 8)
 k_tensor_lut(const SlTensorDev *tensors, int n_tensors, const double *leafC, const unsigned *cnt,
@@ -601,12 +601,22 @@ int slk_residual(const sl_plan *p, float *e, const unsigned char *payload, hipSt
     return launch_residual(p, e, nullptr, payload, st);
 }
 
+// The coded format's placement steps share the launches of B, C and D up to so many (tensors x (bins + 4)): three
+// launches are saved, but every tensor pays for a second workgroup in B and, in each of its workgroups in D, for
+// the registers and the LDS of the placement (tensors of 3 chunks, k = 64, shared / launches of their own: 2 bits,
+// 300 tensors 37.6 / 39.8 us, 500 48.5 / 47.9, 3000 204 / 165; 1 bit, 500 41.3 / 42.2, 1000 62.8 / 56.1; 4 bits,
+// 150 47.2 / 47.3, 500 95.5 / 81.1; tensors of 40 chunks, 2 bits, 300 89.3 / 90.5, 1000 250 / 239).
+#ifndef SL_PLACE_SHARED_UPTO
+#define SL_PLACE_SHARED_UPTO 3300
+#endif
+
 int slk_quantize(const sl_plan *p, float *e, int skip_residual, unsigned char *payload, unsigned char *coded,
                  unsigned char *ws, hipStream_t st)
 {
     if (p->n_chunks == 0) return SL_OK;
     const int k = p->k;
     const SlCodedArgs placing = sl_coded_args(p, coded, ws);     // (used only with `coded`)
+    const bool shared = coded && p->bits != 32 && (long long)p->n_tensors * ((1 << p->bits) + 4) <= SL_PLACE_SHARED_UPTO;
     const float *vals = reinterpret_cast<const float *>(ws + p->ws_vals);
     double *leafA = reinterpret_cast<double *>(ws + p->ws_leafA);
     double *leafC = reinterpret_cast<double *>(ws + p->ws_leafC);
@@ -632,7 +642,7 @@ int slk_quantize(const sl_plan *p, float *e, int skip_residual, unsigned char *p
         return SL_OK;
     }
 
-    hipLaunchKernelGGL(k_tensor_stats, dim3(p->n_tensors, coded ? 2 : 1), dim3(RED_THREADS), 0, st, p->d_tensors,
+    hipLaunchKernelGGL(k_tensor_stats, dim3(p->n_tensors, shared ? 2 : 1), dim3(RED_THREADS), 0, st, p->d_tensors,
                        leafA, (long long)p->n_chunks, k, tstat, placing);
     if ((rc = check_launch())) return rc;
     sl_prof_mark(p, SL_PROF_STATS, st);
@@ -661,16 +671,16 @@ int slk_quantize(const sl_plan *p, float *e, int skip_residual, unsigned char *p
     C.twords = placing.twords;
     C.n_tensors = p->n_tensors;
     C.section = p->cg.section;
-    hipLaunchKernelGGL(fn, dim3(C.code_blocks + (coded ? 1 : 0)), dim3(256), 0, st, C);
+    hipLaunchKernelGGL(fn, dim3(C.code_blocks + (shared ? 1 : 0)), dim3(256), 0, st, C);
     if ((rc = check_launch())) return rc;
     sl_prof_mark(p, SL_PROF_CODES, st);
 
     const int nbins = 1 << p->bits;
     const size_t per_wave_lds = sl_coded_place_words(p->cg) * sizeof(unsigned);
-    const int place_waves = coded ? (int)std::max<size_t>(1, std::min<size_t>(RED_WAVES, 49152 / per_wave_lds)) : 0;
+    const int place_waves = shared ? (int)std::max<size_t>(1, std::min<size_t>(RED_WAVES, 49152 / per_wave_lds)) : 0;
     const long long per_column = (long long)place_waves * nbins;      // groups that one column of workgroups takes
-    const long long place_columns = coded ? (p->n_groups + per_column - 1) / per_column : 0;
-    hipLaunchKernelGGL(coded ? k_tensor_lut<true> : k_tensor_lut<false>, dim3((unsigned)(p->n_tensors + place_columns), nbins), dim3(RED_THREADS),
+    const long long place_columns = shared ? (p->n_groups + per_column - 1) / per_column : 0;
+    hipLaunchKernelGGL(shared ? k_tensor_lut<true> : k_tensor_lut<false>, dim3((unsigned)(p->n_tensors + place_columns), nbins), dim3(RED_THREADS),
                        place_waves * per_wave_lds, st, p->d_tensors, p->n_tensors, leafC, cnt, (long long)p->n_chunks,
                        p->hdr_bytes, p->rec_bytes, nbins, payload, coded, p->cg.cfix, placing, place_waves);
     if ((rc = check_launch())) return rc;
@@ -679,6 +689,10 @@ int slk_quantize(const sl_plan *p, float *e, int skip_residual, unsigned char *p
     if (!skip_residual) {
         if ((rc = launch_residual(p, e, vals, payload, st))) return rc;
         sl_prof_mark(p, SL_PROF_RESIDUAL, st);
+    }
+    if (coded && !shared) {
+        if ((rc = slk_coded_finish(p, coded, ws, st))) return rc;
+        sl_prof_mark(p, SL_PROF_INDEX, st);
     }
     return SL_OK;
 }

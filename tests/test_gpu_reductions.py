@@ -72,3 +72,35 @@ def test_placement_of_long_vectors(oracle, k):
     for what, buf in (("compress", coded), ("transcoder", again)):
         size = sl.coded_size(buf)
         assert size == want.size and np.array_equal(buf[:size].cpu().numpy(), want), what
+
+
+@pytest.mark.parametrize("bits, n_tensors", [(1, 550), (1, 551), (2, 412), (2, 413), (3, 275), (3, 276), (4, 165), (4, 166),
+                                             (32, 512), (32, 513), (2, 1300)])
+def test_lists_of_many_tensors(oracle, bits, n_tensors):
+    """Both sides of the numbers of tensors where the placement steps get launches of their own and where the
+    group scan goes from 1024 to 256 threads; compress and transcoder, eager error update."""
+    from paper_2508_15706_amd import binding as sl
+    k, descs, off = 16, [], 0
+    for t in range(n_tensors):
+        n = (24, 4096 + 40, 64, 2 * 4096, 100)[t % 5] if t != 7 else 4096 * 300 + 24    # 7: more groups than one turn of 16
+        descs.append((1, n, off, sl.SL_LAYOUT_FLAT))
+        off += (n + 63) // 64 * 64
+    rng = np.random.default_rng(100 * bits + n_tensors)
+    d0 = (1e-3 * rng.standard_t(3, off)).astype(np.float32)
+    plan = sl.sl_plan_create_bits(descs, k, bits)
+    pay, ws = sl.alloc_payload(plan), sl.alloc_workspace(plan)
+    pay.fill_(0xAB)
+    cap = sl.sl_rice_max_bytes(plan)
+    coded, again = (torch.full((cap,), 0xCD, dtype=torch.uint8, device="cuda") for _ in range(2))
+    e = torch.zeros(off, dtype=torch.float32, device="cuda")
+    sl.sl_compress_coded(plan, e, torch.from_numpy(d0).cuda(), 0.95, pay, coded, ws)
+    sl.sl_rice_encode(plan, pay, again, ws)
+    torch.cuda.synchronize()
+    e_ref = np.zeros(off, np.float32)
+    want = oracle.compress_b(descs, k, bits, e_ref, d0, 0.95)
+    assert np.array_equal(pay[:plan.payload_bytes].cpu().numpy(), want)
+    assert np.array_equal(e.cpu().numpy().view(np.uint32), e_ref.view(np.uint32))
+    want = oracle.rice_encode_b(descs, k, bits, want)
+    for what, buf in (("compress", coded), ("transcoder", again)):
+        size = sl.coded_size(buf)
+        assert size == want.size and np.array_equal(buf[:size].cpu().numpy(), want), what
