@@ -92,8 +92,14 @@ SL_DEV int place_in_byte(unsigned x, int n)
 // MODE 0: theta update; 1: with DiLoCo's global Nesterov momentum (Eq. (1)); 2: no update at
 // all - the one payload is decoded into a plain payload (R = 1).
 // LISTS (few entries): steps 3 to 5 go through index lists in LDS, see the top of the file.
+// Waves per SIMD: the decode alone (MODE 2) keeps no theta and is short; what it waits for is its chain of memory
+// and LDS trips, so it is held to the registers that allow five waves (85; left to itself it takes 105, four waves:
+// 24,000 chunks, k = 4 28.0 -> 26.0 us, k = 128 27.8 -> 26.0, fp32 values, k = 1024 72 -> 65; six waves spill).
+#ifndef SL_CAPPLY_DECODE_WAVES
+#define SL_CAPPLY_DECODE_WAVES 5
+#endif
 template <bool TWO_BIT, int MODE, bool LISTS>
-__global__ void __launch_bounds__(256) k_apply_coded(CodedApplyArgs A)
+__global__ void __launch_bounds__(256, MODE == 2 ? SL_CAPPLY_DECODE_WAVES : 1) k_apply_coded(CodedApplyArgs A)
 {
     constexpr bool NESTEROV = MODE == 1, DECODE = MODE == 2;
     extern __shared__ __align__(16) unsigned char smem_all[];

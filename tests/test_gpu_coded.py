@@ -300,7 +300,7 @@ def test_apply_nesterov_coded_matches_oracle(sl, oracle, k, R):
 
 
 # --------------------------------------------------------------------------- transcoders
-@pytest.mark.parametrize("k", [4, 20, 32, 64, 128, 256, 1000])
+@pytest.mark.parametrize("k", [4, 8, 12, 16, 20, 24, 32, 64, 128, 256, 1000])
 def test_rice_transcode_matches_oracle(sl, oracle, k):
     """sl_rice_encode produces the oracle's coded bytes from a plain payload, sl_rice_decode restores
     the payload (from the GPU's and from the oracle's coded buffer)."""
