@@ -344,8 +344,12 @@ int sl_compress_impl(sl_plan *p, float *e, const float *delta, const float *thet
                         pay, static_cast<unsigned char *>(coded), ws, st);
     if (rc) return rc;
     sl_prof_mark(p, SL_PROF_SELECT, st);
-    if (p->n_chunks == 0)
-        return coded ? slk_coded_finish(p, static_cast<unsigned char *>(coded), ws, st) : SL_OK;
+    if (p->n_chunks == 0) {
+        if (!coded) return SL_OK;
+        rc = slk_coded_finish(p, static_cast<unsigned char *>(coded), ws, st);
+        sl_prof_mark(p, SL_PROF_INDEX, st);
+        return rc;
+    }
     return slk_quantize(p, e, frozen || defer, pay, static_cast<unsigned char *>(coded), ws, st);
 }
 

@@ -383,3 +383,22 @@ def test_rice_encode_of_a_malformed_record_stays_in_its_buffer(sl, oracle):
     assert sl.sl_coded_fixed_bytes(plan) <= size <= cap
     assert bool((out[cap:] == 0xCD).all())
     plan.close()
+
+
+@pytest.mark.parametrize("case, placed_apart", [("short", 0), ("fp32", 1), ("many", 1), ("empty", 1)])
+def test_profile_counts_the_phases_that_ran(sl, case, placed_apart):
+    """The placement phase has calls exactly where it has launches of its own, every other phase as with plain
+    payloads; two profiled calls."""
+    shapes = {"empty": [], "many": [(1, 4096, FLAT)] * 500}.get(case, [(64, 64, TILE), (1, 8192, FLAT)])
+    descs, n = layout_list(shapes)
+    plan = sl.sl_plan_create_bits(descs, 16, 32 if case == "fp32" else 2)
+    ws, pay = sl.alloc_workspace(plan), sl.alloc_payload(plan)
+    coded = torch.zeros(max(16, sl.sl_rice_max_bytes(plan)), dtype=torch.uint8, device="cuda")
+    e, d = (torch.randn(max(n, 64), device="cuda") for _ in range(2))
+    sl.sl_profile_begin(plan, 4)
+    for _ in range(2):
+        sl.sl_compress_coded(plan, e, d, 0.95, pay, coded, ws, flags=sl.SL_COMPRESS_DEFER_RESIDUAL)
+    calls = [v[1] for v in sl.sl_profile_end(plan).values()]
+    quantized = 2 * (case in ("short", "many"))
+    assert calls == [2, quantized, quantized, 2 * (case != "empty"), 0, 0, 2 * placed_apart], calls
+    assert plan.num_chunks == 0 or sl.coded_size(coded) > 16
