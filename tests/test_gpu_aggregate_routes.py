@@ -1,6 +1,6 @@
 """Both aggregates at the edges of their decode layouts (lanes per worker, workers side by side in a wave,
-steps per worker, batches, records at odd addresses), on spread and on clustered supports, against the
-oracle's aggregate of the same payloads."""
+steps per worker, batches, records at odd addresses), with and without the global momentum, on spread and on
+clustered supports, against the oracle's aggregate of the same payloads."""
 import numpy as np
 import pytest
 import torch
@@ -53,6 +53,19 @@ def test_aggregates_at_layout_edges(oracle, k, R):
             sl.sl_decompress_avg_apply_coded(plan, theta, wires, sizes, 0.8)
         torch.cuda.synchronize()
         assert np.array_equal(theta.cpu().numpy().view(np.uint32), want.view(np.uint32)), call
+    # the same with the global momentum: instantiations of their own, with the momentum's loads beside the decode's
+    mom0 = rng.normal(0, 1e-3, off).astype(np.float32)
+    want, mom_want = theta0.copy(), mom0.copy()
+    oracle.decompress_avg_apply_nesterov_b(descs, k, 2, want, mom_want, refs, 0.8, 0.9)
+    for call in ("plain", "coded"):
+        theta, mom = torch.from_numpy(theta0.copy()).cuda(), torch.from_numpy(mom0.copy()).cuda()
+        if call == "plain":
+            sl.sl_decompress_avg_apply_nesterov(plan, theta, mom, plain, 0.8, 0.9)
+        else:
+            sl.sl_decompress_avg_apply_nesterov_coded(plan, theta, mom, wires, sizes, 0.8, 0.9)
+        torch.cuda.synchronize()
+        assert np.array_equal(theta.cpu().numpy().view(np.uint32), want.view(np.uint32)), call + ", momentum: theta"
+        assert np.array_equal(mom.cpu().numpy().view(np.uint32), mom_want.view(np.uint32)), call + ", momentum"
     back = torch.full((plan.payload_bytes,), 0xEE, dtype=torch.uint8, device="cuda")
     for r in range(min(R, 3)):
         sl.sl_rice_decode(plan, wires[r], sizes[r], back)
