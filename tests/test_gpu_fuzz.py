@@ -76,8 +76,6 @@ def test_random_configuration(sl, oracle, case):
     except sl.SparseLoCoError:
         pytest.skip("generator produced a chunk smaller than k")   # the oracle rejects it as well
     assert plan.num_chunks == oracle.num_chunks(descs)
-    if case % 2:      # short lists take the wave-per-chunk code kernel: every other case forces the other one
-        sl.sl_plan_set_codes_wave_below(plan, 0)
     ws = sl.alloc_workspace(plan)
     theta0 = rng.normal(0, 0.02, n).astype(np.float32)
     theta = torch.from_numpy(theta0.copy()).cuda()

@@ -51,10 +51,8 @@ def gpu_compress(sl, plan, e_host, d_host, beta, flags=0):
     return e.cpu().numpy(), pay[:plan.payload_bytes].cpu().numpy(), pay
 
 
-def check_compress(sl, oracle, descs, n, k, e0, delta, beta, flags=0, what="", wave_below=None):
+def check_compress(sl, oracle, descs, n, k, e0, delta, beta, flags=0, what=""):
     plan = sl.sl_plan_create(descs, k)
-    if wave_below is not None:
-        sl.sl_plan_set_codes_wave_below(plan, wave_below)
     assert plan.num_chunks == oracle.num_chunks(descs)
     assert plan.payload_bytes == oracle.payload_bytes(descs, k)
     e_gpu, pay_gpu, _ = gpu_compress(sl, plan, e0, delta, beta, flags)
@@ -69,12 +67,11 @@ def check_compress(sl, oracle, descs, n, k, e0, delta, beta, flags=0, what="", w
 
 
 # --------------------------------------------------------------------------- compress
-@pytest.mark.parametrize("k,lane_codes", [(k, False) for k in (4, 8, 20, 32, 64, 128, 256, 512, 1000)] +
-                         [(k, True) for k in (4, 8, 20, 32, 64, 128)])
-def test_compress_small_list_all_k_paths(sl, oracle, k, lane_codes):
+@pytest.mark.parametrize("k", [4, 8, 12, 20, 32, 36, 64, 100, 128, 200, 256, 260, 512, 520, 1000])
+def test_compress_small_list_all_k_paths(sl, oracle, k):
     """Several tiles, ragged edges in both directions, 16-column matrix, 1-D tails;
-    k covers every pruning width, the byte-wise record writer and the unpruned path.
-    Up to k = 128 the code kernel is chosen by the length of the list: both choices are run."""
+    k covers every pruning width, the byte-wise record writer, the unpruned path and the code kernel's
+    lanes per chunk and passes."""
     if k <= 256:      # smallest chunk: 22 x 18 = 396 elements
         shapes = [(150, 210, TILE), (1, 9000, FLAT), (1024, 16, TILE), (64, 64, TILE),
                   (1, 4096 + 1030, FLAT), (128, 192, TILE)]
@@ -86,7 +83,7 @@ def test_compress_small_list_all_k_paths(sl, oracle, k, lane_codes):
     rng = np.random.default_rng(100 + k)
     e0 = rng.normal(0, 1e-3, n).astype(np.float32)
     delta = rng.normal(0, 1e-3, n).astype(np.float32)
-    check_compress(sl, oracle, descs, n, k, e0, delta, 0.95, what="small list", wave_below=0 if lane_codes else None)
+    check_compress(sl, oracle, descs, n, k, e0, delta, 0.95, what="small list")
 
 
 def test_compress_dense_case_k_4096(sl, oracle):
