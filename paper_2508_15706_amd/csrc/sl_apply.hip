@@ -5,11 +5,12 @@
 //
 // One wavefront owns one chunk.  The dense average never exists in HBM: the
 // chunk's fp32 accumulators live in LDS (16 KB, or one half of the chunk at a
-// time), the R records (7k/4 bytes each) are staged into LDS with coalesced
-// loads, entries of one worker are distinct positions so they are added without
-// conflicts, workers are added in the order r = 0..R-1, and theta streams
-// through registers once (8 bytes per element of HBM traffic plus R*7k/4 bytes
-// per chunk).
+// time), the R records (7k/4 bytes each at 2 bits) are staged into LDS with
+// coalesced loads or, 2-bit records with much to decode, loaded into registers
+// by the lanes that decode them; entries of one worker are distinct positions
+// so they are added without conflicts, workers are added in the order
+// r = 0..R-1, and theta streams through registers once (8 bytes per element of
+// HBM traffic plus the records).
 #include <algorithm>
 
 #include "sl_device.h"
@@ -17,12 +18,12 @@
 
 namespace {
 
-// When there is much to decode per chunk (R*k entries) at small k, the chunk is
-// aggregated in NH = 2 halves of 32 rows (local indices below / from 2048): 8 KB of
+// When there is much to decode per chunk (R*k entries) entry by entry, the chunk
+// is aggregated in NH = 2 halves of 32 rows (local indices below / from 2048): 8 KB of
 // accumulators per wave instead of 16, so that more waves - and more bytes of
 // theta in flight - fit a compute unit while the decode runs.  With little to
-// decode, and from k = 256 (cheaper decode, records staged 4 KB at a time), one
-// pass (NH = 1) is faster.
+// decode, and where eight entries are decoded at a time (from k = 256, and the
+// direct route), one pass (NH = 1) is faster.
 #ifndef SL_APPLY_HALVES_FROM
 #define SL_APPLY_HALVES_FROM 1536   // R*k from which two halves pay (measured)
 #endif
@@ -34,7 +35,9 @@ namespace {
 // From k = 136 a worker's lanes fill half the wave or more; below, up to four workers share it and add
 // one after the other, which pays later (24,000 chunks, the other routes / direct: k = 136, R = 16
 // 199 / 179 us, k = 200, R = 32 421 / 285; k = 128, R = 16 169 / 173, k = 96, R = 32 339 / 195,
-// k = 128, R = 32 355 / 198, k = 64, R = 32 181 / 193, k = 64, R = 64 419 / 286).
+// k = 128, R = 32 355 / 198, k = 64, R = 32 181 / 193, k = 64, R = 64 419 / 286; between 2048 and 3072 entries
+// nothing was measured below k = 136).  From k = 256 it is taken whatever R: with one to three workers both
+// routes wait for theta (k = 256, R = 1 147 / 149, k = 1024, R = 2 167 / 163; on 2000 chunks, R = 1 16.0 / 16.7).
 #ifndef SL_APPLY_DIRECT_ENTRIES
 #define SL_APPLY_DIRECT_ENTRIES(k) ((k) >= 136 ? 2048 : 3072)
 #endif
@@ -175,9 +178,11 @@ __global__ void __launch_bounds__(256) k_apply(ApplyArgs A)
     }
     // Direct route.  Step s of a chunk: lane (i, o) of the wave loads entries 8o .. 8o+7 (64 lanes further on
     // in each of the dp steps of a worker when its record has more) of worker (s / dp) dw + i: three words
-    // of indices - four, when the record starts in the middle of a word - and 16 bits of codes.  A batch is
-    // DS steps; the first one is under way before the theta loads, each step of a later one is loaded
-    // as soon as the step before it in the same registers has been added.
+    // of indices - four, when the record starts in the middle of a word - and 16 bits of codes.  A batch is the
+    // whole workers that fit DS steps and 16 tables: eight steps from k = 176, five at k = 136 .. 168 (three workers
+    // side by side), four below (four of them).  The first batch is under way before the theta loads - the steps
+    // loaded with it beyond a shorter batch are loaded again with their own -, each step of a later one is loaded as
+    // soon as the step before it in the same registers has been added.
     constexpr int DS = DIRECT ? 8 : 1;
     unsigned dx[DS][4];
     float dlut = 0.f;
