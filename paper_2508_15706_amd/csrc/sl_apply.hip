@@ -77,6 +77,7 @@ struct ApplyArgs {
     unsigned magic_src;
     int lds_per_wave;
     long long n_chunks;
+    unsigned order;          // sl_work_group
     const unsigned char *payload[SL_MAX_WORKERS];
 };
 
@@ -105,7 +106,7 @@ __global__ void __launch_bounds__(256) k_apply(ApplyArgs A)
     extern __shared__ __align__(16) unsigned char smem_all[];
     const int lane = threadIdx.x & 63, k = A.k;
     const int wave = sl_uniform((int)(threadIdx.x >> 6));
-    const long long c = (long long)blockIdx.x * (blockDim.x >> 6) + wave;
+    const long long c = (long long)sl_work_group(blockIdx.x, A.order) * (blockDim.x >> 6) + wave;
     if (c >= A.n_chunks) return;
     unsigned char *smem = smem_all + (size_t)wave * A.lds_per_wave;
     float *acc = reinterpret_cast<float *>(smem);                    // the chunk, or one half of it
@@ -757,6 +758,7 @@ int slk_apply(const sl_plan *p, float *theta, float *mom, float mu, const void *
         }
     }
     const dim3 grid((unsigned)((p->n_chunks + wpb - 1) / wpb)), block(64 * wpb);
+    A.order = sl_order(p, grid.x);
     hipLaunchKernelGGL(fn, grid, block, lds, st, A);
     hipError_t err = hipGetLastError();
     if (err != hipSuccess) {

@@ -70,6 +70,7 @@ struct CodedApplyArgs {
     int rec_bytes;           // MODE 2: bytes of a plain record
     int lds_per_wave;
     long long n_chunks;
+    unsigned order;          // sl_work_group
     const unsigned char *payload[SL_MAX_WORKERS];
     unsigned sec_words[SL_MAX_WORKERS];   // words of each payload's quotient section
 };
@@ -107,7 +108,7 @@ __global__ void __launch_bounds__(256, MODE == 2 ? SL_CAPPLY_DECODE_WAVES : 1) k
     const SlCodedGeom &G = A.G;
     const int lane = threadIdx.x & 63, k = G.k, b = G.b;
     const int wave = sl_uniform((int)(threadIdx.x >> 6));
-    const long long c = (long long)blockIdx.x * (blockDim.x >> 6) + wave;
+    const long long c = (long long)(DECODE ? blockIdx.x : sl_work_group(blockIdx.x, A.order)) * (blockDim.x >> 6) + wave;
     if (c >= A.n_chunks) return;
     unsigned char *smem = smem_all + (size_t)wave * A.lds_per_wave;
     float *acc = reinterpret_cast<float *>(smem);
@@ -950,6 +951,7 @@ int slk_apply_coded(const sl_plan *p, int mode, float *theta, float *mom, float 
         }
     }
     const dim3 grid((unsigned)((p->n_chunks + wpb - 1) / wpb)), block(64 * wpb);
+    A.order = sl_order(p, grid.x);
     hipLaunchKernelGGL(fn, grid, block, lds, st, A);
     hipError_t err = hipGetLastError();
     if (err != hipSuccess) {

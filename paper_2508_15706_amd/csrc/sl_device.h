@@ -68,9 +68,56 @@ SL_DEV void sl_store_stream_u(float *p, sl_f4 v)
     __builtin_nontemporal_store(v, reinterpret_cast<sl_f4u *>(p));
 }
 
+// Four elements at p of which `n` exist (any n; none below 1): one access where all four do, else element by
+// element; what does not exist is read as +0.0f and not written.
+SL_DEV sl_f4 sl_load_edge(const float *p, int n)
+{
+    sl_f4 v = sl_f4{0.f, 0.f, 0.f, 0.f};
+    if (n >= 4) {
+        v = sl_load_stream_u(p);
+    } else {
+#pragma unroll
+        for (int cc = 0; cc < 4; ++cc)
+            if (cc < n) v[cc] = p[cc];
+    }
+    return v;
+}
+SL_DEV void sl_store_edge(float *p, int n, sl_f4 v)
+{
+    if (n >= 4) {
+        sl_store_stream_u(p, v);
+    } else {
+#pragma unroll
+        for (int cc = 0; cc < 4; ++cc)
+            if (cc < n) p[cc] = v[cc];
+    }
+}
+
 SL_DEV int sl_popc(unsigned long long m) { return __builtin_popcountll(m); }
 
 SL_DEV int sl_uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+
+// Which group of adjacent chunks workgroup `i` of a kernel that streams arenas takes: windows of SL_ORDER_WINDOW
+// groups are walked at two places together, half a window apart, by the even and the odd XCDs (workgroups
+// reach the eight XCDs in turn).  `order` (sl_order) is the number of groups in whole windows, the rest is taken in
+// list order; its bit 0 turns the four groups of a place by one from one four to the next.
+// What it is for is the memory's: walked at one place by all XCDs, the rows that are open at a time
+// crowd on part of its channels.  Accumulate pass / aggregate of coded payloads / dense aggregate of four (k = 64, R = 8), list
+// order and this one, us: 178M list 404 / 264 / 786 and 376 / 236 / 754, 510M 1066 / 705 / 2188 and 1002 / 663 / 2062, MoE
+// 1424 / 920 / 2877 and 1350 / 865 / 2771, 1.8B 3582 / 2484 / 7616 and 3572 / 2364 / 7424, the same as flat runs 3972 / 2671 /
+// 7925 and 3753 / 2490 / 7624; the plain aggregate of the 1.8B list (rows 8 KB apart) 2372 and 2390, the only one that
+// lost.  The halves of the whole list in place of windows: the same, but 2470 for the 1.8B coded aggregate (neighbouring chunks
+// share lines of the payloads); windows of 256 groups lose 1 % on the accumulate pass; four or eight places 1 - 3 %
+// behind two except on flat runs; a third, a sixth or random places are worse than list order.
+#define SL_ORDER_WINDOW 1024u
+SL_DEV unsigned sl_work_group(unsigned i, unsigned order)
+{
+    if (i >= (order & ~1u)) return i;
+    const unsigned j = i % SL_ORDER_WINDOW;
+    unsigned o = j >> 1;
+    if (order & 1u) o = (o & ~3u) | ((o + (o >> 2)) & 3u);
+    return i - j + (j & 1u) * (SL_ORDER_WINDOW / 2) + o;
+}
 
 // Cross-lane moves inside a row of 16 lanes as data-parallel-primitive modifiers (no trip
 // through the LDS crossbar, unlike a shuffle).  With all 64 lanes active:

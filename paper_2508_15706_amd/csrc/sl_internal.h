@@ -126,6 +126,16 @@ __host__ __device__ inline long long sl_lut_off(const SlChunkDesc &d, int hdr_by
     return d.rec_off - hdr_bytes - (long long)d.local_chunk * rec_bytes;
 }
 
+// sl_work_group's `order` for a grid of so many groups.  Where a list has many partial chunks - the last column of a
+// matrix's tiles: one group in every few - the slow groups would all come to one or two of the XCDs, so the groups
+// are turned (columns 1000 and 2730, a chunk in 25 partial, plain aggregate of 8: list order 475, paired 488, turned 471 us;
+// on full chunks the turn costs up to 3 %).
+inline unsigned sl_order(const sl_plan *p, unsigned groups)
+{
+    const unsigned whole = groups & ~1023u;
+    return whole | (whole && p->n_partial * 32 >= p->n_chunks ? 1u : 0u);
+}
+
 // Records an event after the kernel of `phase` (phase < 0: start of a call).
 void sl_prof_mark(const sl_plan *p, int phase, hipStream_t st);
 

@@ -9,8 +9,12 @@
 //                     [m <- mu*m + avg ; avg <- avg + mu*m] ; theta <- theta - lr*avg
 //
 // Every "c*y + z" is one fp32 fused multiply-add.  Both kernels are pure
-// streams: one wavefront owns one chunk and moves it in two halves of eight
-// 16-byte accesses per lane per stream, so that many workgroups stay resident.
+// streams, bound by memory: one wavefront owns one chunk and moves it in two halves
+// of eight 16-byte accesses per lane per stream, all loads of a stream under way before the first result -
+// in partial chunks too, where a lane whose four columns exist still moves them with one access (200 x 530 matrices
+// and the like, 3.4M elements, four directions: element by element 60 us, so 23; with momentum 72 and 30).
+#include <type_traits>
+
 #include "sl_device.h"
 #include "sl_internal.h"
 
@@ -22,6 +26,12 @@
 #ifndef SL_DENSE_STEP
 #define SL_DENSE_STEP 8
 #endif
+// LDS that a workgroup asks for and does not use: three of them fit a compute unit then.  With more waves than
+// that the memory has more rows open than it keeps, and is slower (1.8B list: direction 4.88 ms without, 4.75 so; four
+// directions averaged 7.59 and 7.48; 1000- and 2730-column matrices 1.02 and 0.85, 1.20 and 1.12).
+#ifndef SL_STREAM_LDS
+#define SL_STREAM_LDS 54272
+#endif
 namespace {
 
 struct LomArgs {
@@ -31,13 +41,14 @@ struct LomArgs {
     float *dir;
     float mu;
     long long n_chunks;
+    unsigned order;          // sl_work_group
 };
 
 __global__ void __launch_bounds__(256) k_lom_direction(LomArgs A)
 {
     const int lane = threadIdx.x & 63;
     const int wave = sl_uniform((int)(threadIdx.x >> 6));
-    const long long c = (long long)blockIdx.x * (blockDim.x >> 6) + wave;
+    const long long c = (long long)sl_work_group(blockIdx.x, A.order) * (blockDim.x >> 6) + wave;
     if (c >= A.n_chunks) return;
     const SlChunkDesc d = A.desc[c];
     float *mc = A.m + d.base;
@@ -68,18 +79,26 @@ __global__ void __launch_bounds__(256) k_lom_direction(LomArgs A)
         }
     } else {
         const int rows = d.rows, cols = d.cols, last_cols = d.last_cols;
-        for (int i = 0; i < 16; ++i) {
-            const int row = 4 * i + lr;
-            const int lim = row < rows - 1 ? cols : (row == rows - 1 ? last_cols : 0);
-            for (int cc = 0; cc < 4; ++cc) {
-                const int col = lc + cc;
-                if (col < lim) {
-                    const unsigned o = row * stride + col;
-                    const float g = dc[o];
-                    const float m = fmaf(A.mu, mc[o], g);
-                    mc[o] = m;
-                    oc[o] = fmaf(A.mu, m, g);
-                }
+        constexpr int S = SL_LOM_STEP;
+#pragma unroll
+        for (int q = 0; q < 16 / S; ++q) {
+            sl_f4 mv[S], dv[S];
+#pragma unroll
+            for (int u = 0; u < S; ++u) {
+                const int row = 4 * (S * q + u) + lr, n = (row < rows - 1 ? cols : row == rows - 1 ? last_cols : 0) - lc;
+                mv[u] = sl_load_edge(mc + (row * stride + lc), n);
+                dv[u] = sl_load_edge(dc + (row * stride + lc), n);
+            }
+#pragma unroll
+            for (int u = 0; u < S; ++u) {
+                const int row = 4 * (S * q + u) + lr, n = (row < rows - 1 ? cols : row == rows - 1 ? last_cols : 0) - lc;
+                sl_f4 m = mv[u], g = dv[u], o;
+                m.x = fmaf(A.mu, m.x, g.x), m.y = fmaf(A.mu, m.y, g.y);
+                m.z = fmaf(A.mu, m.z, g.z), m.w = fmaf(A.mu, m.w, g.w);
+                o.x = fmaf(A.mu, m.x, g.x), o.y = fmaf(A.mu, m.y, g.y);
+                o.z = fmaf(A.mu, m.z, g.z), o.w = fmaf(A.mu, m.w, g.w);
+                sl_store_edge(mc + (row * stride + lc), n, m);
+                sl_store_edge(oc + (row * stride + lc), n, o);
             }
         }
     }
@@ -92,6 +111,7 @@ struct DenseArgs {
     float neg_lr, inv_R, mu;
     int R;
     long long n_chunks;
+    unsigned order;          // sl_work_group
     const float *dirs[SL_MAX_WORKERS];
 };
 
@@ -100,7 +120,7 @@ __global__ void __launch_bounds__(256) k_dense_avg_apply(DenseArgs A)
 {
     const int lane = threadIdx.x & 63;
     const int wave = sl_uniform((int)(threadIdx.x >> 6));
-    const long long c = (long long)blockIdx.x * (blockDim.x >> 6) + wave;
+    const long long c = (long long)sl_work_group(blockIdx.x, A.order) * (blockDim.x >> 6) + wave;
     if (c >= A.n_chunks) return;
     const SlChunkDesc d = A.desc[c];
     float *tc = A.theta + d.base;
@@ -108,66 +128,63 @@ __global__ void __launch_bounds__(256) k_dense_avg_apply(DenseArgs A)
     const int lr = lane >> 4, lc = (lane & 15) * 4;
     const unsigned stride = (unsigned)d.stride;
     const int R = A.R;
-    if (d.flags & SLC_FULL) {
-        const unsigned o0 = 4u * (lr * stride + lc), step = 16u * stride;
-        constexpr int S = SL_DENSE_STEP;
-#pragma unroll 1
-        for (int q = 0; q < 16 / S; ++q) {
-            sl_f4 th[S], mo[NESTEROV ? S : 1], acc[S];
+    const int rows = d.rows, cols = d.cols, last_cols = d.last_cols;
+    const unsigned o0 = 4u * (lr * stride + lc), step = 16u * stride;
+    constexpr int S = SL_DENSE_STEP;
+    auto part = [&](int q, auto is_full) __attribute__((always_inline)) {
+        constexpr bool full = decltype(is_full)::value;
+        // access u of this step: elements 4 (S q + u) + lr, lc .. lc + 3 of the chunk
+        auto exist = [&](int u) -> int {                    // how many of them (partial chunks)
+            const int row = 4 * (S * q + u) + lr;
+            return (row < rows - 1 ? cols : row == rows - 1 ? last_cols : 0) - lc;
+        };
+        auto load = [&](const float *p, sl_f4 (&v)[S]) __attribute__((always_inline)) {
+            if (full) {
 #pragma unroll
-            for (int u = 0; u < S; ++u) th[u] = sl_load_stream_at(tc, (S * q + u) * step, o0);
+                for (int u = 0; u < S; ++u) v[u] = sl_load_stream_at(p, (S * q + u) * step, o0);
+            } else {
+#pragma unroll
+                for (int u = 0; u < S; ++u) v[u] = sl_load_edge(p + ((4 * (S * q + u) + lr) * stride + lc), exist(u));
+            }
+        };
+        sl_f4 th[S], mo[NESTEROV ? S : 1], acc[S];
+        load(tc, th);
+        if constexpr (NESTEROV) load(mc, mo);
+#pragma unroll
+        for (int u = 0; u < S; ++u) acc[u] = sl_f4{0.f, 0.f, 0.f, 0.f};
+        for (int r = 0; r < R; ++r) {                       // r ascending: the order is part of the result
+            sl_f4 g[S];
+            load(A.dirs[r] + d.base, g);
+#pragma unroll
+            for (int u = 0; u < S; ++u) acc[u] = acc[u] + g[u];
+        }
+#pragma unroll
+        for (int u = 0; u < S; ++u) {
+            auto store = [&](float *p, sl_f4 v) __attribute__((always_inline)) {
+                if (full) sl_store_stream_at(p, (S * q + u) * step, o0, v);
+                else sl_store_edge(p + ((4 * (S * q + u) + lr) * stride + lc), exist(u), v);
+            };
+            sl_f4 g = acc[u] * A.inv_R;
             if constexpr (NESTEROV) {
-#pragma unroll
-                for (int u = 0; u < S; ++u) mo[u] = sl_load_stream_at(mc, (S * q + u) * step, o0);
+                sl_f4 m = mo[u];
+                m.x = fmaf(A.mu, m.x, g.x), m.y = fmaf(A.mu, m.y, g.y);
+                m.z = fmaf(A.mu, m.z, g.z), m.w = fmaf(A.mu, m.w, g.w);
+                store(mc, m);
+                g.x = fmaf(A.mu, m.x, g.x), g.y = fmaf(A.mu, m.y, g.y);
+                g.z = fmaf(A.mu, m.z, g.z), g.w = fmaf(A.mu, m.w, g.w);
             }
-#pragma unroll
-            for (int u = 0; u < S; ++u) acc[u] = sl_f4{0.f, 0.f, 0.f, 0.f};
-            for (int r = 0; r < R; ++r) {                   // r ascending: the order is part of the result
-                const float *gc = A.dirs[r] + d.base;
-                sl_f4 g[S];
-#pragma unroll
-                for (int u = 0; u < S; ++u) g[u] = sl_load_stream_at(gc, (S * q + u) * step, o0);
-#pragma unroll
-                for (int u = 0; u < S; ++u) acc[u] = acc[u] + g[u];
-            }
-#pragma unroll
-            for (int u = 0; u < S; ++u) {
-                sl_f4 g = acc[u] * A.inv_R;
-                if constexpr (NESTEROV) {
-                    sl_f4 m = mo[u];
-                    m.x = fmaf(A.mu, m.x, g.x), m.y = fmaf(A.mu, m.y, g.y);
-                    m.z = fmaf(A.mu, m.z, g.z), m.w = fmaf(A.mu, m.w, g.w);
-                    sl_store_stream_at(mc, (S * q + u) * step, o0, m);
-                    g.x = fmaf(A.mu, m.x, g.x), g.y = fmaf(A.mu, m.y, g.y);
-                    g.z = fmaf(A.mu, m.z, g.z), g.w = fmaf(A.mu, m.w, g.w);
-                }
-                sl_f4 v = th[u];
-                v.x = fmaf(A.neg_lr, g.x, v.x), v.y = fmaf(A.neg_lr, g.y, v.y);
-                v.z = fmaf(A.neg_lr, g.z, v.z), v.w = fmaf(A.neg_lr, g.w, v.w);
-                sl_store_stream_at(tc, (S * q + u) * step, o0, v);
-            }
+            sl_f4 v = th[u];
+            v.x = fmaf(A.neg_lr, g.x, v.x), v.y = fmaf(A.neg_lr, g.y, v.y);
+            v.z = fmaf(A.neg_lr, g.z, v.z), v.w = fmaf(A.neg_lr, g.w, v.w);
+            store(tc, v);
         }
+    };
+    if (d.flags & SLC_FULL) {
+#pragma unroll 1
+        for (int q = 0; q < 16 / S; ++q) part(q, std::true_type{});
     } else {
-        const int rows = d.rows, cols = d.cols, last_cols = d.last_cols;
-        for (int i = 0; i < 16; ++i) {
-            const int row = 4 * i + lr;
-            const int lim = row < rows - 1 ? cols : (row == rows - 1 ? last_cols : 0);
-            for (int cc = 0; cc < 4; ++cc) {
-                const int col = lc + cc;
-                if (col < lim) {
-                    const unsigned o = row * stride + col;
-                    float acc = 0.0f;
-                    for (int r = 0; r < R; ++r) acc = acc + (A.dirs[r] + d.base)[o];
-                    float g = acc * A.inv_R;
-                    if constexpr (NESTEROV) {
-                        const float m = fmaf(A.mu, mc[o], g);
-                        mc[o] = m;
-                        g = fmaf(A.mu, m, g);
-                    }
-                    tc[o] = fmaf(A.neg_lr, g, tc[o]);
-                }
-            }
-        }
+#pragma unroll 1
+        for (int q = 0; q < 16 / S; ++q) part(q, std::false_type{});
     }
 }
 
@@ -193,7 +210,9 @@ int slk_lom_direction(const sl_plan *p, float *m, const float *delta, float mu, 
     A.dir = dir;
     A.mu = mu;
     A.n_chunks = p->n_chunks;
-    hipLaunchKernelGGL(k_lom_direction, dim3((unsigned)((p->n_chunks + 3) / 4)), dim3(256), 0, st, A);
+    const dim3 grid((unsigned)((p->n_chunks + 3) / 4)), block(256);
+    A.order = sl_order(p, grid.x);
+    hipLaunchKernelGGL(k_lom_direction, grid, block, SL_STREAM_LDS, st, A);
     return check_launch();
 }
 
@@ -212,7 +231,8 @@ int slk_dense_avg_apply(const sl_plan *p, float *theta, float *mom, const float 
     A.n_chunks = p->n_chunks;
     for (int r = 0; r < SL_MAX_WORKERS; ++r) A.dirs[r] = r < R ? dirs[r] : nullptr;
     const dim3 grid((unsigned)((p->n_chunks + 3) / 4)), block(256);
-    if (mom) hipLaunchKernelGGL(k_dense_avg_apply<true>, grid, block, 0, st, A);
-    else hipLaunchKernelGGL(k_dense_avg_apply<false>, grid, block, 0, st, A);
+    A.order = sl_order(p, grid.x);
+    if (mom) hipLaunchKernelGGL(k_dense_avg_apply<true>, grid, block, SL_STREAM_LDS, st, A);
+    else hipLaunchKernelGGL(k_dense_avg_apply<false>, grid, block, SL_STREAM_LDS, st, A);
     return check_launch();
 }

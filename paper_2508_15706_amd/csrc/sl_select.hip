@@ -61,6 +61,7 @@ struct SelectArgs {
     double *leafA;          // [2][n_chunks] per-chunk tree sums of x and x*x
     unsigned char *payload;
     long long n_chunks;
+    unsigned order;          // sl_work_group
     // coded wire format written next to the plain record (null: not wanted): the remainder fields go
     // to their place in the buffer, the chunk's quotient bit vector and quotient sum to the workspace
     unsigned char *coded;
@@ -320,7 +321,7 @@ __global__ void SL_SELECT_BOUNDS k_select(SelectArgs A)
     extern __shared__ __align__(16) unsigned char smem_all[];
     const int lane = threadIdx.x & 63;
     const int wave = sl_uniform((int)(threadIdx.x >> 6));
-    const long long c = (long long)blockIdx.x * (blockDim.x >> 6) + wave;
+    const long long c = (long long)sl_work_group(blockIdx.x, A.order) * (blockDim.x >> 6) + wave;
     if (c >= A.n_chunks) return;
     unsigned char *smem = smem_all + (size_t)wave * A.lds_per_wave;
     const SlChunkDesc d = A.desc[c];
@@ -904,6 +905,7 @@ static int launch_select(const sl_plan *p, float *e, const float *delta, const f
     // waves (= chunks) per workgroup: 4 adjacent chunks when their LDS fits
     const int wpb = 4 * (size_t)A.lds_per_wave <= 65536 ? 4 : 1;
     const dim3 grid((unsigned)((p->n_chunks + wpb - 1) / wpb)), block(64 * wpb);
+    A.order = sl_order(p, grid.x);
     const size_t lds = (size_t)A.lds_per_wave * wpb;
 #define SL_LAUNCH_SELECT(MODE, TWO)                                                                   \
     do {                                                                                              \
