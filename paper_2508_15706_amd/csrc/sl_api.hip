@@ -412,9 +412,8 @@ int sl_rice_decode(sl_plan *p, const void *in, size_t in_bytes, void *payload, v
     if (misaligned(in, 16) || misaligned(payload, 16)) return SL_ERR_INVALID_ARG;
     int rc = check_device(p);
     if (rc) return rc;
-    const void *one[1] = {in};
-    return slk_apply_coded(p, 2, nullptr, nullptr, 0.0f, static_cast<unsigned char *>(payload), one, &in_bytes, 1,
-                           0.0f, static_cast<hipStream_t>(stream));
+    return slk_rice_decode(p, static_cast<const unsigned char *>(in), in_bytes, static_cast<unsigned char *>(payload),
+                           static_cast<hipStream_t>(stream));
 }
 
 static int apply_coded(sl_plan *p, float *theta, float *momentum, float mu, const void *const *coded,
@@ -427,7 +426,7 @@ static int apply_coded(sl_plan *p, float *theta, float *momentum, float mu, cons
     int rc = check_device(p);
     if (rc) return rc;
     sl_prof_mark(p, -2, static_cast<hipStream_t>(stream));
-    rc = slk_apply_coded(p, momentum ? 1 : 0, theta, momentum, mu, nullptr, coded, coded_bytes, R, lr,
+    rc = slk_apply_coded(p, theta, momentum, mu, coded, coded_bytes, R, lr,
                          static_cast<hipStream_t>(stream));
     sl_prof_mark(p, SL_PROF_APPLY, static_cast<hipStream_t>(stream));
     return rc;

@@ -1,7 +1,6 @@
 // sl_decompress_avg_apply_coded: the aggregate + outer update (Algorithm 1, "Aggregate + Outer
 // Update"; Eq. (2) lines 3-4) over R payloads in the CODED wire format (sl_coded.h; the
-// appendix "Compression of indices in Top-k" is where the index coder enters the method), and
-// sl_rice_decode, which uses the same decoder to write a plain payload.
+// appendix "Compression of indices in Top-k" is where the index coder enters the method).
 //
 // One wavefront owns one chunk, as in sl_apply.hip: fp32 accumulators of the chunk in LDS,
 // workers added in the order r = 0..R-1, theta streamed through registers once.  What differs is
@@ -53,10 +52,8 @@ struct CodedApplyArgs {
     SlCodedGeom G;
     const SlChunkDesc *desc;
     const SlCodedDesc *cdesc;
-    const SlTensorDev *tensors;
     float *theta;
     float *mom;              // global outer momentum buffer (Nesterov variant), else null
-    unsigned char *plain;    // MODE 2: the plain payload to write
     float mu, neg_lr, inv_R;
     int R;
     int batch;               // workers staged at a time
@@ -67,7 +64,6 @@ struct CodedApplyArgs {
     int uwp_log2;            // log2 of the slots per worker in step 3 (a power of two >= G.ua)
     int E;                   // index lists: entries per lane in step 4, 8, or 4 when k is not a multiple of 8
     int off_t, off_q, off_h; // a slot's table of every eighth zero, its value pairs, its index list (bytes)
-    int rec_bytes;           // MODE 2: bytes of a plain record
     int lds_per_wave;
     long long n_chunks;
     unsigned order;          // sl_work_group
@@ -77,42 +73,20 @@ struct CodedApplyArgs {
 
 SL_DEV void acc_add(float *acc, unsigned j, float q) { acc[j] = acc[j] + q; }
 
-// Place of the set bit of byte x that has n set bits below it, by halving.
-SL_DEV int place_in_byte(unsigned x, int n)
-{
-    const int c4 = __builtin_popcount(x & 15u);
-    const bool up4 = n >= c4;
-    n -= up4 ? c4 : 0;
-    x = up4 ? x >> 4 : x;
-    const int c2 = __builtin_popcount(x & 3u);
-    const bool up2 = n >= c2;
-    n -= up2 ? c2 : 0;
-    x = up2 ? x >> 2 : x;
-    return (up4 ? 4 : 0) + (up2 ? 2 : 0) + (n >= (int)(x & 1u) ? 1 : 0);
-}
-
-// MODE 0: theta update; 1: with DiLoCo's global Nesterov momentum (Eq. (1)); 2: no update at
-// all - the one payload is decoded into a plain payload (R = 1).
+// NESTEROV: with DiLoCo's global Nesterov momentum (Eq. (1)).
 // LISTS (few entries): steps 3 to 5 go through index lists in LDS, see the top of the file.
-// Waves per SIMD: the decode alone (MODE 2) keeps no theta and is short; what it waits for is its chain of memory
-// and LDS trips, so it is held to the registers that allow five waves (85; left to itself it takes 105, four waves:
-// 24,000 chunks, k = 4 28.0 -> 26.0 us, k = 128 27.8 -> 26.0, fp32 values, k = 1024 72 -> 65; six waves spill).
-#ifndef SL_CAPPLY_DECODE_WAVES
-#define SL_CAPPLY_DECODE_WAVES 5
-#endif
-template <bool TWO_BIT, int MODE, bool LISTS>
-__global__ void __launch_bounds__(256, MODE == 2 ? SL_CAPPLY_DECODE_WAVES : 1) k_apply_coded(CodedApplyArgs A)
+template <bool TWO_BIT, bool NESTEROV, bool LISTS>
+__global__ void __launch_bounds__(256) k_apply_coded(CodedApplyArgs A)
 {
-    constexpr bool NESTEROV = MODE == 1, DECODE = MODE == 2;
     extern __shared__ __align__(16) unsigned char smem_all[];
     const SlCodedGeom &G = A.G;
     const int lane = threadIdx.x & 63, k = G.k, b = G.b;
     const int wave = sl_uniform((int)(threadIdx.x >> 6));
-    const long long c = (long long)(DECODE ? blockIdx.x : sl_work_group(blockIdx.x, A.order)) * (blockDim.x >> 6) + wave;
+    const long long c = (long long)sl_work_group(blockIdx.x, A.order) * (blockDim.x >> 6) + wave;
     if (c >= A.n_chunks) return;
     unsigned char *smem = smem_all + (size_t)wave * A.lds_per_wave;
     float *acc = reinterpret_cast<float *>(smem);
-    unsigned char *stage = smem + (DECODE ? 0 : SL_CHUNK * sizeof(float));
+    unsigned char *stage = smem + SL_CHUNK * sizeof(float);
     const SlChunkDesc d = A.desc[c];
     const SlCodedDesc cd = A.cdesc[c];
     const int bits = TWO_BIT ? 2 : G.bits;
@@ -122,7 +96,7 @@ __global__ void __launch_bounds__(256, MODE == 2 ? SL_CAPPLY_DECODE_WAVES : 1) k
     // lies, 16 bits each][step 5 by the lanes of step 4, 2-bit codes: the 16 pairs of values][else: indices]
     const int off_u = 4 * fwp, off_t = A.off_t, off_q = A.off_q, off_h = A.off_h;
 
-    float *tc = DECODE ? nullptr : A.theta + d.base;
+    float *tc = A.theta + d.base;
     const int lr = lane >> 4, lc = (lane & 15) * 4;
     const unsigned stride = (unsigned)d.stride;
     const bool full = d.flags & SLC_FULL;
@@ -192,7 +166,7 @@ __global__ void __launch_bounds__(256, MODE == 2 ? SL_CAPPLY_DECODE_WAVES : 1) k
     unsigned pf_f[PFF], pf_u[PFU], pn_f[PFF], pn_u[PFU];
     const int nb0 = min(A.batch, A.R);
 
-    sl_f4 th[DECODE ? 1 : 16], mo[NESTEROV ? 16 : 1];
+    sl_f4 th[16], mo[NESTEROV ? 16 : 1];
     float *mc = NESTEROV ? A.mom + d.base : nullptr;
     // The first 64 * PF words of the first batch are fetched BEFORE the theta loads: loads complete in
     // order, so the decode then waits for these few words only and runs while the chunk's 16 KB of
@@ -206,48 +180,46 @@ __global__ void __launch_bounds__(256, MODE == 2 ? SL_CAPPLY_DECODE_WAVES : 1) k
 #pragma unroll
         for (int u = 0; u < PFU; ++u) pf_u[u] = src_vector(S, u);
     }
-    if constexpr (!DECODE) {
-        // Sixteen loads are issued for EVERY chunk, so that the wait in front of the words fetched above
-        // is "all but the last sixteen" whatever the chunk: a ragged chunk (a tensor's edge) reads its own
-        // descriptor sixteen times instead, and then loads its elements one by one, without branches (an
-        // element outside the chunk reads the chunk's first one and is replaced by zero).  Were the
-        // sixteen under a condition, the number of loads behind those words would be unknown and the
-        // wait would be for all of them on the full chunks too.
-        {
-            const float *none = reinterpret_cast<const float *>(A.desc + c);
-            const float *ts = full ? tc : none, *ms = (NESTEROV && full) ? mc : none;
-            const unsigned o0 = full ? 4u * (lr * stride + lc) : 0u, step = full ? 16u * stride : 0u;
+    // Sixteen loads are issued for EVERY chunk, so that the wait in front of the words fetched above
+    // is "all but the last sixteen" whatever the chunk: a ragged chunk (a tensor's edge) reads its own
+    // descriptor sixteen times instead, and then loads its elements one by one, without branches (an
+    // element outside the chunk reads the chunk's first one and is replaced by zero).  Were the
+    // sixteen under a condition, the number of loads behind those words would be unknown and the
+    // wait would be for all of them on the full chunks too.
+    {
+        const float *none = reinterpret_cast<const float *>(A.desc + c);
+        const float *ts = full ? tc : none, *ms = (NESTEROV && full) ? mc : none;
+        const unsigned o0 = full ? 4u * (lr * stride + lc) : 0u, step = full ? 16u * stride : 0u;
 #pragma unroll
-            for (int i = 0; i < 16; ++i) th[i] = sl_load_stream_at(ts, i * step, o0);
-            if constexpr (NESTEROV) {
+        for (int i = 0; i < 16; ++i) th[i] = sl_load_stream_at(ts, i * step, o0);
+        if constexpr (NESTEROV) {
 #pragma unroll
-                for (int i = 0; i < 16; ++i) mo[i] = sl_load_stream_at(ms, i * step, o0);
-            }
+            for (int i = 0; i < 16; ++i) mo[i] = sl_load_stream_at(ms, i * step, o0);
         }
-        if (!full) {
-            const int rows = d.rows, cols = d.cols, last_cols = d.last_cols;
+    }
+    if (!full) {
+        const int rows = d.rows, cols = d.cols, last_cols = d.last_cols;
 #pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const int row = 4 * i + lr;
-                const int lim = row < rows - 1 ? cols : (row == rows - 1 ? last_cols : 0);
-                const unsigned o0 = row * stride + lc;
+        for (int i = 0; i < 16; ++i) {
+            const int row = 4 * i + lr;
+            const int lim = row < rows - 1 ? cols : (row == rows - 1 ? last_cols : 0);
+            const unsigned o0 = row * stride + lc;
 #pragma unroll
-                for (int cc = 0; cc < 4; ++cc) {
-                    const bool in = lc + cc < lim;
-                    const unsigned at = in ? o0 + cc : 0u;
-                    const float tv = __builtin_nontemporal_load(tc + at);
-                    th[i][cc] = in ? tv : 0.f;
-                    if constexpr (NESTEROV) {
-                        const float mv = __builtin_nontemporal_load(mc + at);
-                        mo[i][cc] = in ? mv : 0.f;
-                    }
+            for (int cc = 0; cc < 4; ++cc) {
+                const bool in = lc + cc < lim;
+                const unsigned at = in ? o0 + cc : 0u;
+                const float tv = __builtin_nontemporal_load(tc + at);
+                th[i][cc] = in ? tv : 0.f;
+                if constexpr (NESTEROV) {
+                    const float mv = __builtin_nontemporal_load(mc + at);
+                    mo[i][cc] = in ? mv : 0.f;
                 }
             }
         }
-#pragma unroll
-        for (int i = 0; i < 16; ++i)
-            reinterpret_cast<float4 *>(acc)[i * 64 + lane] = make_float4(0.f, 0.f, 0.f, 0.f);
     }
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+        reinterpret_cast<float4 *>(acc)[i * 64 + lane] = make_float4(0.f, 0.f, 0.f, 0.f);
 
     const int L = (k + 7) >> 3;                   // step 4: lanes per worker, eight entries each (without lists)
     const int uwp = 1 << A.uwp_log2;
@@ -312,7 +284,7 @@ __global__ void __launch_bounds__(256, MODE == 2 ? SL_CAPPLY_DECODE_WAVES : 1) k
         // ---- no remainders (b = 0, k above 1419): a gap is its quotient, the vector is the chunk's bit map -
         // bit p is zero exactly where index p is selected - and the entries are added straight from it, the
         // i-th zero with the i-th value, worker after worker.  (Steps 3 to 5 would give the same sums.)
-        if (!DECODE && b == 0) {
+        if (b == 0) {
             const int passes = (G.ua + 63) >> 6;
             for (int r = 0; r < nb; ++r) {
                 const unsigned char *slot = stage + r * A.slot_bytes;
@@ -582,7 +554,7 @@ __global__ void __launch_bounds__(256, MODE == 2 ? SL_CAPPLY_DECODE_WAVES : 1) k
             const int wpp = L <= 64 ? 64 / L : 1;       // workers per pass
             const int ppw = (L + 63) >> 6;              // passes per worker (1 unless L > 64)
             const unsigned fmask = (1u << b) - 1u;
-            if constexpr (TWO_BIT && !DECODE) {
+            if constexpr (TWO_BIT) {
                 // the values of two consecutive codes, by their four bits
                 for (int q = lane; q < 16 * nb; q += 64) {
                     unsigned char *slot = stage + (q >> 4) * A.slot_bytes;
@@ -651,7 +623,7 @@ __global__ void __launch_bounds__(256, MODE == 2 ? SL_CAPPLY_DECODE_WAVES : 1) k
                         const unsigned w0 = raw[wi], w1 = raw[wi + 1], w2 = raw[wi + 2];
                         const unsigned lo = ~__builtin_amdgcn_alignbit(w1, w0, (unsigned)(at & 31));
                         const unsigned hi = ~__builtin_amdgcn_alignbit(w2, w1, (unsigned)(at & 31));
-                        const unsigned skip = (unsigned)place_in_byte(lo & 0xFFu, (int)(note & 7u));
+                        const unsigned skip = (unsigned)sl_place_in_byte(lo & 0xFFu, (int)(note & 7u));
                         start = 8 * byte + (int)skip;
                         z = __builtin_amdgcn_alignbit(hi, lo, skip);
                         zh = hi >> skip;                 // (57 bits at least)
@@ -694,77 +666,38 @@ __global__ void __launch_bounds__(256, MODE == 2 ? SL_CAPPLY_DECODE_WAVES : 1) k
                     unsigned idx[8];
 #pragma unroll
                     for (int e = 0; e < 8; ++e) idx[e] = (unsigned)(base + (pre[e] + (p[e] << b))) & 0xFFFu;
-                    if constexpr (DECODE) {
-                        // the plain record's 12-bit index stream: eight entries are twelve bytes
-                        if (live) {
-                            unsigned char *rec = A.plain + d.rec_off + 12 * o;
-                            const unsigned w0 = idx[0] | (idx[1] << 12) | (idx[2] << 24);
-                            const unsigned w1 = (idx[2] >> 8) | (idx[3] << 4) | (idx[4] << 16) | (idx[5] << 28);
-                            const unsigned w2 = (idx[5] >> 4) | (idx[6] << 8) | (idx[7] << 20);
-                            if ((d.rec_off & 3) == 0 && want == 8) {
-                                reinterpret_cast<unsigned *>(rec)[0] = w0;
-                                reinterpret_cast<unsigned *>(rec)[1] = w1;
-                                reinterpret_cast<unsigned *>(rec)[2] = w2;
-                            } else {
-                                const unsigned w[3] = {w0, w1, w2};
+                    // ---- step 5: these lanes add their entries, worker after worker.  The positions of
+                    // one record are distinct: the reads, then the writes, are issued together.
+                    float v[8];
+                    const unsigned char *vals = slot + 4 * hdrw + G.rem_bytes;
+                    if constexpr (TWO_BIT) {
+                        const unsigned cw = reinterpret_cast<const unsigned short *>(vals)[oo];
 #pragma unroll
-                                for (int q = 0; q < 12; ++q)
-                                    if (q < 6 || want == 8) rec[q] = (unsigned char)(w[q >> 2] >> (8 * (q & 3)));
-                            }
+                        for (int e = 0; e < 4; ++e) {
+                            const float2 q2 = reinterpret_cast<const float2 *>(slot + off_q)[(cw >> (4 * e)) & 15u];
+                            v[2 * e] = q2.x, v[2 * e + 1] = q2.y;
                         }
                     } else {
-                        // ---- step 5: these lanes add their entries, worker after worker.  The positions of
-                        // one record are distinct: the reads, then the writes, are issued together.
-                        float v[8];
-                        const unsigned char *vals = slot + 4 * hdrw + G.rem_bytes;
-                        if constexpr (TWO_BIT) {
-                            const unsigned cw = reinterpret_cast<const unsigned short *>(vals)[oo];
 #pragma unroll
-                            for (int e = 0; e < 4; ++e) {
-                                const float2 q2 = reinterpret_cast<const float2 *>(slot + off_q)[(cw >> (4 * e)) & 15u];
-                                v[2 * e] = q2.x, v[2 * e + 1] = q2.y;
-                            }
-                        } else {
+                        for (int e = 0; e < 8; ++e) v[e] = e < want ? value_at(slot, min(8 * o + e, k - 1)) : 0.f;
+                    }
+                    for (int w = 0; w < wpp; ++w) {
+                        if (live && rl == w) {
+                            float t[8];
 #pragma unroll
-                            for (int e = 0; e < 8; ++e) v[e] = e < want ? value_at(slot, min(8 * o + e, k - 1)) : 0.f;
+                            for (int e = 0; e < 8; ++e) t[e] = acc[idx[e]];
+#pragma unroll
+                            for (int e = 0; e < 8; ++e)
+                                if (e < 4 || want == 8) acc[idx[e]] = t[e] + v[e];
                         }
-                        for (int w = 0; w < wpp; ++w) {
-                            if (live && rl == w) {
-                                float t[8];
-#pragma unroll
-                                for (int e = 0; e < 8; ++e) t[e] = acc[idx[e]];
-#pragma unroll
-                                for (int e = 0; e < 8; ++e)
-                                    if (e < 4 || want == 8) acc[idx[e]] = t[e] + v[e];
-                            }
-                            sl_wave_sync();   // worker r is complete before worker r+1 is added
-                        }
+                        sl_wave_sync();   // worker r is complete before worker r+1 is added
                     }
                 }
             }
             sl_wave_sync();
         }
         }
-        if constexpr (DECODE) {
-            // ---- the value fields as they stand, after the index stream
-            unsigned char *rec = A.plain + d.rec_off + 3 * k / 2;
-            const unsigned char *vals = stage + 4 * hdrw + G.rem_bytes;
-            if ((d.rec_off & 3) == 0 && (k & 7) == 0 && (G.val_bytes & 3) == 0) {
-                for (int q = lane; 4 * q < G.val_bytes; q += 64)
-                    reinterpret_cast<unsigned *>(rec)[q] = reinterpret_cast<const unsigned *>(vals)[q];
-            } else {
-                for (int q = lane; q < G.val_bytes; q += 64) rec[q] = vals[q];
-            }
-            if (d.local_chunk == 0 || d.local_chunk == A.tensors[d.tensor].n_chunks - 1) {
-                const SlTensorDev td = A.tensors[d.tensor];
-                if (d.local_chunk == 0)
-                    for (int q = lane; q < hdrw; q += 64)
-                        reinterpret_cast<unsigned *>(A.plain + td.pay_off)[q] = reinterpret_cast<const unsigned *>(stage)[q];
-                if (d.local_chunk == td.n_chunks - 1)
-                    for (long long q = hdr + td.n_chunks * (long long)A.rec_bytes + lane; q < td.block_bytes; q += 64)
-                        A.plain[td.pay_off + q] = 0;
-            }
-        } else if constexpr (LISTS) {
+        if constexpr (LISTS) {
             // ---- step 5 with lists: the entries of up to eight workers are fetched first (independent LDS
             // reads), then added worker by worker: the additions form a chain of LDS round trips
             for (int rb = 0; rb < nb; rb += 8) {
@@ -798,61 +731,59 @@ __global__ void __launch_bounds__(256, MODE == 2 ? SL_CAPPLY_DECODE_WAVES : 1) k
     do_batch(0, true);
     for (int r0 = A.batch; r0 < A.R; r0 += A.batch) do_batch(r0, false);
 
-    if constexpr (!DECODE) {
-        if (full) {
-            const unsigned o0 = 4u * (lr * stride + lc), step = 16u * stride;
+    if (full) {
+        const unsigned o0 = 4u * (lr * stride + lc), step = 16u * stride;
 #pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const float4 a = reinterpret_cast<const float4 *>(acc)[i * 64 + lane];
-                sl_f4 g;
-                g.x = a.x * A.inv_R, g.y = a.y * A.inv_R, g.z = a.z * A.inv_R, g.w = a.w * A.inv_R;
-                if constexpr (NESTEROV) {
-                    sl_f4 m = mo[i];
-                    m.x = fmaf(A.mu, m.x, g.x), m.y = fmaf(A.mu, m.y, g.y);
-                    m.z = fmaf(A.mu, m.z, g.z), m.w = fmaf(A.mu, m.w, g.w);
-                    sl_store_stream_at(mc, i * step, o0, m);
-                    g.x = fmaf(A.mu, m.x, g.x), g.y = fmaf(A.mu, m.y, g.y);
-                    g.z = fmaf(A.mu, m.z, g.z), g.w = fmaf(A.mu, m.w, g.w);
-                }
-                sl_f4 v = th[i];
-                v.x = fmaf(A.neg_lr, g.x, v.x);
-                v.y = fmaf(A.neg_lr, g.y, v.y);
-                v.z = fmaf(A.neg_lr, g.z, v.z);
-                v.w = fmaf(A.neg_lr, g.w, v.w);
-                sl_store_stream_at(tc, i * step, o0, v);
+        for (int i = 0; i < 16; ++i) {
+            const float4 a = reinterpret_cast<const float4 *>(acc)[i * 64 + lane];
+            sl_f4 g;
+            g.x = a.x * A.inv_R, g.y = a.y * A.inv_R, g.z = a.z * A.inv_R, g.w = a.w * A.inv_R;
+            if constexpr (NESTEROV) {
+                sl_f4 m = mo[i];
+                m.x = fmaf(A.mu, m.x, g.x), m.y = fmaf(A.mu, m.y, g.y);
+                m.z = fmaf(A.mu, m.z, g.z), m.w = fmaf(A.mu, m.w, g.w);
+                sl_store_stream_at(mc, i * step, o0, m);
+                g.x = fmaf(A.mu, m.x, g.x), g.y = fmaf(A.mu, m.y, g.y);
+                g.z = fmaf(A.mu, m.z, g.z), g.w = fmaf(A.mu, m.w, g.w);
             }
-        } else {
-            const int rows = d.rows, cols = d.cols, last_cols = d.last_cols;
+            sl_f4 v = th[i];
+            v.x = fmaf(A.neg_lr, g.x, v.x);
+            v.y = fmaf(A.neg_lr, g.y, v.y);
+            v.z = fmaf(A.neg_lr, g.z, v.z);
+            v.w = fmaf(A.neg_lr, g.w, v.w);
+            sl_store_stream_at(tc, i * step, o0, v);
+        }
+    } else {
+        const int rows = d.rows, cols = d.cols, last_cols = d.last_cols;
 #pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const int row = 4 * i + lr;
-                const int lim = row < rows - 1 ? cols : (row == rows - 1 ? last_cols : 0);
-                const unsigned o0 = row * stride + lc;
-                const float4 a = reinterpret_cast<const float4 *>(acc)[i * 64 + lane];
-                sl_f4 g;
-                g.x = a.x * A.inv_R, g.y = a.y * A.inv_R, g.z = a.z * A.inv_R, g.w = a.w * A.inv_R;
-                sl_f4 m = sl_f4{0.f, 0.f, 0.f, 0.f};
-                if constexpr (NESTEROV) {
-                    m = mo[i];
-                    m.x = fmaf(A.mu, m.x, g.x), m.y = fmaf(A.mu, m.y, g.y);
-                    m.z = fmaf(A.mu, m.z, g.z), m.w = fmaf(A.mu, m.w, g.w);
-                    g.x = fmaf(A.mu, m.x, g.x), g.y = fmaf(A.mu, m.y, g.y);
-                    g.z = fmaf(A.mu, m.z, g.z), g.w = fmaf(A.mu, m.w, g.w);
-                }
-                sl_f4 v = th[i];
-                v.x = fmaf(A.neg_lr, g.x, v.x), v.y = fmaf(A.neg_lr, g.y, v.y);
-                v.z = fmaf(A.neg_lr, g.z, v.z), v.w = fmaf(A.neg_lr, g.w, v.w);
-                if (lc + 3 < lim) {
-                    if constexpr (NESTEROV) sl_store_stream_u(mc + o0, m);
-                    sl_store_stream_u(tc + o0, v);
-                } else {
+        for (int i = 0; i < 16; ++i) {
+            const int row = 4 * i + lr;
+            const int lim = row < rows - 1 ? cols : (row == rows - 1 ? last_cols : 0);
+            const unsigned o0 = row * stride + lc;
+            const float4 a = reinterpret_cast<const float4 *>(acc)[i * 64 + lane];
+            sl_f4 g;
+            g.x = a.x * A.inv_R, g.y = a.y * A.inv_R, g.z = a.z * A.inv_R, g.w = a.w * A.inv_R;
+            sl_f4 m = sl_f4{0.f, 0.f, 0.f, 0.f};
+            if constexpr (NESTEROV) {
+                m = mo[i];
+                m.x = fmaf(A.mu, m.x, g.x), m.y = fmaf(A.mu, m.y, g.y);
+                m.z = fmaf(A.mu, m.z, g.z), m.w = fmaf(A.mu, m.w, g.w);
+                g.x = fmaf(A.mu, m.x, g.x), g.y = fmaf(A.mu, m.y, g.y);
+                g.z = fmaf(A.mu, m.z, g.z), g.w = fmaf(A.mu, m.w, g.w);
+            }
+            sl_f4 v = th[i];
+            v.x = fmaf(A.neg_lr, g.x, v.x), v.y = fmaf(A.neg_lr, g.y, v.y);
+            v.z = fmaf(A.neg_lr, g.z, v.z), v.w = fmaf(A.neg_lr, g.w, v.w);
+            if (lc + 3 < lim) {
+                if constexpr (NESTEROV) sl_store_stream_u(mc + o0, m);
+                sl_store_stream_u(tc + o0, v);
+            } else {
 #pragma unroll
-                    for (int cc = 0; cc < 4; ++cc)
-                        if (lc + cc < lim) {
-                            if constexpr (NESTEROV) mc[o0 + cc] = m[cc];
-                            tc[o0 + cc] = v[cc];
-                        }
-                }
+                for (int cc = 0; cc < 4; ++cc)
+                    if (lc + cc < lim) {
+                        if constexpr (NESTEROV) mc[o0 + cc] = m[cc];
+                        tc[o0 + cc] = v[cc];
+                    }
             }
         }
     }
@@ -867,28 +798,25 @@ int pow2_log2_at_least(int n)
 
 }  // namespace
 
-// mode 0: theta update; 1: with the global momentum `mom`; 2: decode payloads[0] into `plain`.
-int slk_apply_coded(const sl_plan *p, int mode, float *theta, float *mom, float mu, unsigned char *plain,
-                    const void *const *payloads, const size_t *bytes, int R, float lr, hipStream_t st)
+// mom != null: with the global momentum
+int slk_apply_coded(const sl_plan *p, float *theta, float *mom, float mu, const void *const *payloads, const size_t *bytes,
+                    int R, float lr, hipStream_t st)
 {
     if (p->n_chunks == 0) return SL_OK;
     CodedApplyArgs A;
     A.G = p->cg;
     A.desc = p->d_desc;
     A.cdesc = p->d_cdesc;
-    A.tensors = p->d_tensors;
     A.theta = theta;
     A.mom = mom;
-    A.plain = plain;
     A.mu = mu;
     A.neg_lr = -lr;
     A.inv_R = 1.0f / (float)R;
     A.R = R;
     const SlCodedGeom &G = p->cg;
     A.fwp = (G.hdr + G.cfix) >> 2;
-    A.rec_bytes = p->rec_bytes;
     const bool few = (long long)R * G.k < SL_CAPPLY_LISTS_BELOW || (G.k <= 16 && G.bits == 2);
-    const bool lists = mode != 2 && G.k <= 128 && few;
+    const bool lists = G.k <= 128 && few;
     A.E = (G.k & 7) ? 4 : 8;
     const int L = lists ? G.k / A.E : (G.k + 7) / 8;
     auto up16 = [](int v) { return (v + 15) & ~15; };
@@ -897,7 +825,7 @@ int slk_apply_coded(const sl_plan *p, int mode, float *theta, float *mom, float 
         A.slot_bytes = up16(A.off_h + 2 * G.k);
     } else {
         A.off_q = up16(A.off_t + 2 * (L + 1));
-        A.slot_bytes = A.off_q + (mode != 2 && G.bits == 2 ? 128 : 0);
+        A.slot_bytes = A.off_q + (G.bits == 2 ? 128 : 0);
     }
     A.uwp_log2 = pow2_log2_at_least(G.ua);
     int batch = SL_CAPPLY_STAGE / A.slot_bytes;
@@ -931,17 +859,17 @@ int slk_apply_coded(const sl_plan *p, int mode, float *theta, float *mom, float 
         const size_t sec = r < R && bytes[r] > (size_t)G.section ? (bytes[r] - (size_t)G.section) >> 2 : 0;
         A.sec_words[r] = sec > 0xFFFFFFFFull ? 0xFFFFFFFFu : (unsigned)sec;
     }
-    A.lds_per_wave = (int)(((mode == 2 ? 0 : SL_CHUNK * sizeof(float)) + (size_t)batch * A.slot_bytes + 15) & ~(size_t)15);
+    A.lds_per_wave = (int)((SL_CHUNK * sizeof(float) + (size_t)batch * A.slot_bytes + 15) & ~(size_t)15);
     int wpb = 4;
     while (wpb > 1 && (size_t)A.lds_per_wave * wpb > (size_t)p->max_lds) wpb >>= 1;
     const size_t lds = (size_t)A.lds_per_wave * wpb;
     typedef void (*kernel_t)(CodedApplyArgs);
-    static const kernel_t table[2][2][3] = {
-        {{k_apply_coded<false, 0, false>, k_apply_coded<false, 1, false>, k_apply_coded<false, 2, false>},
-         {k_apply_coded<false, 0, true>, k_apply_coded<false, 1, true>, nullptr}},
-        {{k_apply_coded<true, 0, false>, k_apply_coded<true, 1, false>, k_apply_coded<true, 2, false>},
-         {k_apply_coded<true, 0, true>, k_apply_coded<true, 1, true>, nullptr}}};
-    const kernel_t fn = table[p->bits == 2 ? 1 : 0][lists ? 1 : 0][mode];
+    static const kernel_t table[2][2][2] = {
+        {{k_apply_coded<false, false, false>, k_apply_coded<false, true, false>},
+         {k_apply_coded<false, false, true>, k_apply_coded<false, true, true>}},
+        {{k_apply_coded<true, false, false>, k_apply_coded<true, true, false>},
+         {k_apply_coded<true, false, true>, k_apply_coded<true, true, true>}}};
+    const kernel_t fn = table[p->bits == 2 ? 1 : 0][lists ? 1 : 0][mom ? 1 : 0];
     if (lds > 65536) {
         hipError_t aerr = hipFuncSetAttribute(reinterpret_cast<const void *>(fn),
                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);

@@ -53,6 +53,20 @@ SL_DEV int sl_wave_iscan(int v)
     return v + (row >= 1 ? t0 : 0) + (row >= 2 ? t1 : 0) + (row >= 3 ? t2 : 0);
 }
 
+// Place of the set bit of byte x that has n set bits below it, by halving.
+SL_DEV int sl_place_in_byte(unsigned x, int n)
+{
+    const int c4 = __builtin_popcount(x & 15u);
+    const bool up4 = n >= c4;
+    n -= up4 ? c4 : 0;
+    x = up4 ? x >> 4 : x;
+    const int c2 = __builtin_popcount(x & 3u);
+    const bool up2 = n >= c2;
+    n -= up2 ? c2 : 0;
+    x = up2 ? x >> 2 : x;
+    return (up4 ? 4 : 0) + (up2 ? 2 : 0) + (n >= (int)(x & 1u) ? 1 : 0);
+}
+
 // Value of lane `src` (any lane; all lanes call this together).
 SL_DEV int sl_lane_read(int v, int src) { return __builtin_amdgcn_ds_bpermute(4 * src, v); }
 

@@ -176,13 +176,14 @@ int slk_pack_bits(const uint16_t *idx, const uint8_t *codes, const float *values
                   int bits, unsigned char *out, hipStream_t st);
 int slk_rice_encode(const sl_plan *p, const unsigned char *payload, unsigned char *out,
                     unsigned char *ws, hipStream_t st);
+int slk_rice_decode(const sl_plan *p, const unsigned char *in, size_t in_bytes, unsigned char *payload, hipStream_t st);
 // coded wire format: the steps that place the quotient bit vectors once a buffer's writers have run (all of
 // them; the first; the last)
 int slk_coded_finish(const sl_plan *p, unsigned char *out, unsigned char *ws, hipStream_t st);
 int slk_coded_scan(const sl_plan *p, unsigned char *out, unsigned char *ws, hipStream_t st);
 int slk_coded_place(const sl_plan *p, unsigned char *out, unsigned char *ws, hipStream_t st);
-// mode 0: theta update from R coded payloads; 1: with the global momentum `mom`; 2: payloads[0] decoded into `plain`
-int slk_apply_coded(const sl_plan *p, int mode, float *theta, float *mom, float mu, unsigned char *plain,
-                    const void *const *payloads, const size_t *bytes, int R, float lr, hipStream_t st);
+// theta update from R coded payloads (mom != null: with the global momentum)
+int slk_apply_coded(const sl_plan *p, float *theta, float *mom, float mu, const void *const *payloads, const size_t *bytes,
+                    int R, float lr, hipStream_t st);
 int sl_rice_param(int k);
 void sl_note_hip_error(hipError_t e);
