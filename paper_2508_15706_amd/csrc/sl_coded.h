@@ -130,6 +130,10 @@ struct SlVecPlace {
     int nbits;              // k + Q
 };
 
+// words and halfwords of records, which start at any byte where their size is odd
+typedef unsigned __attribute__((aligned(1))) u32_any;
+typedef unsigned short __attribute__((aligned(1))) u16_any;
+
 // pointers into global memory, for addresses that are put together from integers (a generic
 // pointer would turn every access into a flat load that LDS waits have to sit out)
 typedef const unsigned char __attribute__((address_space(1))) *sl_gbytes;
@@ -201,7 +205,8 @@ SL_DEV SlVecPlace sl_coded_dir_entry(const SlCodedGeom &G, sl_gbytes entry, int 
 // in the workspace; then, each step reading what the one before wrote:
 //   sl_coded_scan_tensor   one workgroup per tensor: words of each group's run, their exclusive
 //                          prefix inside the tensor, the tensor's total;
-//   sl_coded_scan_list     one wave: prefix over the tensors, total size, buffer header;
+//   sl_coded_scan_list     one wave: prefix over the tensors, total size, buffer header (on lists of few tensors every
+//                          wave of the last step sums up what is before it, and this one is left out);
 //   sl_coded_place         one wave per group: the 16 vectors shifted into one run, the run and
 //                          the directory entry written.
 // The compressor runs them as extra workgroups of the quantizer's launches (sl_quant.hip), on lists of
@@ -273,6 +278,33 @@ SL_DEV void sl_coded_scan_tensor(const SlCodedArgs &A, int t, unsigned *wsum)
     if (tid == 0) A.twords[t] = carry;
 }
 
+// The buffer header and the zero padding that rounds the buffer up to 16 bytes, for a section of so many words.  One
+// wave (or its first four lanes).
+SL_DEV void sl_coded_header(unsigned long long words, long long section, unsigned char *out)
+{
+    const int lane = threadIdx.x & 63;
+    const unsigned long long end = (unsigned long long)section + 4ull * words;
+    const unsigned long long total = (end + 15ull) & ~15ull;
+    if (lane == 0) {
+        unsigned long long *h = reinterpret_cast<unsigned long long *>(out);
+        h[0] = 0x3230454349524C53ull;                      // "SLRICE02", little endian
+        h[1] = total;
+    }
+    if (end + 4ull * lane < total) *reinterpret_cast<unsigned *>(out + end + 4ull * lane) = 0u;
+}
+
+// Words of the section in front of tensor t's part (t = n_tensors: of the whole section), from the words of each; for lists of
+// few tensors, where a wave has them sooner than a launch of sl_coded_scan_list.  One wave; uniform.
+SL_DEV unsigned long long sl_coded_words_before(const unsigned long long *twords, int t)
+{
+    const int lane = threadIdx.x & 63;
+    unsigned long long v = 0;
+    for (int i = lane; i < t; i += 64) v += twords[i];
+#pragma unroll
+    for (int l = 0; l < 6; ++l) v += sl_partner(v, l);
+    return v;
+}
+
 // Prefix over the tensors (twords[t] becomes the tensor's offset in the section, in words), the
 // buffer header, and the zero padding that rounds the buffer up to 16 bytes.  One wave.
 SL_DEV void sl_coded_scan_list(unsigned long long *twords, int n_tensors, long long section, unsigned char *out)
@@ -291,21 +323,14 @@ SL_DEV void sl_coded_scan_list(unsigned long long *twords, int n_tensors, long l
         if (t < n_tensors) twords[t] = pos + incl - v;
         pos += __shfl(incl, 63);
     }
-    const unsigned long long end = (unsigned long long)section + 4ull * pos;
-    const unsigned long long total = (end + 15ull) & ~15ull;
-    if (lane == 0) {
-        unsigned long long *h = reinterpret_cast<unsigned long long *>(out);
-        h[0] = 0x3230454349524C53ull;                      // "SLRICE02", little endian
-        h[1] = total;
-        twords[n_tensors] = pos;
-    }
-    if (end + 4ull * lane < total) *reinterpret_cast<unsigned *>(out + end + 4ull * lane) = 0u;
+    if (lane == 0) twords[n_tensors] = pos;
+    sl_coded_header(pos, section, out);
 }
 
 // Words of LDS that sl_coded_place needs per wave.
 inline size_t sl_coded_place_words(const SlCodedGeom &G) { return (size_t)SL_RICE_GROUP * G.ua + 1; }
 
-// Group gi (one wave; `run`: its LDS): the chunks' vectors, as the writers left them (G.ua words each,
+// Group gi of a tensor whose part of the section begins at word `before` (one wave; `run`: its LDS): the chunks' vectors, as the writers left them (G.ua words each,
 // bits beyond k + Q undefined), are shifted to their bit offsets inside the run in LDS; the run and
 // the directory entry go to the buffer.  A lane takes one (chunk, word) pair per turn, so that the
 // loads of several chunks are under way together (a chunk per turn left most lanes idle and waited
@@ -315,7 +340,7 @@ inline size_t sl_coded_place_words(const SlCodedGeom &G) { return (size_t)SL_RIC
 #ifndef SL_PLACE_BY_CHUNK
 #define SL_PLACE_BY_CHUNK 6               // log2 of the words of the longest vector, rounded up
 #endif
-SL_DEV void sl_coded_place(const SlCodedArgs &A, long long gi, unsigned *run)
+SL_DEV void sl_coded_place(const SlCodedArgs &A, long long gi, unsigned long long before, unsigned *run)
 {
     const int lane = threadIdx.x & 63;
     const SlCodedGeom &G = A.G;
@@ -324,7 +349,7 @@ SL_DEV void sl_coded_place(const SlCodedArgs &A, long long gi, unsigned *run)
     const long long c0 = td.chunk0 + (long long)g.local_group * SL_RICE_GROUP;
     const int nc = (int)min((long long)SL_RICE_GROUP, td.n_chunks - (long long)g.local_group * SL_RICE_GROUP);
     const unsigned nw = A.gwords[gi];
-    const unsigned long long base = A.twords[g.tensor] + A.goff[gi];    // below 2^32 by the plan's check
+    const unsigned long long base = before + A.goff[gi];    // below 2^32 by the plan's check
 
     const int q = lane < nc ? (int)A.qsum[c0 + lane] : 0;
     const int nbits = lane < nc ? G.k + q : 0;

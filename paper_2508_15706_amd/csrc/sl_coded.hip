@@ -37,13 +37,19 @@ __global__ void __launch_bounds__(64) k_coded_scan_list(SlCodedArgs A)
     sl_coded_scan_list(A.twords, A.n_tensors, A.G.section, A.out);
 }
 
+// SCANNED: sl_coded_scan_list has run; else every wave sums up the words of the tensors before its own, and one
+// more wave writes the buffer header (up to SL_PLACE_SUMS_UPTO tensors: the launch of the list scan takes 4 us).
+template <bool SCANNED>
 __global__ void __launch_bounds__(256) k_coded_place(SlCodedArgs A)
 {
     extern __shared__ __align__(16) unsigned place_lds[];
     const int wave = sl_uniform((int)(threadIdx.x >> 6));
     const long long gi = (long long)blockIdx.x * (blockDim.x >> 6) + wave;
+    if (!SCANNED && gi == A.n_groups) sl_coded_header(sl_coded_words_before(A.twords, A.n_tensors), A.G.section, A.out);
     if (gi >= A.n_groups) return;
-    sl_coded_place(A, gi, place_lds + (size_t)wave * (SL_RICE_GROUP * A.G.ua + 1));
+    const int t = A.groups[gi].tensor;
+    const unsigned long long before = SCANNED ? A.twords[t] : sl_coded_words_before(A.twords, t);
+    sl_coded_place(A, gi, before, place_lds + (size_t)wave * (SL_RICE_GROUP * A.G.ua + 1));
 }
 
 // ------------------------------------------------------------------ transcoders
@@ -70,9 +76,6 @@ struct TransArgs {
     unsigned *uvec;          // encode
     unsigned short *qsum;
 };
-
-typedef unsigned __attribute__((aligned(1))) u32_any;            // records of odd sizes start at any byte
-typedef unsigned short __attribute__((aligned(1))) u16_any;
 
 SL_DEV int div_by(int n, unsigned magic) { return magic ? (int)__umulhi((unsigned)n, magic) : n; }
 
@@ -438,13 +441,26 @@ int slk_coded_scan(const sl_plan *p, unsigned char *out, unsigned char *ws, hipS
     return launched();
 }
 
-int slk_coded_place(const sl_plan *p, unsigned char *out, unsigned char *ws, hipStream_t st)
+#ifndef SL_PLACE_SUMS_UPTO
+#define SL_PLACE_SUMS_UPTO 1024
+#endif
+// The placement steps behind sl_coded_scan_tensor; `scanned`: the list scan has run as well.
+int slk_coded_place(const sl_plan *p, unsigned char *out, unsigned char *ws, bool scanned, hipStream_t st)
 {
+    const SlCodedArgs A = sl_coded_args(p, out, ws);
+    if (!scanned && (p->n_tensors > SL_PLACE_SUMS_UPTO || p->n_groups == 0)) {
+        hipLaunchKernelGGL(k_coded_scan_list, dim3(1), dim3(64), 0, st, A);
+        const int rc = launched();
+        if (rc) return rc;
+        scanned = true;
+    }
+    if (p->n_groups == 0) return SL_OK;
     int wpb = 4;
     const size_t per_wave = sl_coded_place_words(p->cg) * sizeof(unsigned);
     while (wpb > 1 && per_wave * wpb > 65536) wpb >>= 1;
-    hipLaunchKernelGGL(k_coded_place, dim3((unsigned)((p->n_groups + wpb - 1) / wpb)), dim3(64 * wpb), per_wave * wpb, st,
-                       sl_coded_args(p, out, ws));
+    const long long waves = p->n_groups + (scanned ? 0 : 1);
+    hipLaunchKernelGGL(scanned ? k_coded_place<true> : k_coded_place<false>, dim3((unsigned)((waves + wpb - 1) / wpb)), dim3(64 * wpb),
+                       per_wave * wpb, st, A);
     return launched();
 }
 
@@ -453,9 +469,7 @@ int slk_coded_finish(const sl_plan *p, unsigned char *out, unsigned char *ws, hi
 {
     int rc;
     if (p->n_groups > 0 && (rc = slk_coded_scan(p, out, ws, st))) return rc;
-    hipLaunchKernelGGL(k_coded_scan_list, dim3(1), dim3(64), 0, st, sl_coded_args(p, out, ws));
-    if ((rc = launched())) return rc;
-    return p->n_groups > 0 ? slk_coded_place(p, out, ws, st) : SL_OK;
+    return slk_coded_place(p, out, ws, false, st);
 }
 
 namespace {

@@ -178,10 +178,10 @@ int slk_rice_encode(const sl_plan *p, const unsigned char *payload, unsigned cha
                     unsigned char *ws, hipStream_t st);
 int slk_rice_decode(const sl_plan *p, const unsigned char *in, size_t in_bytes, unsigned char *payload, hipStream_t st);
 // coded wire format: the steps that place the quotient bit vectors once a buffer's writers have run (all of
-// them; the first; the last)
+// them; the first; those behind it, or the last alone)
 int slk_coded_finish(const sl_plan *p, unsigned char *out, unsigned char *ws, hipStream_t st);
 int slk_coded_scan(const sl_plan *p, unsigned char *out, unsigned char *ws, hipStream_t st);
-int slk_coded_place(const sl_plan *p, unsigned char *out, unsigned char *ws, hipStream_t st);
+int slk_coded_place(const sl_plan *p, unsigned char *out, unsigned char *ws, bool scanned, hipStream_t st);
 // theta update from R coded payloads (mom != null: with the global momentum)
 int slk_apply_coded(const sl_plan *p, float *theta, float *mom, float mu, const void *const *payloads, const size_t *bytes,
                     int R, float lr, hipStream_t st);

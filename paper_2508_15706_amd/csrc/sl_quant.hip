@@ -477,7 +477,7 @@ k_tensor_lut(const SlTensorDev *tensors, int n_tensors, const double *leafC, con
         const int wave = sl_uniform(tid >> 6);
         const long long gi = ((long long)((int)blockIdx.x - n_tensors) * nbins + b) * place_waves + wave;
         if (wave < place_waves && gi < C.n_groups)
-            sl_coded_place(C, gi, place_lds + (size_t)wave * (SL_RICE_GROUP * C.G.ua + 1));
+            sl_coded_place(C, gi, C.twords[C.groups[gi].tensor], place_lds + (size_t)wave * (SL_RICE_GROUP * C.G.ua + 1));
         return;
     }
     const SlTensorDev td = tensors[blockIdx.x];
@@ -636,7 +636,7 @@ int slk_quantize(const sl_plan *p, float *e, int skip_residual, unsigned char *p
             sl_prof_mark(p, SL_PROF_RESIDUAL, st);
         }
         if (coded) {
-            if ((rc = slk_coded_place(p, coded, ws, st))) return rc;
+            if ((rc = slk_coded_place(p, coded, ws, true, st))) return rc;
             sl_prof_mark(p, SL_PROF_INDEX, st);
         }
         return SL_OK;
