@@ -24,7 +24,10 @@
 //      index;
 //   3. T is bisected over that short list, and a second compaction over the
 //      list emits the selected entries, still in ascending local index; ties
-//      at T go to the lowest indices.
+//      at T go to the lowest indices.  The bisection ends at the first threshold
+//      that exactly k keys reach, after about eight steps in place of one per bit (24,000 chunks, R = 8,
+//      sl_compress: k = 64 247 -> 226 us, k = 256 269 -> 238, k = 384 313 -> 264, 64 chunks 22.6 -> 20.8; about 20, 20, 20 and 0
+//      of it the order of the chunks).
 // A candidate list that overflows (massive ties; a partial chunk with too few
 // non-empty groups) and k > 512 take the general route: T bisected over the
 // registers directly and one ordered compaction over the registers - slower,
@@ -65,7 +68,7 @@ struct SelectArgs {
     // coded wire format written next to the plain record (null: not wanted): the remainder fields go
     // to their place in the buffer, the chunk's quotient bit vector and quotient sum to the workspace
     unsigned char *coded;
-    const SlTensorDev *tensors;
+    const SlCodedDesc *cdesc;
     SlCodedGeom G;
     unsigned *uvec;
     unsigned short *qsum;
@@ -89,21 +92,27 @@ SL_DEV unsigned fmix32(unsigned h)
     return h;
 }
 
-// Largest T in [lo, hi] with count_ge(T) >= k, given count_ge(lo) >= k and
-// 0 <= lo <= hi.  All values are wave-uniform.
+// A threshold T in [lo, hi] with count_ge(T) >= k, given count_ge(lo) >= k and 0 <= lo <= hi: the first one met that
+// exactly k keys reach (`exact`; among n keys that takes about log2(n) steps, not one per bit), else, with ties, the
+// largest with count_ge(T) >= k.  All values are wave-uniform.
 // With `steps` > 0 only that many bits below the highest one in which lo and hi differ are
 // decided and the rest left zero: a value that is not above the exact answer and still has
 // count_ge >= k.
 template <class CountGE>
-SL_DEV int bisect_kth(int lo, int hi, int k, CountGE count_ge, int steps = 0)
+SL_DEV int bisect_kth(int lo, int hi, int k, CountGE count_ge, bool &exact, int steps = 0)
 {
+    exact = false;
     if (lo >= hi) return lo;
     const int top = 31 - __clz(lo ^ hi);
     const int last = steps > 0 ? max(0, top - steps + 1) : 0;
     int T = hi & ~(int)((2u << top) - 1u);
     for (int b = top; b >= last; --b) {
-        const int cand = T | (1 << b);
-        if (count_ge(cand) >= k) T = cand;
+        const int cand = T | (1 << b), n = count_ge(cand);
+        if (n >= k) T = cand;
+        if (n == k) {
+            exact = true;
+            break;
+        }
     }
     return T;
 }
@@ -141,55 +150,63 @@ SL_DEV void select_general(int (&key)[64], const float (&a)[64], unsigned sg0, u
     int T = 0, n_ge = 0, n_gt = -1;         // n_gt: keys above T, where the list already gave it
     const int top = hi > 0 ? 31 - __clz(hi) : 0;
     const int last = top - SL_SELECT_COARSE_BITS + 1;    // lowest bit the coarse stage decides
+    bool exact;
     if (last >= 3) {
         // T1: the leading bits of T.  count(T1) >= k, and count(T1 + width) < k: T1 + width is either
         // beyond every key or a value the bisection tried and rejected.
-        const int T1 = bisect_kth(0, hi, k, count_regs, SL_SELECT_COARSE_BITS);
+        const int T1 = bisect_kth(0, hi, k, count_regs, exact, SL_SELECT_COARSE_BITS);
         const int width = 1 << last, upper = T1 | (width - 1);
-        int n_above = 0, m = 0;
-#pragma unroll
-        for (int r = 0; r < 64; ++r) {
-            // (a position outside the tensor has key -1: never above, and far outside the bucket)
-            const bool in = (unsigned)(key[r] - T1) < (unsigned)width;
-            const unsigned long long mb = sl_ballot(in);
-            n_above += sl_popc(sl_ballot(key[r] > upper));
-            if (mb) {
-                const int pos = m + sl_mbcnt(mb);
-                if (in && pos < SL_SELECT_LIST_CAP) list[pos] = key[r];
-                m += sl_popc(mb);
-            }
-        }
-        sl_wave_sync();
-        if (m <= SL_SELECT_LIST_CAP) {
-            constexpr int SLOTS = SL_SELECT_LIST_CAP / 64;
-            const int nslots = (m + 63) >> 6;
-            int ck[SLOTS];
-#pragma unroll
-            for (int s = 0; s < SLOTS; ++s) {
-                const int p = s * 64 + lane;
-                ck[s] = (s < nslots && p < m) ? list[p] : -1;
-            }
-            auto count_list = [&](int x) {
-                int n = 0;
-#pragma unroll
-                for (int s = 0; s < SLOTS; ++s)
-                    if (s < nslots) n += sl_popc(sl_ballot(ck[s] >= x));
-                return n;
-            };
-            // the (k - n_above)-th largest key of the bucket
-            T = bisect_kth(T1, upper, k - n_above, count_list);
-            n_ge = n_above + count_list(T);
-            n_gt = n_above + (T == upper ? 0 : count_list(T + 1));    // keys above T: beyond the bucket, or in it
+        if (exact) {
+            T = T1;
         } else {
-            T = bisect_kth(T1, upper, k, count_regs);
-            n_ge = count_regs(T);
-        }
-        sl_wave_sync();                     // the list shares LDS with nothing live, but keep its reads
+            int n_above = 0, m = 0;
+#pragma unroll
+            for (int r = 0; r < 64; ++r) {
+                // (a position outside the tensor has key -1: never above, and far outside the bucket)
+                const bool in = (unsigned)(key[r] - T1) < (unsigned)width;
+                const unsigned long long mb = sl_ballot(in);
+                n_above += sl_popc(sl_ballot(key[r] > upper));
+                if (mb) {
+                    const int pos = m + sl_mbcnt(mb);
+                    if (in && pos < SL_SELECT_LIST_CAP) list[pos] = key[r];
+                    m += sl_popc(mb);
+                }
+            }
+            sl_wave_sync();
+            if (m <= SL_SELECT_LIST_CAP) {
+                constexpr int SLOTS = SL_SELECT_LIST_CAP / 64;
+                const int nslots = (m + 63) >> 6;
+                int ck[SLOTS];
+#pragma unroll
+                for (int s = 0; s < SLOTS; ++s) {
+                    const int p = s * 64 + lane;
+                    ck[s] = (s < nslots && p < m) ? list[p] : -1;
+                }
+                auto count_list = [&](int x) {
+                    int n = 0;
+#pragma unroll
+                    for (int s = 0; s < SLOTS; ++s)
+                        if (s < nslots) n += sl_popc(sl_ballot(ck[s] >= x));
+                    return n;
+                };
+                // the (k - n_above)-th largest key of the bucket
+                T = bisect_kth(T1, upper, k - n_above, count_list, exact);
+                if (!exact) {
+                    n_ge = n_above + count_list(T);
+                    n_gt = n_above + (T == upper ? 0 : count_list(T + 1));    // keys above T: beyond the bucket, or in it
+                }
+            } else {
+                T = bisect_kth(T1, upper, k, count_regs, exact);
+                if (!exact) n_ge = count_regs(T);
+            }
+            sl_wave_sync();                 // the list shares LDS with nothing live, but keep its reads
                                             // ahead of whatever the caller stores next
+        }
     } else {
-        T = bisect_kth(0, hi, k, count_regs);
-        n_ge = count_regs(T);
+        T = bisect_kth(0, hi, k, count_regs, exact);
+        if (!exact) n_ge = count_regs(T);
     }
+    if (exact) n_ge = k;
     const bool ties = n_ge != k;            // more keys equal to T than slots left
     int need = 0;                           // tie entries to take, lowest indices first
     if (ties) {
@@ -272,12 +289,13 @@ SL_DEV void prune_bound(const float (&a)[64], int k, int &L, int &hi)
     for (int g = 1; g < G; ++g) lmin = min(lmin, gm[g]), lmax = max(lmax, gm[g]);
     hi = sl_wave_max(lmax);
     const int lo = sl_wave_min(lmin);
+    bool exact;
     L = bisect_kth(lo, hi, k, [&](int x) {
         int n = 0;
 #pragma unroll
         for (int g = 0; g < G; ++g) n += sl_popc(sl_ballot(gm[g] >= x));
         return n;
-    }, SL_SELECT_BOUND_BITS);
+    }, exact, SL_SELECT_BOUND_BITS);
 }
 
 // Groups per lane for a narrow partial chunk, whatever k: only the lanes whose columns exist hold elements (a
@@ -681,16 +699,21 @@ __global__ void SL_SELECT_BOUNDS k_select(SelectArgs A)
                 const int p = s * 64 + lane;
                 ck[s] = (s < nslots && p < ncand) ? (int)(cand[p].x & 0x7FFFFFFFu) : -1;
             }
+            // the usual number of slots without a test for each
+            constexpr int USUAL = GPL <= 2 ? 2 : GPL;
             auto count_cand = [&](int x) {
                 int n = 0;
 #pragma unroll
-                for (int s = 0; s < CAND_SLOTS; ++s)
-                    if (s < nslots) n += sl_popc(sl_ballot(ck[s] >= x));
+                for (int s = 0; s < (USUAL < CAND_SLOTS ? USUAL : CAND_SLOTS); ++s) n += sl_popc(sl_ballot(ck[s] >= x));
+                if (nslots > USUAL) {
+#pragma unroll
+                    for (int s = USUAL; s < CAND_SLOTS; ++s) n += sl_popc(sl_ballot(ck[s] >= x));
+                }
                 return n;
             };
-            const int T = bisect_kth(L, hi, k, count_cand);
-            const int n_ge = count_cand(T);
-            const bool ties = n_ge != k;
+            bool exact;
+            const int T = bisect_kth(L, hi, k, count_cand, exact);
+            const bool ties = !exact && count_cand(T) != k;
             int need = 0;
             if (ties) {
                 int n_gt = 0;
@@ -816,11 +839,10 @@ __global__ void SL_SELECT_BOUNDS k_select(SelectArgs A)
     // the coded form of the index list (the candidate list's LDS is free by now)
     if (A.coded) {
         const SlCodedGeom &G = A.G;
-        const SlTensorDev td = A.tensors[d.tensor];
         unsigned *uv = reinterpret_cast<unsigned *>(smem), *rw = uv + G.ua;
         const int nrw = G.rem_bytes >> 2;
         const int Q = sl_coded_emit(G, lane, sel_idx, uv, rw);
-        unsigned char *fix = A.coded + td.cfix_off + (long long)d.local_chunk * G.cfix;
+        unsigned char *fix = A.coded + A.cdesc[c].fix_off;
         for (int w = lane; w < nrw; w += 64) reinterpret_cast<unsigned *>(fix)[w] = rw[w];
         if (bits == 32) {
             // unquantized: the values follow the remainders as they follow the indices of a plain record
@@ -898,7 +920,7 @@ static int launch_select(const sl_plan *p, float *e, const float *delta, const f
     A.payload = payload;
     A.n_chunks = p->n_chunks;
     A.coded = sub_only ? nullptr : coded;
-    A.tensors = p->d_tensors;
+    A.cdesc = p->d_cdesc;
     A.G = p->cg;
     A.uvec = (sub_only || !coded) ? nullptr : reinterpret_cast<unsigned *>(ws + p->ws_uvec);
     A.qsum = (sub_only || !coded) ? nullptr : reinterpret_cast<unsigned short *>(ws + p->ws_qsum);
