@@ -1,0 +1,50 @@
+"""Selections of more than 512 of a chunk's elements, whose threshold is bracketed by a sample: values for which the bracket holds,
+misses (elements outside the sample's registers differ from those in it) or overflows (uneven columns, ties), partial chunks, the first and the last densities.
+Top-k removed in place and the payload, against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+def chunk_values(rng, n_chunks):
+    x = rng.normal(0, 1e-3, (n_chunks, 4096)).astype(np.float32)
+    x[1] = 1e-3 * rng.standard_t(3, 4096)
+    x[2, np.arange(4096) % 64 < 4] *= 50                # hot columns: one lane in sixteen holds most of the large ones
+    x[3] = rng.integers(-3, 4, 4096)                    # ties
+    x[4] = 0.5                                          # one value
+    x[5] = 0
+    x[6, rng.permutation(4096)[:700]] = 0
+    r = np.arange(4096)
+    sampled = (4 * (r // 256) + r % 4) % 9 == 0         # the registers that the sample takes
+    x[7, sampled] *= 100                                # ... larger than all others, and smaller
+    x[8, sampled] *= 0.01
+    x[9] = np.float32(1e-42) * rng.integers(0, 50, 4096)        # denormal
+    x[10, :8] = [3e38, -3e38, 1e30, 2, -0.0, 1e-45, 3e38, 7]
+    x[11] *= np.repeat(10.0 ** rng.uniform(-6, 2, 64), 64)      # rows of any scale
+    return x.astype(np.float32)
+
+
+@pytest.mark.parametrize("k", [516, 520, 640, 1024, 1416, 1424, 2048, 3000, 4000, 4032, 4052, 4096])
+def test_sampled_selection(oracle, k):
+    from paper_2508_15706_amd import binding as sl
+    rng = np.random.default_rng(k)
+    x = chunk_values(rng, 13).reshape(-1)
+    tail = min(4095, k + 37)                            # a partial chunk that holds little more than k
+    descs = [(1, x.size, 0, 0)]
+    if k < 4096:
+        descs.append((1, tail, x.size, 0))
+        x = np.concatenate([x, rng.normal(0, 1e-3, tail).astype(np.float32)])
+    x = np.concatenate([x, np.zeros(-x.size % 64, np.float32)])
+    plan = sl.sl_plan_create(descs, k)
+    m = torch.from_numpy(x).cuda()
+    sl.sl_sub_topk(plan, m)
+    want = x.copy()
+    oracle.sub_topk(descs, k, want)
+    assert np.array_equal(m.cpu().numpy().view(np.uint32), want.view(np.uint32))
+    e, e_ref, pay = torch.zeros(x.size, device="cuda"), np.zeros_like(x), sl.alloc_payload(plan)
+    sl.sl_compress(plan, e, torch.from_numpy(x).cuda(), 0.95, pay, sl.alloc_workspace(plan))
+    ref = oracle.compress(descs, k, e_ref, x, 0.95)
+    assert np.array_equal(pay[:plan.payload_bytes].cpu().numpy(), ref)
+    assert np.array_equal(e.cpu().numpy().view(np.uint32), e_ref.view(np.uint32))
