@@ -737,7 +737,7 @@ int slk_apply(const sl_plan *p, float *theta, float *mom, float mu, const void *
     // (direct: 16 tables of 16 bytes, 128 bytes of value pairs per worker of a batch)
     const size_t stage_bytes = direct ? 256 + 128 * (size_t)std::min(R, std::min(8 / A.dp, 16 / A.dw) * A.dw) : (size_t)batch * rec_pad;
     A.lds_per_wave = (int)((acc_bytes + stage_bytes + 15) & ~(size_t)15);
-    int wpb = 4;
+    int wpb = sl_chunks_per_group(p);
     while (wpb > 1 && (size_t)A.lds_per_wave * wpb > (size_t)p->max_lds) wpb >>= 1;
     const size_t lds = (size_t)A.lds_per_wave * wpb;
     const bool two = p->bits == 2;

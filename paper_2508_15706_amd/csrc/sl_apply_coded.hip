@@ -860,7 +860,7 @@ int slk_apply_coded(const sl_plan *p, float *theta, float *mom, float mu, const 
         A.sec_words[r] = sec > 0xFFFFFFFFull ? 0xFFFFFFFFu : (unsigned)sec;
     }
     A.lds_per_wave = (int)((SL_CHUNK * sizeof(float) + (size_t)batch * A.slot_bytes + 15) & ~(size_t)15);
-    int wpb = 4;
+    int wpb = sl_chunks_per_group(p);
     while (wpb > 1 && (size_t)A.lds_per_wave * wpb > (size_t)p->max_lds) wpb >>= 1;
     const size_t lds = (size_t)A.lds_per_wave * wpb;
     typedef void (*kernel_t)(CodedApplyArgs);

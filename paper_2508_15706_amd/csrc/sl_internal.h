@@ -126,13 +126,23 @@ __host__ __device__ inline long long sl_lut_off(const SlChunkDesc &d, int hdr_by
     return d.rec_off - hdr_bytes - (long long)d.local_chunk * rec_bytes;
 }
 
+// Chunks (waves) per workgroup of the kernels that give a chunk to a wave: four adjacent ones, so that a workgroup streams
+// 1 KB of every matrix row it touches; but one on lists shorter than a window of sl_work_group, where workgroups of
+// four leave compute units without any, or with one more than others (four / one, us: sl_compress at k = 64, 64 chunks 21.6 / 20.4,
+// 512 23.7 / 22.1, 1024 29.8 / 25.5, 2048 38.1 / 35.4, 3072 48.0 / 45.9; aggregates of eight, k = 64 and 32, 2048 chunks 16.6 / 12.5
+// plain, 17.0 / 11.9 coded; from 4096 on the window's order is better: aggregate 23.9 / 27.3).  Not where one chunk in 32 or
+// more is partial: rows then begin anywhere in a line of memory, and the neighbours that share a line should share
+// an L2 (1155 chunks of a 67-column matrix, aggregate of three: 12.6 / 19.7).
+#define SL_SPREAD_BELOW 4096
+inline int sl_chunks_per_group(const sl_plan *p) { return p->n_chunks < SL_SPREAD_BELOW && p->n_partial * 32 < p->n_chunks ? 1 : 4; }
+
 // sl_work_group's `order` for a grid of so many groups.  Where a list has many partial chunks - the last column of a
 // matrix's tiles: one group in every few - the slow groups would all come to one or two of the XCDs, so the groups
 // are turned (columns 1000 and 2730, a chunk in 25 partial, plain aggregate of 8: list order 475, paired 488, turned 471 us;
 // on full chunks the turn costs up to 3 %).
 inline unsigned sl_order(const sl_plan *p, unsigned groups)
 {
-    const unsigned whole = groups & ~1023u;
+    const unsigned whole = p->n_chunks < SL_SPREAD_BELOW ? 0u : groups & ~1023u;
     return whole | (whole && p->n_partial * 32 >= p->n_chunks ? 1u : 0u);
 }
 

@@ -1046,8 +1046,8 @@ static int launch_select(const sl_plan *p, float *e, const float *delta, const f
     A.G = p->cg;
     A.uvec = (sub_only || !coded) ? nullptr : reinterpret_cast<unsigned *>(ws + p->ws_uvec);
     A.qsum = (sub_only || !coded) ? nullptr : reinterpret_cast<unsigned short *>(ws + p->ws_qsum);
-    // waves (= chunks) per workgroup: 4 adjacent chunks when their LDS fits
-    const int wpb = 4 * (size_t)A.lds_per_wave <= 65536 ? 4 : 1;
+    // (one chunk where the LDS of four does not fit)
+    const int wpb = 4 * (size_t)A.lds_per_wave <= 65536 ? sl_chunks_per_group(p) : 1;
     const dim3 grid((unsigned)((p->n_chunks + wpb - 1) / wpb)), block(64 * wpb);
     A.order = sl_order(p, grid.x);
     const size_t lds = (size_t)A.lds_per_wave * wpb;
