@@ -165,6 +165,7 @@ int sl_plan_create_bits(const sl_tensor *tensors, int n_tensors, int k, int valu
     p->n_chunks = (int64_t)desc.size();
     p->n_elements = n_elements;
     p->n_partial = n_partial;
+    for (const SlTensorDev &D : tdev) p->max_tensor_chunks = std::max<int64_t>(p->max_tensor_chunks, D.n_chunks);
     p->payload_bytes = pay;
 
     size_t off = 0;

@@ -99,6 +99,7 @@ struct sl_plan {
     int64_t n_chunks;
     int64_t n_elements;
     int64_t n_partial;          // chunks without SLC_FULL
+    int64_t max_tensor_chunks;  // chunks of the tensor that has most
     size_t payload_bytes;
     size_t ws_bytes;
     // workspace sections (byte offsets)

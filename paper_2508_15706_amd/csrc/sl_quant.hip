@@ -120,6 +120,59 @@ __device__ void block_tree_sums(const double *const (&leaf)[NS], long long n, Re
     for (int s = 0; s < NS; ++s) sum[s] = sh.result[s];
 }
 
+// Mean and population variance of m values from their sum and sum of squares.
+SL_DEV SlTensorStat stat_of(long long m, double sum, double squares)
+{
+    const double M = (double)m;
+    const double mu = sum / M;
+    const double q = squares / M;
+    const double p = mu * mu;
+    double var = q - p;
+    if (var < 0.0) var = 0.0;
+    SlTensorStat s;
+    s.mu = mu;
+    s.var = var;
+    return s;
+}
+
+// A wave's own statistics of a tensor of at most SL_SHORT_TENSOR chunks: the trees of block_tree_sums over its leaves, all
+// of them loaded before the first is added.  Uniform.
+#define SL_SHORT_TENSOR 1024
+SL_DEV SlTensorStat wave_stats(const SlTensorDev &td, const double *leafA, long long n_chunks_total, int k)
+{
+    constexpr int TILES = SL_SHORT_TENSOR / 256;
+    const int lane = threadIdx.x & 63, n = (int)td.n_chunks;
+    double x[2][TILES][4], sum[2];
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+        for (int q = 0; q < TILES; ++q) {
+            const double *leaf = leafA + s * n_chunks_total + td.chunk0;
+            const int i = 256 * q + 4 * lane;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) x[s][q][u] = 0.0;
+            if (i + 3 < n) {
+                const red_d2 lo = *reinterpret_cast<const red_d2 *>(leaf + i), hi = *reinterpret_cast<const red_d2 *>(leaf + i + 2);
+                x[s][q][0] = lo.x, x[s][q][1] = lo.y, x[s][q][2] = hi.x, x[s][q][3] = hi.y;
+            } else if (i < n) {
+                x[s][q][0] = leaf[i];
+                if (i + 1 < n) x[s][q][1] = leaf[i + 1];
+                if (i + 2 < n) x[s][q][2] = leaf[i + 2];
+            }
+        }
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+        double t[TILES];
+#pragma unroll
+        for (int q = 0; q < TILES; ++q) {
+            t[q] = 0.0;
+            if (256 * q < n) t[q] = sl_wave_tree0((x[s][q][0] + x[s][q][1]) + (x[s][q][2] + x[s][q][3]), 6);
+        }
+        sum[s] = (t[0] + t[1]) + (t[2] + t[3]);
+    }
+    return stat_of(td.n_chunks * (long long)k, sum[0], sum[1]);
+}
+
 // ------------------------------------------------------------------ kernel B
 // One workgroup per tensor: its statistics.  With the coded format, up to SL_PLACE_SHARED_UPTO, a second
 // row of workgroups takes the first placement step (independent of the statistics, and a launch of its
@@ -137,16 +190,7 @@ k_tensor_stats(const SlTensorDev *tensors, const double *leafA, long long n_chun
     const double *const leaf[2] = {leafA + td.chunk0, leafA + n_chunks_total + td.chunk0};
     double S[2];
     block_tree_sums<2>(leaf, td.n_chunks, sh, S);
-    if (threadIdx.x == 0) {
-        const double M = (double)(td.n_chunks * (long long)k);
-        const double mu = S[0] / M;
-        const double q = S[1] / M;
-        const double p = mu * mu;
-        double var = q - p;
-        if (var < 0.0) var = 0.0;
-        tstat[blockIdx.x].mu = mu;
-        tstat[blockIdx.x].var = var;
-    }
+    if (threadIdx.x == 0) tstat[blockIdx.x] = stat_of(td.n_chunks * (long long)k, S[0], S[1]);
 }
 
 // ------------------------------------------------------------------ kernel C
@@ -169,6 +213,10 @@ struct CodeArgs {
     unsigned long long *twords;
     int n_tensors;
     long long section;
+    // SHORT: what kernel B would have read; the workgroups behind the chunks' take its placement step
+    const double *leafA;
+    const SlTensorDev *tensors;
+    SlCodedArgs C;
 };
 
 // Value of lane i ^ (1 << L), exactly (sl_partner's mirrors only do where the lanes of a quad hold the
@@ -296,13 +344,22 @@ SL_DEV double lane_tree(const float *x, const Bins<BITS> &B, int j, int bin)
 // per pass, 176 us for 46,537 chunks of k = 128 at 4 bits (here 30) and 1900 us for 300 chunks of
 // k = 1024 (here 25), where it left most of the chip without a wave.  Waves that stay for
 // several steps and fetch ahead are slower: the registers cost more waves than the overlap gains.
-template <int BITS, int LOG_LPC>
+// SHORT (short lists of short tensors, slk_quantize): there is no kernel B; a wave finds the statistics of its chunks'
+// tensors by itself from at most 16 KB of leaves each, which costs less than the launch (sl_compress at k = 64, plain / coded, us: 64 chunks 20.4 -> 19.1 / 23.0 -> 21.1, 512 22.1 -> 20.8 / 24.7 -> 22.9, 1024 26.3 -> 25.3 / 29.2 -> 27.4).
+template <int BITS, int LOG_LPC, bool SHORT>
 __global__ void __launch_bounds__(256) k_codes(CodeArgs A)
 {
     constexpr int E = 8, LPC = 1 << LOG_LPC, CPW = 64 / LPC, NB = 1 << BITS, LEFT = NB >> LOG_LPC > 0 ? NB >> LOG_LPC : 1;
     constexpr bool WIDE = E * LPC > 128;     // a bin's count needs more than 8 bits
     const int lane = threadIdx.x & 63, k = A.k;
     const int wave = sl_uniform((int)(threadIdx.x >> 6));
+    if constexpr (SHORT) {
+        if (blockIdx.x >= A.code_blocks) {
+            __shared__ unsigned wsum[4];
+            sl_coded_scan_tensor<256>(A.C, (int)(blockIdx.x - A.code_blocks), wsum);
+            return;
+        }
+    }
     if (blockIdx.x == A.code_blocks) {
         if (wave == 0) sl_coded_scan_list(A.twords, A.n_tensors, A.section, A.coded);
         return;
@@ -317,7 +374,17 @@ __global__ void __launch_bounds__(256) k_codes(CodeArgs A)
 
     const float *vin = A.vals + cl * k;
     const SlChunkDesc d = A.desc[cl];
-    const double mu = A.tstat[d.tensor].mu, var = A.tstat[d.tensor].var;
+    double mu = 0.0, var = 0.0;
+    if constexpr (SHORT) {
+        const int t0 = __builtin_amdgcn_readlane(d.tensor, 0), t1 = __builtin_amdgcn_readlane(A.desc[min(cw + CPW, A.n_chunks) - 1].tensor, 0);
+        for (int t = t0; t <= t1; ++t) {
+            const SlTensorStat s = wave_stats(A.tensors[t], A.leafA, A.n_chunks, k);
+            mu = d.tensor == t ? s.mu : mu;
+            var = d.tensor == t ? s.var : var;
+        }
+    } else {
+        mu = A.tstat[d.tensor].mu, var = A.tstat[d.tensor].var;
+    }
     unsigned char *const out1 = A.payload + d.rec_off + 3 * k / 2;
     unsigned char *const out2 = A.coded ? A.coded + A.cdesc[cl].fix_off + A.rem_bytes : nullptr;
 
@@ -451,23 +518,31 @@ __global__ void __launch_bounds__(256) k_codes(CodeArgs A)
 
 typedef void (*codes_kernel)(CodeArgs);
 
-template <int BITS>
+template <int BITS, bool SHORT>
 codes_kernel codes_for(int log_lpc)
 {
-    static const codes_kernel table[7] = {k_codes<BITS, 0>, k_codes<BITS, 1>, k_codes<BITS, 2>, k_codes<BITS, 3>,
-                                          k_codes<BITS, 4>, k_codes<BITS, 5>, k_codes<BITS, 6>};
+    static const codes_kernel table[7] = {k_codes<BITS, 0, SHORT>, k_codes<BITS, 1, SHORT>, k_codes<BITS, 2, SHORT>,
+                                          k_codes<BITS, 3, SHORT>, k_codes<BITS, 4, SHORT>, k_codes<BITS, 5, SHORT>,
+                                          k_codes<BITS, 6, SHORT>};
     return table[log_lpc];
+}
+template <bool SHORT>
+codes_kernel codes_for(int bits, int log_lpc)
+{
+    return bits == 1 ? codes_for<1, SHORT>(log_lpc) : bits == 2 ? codes_for<2, SHORT>(log_lpc)
+           : bits == 3 ? codes_for<3, SHORT>(log_lpc) : codes_for<4, SHORT>(log_lpc);
 }
 
 // ------------------------------------------------------------------ kernel D
 // One workgroup per (tensor, bin): fixed-tree sum of the bin's leaves, integer count, centroid ->
 // LUT[b] in the tensor block's header.  With the placement steps in these launches (PLACE) further
-// workgroups take the last of them, `place_waves` groups each.
+// workgroups take the last of them, `place_waves` groups each; without `scanned` they sum up the words of the tensors before
+// theirs, and the wave behind the last group writes the buffer header.
 template <bool PLACE>
 __global__ void __launch_bounds__(RED_THREADS, 8)
 k_tensor_lut(const SlTensorDev *tensors, int n_tensors, const double *leafC, const unsigned *cnt,
              long long n_chunks_total, int hdr_bytes, int rec_bytes, int nbins, unsigned char *payload,
-             unsigned char *coded, int cfix, SlCodedArgs C, int place_waves)
+             unsigned char *coded, int cfix, SlCodedArgs C, int place_waves, int scanned)
 {
     __shared__ RedShared sh;
     extern __shared__ __align__(16) unsigned place_lds[];
@@ -476,8 +551,13 @@ k_tensor_lut(const SlTensorDev *tensors, int n_tensors, const double *leafC, con
     if (PLACE && (int)blockIdx.x >= n_tensors) {
         const int wave = sl_uniform(tid >> 6);
         const long long gi = ((long long)((int)blockIdx.x - n_tensors) * nbins + b) * place_waves + wave;
-        if (wave < place_waves && gi < C.n_groups)
-            sl_coded_place(C, gi, C.twords[C.groups[gi].tensor], place_lds + (size_t)wave * (SL_RICE_GROUP * C.G.ua + 1));
+        if (wave < place_waves && gi < C.n_groups) {
+            const int t = C.groups[gi].tensor;
+            sl_coded_place(C, gi, scanned ? C.twords[t] : sl_coded_words_before(C.twords, t),
+                           place_lds + (size_t)wave * (SL_RICE_GROUP * C.G.ua + 1));
+        } else if (wave < place_waves && gi == C.n_groups && !scanned) {
+            sl_coded_header(sl_coded_words_before(C.twords, C.n_tensors), C.G.section, C.out);
+        }
         return;
     }
     const SlTensorDev td = tensors[blockIdx.x];
@@ -610,6 +690,10 @@ int slk_residual(const sl_plan *p, float *e, const unsigned char *payload, hipSt
 #define SL_PLACE_SHARED_UPTO 3300
 #endif
 
+// Lists up to so many chunks whose tensors have at most SL_SHORT_TENSOR, and on average at least as many as a code wave,
+// go without kernel B (a wave takes its tensors one after the other: 30 tensors of 38 chunks, 16 chunks per wave, 8.8 -> 8.3 us).
+#define SL_SHORT_LIST 8192
+
 int slk_quantize(const sl_plan *p, float *e, int skip_residual, unsigned char *payload, unsigned char *coded,
                  unsigned char *ws, hipStream_t st)
 {
@@ -642,9 +726,16 @@ int slk_quantize(const sl_plan *p, float *e, int skip_residual, unsigned char *p
         return SL_OK;
     }
 
-    hipLaunchKernelGGL(k_tensor_stats, dim3(p->n_tensors, shared ? 2 : 1), dim3(RED_THREADS), 0, st, p->d_tensors,
-                       leafA, (long long)p->n_chunks, k, tstat, placing);
-    if ((rc = check_launch())) return rc;
+    int log_lpc = 0;
+    while (log_lpc < 6 && (8 << log_lpc) < k) ++log_lpc;
+    const long long per_wave = 64 >> log_lpc;
+    const bool few = p->max_tensor_chunks <= SL_SHORT_TENSOR && p->n_chunks <= SL_SHORT_LIST &&
+                     p->n_tensors * per_wave <= p->n_chunks;
+    if (!few) {
+        hipLaunchKernelGGL(k_tensor_stats, dim3(p->n_tensors, shared ? 2 : 1), dim3(RED_THREADS), 0, st, p->d_tensors,
+                           leafA, (long long)p->n_chunks, k, tstat, placing);
+        if ((rc = check_launch())) return rc;
+    }
     sl_prof_mark(p, SL_PROF_STATS, st);
 
     CodeArgs C;
@@ -659,19 +750,18 @@ int slk_quantize(const sl_plan *p, float *e, int skip_residual, unsigned char *p
     C.coded = coded;
     C.cdesc = p->d_cdesc;
     C.rem_bytes = p->cg.rem_bytes;
-    int log_lpc = 0;
-    while (log_lpc < 6 && (8 << log_lpc) < k) ++log_lpc;
     C.passes = 1;
     while (512 * C.passes < k) C.passes <<= 1;
-    const codes_kernel fn = p->bits == 1 ? codes_for<1>(log_lpc) : p->bits == 2 ? codes_for<2>(log_lpc)
-                            : p->bits == 3 ? codes_for<3>(log_lpc) : codes_for<4>(log_lpc);
-    const long long per_wave = 64 >> log_lpc;
+    const codes_kernel fn = few ? codes_for<true>(p->bits, log_lpc) : codes_for<false>(p->bits, log_lpc);
     const long long per_block = 4ll * per_wave;
     C.code_blocks = (unsigned)((p->n_chunks + per_block - 1) / per_block);
     C.twords = placing.twords;
     C.n_tensors = p->n_tensors;
     C.section = p->cg.section;
-    hipLaunchKernelGGL(fn, dim3(C.code_blocks + (shared ? 1 : 0)), dim3(256), 0, st, C);
+    C.leafA = leafA;
+    C.tensors = p->d_tensors;
+    C.C = placing;
+    hipLaunchKernelGGL(fn, dim3(C.code_blocks + (shared ? few ? p->n_tensors : 1 : 0)), dim3(256), 0, st, C);
     if ((rc = check_launch())) return rc;
     sl_prof_mark(p, SL_PROF_CODES, st);
 
@@ -679,10 +769,10 @@ int slk_quantize(const sl_plan *p, float *e, int skip_residual, unsigned char *p
     const size_t per_wave_lds = sl_coded_place_words(p->cg) * sizeof(unsigned);
     const int place_waves = shared ? (int)std::max<size_t>(1, std::min<size_t>(RED_WAVES, 49152 / per_wave_lds)) : 0;
     const long long per_column = (long long)place_waves * nbins;      // groups that one column of workgroups takes
-    const long long place_columns = shared ? (p->n_groups + per_column - 1) / per_column : 0;
+    const long long place_columns = shared ? (p->n_groups + (few ? 1 : 0) + per_column - 1) / per_column : 0;
     hipLaunchKernelGGL(shared ? k_tensor_lut<true> : k_tensor_lut<false>, dim3((unsigned)(p->n_tensors + place_columns), nbins), dim3(RED_THREADS),
                        place_waves * per_wave_lds, st, p->d_tensors, p->n_tensors, leafC, cnt, (long long)p->n_chunks,
-                       p->hdr_bytes, p->rec_bytes, nbins, payload, coded, p->cg.cfix, placing, place_waves);
+                       p->hdr_bytes, p->rec_bytes, nbins, payload, coded, p->cg.cfix, placing, place_waves, few ? 0 : 1);
     if ((rc = check_launch())) return rc;
     sl_prof_mark(p, SL_PROF_LUT, st);
 
