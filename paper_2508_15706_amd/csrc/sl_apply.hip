@@ -231,28 +231,9 @@ __global__ void __launch_bounds__(256) k_apply(ApplyArgs A)
             for (int i = 0; i < 16; ++i) mo[i] = sl_load_stream_at(mc, i * step, o0);
         }
     } else {
-        // partial chunk: the same loads up front, 16 bytes where a lane's four columns lie inside
-        // the tensor (rows need no alignment), element by element at the edge, nothing outside
-        const int rows = d.rows, cols = d.cols, last_cols = d.last_cols;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const int row = 4 * i + lr;
-            const int lim = row < rows - 1 ? cols : (row == rows - 1 ? last_cols : 0);
-            const unsigned o0 = row * stride + lc;
-            th[i] = sl_f4{0.f, 0.f, 0.f, 0.f};
-            if constexpr (NESTEROV) mo[i] = sl_f4{0.f, 0.f, 0.f, 0.f};
-            if (lc + 3 < lim) {
-                th[i] = sl_load_stream_u(tc + o0);
-                if constexpr (NESTEROV) mo[i] = sl_load_stream_u(mc + o0);
-            } else {
-#pragma unroll
-                for (int cc = 0; cc < 4; ++cc)
-                    if (lc + cc < lim) {
-                        th[i][cc] = tc[o0 + cc];
-                        if constexpr (NESTEROV) mo[i][cc] = mc[o0 + cc];
-                    }
-            }
-        }
+        // (rows need no alignment)
+        sl_load_partial(A.theta, d, 0, lane, th);
+        if constexpr (NESTEROV) sl_load_partial(A.mom, d, 0, lane, mo);
     }
 
     const bool single = A.R <= A.batch;      // every record fits the staging area at once

@@ -83,12 +83,8 @@ __global__ void __launch_bounds__(256) k_lom_direction(LomArgs A)
 #pragma unroll
         for (int q = 0; q < 16 / S; ++q) {
             sl_f4 mv[S], dv[S];
-#pragma unroll
-            for (int u = 0; u < S; ++u) {
-                const int row = 4 * (S * q + u) + lr, n = (row < rows - 1 ? cols : row == rows - 1 ? last_cols : 0) - lc;
-                mv[u] = sl_load_edge(mc + (row * stride + lc), n);
-                dv[u] = sl_load_edge(dc + (row * stride + lc), n);
-            }
+            sl_load_partial(A.m, d, S * q, lane, mv);
+            sl_load_partial(A.delta, d, S * q, lane, dv);
 #pragma unroll
             for (int u = 0; u < S; ++u) {
                 const int row = 4 * (S * q + u) + lr, n = (row < rows - 1 ? cols : row == rows - 1 ? last_cols : 0) - lc;

@@ -708,8 +708,11 @@ __global__ void SL_SELECT_BOUNDS k_select(SelectArgs A)
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             sl_f4 pe[8], pd[8];
+            // (not for the accumulate, with two streams: 12,000 chunks of a 67-column matrix, k = 32, 121 us, with sl_load_partial 136;
+            // Sub-k 85 -> 66)
+            if constexpr (SUBK) sl_load_partial<8, true>(A.e, d, 8 * h, lane, pe);
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
+            for (int u = 0; u < (SUBK ? 0 : 8); ++u) {
                 const int i = 8 * h + u, lim = limit_of(i);
                 const unsigned o0 = (4 * i + lr) * stride + lc;
                 pe[u] = pd[u] = sl_f4{0.f, 0.f, 0.f, 0.f};
