@@ -499,10 +499,15 @@ int trans_args(const sl_plan *p, const unsigned char *in, unsigned char *out, Tr
     return E;
 }
 
+// Four waves per workgroup, fewer where their LDS passes what a launch may ask for without further notice (the encoder's
+// whole fixed records: fp32 values from k = 3976 on, 67,584 bytes at k = 4096).
 int trans_launch(void (*fn)(TransArgs), const TransArgs &A, hipStream_t st)
 {
     const long long waves = A.n_groups << (4 - A.s_log2);
-    hipLaunchKernelGGL(fn, dim3((unsigned)((waves + 3) / 4)), dim3(256), (size_t)A.lds_words * 16, st, A);
+    const size_t per_wave = (size_t)A.lds_words * sizeof(unsigned);
+    int wpb = 4;
+    while (wpb > 1 && per_wave * wpb > 65536) wpb >>= 1;
+    hipLaunchKernelGGL(fn, dim3((unsigned)((waves + wpb - 1) / wpb)), dim3(64 * wpb), per_wave * wpb, st, A);
     return launched();
 }
 

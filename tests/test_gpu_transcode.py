@@ -9,6 +9,7 @@ pytestmark = pytest.mark.gpu
 
 CASES = [(k, 2) for k in (4, 12, 28, 32, 36, 40, 64, 68, 72, 132, 136, 256, 260, 264, 512, 516, 520, 1024, 1416, 1424, 4096)]
 CASES += [(8, 1), (24, 1), (520, 1), (8, 3), (40, 3), (136, 3), (16, 4), (128, 4), (264, 4), (8, 32), (72, 32), (1024, 32)]
+CASES += [(3968, 32), (3976, 32), (4096, 32)]           # the last densities whose fixed records fit four waves' LDS, and beyond
 
 
 @pytest.mark.parametrize("k, bits", CASES)
