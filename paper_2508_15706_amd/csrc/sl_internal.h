@@ -147,6 +147,39 @@ inline unsigned sl_order(const sl_plan *p, unsigned groups)
     return whole | (whole && p->n_partial * 32 >= p->n_chunks ? 1u : 0u);
 }
 
+// Where a lane's 16-byte loads of a partial chunk begin (sl_load_partial; access i: elements lc .. lc + 3 of row 4 i + lr).
+// A lane whose four columns exist loads them; one that the row's end cuts through loads the four elements that
+// end there, begun up to three earlier; one without elements the chunk's first four (a chunk holds at least that many).  Elements
+// before a row's first belong to the tensor too - another row or chunk - but for its first row's, so in a tensor's first
+// chunk no load begins before that chunk: memory outside the tensors is the caller's.
+struct SlPartial {
+    int lr, lc, rows, cols, last_cols, room;      // room: elements before the chunk that a load may begin at
+    unsigned o0, step;                            // bytes from `room` elements before the chunk
+    __host__ __device__ SlPartial(const SlChunkDesc &d, int lane)
+        : lr(lane >> 4), lc((lane & 15) * 4), rows(d.rows), cols(d.cols), last_cols(d.last_cols), room(d.local_chunk ? 4 : 0),
+          o0(4u * ((unsigned)lr * (unsigned)d.stride + (unsigned)(lc + room))), step(16u * (unsigned)d.stride)
+    {
+    }
+    // how many of the access's four elements exist (none below 1)
+    __host__ __device__ int exist(int i) const
+    {
+        const int row = 4 * i + lr;
+        return (row < rows - 1 ? cols : row == rows - 1 ? last_cols : 0) - lc;
+    }
+    __host__ __device__ unsigned place(int i) const { return o0 + (unsigned)i * step; }
+    // elements between the load's first and the access's, 1 <= exist(i) <= 3
+    __host__ __device__ int back(int i) const
+    {
+        const int n = 4 - exist(i), m = (int)(place(i) >> 2);
+        return n < m ? n : m;
+    }
+    __host__ __device__ unsigned load_at(int i) const
+    {
+        const int n = exist(i);
+        return n >= 4 ? place(i) : n > 0 ? place(i) - 4u * (unsigned)back(i) : 4u * (unsigned)room;
+    }
+};
+
 // Records an event after the kernel of `phase` (phase < 0: start of a call).
 void sl_prof_mark(const sl_plan *p, int phase, hipStream_t st);
 
