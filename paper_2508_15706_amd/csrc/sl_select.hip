@@ -35,6 +35,7 @@
 #include <cmath>
 
 #include "sl_coded.h"
+#include "sl_search.h"
 
 namespace {
 
@@ -95,55 +96,6 @@ SL_DEV unsigned fmix32(unsigned h)
     return h;
 }
 
-// A threshold T in [lo, hi] with count_ge(T) >= k, given count_ge(lo) >= k and 0 <= lo <= hi: the first one met that
-// exactly k keys reach (`exact`; among n keys that takes about log2(n) steps, not one per bit), else, with ties, the
-// largest with count_ge(T) >= k.  All values are wave-uniform.
-// With `steps` > 0 only that many bits below the highest one in which lo and hi differ are
-// decided and the rest left zero: a value that is not above the exact answer and still has
-// count_ge >= k.
-template <class CountGE>
-SL_DEV int bisect_kth(int lo, int hi, int k, CountGE count_ge, bool &exact, int steps = 0)
-{
-    exact = false;
-    if (lo >= hi) return lo;
-    const int top = 31 - __clz(lo ^ hi);
-    const int last = steps > 0 ? max(0, top - steps + 1) : 0;
-    int T = hi & ~(int)((2u << top) - 1u);
-    for (int b = top; b >= last; --b) {
-        const int cand = T | (1 << b), n = count_ge(cand);
-        if (n >= k) T = cand;
-        if (n == k) {
-            exact = true;
-            break;
-        }
-    }
-    return T;
-}
-
-// A threshold T that exactly k keys reach, or, with ties, the largest that at least k reach (`exact` says which), given
-// count_ge(lo) = n_lo >= k > n_hi = count_ge(hi) and lo < hi; afterwards hi and n_hi are the next value tried above
-// T (T + 1, unless `exact`) and its count.  Steps go to where k would lie if the keys between lo and hi were spread evenly -
-// three or four of them reach it among hundreds of keys - and every third one to the middle, which bounds their number
-// whatever the keys.  With `steps` > 0 only that many are taken.  All values are wave-uniform.
-template <class CountGE>
-SL_DEV int find_kth(int lo, int &hi, int &n_lo, int &n_hi, int k, CountGE count_ge, bool &exact, int steps = 0)
-{
-    exact = n_lo == k;
-    for (int it = 1; !exact && hi - lo > 1 && it != steps; ++it) {
-        int mid = lo + ((hi - lo) >> 1);
-        if (it % 3) {
-            const float part = (float)(2 * (n_lo - k) + 1) * __builtin_amdgcn_rcpf((float)(2 * (n_lo - n_hi)));
-            mid = sl_uniform(lo + (int)((float)(hi - lo) * part));
-            mid = max(lo + 1, min(hi - 1, mid));
-        }
-        const int n = count_ge(mid);
-        exact = n == k;
-        if (n >= k) lo = mid, n_lo = n;
-        else hi = mid, n_hi = n;
-    }
-    return lo;
-}
-
 // General route.  key[r] is the magnitude key of register r, or -1 for a
 // position outside the tensor; sg0/sg1 hold the sign of register r at bit
 // 31 - (r & 31) of sg[r / 32].  Writes the k selected (value, index) pairs in
@@ -185,35 +137,15 @@ SL_DEV void select_general(int (&key)[64], const float (&a)[64], unsigned sg0, u
     bool found = false;
     if constexpr (SAMPLED) {
         const int ks = (k + 4) >> 3;
-        if (margin > 0 && hi > 0 && hi != 0x7FFFFFFF) {
+        if (margin > 0 && sl_sample_serves(hi)) {
             auto count_sample = [&](int x) {
                 int n = 0;
 #pragma unroll
                 for (int s = 0; s < 8; ++s) n += sl_popc(sl_ballot(key[9 * s] >= x));     // rows and columns of all residues
                 return n;
             };
-            // the bracket's lower end: the lanes' largest keys are about the chunk's upper 64th, their smallest a start that
-            // outliers do not move; from there down by growing steps, then between the last two
-            int from = sl_wave_min(lmax), to = hi + 1, n_to = 0, n_from = count_sample(from);
-            for (int d = 1 << 22; n_from < ks + margin && from > 0; d <<= 1) {
-                to = from, n_to = n_from;
-                from = d < from ? from - d : 0;
-                n_from = count_sample(from);
-            }
-            bool exact = false;
-            if (n_from >= ks + margin) from = find_kth(from, to, n_from, n_to, ks + margin, count_sample, exact, 8);
-            // its upper end, up from there in the same way
-            int upto = from, n_upto = n_from, beyond = hi + 1, n_beyond = 0;
-            for (int d = 1 << 21; d < hi - upto; d <<= 1) {
-                const int n = count_sample(upto + d);
-                if (n < ks - margin) {
-                    beyond = upto + d, n_beyond = n;
-                    break;
-                }
-                upto += d, n_upto = n;
-            }
-            if (beyond > upto) upto = find_kth(upto, beyond, n_upto, n_beyond, ks - margin, count_sample, exact, 8);
-            if (upto <= from) upto = beyond;
+            int from, upto;
+            sl_sample_bracket(sl_wave_min(lmax), hi, ks, margin, count_sample, from, upto);
             const unsigned width = (unsigned)(upto - from);
             int mine = 0, above = 0;                // this lane's keys inside the bracket and above it
 #pragma unroll
@@ -254,7 +186,8 @@ SL_DEV void select_general(int (&key)[64], const float (&a)[64], unsigned sg0, u
                     return n;
                 };
                 int top = upto;
-                T = find_kth(from, top, n_lo, n_hi, k, count_list, exact);
+                bool exact;
+                T = sl_find_kth(from, top, n_lo, n_hi, k, count_list, exact);
                 n_ge = n_lo;
                 n_gt = exact ? -1 : n_hi;
                 found = true;
@@ -269,7 +202,7 @@ SL_DEV void select_general(int (&key)[64], const float (&a)[64], unsigned sg0, u
     if (last >= 3) {
         // T1: the leading bits of T.  count(T1) >= k, and count(T1 + width) < k: T1 + width is either
         // beyond every key or a value the bisection tried and rejected.
-        const int T1 = bisect_kth(0, hi, k, count_regs, exact, SL_SELECT_COARSE_BITS);
+        const int T1 = sl_bisect_kth(0, hi, k, count_regs, exact, SL_SELECT_COARSE_BITS);
         const int width = 1 << last, upper = T1 | (width - 1);
         if (exact) {
             T = T1;
@@ -305,20 +238,20 @@ SL_DEV void select_general(int (&key)[64], const float (&a)[64], unsigned sg0, u
                     return n;
                 };
                 // the (k - n_above)-th largest key of the bucket
-                T = bisect_kth(T1, upper, k - n_above, count_list, exact);
+                T = sl_bisect_kth(T1, upper, k - n_above, count_list, exact);
                 if (!exact) {
                     n_ge = n_above + count_list(T);
                     n_gt = n_above + (T == upper ? 0 : count_list(T + 1));    // keys above T: beyond the bucket, or in it
                 }
             } else {
-                T = bisect_kth(T1, upper, k, count_regs, exact);
+                T = sl_bisect_kth(T1, upper, k, count_regs, exact);
                 if (!exact) n_ge = count_regs(T);
             }
             sl_wave_sync();                 // the list shares LDS with nothing live, but keep its reads
                                             // ahead of whatever the caller stores next
         }
     } else {
-        T = bisect_kth(0, hi, k, count_regs, exact);
+        T = sl_bisect_kth(0, hi, k, count_regs, exact);
         if (!exact) n_ge = count_regs(T);
     }
     if (exact) n_ge = k;
@@ -406,7 +339,7 @@ SL_DEV void prune_bound(const float (&a)[64], int k, int &L, int &hi)
     hi = sl_wave_max(lmax);
     const int lo = sl_wave_min(lmin);
     bool exact;
-    L = bisect_kth(lo, hi, k, [&](int x) {
+    L = sl_bisect_kth(lo, hi, k, [&](int x) {
         int n = 0;
 #pragma unroll
         for (int g = 0; g < G; ++g) n += sl_popc(sl_ballot(gm[g] >= x));
@@ -831,7 +764,7 @@ __global__ void SL_SELECT_BOUNDS k_select(SelectArgs A)
                 return n;
             };
             bool exact;
-            const int T = bisect_kth(L, hi, k, count_cand, exact);
+            const int T = sl_bisect_kth(L, hi, k, count_cand, exact);
             const bool ties = !exact && count_cand(T) != k;
             int need = 0;
             if (ties) {

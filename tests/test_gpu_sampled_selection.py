@@ -48,3 +48,34 @@ def test_sampled_selection(oracle, k):
     ref = oracle.compress(descs, k, e_ref, x, 0.95)
     assert np.array_equal(pay[:plan.payload_bytes].cpu().numpy(), ref)
     assert np.array_equal(e.cpu().numpy().view(np.uint32), e_ref.view(np.uint32))
+
+
+@pytest.mark.parametrize("k", [520, 1024, 2048, 4000])
+def test_sampled_selection_non_finite(oracle, k):
+    """Infinities and NaNs of every payload (the largest keys, up to one below 2^31 - 1): chunks that hold them are selected
+    by the bits of their elements like any other."""
+    from paper_2508_15706_amd import binding as sl
+    rng = np.random.default_rng(k)
+    x = rng.normal(0, 1e-3, (9, 4096)).astype(np.float32).view(np.uint32)
+    r = np.arange(4096)
+    sampled = (4 * (r // 256) + r % 4) % 9 == 0
+    payload = lambda n, low: (rng.integers(low, 0x7FFFFFFF, n) | rng.integers(0, 2, n) << 31).astype(np.uint32)  # noqa: E731
+    x[0, rng.permutation(4096)[:60]] = 0x7F800000       # infinity
+    x[1, rng.permutation(4096)[:60]] = 0x7FC00000       # the usual NaN
+    x[2, rng.permutation(4096)[:300]] = payload(300, 0x7F800001)
+    x[3] = 0
+    x[3, sampled] = payload(sampled.sum(), 0x7FE00001)  # the sample's registers NaN, all others zero
+    x[4, sampled] = 0
+    x[4, ~sampled] = payload((~sampled).sum(), 0x7FE00001)
+    x[5] = 0x7FFFFFFE
+    x[6, :2100] = 0xFF800000
+    x[7] = payload(4096, 0x7F800001)
+    x[8, 100:160] = 0x7FFFFFFF
+    x = x.reshape(-1)
+    descs = [(1, x.size, 0, 0)]
+    m = torch.from_numpy(x.view(np.float32).copy()).cuda()
+    sl.sl_sub_topk(sl.sl_plan_create(descs, k), m)
+    at = oracle.sub_topk(descs, k, x.view(np.float32).copy(), want_idx=True).reshape(9, k).astype(np.int64)
+    want = x.copy()
+    want[(4096 * np.arange(9)[:, None] + at).reshape(-1)] = 0
+    assert np.array_equal(m.cpu().numpy().view(np.uint32), want)
