@@ -166,6 +166,10 @@ int sl_plan_create_bits(const sl_tensor *tensors, int n_tensors, int k, int valu
     p->n_elements = n_elements;
     p->n_partial = n_partial;
     for (const SlTensorDev &D : tdev) p->max_tensor_chunks = std::max<int64_t>(p->max_tensor_chunks, D.n_chunks);
+    for (int64_t c = 0, per_wave = 64 >> sl_code_lanes_log2(k); c < p->n_chunks; c += per_wave) {
+        const SlChunkDesc &last = desc[(size_t)std::min<int64_t>(c + per_wave, p->n_chunks) - 1];
+        p->max_wave_tensors = std::max(p->max_wave_tensors, last.tensor - desc[(size_t)c].tensor + 1);
+    }
     p->payload_bytes = pay;
 
     size_t off = 0;

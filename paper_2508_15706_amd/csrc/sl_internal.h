@@ -100,6 +100,7 @@ struct sl_plan {
     int64_t n_elements;
     int64_t n_partial;          // chunks without SLC_FULL
     int64_t max_tensor_chunks;  // chunks of the tensor that has most
+    int max_wave_tensors;       // tensors that a wave of the code kernel meets among its chunks, at most
     size_t payload_bytes;
     size_t ws_bytes;
     // workspace sections (byte offsets)
@@ -120,6 +121,14 @@ struct sl_plan {
     // optional per-kernel timing (sl_profile_begin / sl_profile_end)
     struct SlProfile *prof;
 };
+
+// log2 of the lanes that the code kernel gives to a chunk, eight entries each; a wave takes 64 >> this consecutive chunks.
+inline int sl_code_lanes_log2(int k)
+{
+    int l = 0;
+    while (l < 6 && (8 << l) < k) ++l;
+    return l;
+}
 
 // Byte offset of the LUT header of the chunk's tensor block inside a payload.
 __host__ __device__ inline long long sl_lut_off(const SlChunkDesc &d, int hdr_bytes, int rec_bytes)

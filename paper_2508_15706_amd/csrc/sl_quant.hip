@@ -690,9 +690,13 @@ int slk_residual(const sl_plan *p, float *e, const unsigned char *payload, hipSt
 #define SL_PLACE_SHARED_UPTO 3300
 #endif
 
-// Lists up to so many chunks whose tensors have at most SL_SHORT_TENSOR, and on average at least as many as a code wave,
-// go without kernel B (a wave takes its tensors one after the other: 30 tensors of 38 chunks, 16 chunks per wave, 8.8 -> 8.3 us).
+// Lists up to so many chunks whose tensors have at most SL_SHORT_TENSOR go without kernel B where no wave of the code kernel
+// meets more than two tensors: it takes their statistics one after the other, about 1 us each, and the launch is
+// worth 2 (sl_compress, kernel B / without, us: one wave among 164 with 2 tensors 21.2 / 20.9, with 3 21.2 / 21.7, 4 21.2 / 22.6, 8 21.3 / 26.4;
+// every wave with 2, k = 64, 24.5 / 24.4, with 3 30.1 / 31.2; a run of 57 one-chunk tensors at k = 8 25.8 / 56.7; 3.4M elements in
+// matrices of odd sides and their vectors, five in a wave, k = 32, 39.2 / 41.0; one tensor of 3 chunks 17.9 / 16.5).
 #define SL_SHORT_LIST 8192
+#define SL_SHORT_WAVE_TENSORS 2
 
 int slk_quantize(const sl_plan *p, float *e, int skip_residual, unsigned char *payload, unsigned char *coded,
                  unsigned char *ws, hipStream_t st)
@@ -726,11 +730,9 @@ int slk_quantize(const sl_plan *p, float *e, int skip_residual, unsigned char *p
         return SL_OK;
     }
 
-    int log_lpc = 0;
-    while (log_lpc < 6 && (8 << log_lpc) < k) ++log_lpc;
-    const long long per_wave = 64 >> log_lpc;
+    const int log_lpc = sl_code_lanes_log2(k);
     const bool few = p->max_tensor_chunks <= SL_SHORT_TENSOR && p->n_chunks <= SL_SHORT_LIST &&
-                     p->n_tensors * per_wave <= p->n_chunks;
+                     p->max_wave_tensors <= SL_SHORT_WAVE_TENSORS;
     if (!few) {
         hipLaunchKernelGGL(k_tensor_stats, dim3(p->n_tensors, shared ? 2 : 1), dim3(RED_THREADS), 0, st, p->d_tensors,
                            leafA, (long long)p->n_chunks, k, tstat, placing);
@@ -753,7 +755,7 @@ int slk_quantize(const sl_plan *p, float *e, int skip_residual, unsigned char *p
     C.passes = 1;
     while (512 * C.passes < k) C.passes <<= 1;
     const codes_kernel fn = few ? codes_for<true>(p->bits, log_lpc) : codes_for<false>(p->bits, log_lpc);
-    const long long per_block = 4ll * per_wave;
+    const long long per_block = 4ll * (64 >> log_lpc);
     C.code_blocks = (unsigned)((p->n_chunks + per_block - 1) / per_block);
     C.twords = placing.twords;
     C.n_tensors = p->n_tensors;

@@ -1,5 +1,5 @@
 """Lists on both sides of the rules for short ones: statistics found by the code kernel itself (tensors of up to 1024 chunks,
-lists of up to 8192, a code wave of chunks per tensor), one chunk per workgroup below 4096 chunks.  Payload, coded bytes, e and both
+lists of up to 8192, at most two tensors in any code wave), one chunk per workgroup below 4096 chunks.  Payload, coded bytes, e and both
 aggregates against the oracle."""
 import numpy as np
 import pytest
@@ -10,6 +10,10 @@ pytestmark = pytest.mark.gpu
 CASES = [(64, 2, [1024]), (64, 2, [1025]), (16, 4, [3, 1024, 1, 17]), (8, 1, [1] * 40), (8, 2, [64] * 5), (8, 2, [63] * 5),
          (4, 2, [250, 1]), (520, 3, [65, 2]), (1024, 2, [9, 1, 1]), (32, 2, [255, 256, 257]), (16, 2, [1024] * 8),
          (16, 2, [1024] * 8 + [1]), (16, 2, [4095]), (40, 32, [20])]
+# two and three tensors in a code wave; a run of one-chunk tensors beside long ones; fewer chunks than a code wave takes; coded
+# placement in launches of its own behind statistics found by the code kernel
+CASES += [(8, 2, [32] * 6), (8, 2, [21] * 6), (64, 4, [15, 1, 7, 9]), (8, 2, [1000] * 4 + [1] * 57), (64, 2, [1]), (16, 1, [3, 2]),
+          (64, 4, [8] * 170), (264, 4, [2] * 200)]
 
 
 @pytest.mark.parametrize("k, bits, sizes", CASES, ids=lambda v: str(v).replace(" ", "")[:24])
