@@ -162,10 +162,11 @@ inline unsigned sl_order(const sl_plan *p, unsigned groups)
 // before a row's first belong to the tensor too - another row or chunk - but for its first row's, so in a tensor's first
 // chunk no load begins before that chunk: memory outside the tensors is the caller's.
 struct SlPartial {
-    int lr, lc, rows, cols, last_cols, room;      // room: elements before the chunk that a load may begin at
+    const SlChunkDesc &d;                         // (copies of its fields cost the momentum aggregate 2 %)
+    int lr, lc, room;                             // room: elements before the chunk that a load may begin at
     unsigned o0, step;                            // bytes from `room` elements before the chunk
-    __host__ __device__ SlPartial(const SlChunkDesc &d, int lane)
-        : lr(lane >> 4), lc((lane & 15) * 4), rows(d.rows), cols(d.cols), last_cols(d.last_cols), room(d.local_chunk ? 4 : 0),
+    __host__ __device__ SlPartial(const SlChunkDesc &chunk, int lane)
+        : d(chunk), lr(lane >> 4), lc((lane & 15) * 4), room(d.local_chunk ? 4 : 0),
           o0(4u * ((unsigned)lr * (unsigned)d.stride + (unsigned)(lc + room))), step(16u * (unsigned)d.stride)
     {
     }
@@ -173,7 +174,7 @@ struct SlPartial {
     __host__ __device__ int exist(int i) const
     {
         const int row = 4 * i + lr;
-        return (row < rows - 1 ? cols : row == rows - 1 ? last_cols : 0) - lc;
+        return (row < d.rows - 1 ? d.cols : row == d.rows - 1 ? d.last_cols : 0) - lc;
     }
     __host__ __device__ unsigned place(int i) const { return o0 + (unsigned)i * step; }
     // elements between the load's first and the access's, 1 <= exist(i) <= 3
