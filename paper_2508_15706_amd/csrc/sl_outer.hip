@@ -26,9 +26,11 @@
 #ifndef SL_DENSE_STEP
 #define SL_DENSE_STEP 8
 #endif
-// LDS that a workgroup asks for and does not use: three of them fit a compute unit then.  With more waves than
-// that the memory has more rows open than it keeps, and is slower (1.8B list: direction 4.88 ms without, 4.75 so; four
-// directions averaged 7.59 and 7.48; 1000- and 2730-column matrices 1.02 and 0.85, 1.20 and 1.12).
+// LDS that a workgroup asks for and does not use: two of them fit a compute unit then (the compute unit's 160 KB are handed out
+// in pieces of 1280 bytes, and three times 43 of these are more).  With more waves the memory has more rows open
+// than it keeps, and is slower (direction / four directions averaged, ms, with as many workgroups as the registers allow, three (53,760
+// bytes), two: 1.8B list 5.06 / 7.66, 4.86 / 7.66, 4.84 / 7.40; 400,000 x 1000 1.85 / 2.27, 1.64 / 2.26, 1.56 / 2.16; 178M list and
+// 786,432 x 768 within 2 %).  The average with momentum has registers for two workgroups only and takes the same time either way.
 #ifndef SL_STREAM_LDS
 #define SL_STREAM_LDS 54272
 #endif
