@@ -361,7 +361,8 @@ int sl_rice_decode(sl_plan *plan, const void *in, size_t in_bytes, void *payload
  * A phase's time runs from the end of the previous kernel on the stream to the
  * end of its own, so it includes the launch gap before it. */
 enum { SL_PROF_SELECT = 0,  /* accumulate + chunk Top-k          (sl_compress)   */
-       SL_PROF_STATS = 1,   /* per-tensor mean / variance                        */
+       SL_PROF_STATS = 1,   /* per-tensor mean / variance (on short lists part of
+                               CODES: counted, with no kernel and next to no time) */
        SL_PROF_CODES = 2,   /* 2-bit codes + record codes                        */
        SL_PROF_LUT = 3,     /* per-tensor centroids                              */
        SL_PROF_RESIDUAL = 4,/* e <- a - LUT[code] at the selected positions      */

@@ -158,7 +158,6 @@ SL_DEV int sl_uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
 // lost.  The halves of the whole list in place of windows: the same, but 2470 for the 1.8B coded aggregate (neighbouring chunks
 // share lines of the payloads); windows of 256 groups lose 1 % on the accumulate pass; four or eight places 1 - 3 %
 // behind two except on flat runs; a third, a sixth or random places are worse than list order.
-#define SL_ORDER_WINDOW 1024u
 SL_DEV unsigned sl_work_group(unsigned i, unsigned order)
 {
     if (i >= (order & ~1u)) return i;

@@ -150,9 +150,11 @@ inline int sl_chunks_per_group(const sl_plan *p) { return p->n_chunks < SL_SPREA
 // matrix's tiles: one group in every few - the slow groups would all come to one or two of the XCDs, so the groups
 // are turned (columns 1000 and 2730, a chunk in 25 partial, plain aggregate of 8: list order 475, paired 488, turned 471 us;
 // on full chunks the turn costs up to 3 %).
+#define SL_ORDER_WINDOW 1024u             // groups of a window: whole windows only are walked in another order than the list's
+static_assert((SL_ORDER_WINDOW & (SL_ORDER_WINDOW - 1)) == 0 && SL_ORDER_WINDOW >= 8, "sl_work_group permutes halves and fours");
 inline unsigned sl_order(const sl_plan *p, unsigned groups)
 {
-    const unsigned whole = p->n_chunks < SL_SPREAD_BELOW ? 0u : groups & ~1023u;
+    const unsigned whole = p->n_chunks < SL_SPREAD_BELOW ? 0u : groups & ~(SL_ORDER_WINDOW - 1);
     return whole | (whole && p->n_partial * 32 >= p->n_chunks ? 1u : 0u);
 }
 

@@ -29,9 +29,9 @@
 //      sl_compress: k = 64 247 -> 226 us, k = 256 269 -> 238, k = 384 313 -> 264, 64 chunks 22.6 -> 20.8; about 20, 20, 20 and 0
 //      of it the order of the chunks).
 // A candidate list that overflows (massive ties; a partial chunk with too few
-// non-empty groups) and k > 512 take the general route: T bisected over the
-// registers directly and one ordered compaction over the registers - slower,
-// same result.
+// non-empty groups) and k > 512 take the general route (select_general): T from a bracket that a
+// sample gives, or bisected over the registers directly, and one ordered
+// compaction over the registers - slower, same result.
 #include <cmath>
 
 #include "sl_coded.h"
@@ -117,8 +117,9 @@ SL_DEV unsigned fmix32(unsigned h)
 #define SL_SELECT_COARSE_BITS 12
 #endif
 #define SL_SELECT_LIST_CAP 512
-#define SL_SELECT_COLUMN 20              // rows of the sampled route's list (64 ints each): it may reach into sel_val,
-                                         // which is written once the list is done with
+#define SL_SELECT_COLUMN 20              // rows of the sampled route's list (64 ints each): it may reach into sel_val
+                                         // and sel_idx, which are written once the list is done with
+static_assert(64 * 4 * SL_SELECT_COLUMN <= 4 * SL_SELECT_LIST_CAP + 6 * 516, "the list fits a wave's LDS at the smallest k that is sampled");
 template <bool VALUES_FROM_A, bool SAMPLED>
 SL_DEV void select_general(int (&key)[64], const float (&a)[64], unsigned sg0, unsigned sg1, int k, int margin, int lane,
                            float *sel_val, unsigned short *sel_idx, int *list)
@@ -196,65 +197,65 @@ SL_DEV void select_general(int (&key)[64], const float (&a)[64], unsigned sg0, u
         }
     }
     if (!found) {
-    const int top = hi > 0 ? 31 - __clz(hi) : 0;
-    const int last = top - SL_SELECT_COARSE_BITS + 1;    // lowest bit the coarse stage decides
-    bool exact;
-    if (last >= 3) {
-        // T1: the leading bits of T.  count(T1) >= k, and count(T1 + width) < k: T1 + width is either
-        // beyond every key or a value the bisection tried and rejected.
-        const int T1 = sl_bisect_kth(0, hi, k, count_regs, exact, SL_SELECT_COARSE_BITS);
-        const int width = 1 << last, upper = T1 | (width - 1);
-        if (exact) {
-            T = T1;
-        } else {
-            int n_above = 0, m = 0;
-#pragma unroll
-            for (int r = 0; r < 64; ++r) {
-                // (a position outside the tensor has key -1: never above, and far outside the bucket)
-                const bool in = (unsigned)(key[r] - T1) < (unsigned)width;
-                const unsigned long long mb = sl_ballot(in);
-                n_above += sl_popc(sl_ballot(key[r] > upper));
-                if (mb) {
-                    const int pos = m + sl_mbcnt(mb);
-                    if (in && pos < SL_SELECT_LIST_CAP) list[pos] = key[r];
-                    m += sl_popc(mb);
-                }
-            }
-            sl_wave_sync();
-            if (m <= SL_SELECT_LIST_CAP) {
-                constexpr int SLOTS = SL_SELECT_LIST_CAP / 64;
-                const int nslots = (m + 63) >> 6;
-                int ck[SLOTS];
-#pragma unroll
-                for (int s = 0; s < SLOTS; ++s) {
-                    const int p = s * 64 + lane;
-                    ck[s] = (s < nslots && p < m) ? list[p] : -1;
-                }
-                auto count_list = [&](int x) {
-                    int n = 0;
-#pragma unroll
-                    for (int s = 0; s < SLOTS; ++s)
-                        if (s < nslots) n += sl_popc(sl_ballot(ck[s] >= x));
-                    return n;
-                };
-                // the (k - n_above)-th largest key of the bucket
-                T = sl_bisect_kth(T1, upper, k - n_above, count_list, exact);
-                if (!exact) {
-                    n_ge = n_above + count_list(T);
-                    n_gt = n_above + (T == upper ? 0 : count_list(T + 1));    // keys above T: beyond the bucket, or in it
-                }
+        const int top = hi > 0 ? 31 - __clz(hi) : 0;
+        const int last = top - SL_SELECT_COARSE_BITS + 1;    // lowest bit the coarse stage decides
+        bool exact;
+        if (last >= 3) {
+            // T1: the leading bits of T.  count(T1) >= k, and count(T1 + width) < k: T1 + width is either
+            // beyond every key or a value the bisection tried and rejected.
+            const int T1 = sl_bisect_kth(0, hi, k, count_regs, exact, SL_SELECT_COARSE_BITS);
+            const int width = 1 << last, upper = T1 | (width - 1);
+            if (exact) {
+                T = T1;
             } else {
-                T = sl_bisect_kth(T1, upper, k, count_regs, exact);
-                if (!exact) n_ge = count_regs(T);
+                int n_above = 0, m = 0;
+#pragma unroll
+                for (int r = 0; r < 64; ++r) {
+                    // (a position outside the tensor has key -1: never above, and far outside the bucket)
+                    const bool in = (unsigned)(key[r] - T1) < (unsigned)width;
+                    const unsigned long long mb = sl_ballot(in);
+                    n_above += sl_popc(sl_ballot(key[r] > upper));
+                    if (mb) {
+                        const int pos = m + sl_mbcnt(mb);
+                        if (in && pos < SL_SELECT_LIST_CAP) list[pos] = key[r];
+                        m += sl_popc(mb);
+                    }
+                }
+                sl_wave_sync();
+                if (m <= SL_SELECT_LIST_CAP) {
+                    constexpr int SLOTS = SL_SELECT_LIST_CAP / 64;
+                    const int nslots = (m + 63) >> 6;
+                    int ck[SLOTS];
+#pragma unroll
+                    for (int s = 0; s < SLOTS; ++s) {
+                        const int p = s * 64 + lane;
+                        ck[s] = (s < nslots && p < m) ? list[p] : -1;
+                    }
+                    auto count_list = [&](int x) {
+                        int n = 0;
+#pragma unroll
+                        for (int s = 0; s < SLOTS; ++s)
+                            if (s < nslots) n += sl_popc(sl_ballot(ck[s] >= x));
+                        return n;
+                    };
+                    // the (k - n_above)-th largest key of the bucket
+                    T = sl_bisect_kth(T1, upper, k - n_above, count_list, exact);
+                    if (!exact) {
+                        n_ge = n_above + count_list(T);
+                        n_gt = n_above + (T == upper ? 0 : count_list(T + 1));    // keys above T: beyond the bucket, or in it
+                    }
+                } else {
+                    T = sl_bisect_kth(T1, upper, k, count_regs, exact);
+                    if (!exact) n_ge = count_regs(T);
+                }
+                sl_wave_sync();                 // the list shares LDS with nothing live, but keep its reads
+                                                // ahead of whatever the caller stores next
             }
-            sl_wave_sync();                 // the list shares LDS with nothing live, but keep its reads
-                                            // ahead of whatever the caller stores next
+        } else {
+            T = sl_bisect_kth(0, hi, k, count_regs, exact);
+            if (!exact) n_ge = count_regs(T);
         }
-    } else {
-        T = sl_bisect_kth(0, hi, k, count_regs, exact);
-        if (!exact) n_ge = count_regs(T);
-    }
-    if (exact) n_ge = k;
+        if (exact) n_ge = k;
     }
     const bool ties = n_ge != k;            // more keys equal to T than slots left
     int need = 0;                           // tie entries to take, lowest indices first
@@ -641,8 +642,8 @@ __global__ void SL_SELECT_BOUNDS k_select(SelectArgs A)
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             sl_f4 pe[8], pd[8];
-            // (not for the accumulate, with two streams: 12,000 chunks of a 67-column matrix, k = 32, 121 us, with sl_load_partial 136;
-            // Sub-k 85 -> 66)
+            // (not for the accumulate: with one call per stream the second stream's loads are issued only once the first one's
+            // are placed; 12,000 chunks of a 67-column matrix, k = 32, 121 us as it is, 136 so; Sub-k 85 -> 66)
             if constexpr (SUBK) sl_load_partial<8, true>(A.e, d, 8 * h, lane, pe);
 #pragma unroll
             for (int u = 0; u < (SUBK ? 0 : 8); ++u) {
