@@ -113,7 +113,14 @@ struct DenseArgs {
     const float *dirs[SL_MAX_WORKERS];
 };
 
-template <bool NESTEROV>
+// SHORT: without it the compiler waits for a worker's first loads before it requests the last three, two trips to memory per
+// worker.  Lists that give every compute unit a few waves only pay for that (us, so / SHORT, four directions and four with momentum: 864
+// chunks 17.0 / 14.9 and 22.4 / 20.5, 1024 20.6 / 19.3 and 27.7 / 27.0, 4200 75.5 / 73.3 and 101.0 / 98.8); long ones are faster
+// with fewer loads open at a time (6144 98.6 / 99.5, 16384 260 / 273, 1.8B list 7362 / 7454), and so are ragged ones at every length (32,000 x
+// 100 19.0 / 20.0, 200 x 530 15.4 / 16.2): the loads of their partial chunks come one by one, and neighbours that share lines should
+// meet.  The line lies between the two.
+#define SL_DENSE_SHORT_BELOW 5120
+template <bool NESTEROV, bool SHORT>
 __global__ void __launch_bounds__(256) k_dense_avg_apply(DenseArgs A)
 {
     const int lane = threadIdx.x & 63;
@@ -153,6 +160,7 @@ __global__ void __launch_bounds__(256) k_dense_avg_apply(DenseArgs A)
         for (int r = 0; r < R; ++r) {                       // r ascending: the order is part of the result
             sl_f4 g[S];
             load(A.dirs[r] + d.base, g);
+            if (full && SHORT) __builtin_amdgcn_sched_barrier(0);       // (all eight requested before the first is waited for)
 #pragma unroll
             for (int u = 0; u < S; ++u) acc[u] = acc[u] + g[u];
         }
@@ -230,7 +238,8 @@ int slk_dense_avg_apply(const sl_plan *p, float *theta, float *mom, const float 
     for (int r = 0; r < SL_MAX_WORKERS; ++r) A.dirs[r] = r < R ? dirs[r] : nullptr;
     const dim3 grid((unsigned)((p->n_chunks + 3) / 4)), block(256);
     A.order = sl_order(p, grid.x);
-    if (mom) hipLaunchKernelGGL(k_dense_avg_apply<true>, grid, block, SL_STREAM_LDS, st, A);
-    else hipLaunchKernelGGL(k_dense_avg_apply<false>, grid, block, SL_STREAM_LDS, st, A);
+    const bool is_short = p->n_chunks < SL_DENSE_SHORT_BELOW && p->n_partial * 32 < p->n_chunks;
+    if (is_short) hipLaunchKernelGGL((mom ? k_dense_avg_apply<true, true> : k_dense_avg_apply<false, true>), grid, block, SL_STREAM_LDS, st, A);
+    else hipLaunchKernelGGL((mom ? k_dense_avg_apply<true, false> : k_dense_avg_apply<false, false>), grid, block, SL_STREAM_LDS, st, A);
     return check_launch();
 }

@@ -57,3 +57,19 @@ def test_work_order(oracle, chunks, partial):
     sl.sl_sub_topk(plan, m)
     oracle.sub_topk(descs, k, m_ref)
     same(m, m_ref, "Sub-k")
+
+
+@pytest.mark.parametrize("chunks", [5119, 5120])
+@pytest.mark.parametrize("momentum", [False, True])
+def test_dense_average_lengths(oracle, chunks, momentum):
+    """Both sides of the length below which the dense average requests a worker's loads together."""
+    from paper_2508_15706_amd import binding as sl
+    descs, n = [(64 * chunks, 64, 0, 1)], 4096 * chunks
+    gen = torch.Generator(device="cuda").manual_seed(chunks)
+    theta, m, a, b, c = (torch.empty(n, device="cuda").normal_(0, 1e-2, generator=gen) for _ in range(5))
+    want, m_ref = theta.cpu().numpy(), m.cpu().numpy() if momentum else None
+    sl.sl_dense_avg_apply(sl.sl_plan_create(descs, 8), theta, m if momentum else None, [a, b, c], 0.7, 0.9)
+    oracle.dense_avg_apply(descs, want, [x.cpu().numpy() for x in (a, b, c)], 0.7, m=m_ref, mu=0.9)
+    assert np.array_equal(theta.cpu().numpy().view(np.uint32), want.view(np.uint32))
+    if momentum:
+        assert np.array_equal(m.cpu().numpy().view(np.uint32), m_ref.view(np.uint32))
