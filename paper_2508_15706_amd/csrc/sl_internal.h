@@ -137,14 +137,18 @@ __host__ __device__ inline long long sl_lut_off(const SlChunkDesc &d, int hdr_by
 }
 
 // Chunks (waves) per workgroup of the kernels that give a chunk to a wave: four adjacent ones, so that a workgroup streams
-// 1 KB of every matrix row it touches; but one on lists shorter than a window of sl_work_group, where workgroups of
-// four leave compute units without any, or with one more than others (four / one, us: sl_compress at k = 64, 64 chunks 21.6 / 20.4,
-// 512 23.7 / 22.1, 1024 29.8 / 25.5, 2048 38.1 / 35.4, 3072 48.0 / 45.9; aggregates of eight, k = 64 and 32, 2048 chunks 16.6 / 12.5
-// plain, 17.0 / 11.9 coded; from 4096 on the window's order is better: aggregate 23.9 / 27.3).  Not where one chunk in 32 or
-// more is partial: rows then begin anywhere in a line of memory, and the neighbours that share a line should share
-// an L2 (1155 chunks of a 67-column matrix, aggregate of three: 12.6 / 19.7).
-#define SL_SPREAD_BELOW 4096
-inline int sl_chunks_per_group(const sl_plan *p) { return p->n_chunks < SL_SPREAD_BELOW && p->n_partial * 32 < p->n_chunks ? 1 : 4; }
+// 1 KB of every matrix row it touches; but one on lists so short that workgroups of four, dealt to the compute units in one turn or two,
+// would leave a third of the places without any.  Four / one, us (matrices, R = 4, k = 64): sl_compress, 64 chunks 21.4 / 20.7,
+// 512 23.8 / 23.0, 960 27.8 / 28.3, 1024 27.8 / 28.7, 1280 35.0 / 33.6, 1800 39.2 / 39.4, 3072 51.4 / 54.8, 3840 59.2 / 63.7; plain aggregate
+// 512 8.5 / 8.4, 1280 8.9 / 8.4, 2048 11.1 / 11.8, 3072 20.0 / 21.1; coded 1280 9.8 / 9.4, 3072 19.4 / 21.2; Sub-k 64 12.3 / 11.9, 768 12.6 /
+// 13.2, 3072 20.2 / 21.0.  Not where one chunk in 32 or more is partial: rows then begin anywhere in a line of memory, and the neighbours
+// that share a line should share an L2 (1155 chunks of a 67-column matrix, aggregate of three: 12.6 / 19.7).
+#define SL_COMPUTE_UNITS 256
+inline int sl_chunks_per_group(const sl_plan *p)
+{
+    const int64_t groups = (p->n_chunks + 3) / 4, turns = (groups + SL_COMPUTE_UNITS - 1) / SL_COMPUTE_UNITS;
+    return turns <= 2 && 3 * groups <= 2 * SL_COMPUTE_UNITS * turns && p->n_partial * 32 < p->n_chunks ? 1 : 4;
+}
 
 // sl_work_group's `order` for a grid of so many groups.  Where a list has many partial chunks - the last column of a
 // matrix's tiles: one group in every few - the slow groups would all come to one or two of the XCDs, so the groups
@@ -154,7 +158,7 @@ inline int sl_chunks_per_group(const sl_plan *p) { return p->n_chunks < SL_SPREA
 static_assert((SL_ORDER_WINDOW & (SL_ORDER_WINDOW - 1)) == 0 && SL_ORDER_WINDOW >= 8, "sl_work_group permutes halves and fours");
 inline unsigned sl_order(const sl_plan *p, unsigned groups)
 {
-    const unsigned whole = p->n_chunks < SL_SPREAD_BELOW ? 0u : groups & ~(SL_ORDER_WINDOW - 1);
+    const unsigned whole = p->n_chunks < 4 * SL_ORDER_WINDOW ? 0u : groups & ~(SL_ORDER_WINDOW - 1);
     return whole | (whole && p->n_partial * 32 >= p->n_chunks ? 1u : 0u);
 }
 

@@ -983,8 +983,9 @@ static int launch_select(const sl_plan *p, float *e, const float *delta, const f
     A.G = p->cg;
     A.uvec = (sub_only || !coded) ? nullptr : reinterpret_cast<unsigned *>(ws + p->ws_uvec);
     A.qsum = (sub_only || !coded) ? nullptr : reinterpret_cast<unsigned short *>(ws + p->ws_qsum);
-    // (one chunk where the LDS of four does not fit)
-    const int wpb = 4 * (size_t)A.lds_per_wave <= 65536 ? sl_chunks_per_group(p) : 1;
+    // (one chunk where the LDS of four does not fit; four at high densities, where a wave's time is its instructions: 512 chunks, four /
+    // one, k = 256 29.4 / 29.9 us, k = 1024 53.0 / 54.9, coded 68.3 / 70.1)
+    const int wpb = 4 * (size_t)A.lds_per_wave > 65536 ? 1 : k > 128 ? 4 : sl_chunks_per_group(p);
     const dim3 grid((unsigned)((p->n_chunks + wpb - 1) / wpb)), block(64 * wpb);
     A.order = sl_order(p, grid.x);
     const size_t lds = (size_t)A.lds_per_wave * wpb;

@@ -1,5 +1,5 @@
 """Lists on both sides of the rules for short ones: statistics found by the code kernel itself (tensors of up to 1024 chunks,
-lists of up to 8192, at most two tensors in any code wave), one chunk per workgroup below 4096 chunks.  Payload, coded bytes, e and both
+lists of up to 8192, at most two tensors in any code wave), one chunk per workgroup up to 680 chunks and from 1025 to 1364.  Payload, coded bytes, e and both
 aggregates against the oracle."""
 import numpy as np
 import pytest
@@ -14,6 +14,8 @@ CASES = [(64, 2, [1024]), (64, 2, [1025]), (16, 4, [3, 1024, 1, 17]), (8, 1, [1]
 # placement in launches of its own behind statistics found by the code kernel
 CASES += [(8, 2, [32] * 6), (8, 2, [21] * 6), (64, 4, [15, 1, 7, 9]), (8, 2, [1000] * 4 + [1] * 57), (64, 2, [1]), (16, 1, [3, 2]),
           (64, 4, [8] * 170), (264, 4, [2] * 200)]
+# where workgroups change between one chunk and four, at a low and a high density
+CASES += [(64, 2, [679, 1]), (64, 2, [681]), (128, 2, [1025, 339]), (136, 2, [600, 764]), (64, 2, [1365])]
 
 
 @pytest.mark.parametrize("k, bits, sizes", CASES, ids=lambda v: str(v).replace(" ", "")[:24])
