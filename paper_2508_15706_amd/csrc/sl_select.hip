@@ -106,7 +106,10 @@ SL_DEV unsigned fmix32(unsigned h)
 // and k / 8 + m (m two and a half standard deviations, sample_margin) bracket T but for one chunk in eighty or so.  One pass over all registers
 // counts the keys above the bracket and lets every lane put its own keys inside it (six on average) into a column of `list`;
 // T is found among those.  A dozen passes over the registers, which this replaces, are half of the instructions (24,000 chunks, sl_compress: k = 520 405 -> 354 us, 1024 368 -> 322, 2048 591 -> 518, 4000 954 -> 903; 123,505 chunks with heavy tails, k = 1024, this kernel 1505 -> 1240).
-// Where T is not inside, or a lane's column overflows (ties, uneven columns), it is found in two stages.  A pass over all 64 registers
+// Not on lists below SL_SAMPLE_FROM chunks, where a wave has its SIMD almost to itself and the sample's chain of steps is
+// longer than the passes it saves (sl_compress, two stages / sample, us: 256 chunks, k = 1024 47.5 / 51.0, 2048 chunks 75.9 / 79.2, 3072 93.5 /
+// 95.4, 3840 118.0 / 114.6, 8192 201 / 190; k = 520 3072 88.5 / 90.0, 3840 111.4 / 107.2; k = 2048 2048 93.4 / 97.0, 3072 134.7 / 131.0).
+// There, and where T is not inside, or a lane's column overflows (ties, uneven columns), it is found in two stages.  A pass over all 64 registers
 // of every lane is the expensive unit there, so only the leading SL_SELECT_COARSE_BITS bits of T are
 // bisected that way; this leaves T inside a bucket [T1, T1 + width) that holds few keys (about
 // fifty at a quarter density on Gaussian data).  One more pass copies the bucket's keys to
@@ -119,6 +122,7 @@ SL_DEV unsigned fmix32(unsigned h)
 #define SL_SELECT_LIST_CAP 512
 #define SL_SELECT_COLUMN 20              // rows of the sampled route's list (64 ints each): it may reach into sel_val
                                          // and sel_idx, which are written once the list is done with
+#define SL_SAMPLE_FROM 3328              // thirteen chunks per compute unit
 static_assert(64 * 4 * SL_SELECT_COLUMN <= 4 * SL_SELECT_LIST_CAP + 6 * 516, "the list fits a wave's LDS at the smallest k that is sampled");
 template <bool VALUES_FROM_A, bool SAMPLED>
 SL_DEV void select_general(int (&key)[64], const float (&a)[64], unsigned sg0, unsigned sg1, int k, int margin, int lane,
@@ -956,7 +960,7 @@ static int launch_select(const sl_plan *p, float *e, const float *delta, const f
     {
         const double share = (double)k / SL_CHUNK;
         const int margin = (int)(2.5 * std::sqrt(512.0 * share * (1.0 - share))) + 1;
-        A.sample_margin = k > 512 && k / 8 + margin < 511 ? margin : 0;
+        A.sample_margin = k > 512 && p->n_chunks >= SL_SAMPLE_FROM && k / 8 + margin < 511 ? margin : 0;
     }
     {
         size_t b = pruned ? sizeof(uint2) * cand_cap(k > 256 ? 16 : 8) : sizeof(int) * SL_SELECT_LIST_CAP;

@@ -1,4 +1,4 @@
-"""Selections of more than 512 of a chunk's elements, whose threshold is bracketed by a sample: values for which the bracket holds,
+"""Selections of more than 512 of a chunk's elements, whose threshold is bracketed by a sample on lists of 3328 chunks and more: values for which the bracket holds,
 misses (elements outside the sample's registers differ from those in it) or overflows (uneven columns, ties), partial chunks, the first and the last densities.
 Top-k removed in place and the payload, against the oracle."""
 import numpy as np
@@ -50,12 +50,8 @@ def test_sampled_selection(oracle, k):
     assert np.array_equal(e.cpu().numpy().view(np.uint32), e_ref.view(np.uint32))
 
 
-@pytest.mark.parametrize("k", [520, 1024, 2048, 4000])
-def test_sampled_selection_non_finite(oracle, k):
-    """Infinities and NaNs of every payload (the largest keys, up to one below 2^31 - 1): chunks that hold them are selected
-    by the bits of their elements like any other."""
-    from paper_2508_15706_amd import binding as sl
-    rng = np.random.default_rng(k)
+def non_finite_values(rng):
+    """Nine chunks with infinities and NaNs of every payload (the largest keys, up to one below 2^31 - 1), as words."""
     x = rng.normal(0, 1e-3, (9, 4096)).astype(np.float32).view(np.uint32)
     r = np.arange(4096)
     sampled = (4 * (r // 256) + r % 4) % 9 == 0
@@ -71,7 +67,14 @@ def test_sampled_selection_non_finite(oracle, k):
     x[6, :2100] = 0xFF800000
     x[7] = payload(4096, 0x7F800001)
     x[8, 100:160] = 0x7FFFFFFF
-    x = x.reshape(-1)
+    return x
+
+
+@pytest.mark.parametrize("k", [520, 1024, 2048, 4000])
+def test_sampled_selection_non_finite(oracle, k):
+    """Chunks that hold infinities and NaNs are selected by the bits of their elements like any other."""
+    from paper_2508_15706_amd import binding as sl
+    x = non_finite_values(np.random.default_rng(k)).reshape(-1)
     descs = [(1, x.size, 0, 0)]
     m = torch.from_numpy(x.view(np.float32).copy()).cuda()
     sl.sl_sub_topk(sl.sl_plan_create(descs, k), m)
@@ -79,3 +82,28 @@ def test_sampled_selection_non_finite(oracle, k):
     want = x.copy()
     want[(4096 * np.arange(9)[:, None] + at).reshape(-1)] = 0
     assert np.array_equal(m.cpu().numpy().view(np.uint32), want)
+
+
+@pytest.mark.parametrize("k, chunks", [(516, 3328), (520, 3327), (520, 3328), (640, 3328), (1024, 3328), (1416, 3328), (1424, 3328), (2048, 3328),
+                                       (3000, 3328), (4000, 3328), (4032, 3328), (4052, 3328)])
+def test_sampled_selection_long_lists(oracle, k, chunks):
+    """The length from which the sample is used: the chunks of the tests above among others of normal values."""
+    from paper_2508_15706_amd import binding as sl
+    rng = np.random.default_rng(k)
+    odd = np.concatenate([chunk_values(rng, 13), non_finite_values(rng).view(np.float32)])
+    x = np.concatenate([odd, np.tile(rng.normal(0, 1e-3, (61, 4096)).astype(np.float32), (60, 1))])[:chunks]
+    descs, n = [(1, x.size, 0, 0)], x.size
+    plan = sl.sl_plan_create(descs, k)
+    m = torch.from_numpy(x.reshape(-1).copy()).cuda()
+    sl.sl_sub_topk(plan, m)
+    at = oracle.sub_topk(descs, k, x.reshape(-1).copy(), want_idx=True).reshape(chunks, k).astype(np.int64)
+    want = x.reshape(-1).view(np.uint32).copy()
+    want[(4096 * np.arange(chunks)[:, None] + at).reshape(-1)] = 0
+    assert np.array_equal(m.cpu().numpy().view(np.uint32), want)
+    x[13:22] = x[22:31]                                  # (a NaN's payload is not part of what a sum promises)
+    x = x.reshape(-1)
+    e, e_ref, pay = torch.zeros(n, device="cuda"), np.zeros_like(x), sl.alloc_payload(plan)
+    sl.sl_compress(plan, e, torch.from_numpy(x).cuda(), 0.95, pay, sl.alloc_workspace(plan))
+    ref = oracle.compress(descs, k, e_ref, x, 0.95)
+    assert np.array_equal(pay[:plan.payload_bytes].cpu().numpy(), ref)
+    assert np.array_equal(e.cpu().numpy().view(np.uint32), e_ref.view(np.uint32))
