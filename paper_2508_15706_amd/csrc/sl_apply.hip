@@ -121,6 +121,10 @@ __global__ void __launch_bounds__(256) k_apply(ApplyArgs A)
     float *tc = A.theta + d.base;
     const int lr = lane >> 4, lc = (lane & 15) * 4;
     const unsigned stride = (unsigned)d.stride;
+    unsigned lane_at = 4u * (lr * stride + lc);      // the lane's place in its rows, in bytes
+    // (settled here on the direct route: formed behind the records' loads it got a register that one of them was still to fill, and the
+    // requests for theta waited for all records; 510M list, R = 16, k = 256 814 us, so 796)
+    if constexpr (DIRECT) asm volatile("" : "+v"(lane_at));
     const bool full = d.flags & SLC_FULL;
 
     // Word w of a batch's staging area: worker r = w / wpr, word q of (LUT, record padded to words)
@@ -223,7 +227,7 @@ __global__ void __launch_bounds__(256) k_apply(ApplyArgs A)
     sl_f4 th[16], mo[NESTEROV ? 16 : 1];
     float *mc = NESTEROV ? A.mom + d.base : nullptr;
     if (full) {
-        const unsigned o0 = 4u * (lr * stride + lc), step = 16u * stride;
+        const unsigned o0 = lane_at, step = 16u * stride;
 #pragma unroll
         for (int i = 0; i < 16; ++i) th[i] = sl_load_stream_at(tc, i * step, o0);
         if constexpr (NESTEROV) {
@@ -426,7 +430,7 @@ __global__ void __launch_bounds__(256) k_apply(ApplyArgs A)
         }
 
         if (full) {
-            const unsigned o0 = 4u * (lr * stride + lc), step = 16u * stride;
+            const unsigned o0 = lane_at, step = 16u * stride;
 #pragma unroll
             for (int i8 = 0; i8 < ROWS4; ++i8) {
                 const int i = ROWS4 * h + i8;

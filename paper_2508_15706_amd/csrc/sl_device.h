@@ -101,16 +101,18 @@ SL_DEV void sl_store_edge(float *p, int n, sl_f4 v)
 // payloads, k = 32, us: 1155 chunks of a 67-column matrix 12.2 -> 10.0 / 12.8 -> 13.0, 900 of 530 columns 20.4 -> 10.6 / 17.4 -> 13.9,
 // 12,000 of 67 columns 112 -> 66 / 89 -> 80, 24,000 of 1000 columns 257 -> 189 / 235 -> 187, the last also by the order of the
 // chunks; with momentum 2000 chunks of 100 columns are 4 % slower, all others faster).
-// Where the edge cuts through a lane's columns, the load ends with the row's last element (SlPartial) and its elements are
+// Where the edge cuts through a lane's columns, the load ends with the row's last element (sl_partial_load_at) and its elements are
 // moved into place afterwards.
 template <int N, bool ZERO = false>
 SL_DEV void sl_load_partial(const float *arena, const SlChunkDesc &d, int i0, int lane, sl_f4 (&v)[N])
 {
-    const SlPartial P(d, lane);
-    const float *p = arena + (d.base - P.room);
-    auto exist = [&](int u) -> int { return P.exist(i0 + u); };
+    const int lr = lane >> 4, lc = (lane & 15) * 4, room = sl_partial_room(d);
+    const float *p = arena + (d.base - room);
+    const unsigned o0 = sl_partial_origin(d, lr, lc, room), step = 16u * (unsigned)d.stride;
+    auto exist = [&](int u) -> int { return sl_partial_exist(d, lr, lc, i0 + u); };
+    auto place = [&](int u) -> unsigned { return o0 + (unsigned)(i0 + u) * step; };
 #pragma unroll
-    for (int u = 0; u < N; ++u) v[u] = sl_load_stream_at(p, 0u, P.load_at(i0 + u));
+    for (int u = 0; u < N; ++u) v[u] = sl_load_stream_at(p, 0u, sl_partial_load_at(exist(u), place(u), room));
     // the four elements from the one that lies `by` places into a load on
     auto moved = [&](sl_f4 w, bool one, bool two) -> sl_f4 {
         const float x0 = one ? w.y : w.x, x1 = one ? w.z : w.y, x2 = one ? w.w : w.z;
@@ -121,8 +123,8 @@ SL_DEV void sl_load_partial(const float *arena, const SlChunkDesc &d, int i0, in
         return sl_f4{n > 0 ? w.x : 0.f, n > 1 ? w.y : 0.f, n > 2 ? w.z : 0.f, n > 3 ? w.w : 0.f};
     };
     const bool cut = ((d.cols | d.last_cols) & 3) != 0;
-    if (cut && d.cols == d.last_cols && P.room) {              // a tile: the same columns in every row
-        const int n0 = d.cols - P.lc;
+    if (cut && d.cols == d.last_cols && room) {              // a tile: the same columns in every row
+        const int n0 = d.cols - lc;
         const int by = n0 > 0 && n0 < 4 ? 4 - n0 : 0;
         const bool one = by & 1, two = by & 2;
 #pragma unroll
@@ -130,7 +132,7 @@ SL_DEV void sl_load_partial(const float *arena, const SlChunkDesc &d, int i0, in
     } else if (cut) {
 #pragma unroll
         for (int u = 0; u < N; ++u) {
-            const int n = exist(u), by = n > 0 && n < 4 ? P.back(i0 + u) : 0;
+            const int n = exist(u), by = n > 0 && n < 4 ? sl_partial_back(n, place(u)) : 0;
             v[u] = kept(moved(v[u], by & 1, by & 2), n);
         }
     } else if constexpr (ZERO) {

@@ -166,34 +166,33 @@ inline unsigned sl_order(const sl_plan *p, unsigned groups)
 // end there, begun up to three earlier; one without elements the chunk's first four (a chunk holds at least that many).  Elements
 // before a row's first belong to the tensor too - another row or chunk - but for its first row's, so in a tensor's first
 // chunk no load begins before that chunk: memory outside the tensors is the caller's.
-struct SlPartial {
-    const SlChunkDesc &d;                         // (copies of its fields cost the momentum aggregate 2 %)
-    int lr, lc, room;                             // room: elements before the chunk that a load may begin at
-    unsigned o0, step;                            // bytes from `room` elements before the chunk
-    __host__ __device__ SlPartial(const SlChunkDesc &chunk, int lane)
-        : d(chunk), lr(lane >> 4), lc((lane & 15) * 4), room(d.local_chunk ? 4 : 0),
-          o0(4u * ((unsigned)lr * (unsigned)d.stride + (unsigned)(lc + room))), step(16u * (unsigned)d.stride)
-    {
-    }
-    // how many of the access's four elements exist (none below 1)
-    __host__ __device__ int exist(int i) const
-    {
-        const int row = 4 * i + lr;
-        return (row < d.rows - 1 ? d.cols : row == d.rows - 1 ? d.last_cols : 0) - lc;
-    }
-    __host__ __device__ unsigned place(int i) const { return o0 + (unsigned)i * step; }
-    // elements between the load's first and the access's, 1 <= exist(i) <= 3
-    __host__ __device__ int back(int i) const
-    {
-        const int n = 4 - exist(i), m = (int)(place(i) >> 2);
-        return n < m ? n : m;
-    }
-    __host__ __device__ unsigned load_at(int i) const
-    {
-        const int n = exist(i);
-        return n >= 4 ? place(i) : n > 0 ? place(i) - 4u * (unsigned)back(i) : 4u * (unsigned)room;
-    }
-};
+// (Functions of plain values: the same arithmetic as methods of a struct led to other registers in the aggregates' full chunks; 510M
+// list, coded aggregate, us, so / with the struct: k = 256, R = 16 1172 / 1197, k = 128, R = 16 772 / 804, k = 64, R = 32 1042 / 1069.)
+#define SL_HD __host__ __device__ __attribute__((always_inline)) inline
+// elements before the chunk that a load may begin at
+SL_HD int sl_partial_room(const SlChunkDesc &d) { return d.local_chunk ? 4 : 0; }
+// how many of access i's four elements exist (none below 1)
+SL_HD int sl_partial_exist(const SlChunkDesc &d, int lr, int lc, int i)
+{
+    const int row = 4 * i + lr;
+    return (row < d.rows - 1 ? d.cols : row == d.rows - 1 ? d.last_cols : 0) - lc;
+}
+// bytes from `room` elements before the chunk to access 0; 16 * stride more for each further one
+SL_HD unsigned sl_partial_origin(const SlChunkDesc &d, int lr, int lc, int room)
+{
+    return 4u * ((unsigned)lr * (unsigned)d.stride + (unsigned)(lc + room));
+}
+// elements between the first of the load and the first of the access at `place`, 1 <= exist <= 3
+SL_HD int sl_partial_back(int exist, unsigned place)
+{
+    const int n = 4 - exist, m = (int)(place >> 2);
+    return n < m ? n : m;
+}
+// where the load begins
+SL_HD unsigned sl_partial_load_at(int exist, unsigned place, int room)
+{
+    return exist >= 4 ? place : exist > 0 ? place - 4u * (unsigned)sl_partial_back(exist, place) : 4u * (unsigned)room;
+}
 
 // Records an event after the kernel of `phase` (phase < 0: start of a call).
 void sl_prof_mark(const sl_plan *p, int phase, hipStream_t st);

@@ -1,4 +1,4 @@
-// Every load that a partial chunk's lanes make (SlPartial), over matrices and runs of many shapes: none leaves its
+// Every load that a partial chunk's lanes make (sl_partial_load_at), over matrices and runs of many shapes: none leaves its
 // tensor, and the elements that exist are where the lane looks for them.  Prints the first violation.
 #include <algorithm>
 #include <cstdio>
@@ -13,14 +13,15 @@ static bool check(long long rows, long long cols, long long offset, bool tile)
         d.local_chunk = (int)local++;
         if (d.rows == 64 && d.cols == 64 && d.last_cols == 64) return true;
         for (int lane = 0; lane < 64; ++lane) {
-            const SlPartial P(d, lane);
+            const int lr = lane >> 4, lc = (lane & 15) * 4, room = sl_partial_room(d);
             for (int i = 0; i < 16; ++i) {
-                const long long first = d.base - P.room + (P.load_at(i) >> 2);
-                bool ok = (P.load_at(i) & 3) == 0 && first >= offset && first + 4 <= offset + n;
-                const long long want = d.base + (4 * i + P.lr) * (long long)d.stride + P.lc;
-                const int e = P.exist(i);
+                const int e = sl_partial_exist(d, lr, lc, i);
+                const unsigned place = sl_partial_origin(d, lr, lc, room) + (unsigned)i * 16u * (unsigned)d.stride;
+                const unsigned at = sl_partial_load_at(e, place, room);
+                const long long first = d.base - room + (at >> 2), want = d.base + (4 * i + lr) * (long long)d.stride + lc;
+                bool ok = (at & 3) == 0 && first >= offset && first + 4 <= offset + n;
                 if (e >= 4) ok = ok && first == want;
-                else if (e > 0) ok = ok && first + P.back(i) == want && P.back(i) + e <= 4;
+                else if (e > 0) ok = ok && first + sl_partial_back(e, place) == want && sl_partial_back(e, place) + e <= 4;
                 if (!ok) {
                     std::printf("%lld x %lld at %lld, %s: chunk %d lane %d access %d loads from %lld\n", rows, cols, offset,
                                 tile ? "tiles" : "runs", d.local_chunk, lane, i, first - offset);
