@@ -21,9 +21,9 @@
 // Steps 3 and 4 run for all workers of a batch at once, so their cost per chunk hardly grows
 // with R; only step 5 is a chain over the workers.
 // What bounds it: above R * k of about 1024 entries per chunk the number of instructions, two waves per
-// SIMD sharing the issue slots (LDS: 16 KB of accumulators per wave).  A chunk at k = 256, R = 16 takes 3226 vector,
-// 813 scalar and 488 LDS instructions (50 vector lane slots per entry), and its wave issues in 47 % of
-// its cycles (1183 us for 123,505 chunks); with lists everywhere, a lane per word of the longest possible vector and
+// SIMD sharing the issue slots (LDS: 16 KB of accumulators per wave).  A chunk at k = 256, R = 16 takes 3183 vector,
+// 821 scalar and 488 LDS instructions (50 vector lane slots per entry), and its wave issues in 47 % of
+// its cycles (1174 us for 123,505 chunks); with lists everywhere, a lane per word of the longest possible vector and
 // as many turns as the fullest word has zeros, it took 3500, 1233 and 538 (1404 us).
 #include "sl_coded.h"
 
