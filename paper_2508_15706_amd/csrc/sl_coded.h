@@ -77,12 +77,10 @@ SL_DEV int sl_lane_read(int v, int src) { return __builtin_amdgcn_ds_bpermute(4 
 // orders its own earlier LDS accesses before the call and reads uv / rw after it.
 // Indices that are not strictly ascending (a malformed plain record - a compressor never
 // produces one) are coded as gap 0, and a vector that would outgrow k + qmax bits is cut there.
-SL_DEV int sl_coded_emit(const SlCodedGeom &G, int lane, const unsigned short *idx, unsigned *uv, unsigned *rw)
+// (The _filled form: uv holds ones and rw zeros already.)
+SL_DEV int sl_coded_emit_filled(const SlCodedGeom &G, int lane, const unsigned short *idx, unsigned *uv, unsigned *rw)
 {
-    const int k = G.k, b = G.b, nrw = G.rem_bytes >> 2;
-    for (int w = lane; w < G.ua; w += 64) uv[w] = 0xFFFFFFFFu;
-    for (int w = lane; w < nrw; w += 64) rw[w] = 0u;
-    sl_wave_sync();
+    const int k = G.k, b = G.b;
     const int limit = k + G.qmax;            // bits of the longest vector
     // A lane owns ceil(k / 64) CONSECUTIVE entries: one wave scan for the whole chunk, and the lanes of one
     // store instruction are that many entries apart, so that at high densities they land in different
@@ -116,6 +114,13 @@ SL_DEV int sl_coded_emit(const SlCodedGeom &G, int lane, const unsigned short *i
     const int carry = __builtin_amdgcn_readlane(incl, 63);
     sl_wave_sync();
     return min(carry, G.qmax);
+}
+SL_DEV int sl_coded_emit(const SlCodedGeom &G, int lane, const unsigned short *idx, unsigned *uv, unsigned *rw)
+{
+    for (int w = lane; w < G.ua; w += 64) uv[w] = 0xFFFFFFFFu;
+    for (int w = lane; w < (G.rem_bytes >> 2); w += 64) rw[w] = 0u;
+    sl_wave_sync();
+    return sl_coded_emit_filled(G, lane, idx, uv, rw);
 }
 
 // ---------------------------------------------------------------------------------- reader

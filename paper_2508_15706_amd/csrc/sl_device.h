@@ -103,16 +103,23 @@ SL_DEV void sl_store_edge(float *p, int n, sl_f4 v)
 // chunks; with momentum 2000 chunks of 100 columns are 4 % slower, all others faster).
 // Where the edge cuts through a lane's columns, the load ends with the row's last element (sl_partial_load_at) and its elements are
 // moved into place afterwards.
-template <int N, bool ZERO = false>
-SL_DEV void sl_load_partial(const float *arena, const SlChunkDesc &d, int i0, int lane, sl_f4 (&v)[N])
+template <int N>
+SL_DEV void sl_partial_request(const float *arena, const SlChunkDesc &d, int i0, int lane, sl_f4 (&v)[N])
 {
     const int lr = lane >> 4, lc = (lane & 15) * 4, room = sl_partial_room(d);
     const float *p = arena + (d.base - room);
     const unsigned o0 = sl_partial_origin(d, lr, lc, room), step = 16u * (unsigned)d.stride;
+#pragma unroll
+    for (int u = 0; u < N; ++u)
+        v[u] = sl_load_stream_at(p, 0u, sl_partial_load_at(sl_partial_exist(d, lr, lc, i0 + u), o0 + (unsigned)(i0 + u) * step, room));
+}
+template <bool ZERO = false, int N>
+SL_DEV void sl_partial_place(const SlChunkDesc &d, int i0, int lane, sl_f4 (&v)[N])
+{
+    const int lr = lane >> 4, lc = (lane & 15) * 4, room = sl_partial_room(d);
+    const unsigned o0 = sl_partial_origin(d, lr, lc, room), step = 16u * (unsigned)d.stride;
     auto exist = [&](int u) -> int { return sl_partial_exist(d, lr, lc, i0 + u); };
     auto place = [&](int u) -> unsigned { return o0 + (unsigned)(i0 + u) * step; };
-#pragma unroll
-    for (int u = 0; u < N; ++u) v[u] = sl_load_stream_at(p, 0u, sl_partial_load_at(exist(u), place(u), room));
     // the four elements from the one that lies `by` places into a load on
     auto moved = [&](sl_f4 w, bool one, bool two) -> sl_f4 {
         const float x0 = one ? w.y : w.x, x1 = one ? w.z : w.y, x2 = one ? w.w : w.z;
@@ -142,6 +149,12 @@ SL_DEV void sl_load_partial(const float *arena, const SlChunkDesc &d, int i0, in
             v[u] = sl_f4{in ? v[u].x : 0.f, in ? v[u].y : 0.f, in ? v[u].z : 0.f, in ? v[u].w : 0.f};
         }
     }
+}
+template <int N, bool ZERO = false>
+SL_DEV void sl_load_partial(const float *arena, const SlChunkDesc &d, int i0, int lane, sl_f4 (&v)[N])
+{
+    sl_partial_request(arena, d, i0, lane, v);
+    sl_partial_place<ZERO>(d, i0, lane, v);
 }
 
 SL_DEV int sl_popc(unsigned long long m) { return __builtin_popcountll(m); }

@@ -136,11 +136,10 @@ __host__ __device__ inline long long sl_lut_off(const SlChunkDesc &d, int hdr_by
     return d.rec_off - hdr_bytes - (long long)d.local_chunk * rec_bytes;
 }
 
-// Chunks (waves) per workgroup of the kernels that give a chunk to a wave: four adjacent ones, so that a workgroup streams
+// Chunks (waves) per workgroup of the aggregates: four adjacent ones, so that a workgroup streams
 // 1 KB of every matrix row it touches; but one on lists so short that workgroups of four, dealt to the compute units in one turn or two,
-// would leave a third of the places without any.  Four / one, us (matrices, R = 4, k = 64): sl_compress, 64 chunks 21.4 / 20.7,
-// 512 23.8 / 23.0, 960 27.8 / 28.3, 1024 27.8 / 28.7, 1280 35.0 / 33.6, 1800 39.2 / 39.4, 3072 51.4 / 54.8, 3840 59.2 / 63.7; plain aggregate
-// 512 8.5 / 8.4, 1280 8.9 / 8.4, 2048 11.1 / 11.8, 3072 20.0 / 21.1; coded 1280 9.8 / 9.4, 3072 19.4 / 21.2.  Not where one chunk in 32 or more is partial: rows then begin anywhere in a line of memory, and the neighbours
+// would leave a third of the places without any.  Four / one, us (matrices, R = 4, k = 64): plain aggregate
+// 512 chunks 8.5 / 8.4, 1280 8.9 / 8.4, 2048 11.1 / 11.8, 3072 20.0 / 21.1; coded 1280 9.8 / 9.4, 3072 19.4 / 21.2.  Not where one chunk in 32 or more is partial: rows then begin anywhere in a line of memory, and the neighbours
 // that share a line should share an L2 (1155 chunks of a 67-column matrix, aggregate of three: 12.6 / 19.7).
 #define SL_COMPUTE_UNITS 256
 inline int sl_chunks_per_group(const sl_plan *p)

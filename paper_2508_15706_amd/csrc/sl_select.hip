@@ -1,4 +1,4 @@
-// Kernel A of sl_compress: error-feedback accumulate fused with the chunk-wise
+// Kernel A of sl_compress (short lists: sl_select_group.hip): error-feedback accumulate fused with the chunk-wise
 // Top-k selection (Eq. (2) line 1 and the Top-k of line 2; Section 3.3 last
 // paragraph for the chunking).
 //
@@ -36,49 +36,16 @@
 
 #include "sl_coded.h"
 #include "sl_search.h"
+#include "sl_select.h"
 
 namespace {
 
 // LDS candidate list of the pruned route, entries of 8 bytes: 512, or 1024 with 16 groups per lane
 constexpr int cand_cap(int gpl) { return gpl == 16 ? 1024 : 512; }
 
-#ifndef SL_SELECT_BOUND_BITS
-#define SL_SELECT_BOUND_BITS 12   // bits of the pruning bound that are decided (0 = all)
-#endif
 #ifndef SL_SELECT_PFE8
 #define SL_SELECT_PFE8 4
 #endif
-
-struct SelectArgs {
-    const SlChunkDesc *desc;
-    float *e;
-    const float *delta;             // the pseudo-gradient, or theta_outer when theta_local is set
-    const float *theta_local;       // non-null: delta = theta_outer - theta_local, formed on the fly
-    const unsigned char *pending;   // payload whose values are still to be subtracted from e
-    float beta;
-    int frozen;
-    int k;
-    int bits, hdr_bytes, rec_bytes; // value width of the payloads and the sizes that follow from it
-    unsigned seed_hash;     // Random-k: fmix32(seed), see random_key
-    int sample_margin;      // select_general: ranks of the sample's bracket, k / 8 -+ this (0: no sample)
-    int lds_per_wave;
-    int pend_off;           // offset of the pending-correction tables in a wave's LDS
-    int pend_words;         // the pending record is staged in LDS as whole words (large k), see pend_half
-    float *vals;            // [n_chunks * k] selected values, canonical order
-    double *leafA;          // [2][n_chunks] per-chunk tree sums of x and x*x
-    unsigned char *payload;
-    long long n_chunks;
-    unsigned order;          // sl_work_group
-    // coded wire format written next to the plain record (null: not wanted): the remainder fields go
-    // to their place in the buffer, the chunk's quotient bit vector and quotient sum to the workspace
-    unsigned char *coded;
-    const SlCodedDesc *cdesc;
-    SlCodedGeom G;
-    unsigned *uvec;
-    unsigned short *qsum;
-};
-
-SL_DEV int key_of(float x) { return (int)(__float_as_uint(x) & 0x7FFFFFFFu); }
 
 // Random-k (the paper's ablation "Random-k vs. Top-k"): every position gets a
 // pseudo-random 31-bit key from a counter-based generator built on the 32-bit
@@ -987,9 +954,10 @@ static int launch_select(const sl_plan *p, float *e, const float *delta, const f
     A.G = p->cg;
     A.uvec = (sub_only || !coded) ? nullptr : reinterpret_cast<unsigned *>(ws + p->ws_uvec);
     A.qsum = (sub_only || !coded) ? nullptr : reinterpret_cast<unsigned short *>(ws + p->ws_qsum);
-    // (one chunk where the LDS of four does not fit; four at high densities, where a wave's time is its instructions: 512 chunks, four /
-    // one, k = 256 29.4 / 29.9 us, k = 1024 53.0 / 54.9, coded 68.3 / 70.1)
-    const int wpb = 4 * (size_t)A.lds_per_wave > 65536 ? 1 : k > 128 ? 4 : sl_chunks_per_group(p);
+    const int waves = random ? 1 : sl_select_waves(p->n_chunks, k);
+    if (waves > 1) return slk_select_group(A, sub_only, waves, st);
+    // (one chunk per workgroup where the LDS of four does not fit)
+    const int wpb = 4 * (size_t)A.lds_per_wave > 65536 ? 1 : random && k <= 128 ? sl_chunks_per_group(p) : 4;
     const dim3 grid((unsigned)((p->n_chunks + wpb - 1) / wpb)), block(64 * wpb);
     A.order = sl_order(p, grid.x);
     const size_t lds = (size_t)A.lds_per_wave * wpb;
