@@ -1,4 +1,4 @@
-// sl_decompress_avg_apply: dequantise R workers' sparse payloads, average and
+// sl_decompress_avg_apply (short lists: sl_apply_group.hip): dequantise R workers' sparse payloads, average and
 // take the outer SGD step in one pass over theta (Algorithm 1, "Aggregate +
 // Outer Update"; Eq. (2) lines 3-4), and the stand-alone record encoder
 // sl_pack_indices (12-bit index fields + 2-bit codes).
@@ -682,6 +682,7 @@ int slk_apply(const sl_plan *p, float *theta, float *mom, float mu, const void *
               float lr, hipStream_t st)
 {
     if (p->n_chunks == 0) return SL_OK;
+    if (const int waves = sl_apply_waves(p, R, false); waves > 1) return slk_apply_group(p, theta, mom, mu, payloads, nullptr, R, lr, waves, st);
     ApplyArgs A;
     A.desc = p->d_desc;
     A.theta = theta;

@@ -1,4 +1,4 @@
-// sl_decompress_avg_apply_coded: the aggregate + outer update (Algorithm 1, "Aggregate + Outer
+// sl_decompress_avg_apply_coded (short lists: sl_apply_group.hip): the aggregate + outer update (Algorithm 1, "Aggregate + Outer
 // Update"; Eq. (2) lines 3-4) over R payloads in the CODED wire format (sl_coded.h; the
 // appendix "Compression of indices in Top-k" is where the index coder enters the method).
 //
@@ -789,6 +789,7 @@ int slk_apply_coded(const sl_plan *p, float *theta, float *mom, float mu, const 
                     int R, float lr, hipStream_t st)
 {
     if (p->n_chunks == 0) return SL_OK;
+    if (const int waves = sl_apply_waves(p, R, true); waves > 1) return slk_apply_group(p, theta, mom, mu, payloads, bytes, R, lr, waves, st);
     CodedApplyArgs A;
     A.G = p->cg;
     A.desc = p->d_desc;

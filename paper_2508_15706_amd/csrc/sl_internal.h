@@ -148,6 +148,24 @@ inline int sl_chunks_per_group(const sl_plan *p)
     return turns <= 2 && 3 * groups <= 2 * SL_COMPUTE_UNITS * turns && p->n_partial * 32 < p->n_chunks ? 1 : 4;
 }
 
+// Waves per chunk of the aggregates: several (sl_apply_group.hip) on short lists with few workers, one else.  With a wave per worker
+// and a list of entries for each the work grows with R, and with k, where the other routes' does less.  One wave and the number taken
+// here, us (in a graph, lr update of full chunks): plain, k = 64, R = 4: 64 chunks 4.4 -> 3.7, 512 5.1 -> 4.5, 1024 9.0 -> 5.8, 2048 16.9 ->
+// 13.6; R = 8 256 5.2 -> 4.5, 1024 9.7 -> 7.1, 2048 17.2 -> 16.1; k = 256, R = 4 512 5.9 -> 5.9, 1024 9.8 -> 7.9; fp32 values, k = 64, R = 3 1024
+// 9.6 -> 5.6; coded, k = 64, R = 4 256 6.9 -> 5.7, 1024 10.5 -> 8.4; R = 8 256 7.1 -> 6.3.  Beyond the lines: plain, k = 512, R = 3 256 5.7 -> 7.1; k =
+// 16, R = 16 512 7.1 -> 7.4; 4096, k = 64, R = 4 24.2 -> 24.8; 1155 chunks of 67 columns 9.0 -> 9.1 (900 of 530 columns 10.7 -> 9.5); coded, k = 64, R =
+// 8 1024 11.0 -> 11.1; k = 256, R = 4 256 7.0 -> 8.3; 2048, R = 4 16.5 -> 16.2, k = 128 16.5 -> 18.3.
+inline int sl_apply_waves(const sl_plan *p, int R, bool coded)
+{
+    const int64_t n = p->n_chunks;
+    const int k = p->k;
+    if (coded) return k > 128 ? 1 : n <= 256 && R <= 8 ? 8 : n <= 1024 && R <= 4 ? 4 : 1;
+    if (k > 256 || R > 8) return 1;
+    if (n <= 512) return 8;
+    if (n <= 1024) return 4;
+    return R * k <= 1024 && n <= (p->n_partial * 32 >= n ? 1280 : 2048) ? 4 : 1;
+}
+
 // sl_work_group's `order` for a grid of so many groups.  Where a list has many partial chunks - the last column of a
 // matrix's tiles: one group in every few - the slow groups would all come to one or two of the XCDs, so the groups
 // are turned (columns 1000 and 2730, a chunk in 25 partial, plain aggregate of 8: list order 475, paired 488, turned 471 us;
@@ -242,5 +260,8 @@ int slk_coded_place(const sl_plan *p, unsigned char *out, unsigned char *ws, boo
 // theta update from R coded payloads (mom != null: with the global momentum)
 int slk_apply_coded(const sl_plan *p, float *theta, float *mom, float mu, const void *const *payloads, const size_t *bytes,
                     int R, float lr, hipStream_t st);
+// either of them with several waves per chunk (bytes != null: coded payloads)
+int slk_apply_group(const sl_plan *p, float *theta, float *mom, float mu, const void *const *payloads, const size_t *bytes, int R, float lr,
+                    int waves, hipStream_t st);
 int sl_rice_param(int k);
 void sl_note_hip_error(hipError_t e);
