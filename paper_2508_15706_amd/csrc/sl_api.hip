@@ -70,7 +70,7 @@ int sl_plan_create_bits(const sl_tensor *tensors, int n_tensors, int k, int valu
     std::vector<SlChunkDesc> desc;
     std::vector<SlTensorDev> tdev;
     std::vector<SlGroup> groups;
-    int64_t n_elements = 0, n_partial = 0;
+    int64_t n_elements = 0, n_partial = 0, n_unaligned = 0;
     size_t pay = 0;
 
     // tensors must not overlap: results would depend on processing order
@@ -152,7 +152,10 @@ int sl_plan_create_bits(const sl_tensor *tensors, int n_tensors, int k, int valu
     } catch (const std::bad_alloc &) {
         return SL_ERR_NOMEM;
     }
-    for (const SlChunkDesc &d : desc) n_partial += !(d.flags & SLC_FULL);
+    for (const SlChunkDesc &d : desc) {
+        n_partial += !(d.flags & SLC_FULL);
+        n_unaligned += ((d.base | d.stride) & 15) != 0;
+    }
 
     sl_plan *p = new (std::nothrow) sl_plan();
     if (!p) return SL_ERR_NOMEM;
@@ -165,6 +168,7 @@ int sl_plan_create_bits(const sl_tensor *tensors, int n_tensors, int k, int valu
     p->n_chunks = (int64_t)desc.size();
     p->n_elements = n_elements;
     p->n_partial = n_partial;
+    p->n_unaligned = n_unaligned;
     for (const SlTensorDev &D : tdev) p->max_tensor_chunks = std::max<int64_t>(p->max_tensor_chunks, D.n_chunks);
     for (int64_t c = 0, per_wave = 64 >> sl_code_lanes_log2(k); c < p->n_chunks; c += per_wave) {
         const SlChunkDesc &last = desc[(size_t)std::min<int64_t>(c + per_wave, p->n_chunks) - 1];

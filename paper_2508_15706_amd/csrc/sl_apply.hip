@@ -97,7 +97,8 @@ struct ApplyArgs {
 //      instructions per word and a trip to memory per batch (123,505 chunks, k = 1024, R = 8: 1363 us, direct
 //      1024; 24,000 chunks, k = 512, R = 16: 289 and 223).
 // The routes are separate instantiations, so that none pays for another's registers.
-template <bool TWO_BIT, bool NESTEROV, int NH, int ROUTE>
+// KEEP: the arenas' accesses without the streaming hint (sl_rows_unaligned).
+template <bool TWO_BIT, bool NESTEROV, int NH, int ROUTE, bool KEEP>
 __global__ void __launch_bounds__(256) k_apply(ApplyArgs A)
 {
     constexpr bool SMALLK = ROUTE == 0, OCTETS = ROUTE == 2, DIRECT = OCTETS && TWO_BIT;
@@ -229,15 +230,15 @@ __global__ void __launch_bounds__(256) k_apply(ApplyArgs A)
     if (full) {
         const unsigned o0 = lane_at, step = 16u * stride;
 #pragma unroll
-        for (int i = 0; i < 16; ++i) th[i] = sl_load_stream_at(tc, i * step, o0);
+        for (int i = 0; i < 16; ++i) th[i] = sl_load_stream_at<KEEP>(tc, i * step, o0);
         if constexpr (NESTEROV) {
 #pragma unroll
-            for (int i = 0; i < 16; ++i) mo[i] = sl_load_stream_at(mc, i * step, o0);
+            for (int i = 0; i < 16; ++i) mo[i] = sl_load_stream_at<KEEP>(mc, i * step, o0);
         }
     } else {
         // (rows need no alignment)
-        sl_load_partial(A.theta, d, 0, lane, th);
-        if constexpr (NESTEROV) sl_load_partial(A.mom, d, 0, lane, mo);
+        sl_load_partial<16, false, KEEP>(A.theta, d, 0, lane, th);
+        if constexpr (NESTEROV) sl_load_partial<16, false, KEEP>(A.mom, d, 0, lane, mo);
     }
 
     const bool single = A.R <= A.batch;      // every record fits the staging area at once
@@ -441,7 +442,7 @@ __global__ void __launch_bounds__(256) k_apply(ApplyArgs A)
                     sl_f4 m = mo[i];
                     m.x = fmaf(A.mu, m.x, g.x), m.y = fmaf(A.mu, m.y, g.y);
                     m.z = fmaf(A.mu, m.z, g.z), m.w = fmaf(A.mu, m.w, g.w);
-                    sl_store_stream_at(mc, i * step, o0, m);
+                    sl_store_stream_at<KEEP>(mc, i * step, o0, m);
                     g.x = fmaf(A.mu, m.x, g.x), g.y = fmaf(A.mu, m.y, g.y);
                     g.z = fmaf(A.mu, m.z, g.z), g.w = fmaf(A.mu, m.w, g.w);
                 }
@@ -450,7 +451,7 @@ __global__ void __launch_bounds__(256) k_apply(ApplyArgs A)
                 v.y = fmaf(A.neg_lr, g.y, v.y);
                 v.z = fmaf(A.neg_lr, g.z, v.z);
                 v.w = fmaf(A.neg_lr, g.w, v.w);
-                sl_store_stream_at(tc, i * step, o0, v);
+                sl_store_stream_at<KEEP>(tc, i * step, o0, v);
             }
         } else {
             const int rows = d.rows, cols = d.cols, last_cols = d.last_cols;
@@ -474,8 +475,8 @@ __global__ void __launch_bounds__(256) k_apply(ApplyArgs A)
                 v.x = fmaf(A.neg_lr, g.x, v.x), v.y = fmaf(A.neg_lr, g.y, v.y);
                 v.z = fmaf(A.neg_lr, g.z, v.z), v.w = fmaf(A.neg_lr, g.w, v.w);
                 if (lc + 3 < lim) {
-                    if constexpr (NESTEROV) sl_store_stream_u(mc + o0, m);
-                    sl_store_stream_u(tc + o0, v);
+                    if constexpr (NESTEROV) sl_store_stream_u<KEEP>(mc + o0, m);
+                    sl_store_stream_u<KEEP>(tc + o0, v);
                 } else {
 #pragma unroll
                     for (int cc = 0; cc < 4; ++cc)
@@ -729,12 +730,14 @@ int slk_apply(const sl_plan *p, float *theta, float *mom, float mu, const void *
     const bool two = p->bits == 2;
     typedef void (*kernel_t)(ApplyArgs);
     const int route = octets ? 2 : (!halves && p->k <= 128) ? 0 : 1;
-#define SL_APPLY_ROUTES(TWO, NEST) \
-    {k_apply<TWO, NEST, 1, 0>, k_apply<TWO, NEST, 1, 1>, k_apply<TWO, NEST, 1, 2>, k_apply<TWO, NEST, 2, 1>}
-    static const kernel_t table[2][2][4] = {{SL_APPLY_ROUTES(false, false), SL_APPLY_ROUTES(false, true)},
-                                            {SL_APPLY_ROUTES(true, false), SL_APPLY_ROUTES(true, true)}};
+#define SL_APPLY_ROUTES(TWO, NEST, KEEP) \
+    {k_apply<TWO, NEST, 1, 0, KEEP>, k_apply<TWO, NEST, 1, 1, KEEP>, k_apply<TWO, NEST, 1, 2, KEEP>, k_apply<TWO, NEST, 2, 1, KEEP>}
+#define SL_APPLY_KINDS(KEEP) \
+    {{SL_APPLY_ROUTES(false, false, KEEP), SL_APPLY_ROUTES(false, true, KEEP)}, {SL_APPLY_ROUTES(true, false, KEEP), SL_APPLY_ROUTES(true, true, KEEP)}}
+    static const kernel_t table[2][2][2][4] = {SL_APPLY_KINDS(false), SL_APPLY_KINDS(true)};
+#undef SL_APPLY_KINDS
 #undef SL_APPLY_ROUTES
-    const kernel_t fn = table[two ? 1 : 0][mom ? 1 : 0][halves ? 3 : route];   // (two halves: entry by entry only)
+    const kernel_t fn = table[sl_rows_unaligned(p) ? 1 : 0][two ? 1 : 0][mom ? 1 : 0][halves ? 3 : route];   // (two halves: entry by entry only)
     if (lds > 65536) {
         hipError_t aerr = hipFuncSetAttribute(reinterpret_cast<const void *>(fn),
                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);

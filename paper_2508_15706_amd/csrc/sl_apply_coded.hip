@@ -75,7 +75,8 @@ SL_DEV void acc_add(float *acc, unsigned j, float q) { acc[j] = acc[j] + q; }
 
 // NESTEROV: with DiLoCo's global Nesterov momentum (Eq. (1)).
 // LISTS (few entries): steps 3 to 5 go through index lists in LDS, see the top of the file.
-template <bool TWO_BIT, bool NESTEROV, bool LISTS>
+// KEEP: the arenas' accesses without the streaming hint (sl_rows_unaligned).
+template <bool TWO_BIT, bool NESTEROV, bool LISTS, bool KEEP>
 __global__ void __launch_bounds__(256) k_apply_coded(CodedApplyArgs A)
 {
     extern __shared__ __align__(16) unsigned char smem_all[];
@@ -190,15 +191,15 @@ __global__ void __launch_bounds__(256) k_apply_coded(CodedApplyArgs A)
         const float *ts = full ? tc : none, *ms = (NESTEROV && full) ? mc : none;
         const unsigned o0 = full ? 4u * (lr * stride + lc) : 0u, step = full ? 16u * stride : 0u;
 #pragma unroll
-        for (int i = 0; i < 16; ++i) th[i] = sl_load_stream_at(ts, i * step, o0);
+        for (int i = 0; i < 16; ++i) th[i] = sl_load_stream_at<KEEP>(ts, i * step, o0);
         if constexpr (NESTEROV) {
 #pragma unroll
-            for (int i = 0; i < 16; ++i) mo[i] = sl_load_stream_at(ms, i * step, o0);
+            for (int i = 0; i < 16; ++i) mo[i] = sl_load_stream_at<KEEP>(ms, i * step, o0);
         }
     }
     if (!full) {
-        sl_load_partial(A.theta, d, 0, lane, th);
-        if constexpr (NESTEROV) sl_load_partial(A.mom, d, 0, lane, mo);
+        sl_load_partial<16, false, KEEP>(A.theta, d, 0, lane, th);
+        if constexpr (NESTEROV) sl_load_partial<16, false, KEEP>(A.mom, d, 0, lane, mo);
         // (waited for here: loads of this block in flight behind it would be counted by the wait in front of the staged words
         // on full chunks too: 24,000 of them, k = 256, R = 16, 238 us without this, 229 with it)
         __builtin_amdgcn_s_waitcnt(0x0F70);                  // vmcnt(0)
@@ -728,7 +729,7 @@ __global__ void __launch_bounds__(256) k_apply_coded(CodedApplyArgs A)
                 sl_f4 m = mo[i];
                 m.x = fmaf(A.mu, m.x, g.x), m.y = fmaf(A.mu, m.y, g.y);
                 m.z = fmaf(A.mu, m.z, g.z), m.w = fmaf(A.mu, m.w, g.w);
-                sl_store_stream_at(mc, i * step, o0, m);
+                sl_store_stream_at<KEEP>(mc, i * step, o0, m);
                 g.x = fmaf(A.mu, m.x, g.x), g.y = fmaf(A.mu, m.y, g.y);
                 g.z = fmaf(A.mu, m.z, g.z), g.w = fmaf(A.mu, m.w, g.w);
             }
@@ -737,7 +738,7 @@ __global__ void __launch_bounds__(256) k_apply_coded(CodedApplyArgs A)
             v.y = fmaf(A.neg_lr, g.y, v.y);
             v.z = fmaf(A.neg_lr, g.z, v.z);
             v.w = fmaf(A.neg_lr, g.w, v.w);
-            sl_store_stream_at(tc, i * step, o0, v);
+            sl_store_stream_at<KEEP>(tc, i * step, o0, v);
         }
     } else {
         const int rows = d.rows, cols = d.cols, last_cols = d.last_cols;
@@ -761,8 +762,8 @@ __global__ void __launch_bounds__(256) k_apply_coded(CodedApplyArgs A)
             v.x = fmaf(A.neg_lr, g.x, v.x), v.y = fmaf(A.neg_lr, g.y, v.y);
             v.z = fmaf(A.neg_lr, g.z, v.z), v.w = fmaf(A.neg_lr, g.w, v.w);
             if (lc + 3 < lim) {
-                if constexpr (NESTEROV) sl_store_stream_u(mc + o0, m);
-                sl_store_stream_u(tc + o0, v);
+                if constexpr (NESTEROV) sl_store_stream_u<KEEP>(mc + o0, m);
+                sl_store_stream_u<KEEP>(tc + o0, v);
             } else {
 #pragma unroll
                 for (int cc = 0; cc < 4; ++cc)
@@ -851,12 +852,14 @@ int slk_apply_coded(const sl_plan *p, float *theta, float *mom, float mu, const 
     while (wpb > 1 && (size_t)A.lds_per_wave * wpb > (size_t)p->max_lds) wpb >>= 1;
     const size_t lds = (size_t)A.lds_per_wave * wpb;
     typedef void (*kernel_t)(CodedApplyArgs);
-    static const kernel_t table[2][2][2] = {
-        {{k_apply_coded<false, false, false>, k_apply_coded<false, true, false>},
-         {k_apply_coded<false, false, true>, k_apply_coded<false, true, true>}},
-        {{k_apply_coded<true, false, false>, k_apply_coded<true, true, false>},
-         {k_apply_coded<true, false, true>, k_apply_coded<true, true, true>}}};
-    const kernel_t fn = table[p->bits == 2 ? 1 : 0][lists ? 1 : 0][mom ? 1 : 0];
+#define SL_CAPPLY_KINDS(KEEP)                                                                             \
+    {{{k_apply_coded<false, false, false, KEEP>, k_apply_coded<false, true, false, KEEP>},                   \
+      {k_apply_coded<false, false, true, KEEP>, k_apply_coded<false, true, true, KEEP>}},                    \
+     {{k_apply_coded<true, false, false, KEEP>, k_apply_coded<true, true, false, KEEP>},                     \
+      {k_apply_coded<true, false, true, KEEP>, k_apply_coded<true, true, true, KEEP>}}}
+    static const kernel_t table[2][2][2][2] = {SL_CAPPLY_KINDS(false), SL_CAPPLY_KINDS(true)};
+#undef SL_CAPPLY_KINDS
+    const kernel_t fn = table[sl_rows_unaligned(p) ? 1 : 0][p->bits == 2 ? 1 : 0][lists ? 1 : 0][mom ? 1 : 0];
     if (lds > 65536) {
         hipError_t aerr = hipFuncSetAttribute(reinterpret_cast<const void *>(fn),
                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);

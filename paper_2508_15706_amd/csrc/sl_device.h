@@ -47,36 +47,61 @@ SL_DEV void sl_store_stream(float *p, sl_f4 v)
     __builtin_nontemporal_store(v, reinterpret_cast<sl_f4 *>(p));
 }
 
+// KEEP: without the streaming hint, for rows that do not begin on a 64-byte piece of memory.  The pieces that two tiles share - one in
+// four or five of each - are read and written by two waves; a streamed piece is given up between the two, so that it is read twice and,
+// worse, written back in parts that the memory has to merge (24,576 chunks, us, streamed / kept: 1001 columns, aggregate 241 / 161, of
+// coded payloads 223 / 178, direction 445 / 377, two directions averaged 388 / 314, accumulate 304 / 285; 1000 columns 194 / 157, 189 / 167,
+// 379 / 358, 351 / 309, 297 / 295; 127 columns 257 / 180, 259 / 206, 552 / 440, 435 / 350, 367 / 324).  Aligned rows want the hint: 1024
+// columns 132 / 146, 132 / 144, 270 / 299, 264 / 292, 226 / 254; 1008 columns (64-byte rows) 149 / 155, 158 / 167, 311 / 339, 303 / 308, 263 / 291.  So do
+// reads alone (Sub-k, 1001 columns 132 / 139).  Kept loads with streamed stores lie in between.
+template <bool KEEP>
+SL_DEV sl_f4 sl_access_load(const sl_f4u *p)
+{
+    if constexpr (KEEP) return *p;
+    else return __builtin_nontemporal_load(p);
+}
+template <bool KEEP>
+SL_DEV void sl_access_store(sl_f4u *p, sl_f4 v)
+{
+    if constexpr (KEEP) *p = v;
+    else __builtin_nontemporal_store(v, p);
+}
+
 // (`row_off` is a wave-uniform byte offset and goes into the scalar base, so
 // that all accesses of a chunk share the single vector offset `lane_off`.)
+template <bool KEEP = false>
 SL_DEV sl_f4 sl_load_stream_at(const float *base, unsigned row_off, unsigned lane_off)
 {
     const char *row = reinterpret_cast<const char *>(base) + row_off;
-    return __builtin_nontemporal_load(reinterpret_cast<const sl_f4u *>(row + lane_off));
+    return sl_access_load<KEEP>(reinterpret_cast<const sl_f4u *>(row + lane_off));
 }
+template <bool KEEP = false>
 SL_DEV void sl_store_stream_at(float *base, unsigned row_off, unsigned lane_off, sl_f4 v)
 {
     char *row = reinterpret_cast<char *>(base) + row_off;
-    __builtin_nontemporal_store(v, reinterpret_cast<sl_f4u *>(row + lane_off));
+    sl_access_store<KEEP>(reinterpret_cast<sl_f4u *>(row + lane_off), v);
 }
 
 // 16-byte streaming accesses at an address that is only 4-byte aligned.
+template <bool KEEP = false>
 SL_DEV sl_f4 sl_load_stream_u(const float *p)
 {
-    return __builtin_nontemporal_load(reinterpret_cast<const sl_f4u *>(p));
+    return sl_access_load<KEEP>(reinterpret_cast<const sl_f4u *>(p));
 }
+template <bool KEEP = false>
 SL_DEV void sl_store_stream_u(float *p, sl_f4 v)
 {
-    __builtin_nontemporal_store(v, reinterpret_cast<sl_f4u *>(p));
+    sl_access_store<KEEP>(reinterpret_cast<sl_f4u *>(p), v);
 }
 
 // Four elements at p of which `n` exist (any n; none below 1): one access where all four do, else element by
 // element; what does not exist is read as +0.0f and not written.
+template <bool KEEP = false>
 SL_DEV sl_f4 sl_load_edge(const float *p, int n)
 {
     sl_f4 v = sl_f4{0.f, 0.f, 0.f, 0.f};
     if (n >= 4) {
-        v = sl_load_stream_u(p);
+        v = sl_load_stream_u<KEEP>(p);
     } else {
 #pragma unroll
         for (int cc = 0; cc < 4; ++cc)
@@ -84,10 +109,11 @@ SL_DEV sl_f4 sl_load_edge(const float *p, int n)
     }
     return v;
 }
+template <bool KEEP = false>
 SL_DEV void sl_store_edge(float *p, int n, sl_f4 v)
 {
     if (n >= 4) {
-        sl_store_stream_u(p, v);
+        sl_store_stream_u<KEEP>(p, v);
     } else {
 #pragma unroll
         for (int cc = 0; cc < 4; ++cc)
@@ -103,7 +129,7 @@ SL_DEV void sl_store_edge(float *p, int n, sl_f4 v)
 // chunks; with momentum 2000 chunks of 100 columns are 4 % slower, all others faster).
 // Where the edge cuts through a lane's columns, the load ends with the row's last element (sl_partial_load_at) and its elements are
 // moved into place afterwards.
-template <int N>
+template <bool KEEP = false, int N>
 SL_DEV void sl_partial_request(const float *arena, const SlChunkDesc &d, int i0, int lane, sl_f4 (&v)[N])
 {
     const int lr = lane >> 4, lc = (lane & 15) * 4, room = sl_partial_room(d);
@@ -111,7 +137,7 @@ SL_DEV void sl_partial_request(const float *arena, const SlChunkDesc &d, int i0,
     const unsigned o0 = sl_partial_origin(d, lr, lc, room), step = 16u * (unsigned)d.stride;
 #pragma unroll
     for (int u = 0; u < N; ++u)
-        v[u] = sl_load_stream_at(p, 0u, sl_partial_load_at(sl_partial_exist(d, lr, lc, i0 + u), o0 + (unsigned)(i0 + u) * step, room));
+        v[u] = sl_load_stream_at<KEEP>(p, 0u, sl_partial_load_at(sl_partial_exist(d, lr, lc, i0 + u), o0 + (unsigned)(i0 + u) * step, room));
 }
 template <bool ZERO = false, int N>
 SL_DEV void sl_partial_place(const SlChunkDesc &d, int i0, int lane, sl_f4 (&v)[N])
@@ -150,10 +176,10 @@ SL_DEV void sl_partial_place(const SlChunkDesc &d, int i0, int lane, sl_f4 (&v)[
         }
     }
 }
-template <int N, bool ZERO = false>
+template <int N, bool ZERO = false, bool KEEP = false>
 SL_DEV void sl_load_partial(const float *arena, const SlChunkDesc &d, int i0, int lane, sl_f4 (&v)[N])
 {
-    sl_partial_request(arena, d, i0, lane, v);
+    sl_partial_request<KEEP>(arena, d, i0, lane, v);
     sl_partial_place<ZERO>(d, i0, lane, v);
 }
 

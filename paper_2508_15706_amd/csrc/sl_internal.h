@@ -99,6 +99,7 @@ struct sl_plan {
     int64_t n_chunks;
     int64_t n_elements;
     int64_t n_partial;          // chunks without SLC_FULL
+    int64_t n_unaligned;        // chunks whose rows do not all begin on a multiple of 16 elements
     int64_t max_tensor_chunks;  // chunks of the tensor that has most
     int max_wave_tensors;       // tensors that a wave of the code kernel meets among its chunks, at most
     size_t payload_bytes;
@@ -147,6 +148,10 @@ inline int sl_chunks_per_group(const sl_plan *p)
     const int64_t groups = (p->n_chunks + 3) / 4, turns = (groups + SL_COMPUTE_UNITS - 1) / SL_COMPUTE_UNITS;
     return turns <= 2 && 3 * groups <= 2 * SL_COMPUTE_UNITS * turns && p->n_partial * 32 < p->n_chunks ? 1 : 4;
 }
+
+// Do the accesses of this list go without the streaming hint (sl_access_load)?  Unaligned rows lose up to half with it, aligned ones a tenth
+// without: from a quarter of the chunks on.  (Arenas that do not begin on 64 bytes are not looked at.)
+inline bool sl_rows_unaligned(const sl_plan *p) { return 4 * p->n_unaligned >= p->n_chunks; }
 
 // Waves per chunk of the aggregates: several (sl_apply_group.hip) on short lists with few workers, one else.  With a wave per worker
 // and a list of entries for each the work grows with R, and with k, where the other routes' does less.  One wave and the number taken

@@ -46,6 +46,8 @@ struct LomArgs {
     unsigned order;          // sl_work_group
 };
 
+// KEEP: without the streaming hint (sl_rows_unaligned).
+template <bool KEEP>
 __global__ void __launch_bounds__(256) k_lom_direction(LomArgs A)
 {
     const int lane = threadIdx.x & 63;
@@ -65,9 +67,9 @@ __global__ void __launch_bounds__(256) k_lom_direction(LomArgs A)
         for (int q = 0; q < 16 / S; ++q) {
             sl_f4 mv[S], dv[S];
 #pragma unroll
-            for (int u = 0; u < S; ++u) mv[u] = sl_load_stream_at(mc, (S * q + u) * step, o0);
+            for (int u = 0; u < S; ++u) mv[u] = sl_load_stream_at<KEEP>(mc, (S * q + u) * step, o0);
 #pragma unroll
-            for (int u = 0; u < S; ++u) dv[u] = sl_load_stream_at(dc, (S * q + u) * step, o0);
+            for (int u = 0; u < S; ++u) dv[u] = sl_load_stream_at<KEEP>(dc, (S * q + u) * step, o0);
 #pragma unroll
             for (int u = 0; u < S; ++u) {
                 sl_f4 m = mv[u], g = dv[u], o;
@@ -75,8 +77,8 @@ __global__ void __launch_bounds__(256) k_lom_direction(LomArgs A)
                 m.z = fmaf(A.mu, m.z, g.z), m.w = fmaf(A.mu, m.w, g.w);
                 o.x = fmaf(A.mu, m.x, g.x), o.y = fmaf(A.mu, m.y, g.y);
                 o.z = fmaf(A.mu, m.z, g.z), o.w = fmaf(A.mu, m.w, g.w);
-                sl_store_stream_at(mc, (S * q + u) * step, o0, m);
-                sl_store_stream_at(oc, (S * q + u) * step, o0, o);
+                sl_store_stream_at<KEEP>(mc, (S * q + u) * step, o0, m);
+                sl_store_stream_at<KEEP>(oc, (S * q + u) * step, o0, o);
             }
         }
     } else {
@@ -85,8 +87,8 @@ __global__ void __launch_bounds__(256) k_lom_direction(LomArgs A)
 #pragma unroll
         for (int q = 0; q < 16 / S; ++q) {
             sl_f4 mv[S], dv[S];
-            sl_load_partial(A.m, d, S * q, lane, mv);
-            sl_load_partial(A.delta, d, S * q, lane, dv);
+            sl_load_partial<S, false, KEEP>(A.m, d, S * q, lane, mv);
+            sl_load_partial<S, false, KEEP>(A.delta, d, S * q, lane, dv);
 #pragma unroll
             for (int u = 0; u < S; ++u) {
                 const int row = 4 * (S * q + u) + lr, n = (row < rows - 1 ? cols : row == rows - 1 ? last_cols : 0) - lc;
@@ -95,8 +97,8 @@ __global__ void __launch_bounds__(256) k_lom_direction(LomArgs A)
                 m.z = fmaf(A.mu, m.z, g.z), m.w = fmaf(A.mu, m.w, g.w);
                 o.x = fmaf(A.mu, m.x, g.x), o.y = fmaf(A.mu, m.y, g.y);
                 o.z = fmaf(A.mu, m.z, g.z), o.w = fmaf(A.mu, m.w, g.w);
-                sl_store_edge(mc + (row * stride + lc), n, m);
-                sl_store_edge(oc + (row * stride + lc), n, o);
+                sl_store_edge<KEEP>(mc + (row * stride + lc), n, m);
+                sl_store_edge<KEEP>(oc + (row * stride + lc), n, o);
             }
         }
     }
@@ -120,7 +122,7 @@ struct DenseArgs {
 // 100 19.0 / 20.0, 200 x 530 15.4 / 16.2): the loads of their partial chunks come one by one, and neighbours that share lines should
 // meet.  The line lies between the two.
 #define SL_DENSE_SHORT_BELOW 5120
-template <bool NESTEROV, bool SHORT>
+template <bool NESTEROV, bool SHORT, bool KEEP>
 __global__ void __launch_bounds__(256) k_dense_avg_apply(DenseArgs A)
 {
     const int lane = threadIdx.x & 63;
@@ -146,10 +148,10 @@ __global__ void __launch_bounds__(256) k_dense_avg_apply(DenseArgs A)
         auto load = [&](const float *p, sl_f4 (&v)[S]) __attribute__((always_inline)) {
             if (full) {
 #pragma unroll
-                for (int u = 0; u < S; ++u) v[u] = sl_load_stream_at(p, (S * q + u) * step, o0);
+                for (int u = 0; u < S; ++u) v[u] = sl_load_stream_at<KEEP>(p, (S * q + u) * step, o0);
             } else {
 #pragma unroll
-                for (int u = 0; u < S; ++u) v[u] = sl_load_edge(p + ((4 * (S * q + u) + lr) * stride + lc), exist(u));
+                for (int u = 0; u < S; ++u) v[u] = sl_load_edge<KEEP>(p + ((4 * (S * q + u) + lr) * stride + lc), exist(u));
             }
         };
         sl_f4 th[S], mo[NESTEROV ? S : 1], acc[S];
@@ -167,8 +169,8 @@ __global__ void __launch_bounds__(256) k_dense_avg_apply(DenseArgs A)
 #pragma unroll
         for (int u = 0; u < S; ++u) {
             auto store = [&](float *p, sl_f4 v) __attribute__((always_inline)) {
-                if (full) sl_store_stream_at(p, (S * q + u) * step, o0, v);
-                else sl_store_edge(p + ((4 * (S * q + u) + lr) * stride + lc), exist(u), v);
+                if (full) sl_store_stream_at<KEEP>(p, (S * q + u) * step, o0, v);
+                else sl_store_edge<KEEP>(p + ((4 * (S * q + u) + lr) * stride + lc), exist(u), v);
             };
             sl_f4 g = acc[u] * A.inv_R;
             if constexpr (NESTEROV) {
@@ -218,7 +220,7 @@ int slk_lom_direction(const sl_plan *p, float *m, const float *delta, float mu, 
     A.n_chunks = p->n_chunks;
     const dim3 grid((unsigned)((p->n_chunks + 3) / 4)), block(256);
     A.order = sl_order(p, grid.x);
-    hipLaunchKernelGGL(k_lom_direction, grid, block, SL_STREAM_LDS, st, A);
+    hipLaunchKernelGGL(sl_rows_unaligned(p) ? k_lom_direction<true> : k_lom_direction<false>, grid, block, SL_STREAM_LDS, st, A);
     return check_launch();
 }
 
@@ -239,7 +241,11 @@ int slk_dense_avg_apply(const sl_plan *p, float *theta, float *mom, const float 
     const dim3 grid((unsigned)((p->n_chunks + 3) / 4)), block(256);
     A.order = sl_order(p, grid.x);
     const bool is_short = p->n_chunks < SL_DENSE_SHORT_BELOW && p->n_partial * 32 < p->n_chunks;
-    if (is_short) hipLaunchKernelGGL((mom ? k_dense_avg_apply<true, true> : k_dense_avg_apply<false, true>), grid, block, SL_STREAM_LDS, st, A);
-    else hipLaunchKernelGGL((mom ? k_dense_avg_apply<true, false> : k_dense_avg_apply<false, false>), grid, block, SL_STREAM_LDS, st, A);
+    typedef void (*kernel_t)(DenseArgs);
+#define SL_DENSE_KINDS(KEEP) {{k_dense_avg_apply<false, false, KEEP>, k_dense_avg_apply<false, true, KEEP>}, \
+                              {k_dense_avg_apply<true, false, KEEP>, k_dense_avg_apply<true, true, KEEP>}}
+    static const kernel_t table[2][2][2] = {SL_DENSE_KINDS(false), SL_DENSE_KINDS(true)};
+#undef SL_DENSE_KINDS
+    hipLaunchKernelGGL(table[sl_rows_unaligned(p) ? 1 : 0][mom ? 1 : 0][is_short ? 1 : 0], grid, block, SL_STREAM_LDS, st, A);
     return check_launch();
 }

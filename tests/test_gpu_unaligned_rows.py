@@ -1,0 +1,81 @@
+"""Long lists of matrices whose rows begin anywhere (their kernels go without the streaming hint, one wave per chunk), with
+last columns of every remainder, and lists in which a quarter of the chunks, or one chunk less, are such: accumulate (eager, deferred
+with a pending record, from parameters), both aggregates with and without momentum, the dense steps, against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+# (k, value bits, workers, shapes)
+CASES = [(16, 2, 3, [(64 * 100, 64 * 63 + 1, 1)]), (64, 4, 2, [(64 * 99 + 30, 64 * 63 + 2, 1), (1, 4096 * 3 + 66, 0)]),
+         (32, 2, 9, [(64 * 3100, 67, 1), (66, 131, 1)]), (128, 32, 2, [(64 * 98 + 5, 64 * 63 + 30, 1)]), (200, 2, 12, [(64 * 40, 64 * 63 + 5, 1)]),
+         (264, 1, 2, [(64 * 30, 64 * 31 + 10, 1)]), (520, 2, 8, [(64 * 55, 64 * 63 + 9, 1)]), (256, 3, 2, [(64 * 45, 64 * 63 + 20, 1)]),
+         (64, 2, 2, [(64, 64 * 1575 + 1, 1), (64 * 4728, 64, 1)]), (64, 2, 2, [(64, 64 * 1575 + 1, 1), (64 * 4729, 64, 1)])]
+
+
+@pytest.mark.parametrize("case", range(len(CASES)))
+def test_unaligned_rows(oracle, case):
+    from paper_2508_15706_amd import binding as sl
+    k, bits, R, shapes = CASES[case]
+    descs, n = [], 0
+    for r, c, lay in shapes:
+        descs.append((r, c, n, lay))
+        n += (r * c + 63) // 64 * 64
+    if any((r * c % 4096 or 4096) < k if lay == 0 else (r % 64 or 64) * (c % 64 or 64) < k for r, c, _, lay in descs):
+        descs = [(r - r % 64, c, o, lay) if lay else (r, c - c % 4096, o, lay) for r, c, o, lay in descs]
+    gen = torch.Generator(device="cuda").manual_seed(case)
+    new = lambda s: torch.empty(n, device="cuda").normal_(0, s, generator=gen)  # noqa: E731
+    host = lambda x: x.cpu().numpy()  # noqa: E731
+    same = lambda got, want, what: np.testing.assert_array_equal(host(got).view(np.uint32), want.view(np.uint32), what)  # noqa: E731
+    plan = sl.sl_plan_create_bits(descs, k, bits)
+    ws, pay, pay2, wire = sl.alloc_workspace(plan), sl.alloc_payload(plan), sl.alloc_payload(plan), sl.alloc_coded(plan)
+    e, d0, d1 = new(1e-3), new(1e-3), new(1e-3)
+    e_ref, start = host(e), e.clone()
+    sl.sl_compress(plan, e, d0, 0.95, pay, ws, flags=sl.SL_COMPRESS_DEFER_RESIDUAL)
+    ref = oracle.compress_b(descs, k, bits, e_ref, host(d0), 0.95)
+    assert np.array_equal(host(pay)[:plan.payload_bytes], ref)
+    sl.sl_compress_coded(plan, e, d1, 0.95, pay2, wire, ws, flags=sl.SL_COMPRESS_DEFER_RESIDUAL, pending=pay)
+    ref2 = oracle.compress_b(descs, k, bits, e_ref, host(d1), 0.95)
+    assert np.array_equal(host(pay2)[:plan.payload_bytes], ref2)
+    assert np.array_equal(host(wire)[:sl.coded_size(wire)], oracle.rice_encode_b(descs, k, bits, ref2))
+    sl.sl_residual_apply(plan, e, pay2)
+    same(e, e_ref, "e")
+    e.copy_(start)
+    e_ref, outer = host(start), new(0.02)
+    local = outer - d1
+    sl.sl_compress_params(plan, e, outer, local, 0.95, pay, ws)
+    ref = oracle.compress_b(descs, k, bits, e_ref, host(outer) - host(local), 0.95)
+    assert np.array_equal(host(pay)[:plan.payload_bytes], ref)
+    same(e, e_ref, "e of parameters")
+    # aggregates of the two payloads in turn
+    pays, refs = [pay if r % 2 else pay2 for r in range(R)], [ref if r % 2 else ref2 for r in range(R)]
+    wire2 = sl.alloc_coded(plan)
+    sl.sl_rice_encode(plan, pay, wire2, ws)
+    wires = [wire2 if r % 2 else wire for r in range(R)]
+    sizes = [w.numel() for w in wires]
+    theta0, m0 = new(0.02), new(1e-3)
+    want, want_n, want_m = host(theta0), host(theta0), host(m0)
+    oracle.decompress_avg_apply_b(descs, k, bits, want, refs, 0.8)
+    oracle.decompress_avg_apply_nesterov_b(descs, k, bits, want_n, want_m, refs, 0.8, 0.9)
+    for what, call, moved in (("plain", lambda t, m: sl.sl_decompress_avg_apply(plan, t, pays, 0.8), False),
+                              ("coded", lambda t, m: sl.sl_decompress_avg_apply_coded(plan, t, wires, sizes, 0.8), False),
+                              ("plain, momentum", lambda t, m: sl.sl_decompress_avg_apply_nesterov(plan, t, m, pays, 0.8, 0.9), True),
+                              ("coded, momentum", lambda t, m: sl.sl_decompress_avg_apply_nesterov_coded(plan, t, m, wires, sizes, 0.8, 0.9), True)):
+        t, m = theta0.clone(), m0.clone()
+        call(t, m)
+        same(t, want_n if moved else want, what)
+        same(m, want_m if moved else host(m0), what)
+    # dense steps
+    m, direction = m0.clone(), torch.zeros_like(m0)
+    sl.sl_lom_direction(plan, m, d0, 0.9, direction)
+    m_ref = host(m0)
+    dir_ref = oracle.lom_direction(descs, m_ref, host(d0), 0.9, out=np.zeros(n, np.float32))
+    same(m, m_ref, "m")
+    same(direction, dir_ref, "dir")
+    for mom in (False, True):
+        t, want = theta0.clone(), host(theta0)
+        sl.sl_dense_avg_apply(plan, t, m if mom else None, [d0, direction, d1], 0.7, 0.9)
+        oracle.dense_avg_apply(descs, want, [host(d0), dir_ref, host(d1)], 0.7, m=m_ref if mom else None, mu=0.9)
+        same(t, want, "dense")
+        same(m, m_ref, "momentum")
