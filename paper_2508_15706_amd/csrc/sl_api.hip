@@ -350,7 +350,7 @@ int sl_compress_impl(sl_plan *p, float *e, const float *delta, const float *thet
                                seed, st);
     else
         rc = slk_select(p, e, delta, theta_local, beta, frozen, static_cast<const unsigned char *>(pending),
-                        pay, static_cast<unsigned char *>(coded), ws, st);
+                        pay, static_cast<unsigned char *>(coded), ws, !frozen && !defer, st);
     if (rc) return rc;
     sl_prof_mark(p, SL_PROF_SELECT, st);
     if (p->n_chunks == 0) {

@@ -231,7 +231,7 @@ int sl_noalloc_scratch(int device, void **out);
 // launchers (defined next to their kernels)
 int slk_select(const sl_plan *p, float *e, const float *delta, const float *theta_local, float beta,
                int frozen, const unsigned char *pending, unsigned char *payload, unsigned char *coded,
-               unsigned char *ws, hipStream_t st);
+               unsigned char *ws, bool update_follows, hipStream_t st);       // update_follows: slk_quantize takes step E
 // the same with Random-k in place of Top-k
 int slk_select_random(const sl_plan *p, float *e, const float *delta, float beta, int frozen,
                       const unsigned char *pending, unsigned char *payload, unsigned char *ws, unsigned seed,

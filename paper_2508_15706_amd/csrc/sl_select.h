@@ -53,8 +53,8 @@ inline int sl_select_waves(int64_t n_chunks, int k)
     return n_chunks <= (k <= 128 ? 6144 : k <= 256 ? 2048 : k <= 512 ? 768 : 3072) ? 4 : 1;
 }
 
-// The workgroup-per-chunk form (sl_select_group.hip), `waves` 4 or 8; A as for the other one but for the LDS.
-int slk_select_group(const SelectArgs &A, bool sub_only, int waves, hipStream_t st);
+// The workgroup-per-chunk form (sl_select_group.hip), `waves` 4 or 8, `keep`: without the streaming hint; A as for the other one but for the LDS.
+int slk_select_group(const SelectArgs &A, bool sub_only, int waves, bool keep, hipStream_t st);
 
 // The wave-per-chunk form without the streaming hint (sl_select_kept.hip).
 void (*sl_select_kept(int k, bool two_bit, bool params))(SelectArgs);

@@ -14,9 +14,11 @@ static unsigned host_fmix32(unsigned h)
     return h;
 }
 
+#define SL_UPDATE_KEPT_FROM 2048
+#define SL_UPDATE_KEPT_UPTO 9216
 static int launch_select(const sl_plan *p, float *e, const float *delta, const float *theta_local, float beta,
                          int frozen, const unsigned char *pending, unsigned char *payload, unsigned char *coded,
-                         unsigned char *ws, bool sub_only, bool random, unsigned seed, hipStream_t st)
+                         unsigned char *ws, bool update_follows, bool sub_only, bool random, unsigned seed, hipStream_t st)
 {
     if (p->n_chunks == 0) return SL_OK;
     const int k = p->k;
@@ -65,7 +67,12 @@ static int launch_select(const sl_plan *p, float *e, const float *delta, const f
     A.uvec = (sub_only || !coded) ? nullptr : reinterpret_cast<unsigned *>(ws + p->ws_uvec);
     A.qsum = (sub_only || !coded) ? nullptr : reinterpret_cast<unsigned short *>(ws + p->ws_qsum);
     const int waves = random ? 1 : sl_select_waves(p->n_chunks, k);
-    if (waves > 1) return slk_select_group(A, sub_only, waves, st);
+    // Without the streaming hint: unaligned rows, and error buffers that the caches still hold when step E writes at the selected places
+    // (sl_compress, with the hint / without, us: 1500 chunks, k = 128 37.6 / 38.4, 2048 43.8 / 43.1, 4096 67.1 / 60.6, 8192 118.8 / 106.6, 12,288 165.7 / 165.6,
+    // 16,384 210 / 235).  With several waves per chunk unaligned rows gain from it on longer lists only (deferred, k = 32: 4000 chunks of 1001 columns 70.3 /
+    // 60.2, 900 of 530 29.4 / 30.7).
+    const bool keep = update_follows && p->n_chunks >= SL_UPDATE_KEPT_FROM && p->n_chunks <= SL_UPDATE_KEPT_UPTO;
+    if (waves > 1) return slk_select_group(A, sub_only, waves, keep || (sl_rows_unaligned(p) && p->n_chunks > 2048 && !sub_only), st);
     // (one chunk per workgroup where the LDS of four does not fit)
     const int wpb = 4 * (size_t)A.lds_per_wave > 65536 ? 1 : random && k <= 128 ? sl_chunks_per_group(p) : 4;
     const dim3 grid((unsigned)((p->n_chunks + wpb - 1) / wpb)), block(64 * wpb);
@@ -75,7 +82,7 @@ static int launch_select(const sl_plan *p, float *e, const float *delta, const f
     select_kernel fn;
     if (sub_only) fn = select_for<2, false, false>(k);
     else if (random) fn = two ? k_select<0, 0, true, false, true> : k_select<0, 0, false, false, true>;
-    else fn = sl_rows_unaligned(p) ? sl_select_kept(k, two, theta_local != nullptr) : select_for<false>(k, two, theta_local != nullptr);
+    else fn = keep || sl_rows_unaligned(p) ? sl_select_kept(k, two, theta_local != nullptr) : select_for<false>(k, two, theta_local != nullptr);
     hipLaunchKernelGGL(fn, grid, block, lds, st, A);
     hipError_t err = hipGetLastError();
     if (err != hipSuccess) {
@@ -87,19 +94,19 @@ static int launch_select(const sl_plan *p, float *e, const float *delta, const f
 
 int slk_select(const sl_plan *p, float *e, const float *delta, const float *theta_local, float beta,
                int frozen, const unsigned char *pending, unsigned char *payload, unsigned char *coded,
-               unsigned char *ws, hipStream_t st)
+               unsigned char *ws, bool update_follows, hipStream_t st)
 {
-    return launch_select(p, e, delta, theta_local, beta, frozen, pending, payload, coded, ws, false, false, 0u, st);
+    return launch_select(p, e, delta, theta_local, beta, frozen, pending, payload, coded, ws, update_follows, false, false, 0u, st);
 }
 
 int slk_select_random(const sl_plan *p, float *e, const float *delta, float beta, int frozen,
                       const unsigned char *pending, unsigned char *payload, unsigned char *ws, unsigned seed,
                       hipStream_t st)
 {
-    return launch_select(p, e, delta, nullptr, beta, frozen, pending, payload, nullptr, ws, false, true, seed, st);
+    return launch_select(p, e, delta, nullptr, beta, frozen, pending, payload, nullptr, ws, false, false, true, seed, st);
 }
 
 int slk_sub_topk(const sl_plan *p, float *m, hipStream_t st)
 {
-    return launch_select(p, m, nullptr, nullptr, 1.0f, 0, nullptr, nullptr, nullptr, nullptr, true, false, 0u, st);
+    return launch_select(p, m, nullptr, nullptr, 1.0f, 0, nullptr, nullptr, nullptr, nullptr, false, true, false, 0u, st);
 }

@@ -32,7 +32,8 @@ constexpr int lds_buffer(int m) { return LDS_LIST + 4 * (m > SAMPLE ? m : SAMPLE
 constexpr int LDS_CAND = 6 * CAND_CAP + 4 * CAND_PAD;    // keys, then index and sign in 16 bits
 
 // M: group maxima that bound the threshold from below, at least 2k of them; 0: no such bound (k > 512).
-template <int WAVES, int M>
+// KEEP: the arenas' accesses without the streaming hint (sl_access_load).
+template <int WAVES, int M, bool KEEP>
 // (Registers for four waves per SIMD above k = 512, where the sums of 64 entries per lane would take more; below, a bound on them that is
 // met anyway changes the schedule for the worse: 2048 chunks, k = 64, sl_compress 38.7 us without, 41.8 with it.)
 __global__ void __launch_bounds__(64 * WAVES, M > 0 ? 1 : 4) k_select_group(SelectArgs A, int sub, int sel_off, int margin)
@@ -82,20 +83,20 @@ __global__ void __launch_bounds__(64 * WAVES, M > 0 ? 1 : 4) k_select_group(Sele
     if (full) {
         if (need_e) {
 #pragma unroll
-            for (int u = 0; u < NA; ++u) ev[u] = sl_load_stream_at(ec, u * step, o0);
+            for (int u = 0; u < NA; ++u) ev[u] = sl_load_stream_at<KEEP>(ec, u * step, o0);
         }
         if (!sub) {
 #pragma unroll
-            for (int u = 0; u < NA; ++u) dv[u] = sl_load_stream_at(A.delta + d.base, u * step, o0);
+            for (int u = 0; u < NA; ++u) dv[u] = sl_load_stream_at<KEEP>(A.delta + d.base, u * step, o0);
         }
         if (A.theta_local) {
 #pragma unroll
-            for (int u = 0; u < NA; ++u) tv[u] = sl_load_stream_at(A.theta_local + d.base, u * step, o0);
+            for (int u = 0; u < NA; ++u) tv[u] = sl_load_stream_at<KEEP>(A.theta_local + d.base, u * step, o0);
         }
     } else {
-        if (need_e) sl_partial_request(A.e, d, NA * wave, lane, ev);
-        if (!sub) sl_partial_request(A.delta, d, NA * wave, lane, dv);
-        if (A.theta_local) sl_partial_request(A.theta_local, d, NA * wave, lane, tv);
+        if (need_e) sl_partial_request<KEEP>(A.e, d, NA * wave, lane, ev);
+        if (!sub) sl_partial_request<KEEP>(A.delta, d, NA * wave, lane, dv);
+        if (A.theta_local) sl_partial_request<KEEP>(A.theta_local, d, NA * wave, lane, tv);
     }
     // The pending record, an entry per thread (k <= 512); above, where records are whole words, eight entries.
     if (pend) {
@@ -183,10 +184,10 @@ __global__ void __launch_bounds__(64 * WAVES, M > 0 ? 1 : 4) k_select_group(Sele
         }
         int n = 4;
         if (full) {
-            if (need_e && !sub) sl_store_stream_at(ec, u * step, o0, v);
+            if (need_e && !sub) sl_store_stream_at<KEEP>(ec, u * step, o0, v);
         } else {
             n = sl_partial_exist(d, lr, lc, NA * wave + u);
-            if (need_e && !sub) sl_store_edge(ec + ((4u * (NA * wave + u) + lr) * stride + lc), n, v);
+            if (need_e && !sub) sl_store_edge<KEEP>(ec + ((4u * (NA * wave + u) + lr) * stride + lc), n, v);
         }
 #pragma unroll
         for (int cc = 0; cc < 4; ++cc) {
@@ -569,7 +570,7 @@ __global__ void __launch_bounds__(64 * WAVES, M > 0 ? 1 : 4) k_select_group(Sele
 
 }  // namespace
 
-int slk_select_group(const SelectArgs &A, bool sub_only, int waves, hipStream_t st)
+int slk_select_group(const SelectArgs &A, bool sub_only, int waves, bool keep, hipStream_t st)
 {
     const int k = A.k, m = k <= 64 ? 128 : k <= 128 ? 256 : k <= 256 ? 512 : k <= 512 ? 1024 : 0;
     size_t at = lds_buffer(m) + (A.pending ? SL_CHUNK * sizeof(float) : (size_t)LDS_CAND);
@@ -580,18 +581,13 @@ int slk_select_group(const SelectArgs &A, bool sub_only, int waves, hipStream_t 
     int margin = (int)(2.5 * std::sqrt(SAMPLE * share * (1.0 - share))) + 1;
     const dim3 grid((unsigned)A.n_chunks);
     const int sub = sub_only ? 1 : 0;
-#define SL_LAUNCH_GROUP(W)                                                                                                   \
-    do {                                                                                                                    \
-        const dim3 block(64 * W);                                                                                           \
-        if (m == 128) hipLaunchKernelGGL((k_select_group<W, 128>), grid, block, at, st, A, sub, sel_off, margin);            \
-        else if (m == 256) hipLaunchKernelGGL((k_select_group<W, 256>), grid, block, at, st, A, sub, sel_off, margin);       \
-        else if (m == 512) hipLaunchKernelGGL((k_select_group<W, 512>), grid, block, at, st, A, sub, sel_off, margin);       \
-        else if (m == 1024) hipLaunchKernelGGL((k_select_group<W, 1024>), grid, block, at, st, A, sub, sel_off, margin);     \
-        else hipLaunchKernelGGL((k_select_group<W, 0>), grid, block, at, st, A, sub, sel_off, margin);                       \
-    } while (0)
-    if (waves == 8) SL_LAUNCH_GROUP(8);
-    else SL_LAUNCH_GROUP(4);
-#undef SL_LAUNCH_GROUP
+    typedef void (*kernel_t)(SelectArgs, int, int, int);
+#define SL_GROUP_KINDS(W, KEEP) \
+    {k_select_group<W, 128, KEEP>, k_select_group<W, 256, KEEP>, k_select_group<W, 512, KEEP>, k_select_group<W, 1024, KEEP>, k_select_group<W, 0, KEEP>}
+    static const kernel_t table[2][2][5] = {{SL_GROUP_KINDS(4, false), SL_GROUP_KINDS(4, true)}, {SL_GROUP_KINDS(8, false), SL_GROUP_KINDS(8, true)}};
+#undef SL_GROUP_KINDS
+    const kernel_t fn = table[waves == 8 ? 1 : 0][keep ? 1 : 0][m == 128 ? 0 : m == 256 ? 1 : m == 512 ? 2 : m == 1024 ? 3 : 4];
+    hipLaunchKernelGGL(fn, grid, dim3(64 * waves), at, st, A, sub, sel_off, margin);
     hipError_t err = hipGetLastError();
     if (err != hipSuccess) {
         sl_note_hip_error(err);

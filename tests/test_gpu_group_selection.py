@@ -1,5 +1,5 @@
 """Selection with several waves on one chunk (short lists) and with one: list lengths on both sides of every place where the
-number of waves changes, with partial chunks - narrow tiles, run tails with fewer groups than k, more than the candidate list
+number of waves changes, or the streaming hint comes and goes with the eager update, with partial chunks - narrow tiles, run tails with fewer groups than k, more than the candidate list
 holds - all-zero chunks, chunks of few distinct values (ties), clustered ones, and heavy tails.  Eager, deferred (the
 record of the round before is still pending), frozen, from parameters, coded, and Sub-k, against the oracle."""
 import numpy as np
@@ -10,7 +10,7 @@ pytestmark = pytest.mark.gpu
 
 # (k, value bits, chunks of the list): 8 | 4 | 1 waves
 CASES = [(32, 2, 512), (64, 2, 513), (128, 1, 6144), (64, 4, 6145), (136, 2, 512), (200, 3, 2048), (256, 2, 2049), (264, 2, 512), (512, 32, 768),
-         (500, 2, 769), (520, 2, 512), (1024, 4, 3072), (2048, 2, 3073), (4, 2, 513), (4096, 2, 40), (1448, 32, 600)]
+         (500, 2, 769), (64, 2, 2047), (32, 3, 2048), (136, 2, 9216), (256, 2, 9217), (520, 2, 512), (1024, 4, 3072), (2048, 2, 3073), (4, 2, 513), (4096, 2, 40), (1448, 32, 600)]
 
 
 @pytest.mark.parametrize("k, bits, chunks", CASES)
