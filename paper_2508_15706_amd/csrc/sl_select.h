@@ -19,6 +19,7 @@ struct SelectArgs {
     int bits, hdr_bytes, rec_bytes; // value width of the payloads and the sizes that follow from it
     unsigned seed_hash;     // Random-k: fmix32(seed), see random_key
     int sample_margin;      // select_general: ranks of the sample's bracket, k / 8 -+ this (0: no sample)
+    int pieces;             // Sub-k: whole 64-byte pieces are written back
     int lds_per_wave;
     int pend_off;           // offset of the pending-correction tables in a wave's LDS
     int pend_words;         // the pending record is staged in LDS as whole words (large k), see pend_half

@@ -15,6 +15,7 @@ static unsigned host_fmix32(unsigned h)
 }
 
 #define SL_UPDATE_KEPT_FROM 2048
+#define SL_PIECES_FROM 16384
 #define SL_UPDATE_KEPT_UPTO 9216
 static int launch_select(const sl_plan *p, float *e, const float *delta, const float *theta_local, float beta,
                          int frozen, const unsigned char *pending, unsigned char *payload, unsigned char *coded,
@@ -57,6 +58,7 @@ static int launch_select(const sl_plan *p, float *e, const float *delta, const f
         }
         A.lds_per_wave = (int)((b + 15) & ~(size_t)15);
     }
+    A.pieces = sub_only && p->n_chunks >= SL_PIECES_FROM;
     A.vals = sub_only ? nullptr : reinterpret_cast<float *>(ws + p->ws_vals);
     A.leafA = sub_only ? nullptr : reinterpret_cast<double *>(ws + p->ws_leafA);
     A.payload = payload;

@@ -768,7 +768,34 @@ __global__ void SL_SELECT_BOUNDS k_select(SelectArgs A)
     sl_wave_sync();
 
     if constexpr (SUBK) {
-        // m - Top-k(m): x - x = +0.0 at the selected positions, the rest stays as it is
+        // m - Top-k(m): x - x = +0.0 at the selected positions, the rest stays as it is.  On long lists a full chunk of aligned rows writes back the
+        // 64-byte pieces that hold a selected position, from the registers: where the caches do not hold the buffer, a write of four bytes costs
+        // the memory a read and a write of its piece (49,152 chunks, us, k = 64 255 -> 190, k = 128 355 -> 210, k = 512 500 -> 300; 24,576, k = 64
+        // 115 -> 95; 12,288, k = 64 49 -> 55, so not there).  The selected positions go to LDS as bits, of which a lane looks at its own
+        // four and its piece's sixteen per access.
+        if (A.pieces && full && ((d.base | stride) & 15) == 0) {
+            unsigned *marks = reinterpret_cast<unsigned *>(smem);       // (in the place of the candidates, 2 KB at least)
+#pragma unroll
+            for (int u = 0; u < 2; ++u) marks[64 * u + lane] = 0u;
+            sl_wave_sync();
+            for (int p = lane; p < k; p += 64) {
+                const unsigned j = sel_idx[p];
+                sl_lds_or(&marks[j >> 5], 1u << (j & 31u));
+            }
+            sl_wave_sync();
+            const unsigned o0 = 4u * (lr * stride + lc), step = 16u * stride;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const unsigned w = marks[8 * i + (lane >> 3)] >> (4 * (lane & 7)), piece = marks[8 * i + (lane >> 3)] >> (16 * ((lane >> 2) & 1));
+                if (piece & 0xFFFFu) {
+                    sl_f4 v;
+#pragma unroll
+                    for (int cc = 0; cc < 4; ++cc) v[cc] = (w >> cc) & 1u ? 0.0f : a[4 * i + cc];
+                    sl_store_stream_at(ec, i * step, o0, v);
+                }
+            }
+            return;
+        }
         for (int p = lane; p < k; p += 64) {
             const unsigned j = sel_idx[p];
             ec[(j >> 6) * stride + (j & 63u)] = 0.0f;

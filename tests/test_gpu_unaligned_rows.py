@@ -79,3 +79,25 @@ def test_unaligned_rows(oracle, case):
         oracle.dense_avg_apply(descs, want, [host(d0), dir_ref, host(d1)], 0.7, m=m_ref if mom else None, mu=0.9)
         same(t, want, "dense")
         same(m, m_ref, "momentum")
+
+
+@pytest.mark.parametrize("k, chunks", [(4, 16384), (64, 16383), (128, 16385), (264, 16384), (600, 16384), (4096, 16384)])
+def test_subk_of_long_lists(oracle, k, chunks):
+    """Sub-k on both sides of the length from which whole pieces are written back; aligned matrices, one whose rows are not, a run with a
+    tail, chunks of zeros and of one value."""
+    from paper_2508_15706_amd import binding as sl
+    shapes = [(64 * 4, 64 * 5 if k > 512 else 64 * 4 + 17, 1), (1, 4096 * 2 + (4096 if k > 600 else 700), 0)]
+    shapes.append((64 * (chunks - 20 - 3), 64, 1))
+    descs, n = [], 0
+    for r, c, lay in shapes:
+        descs.append((r, c, n, lay))
+        n += (r * c + 63) // 64 * 64
+    plan = sl.sl_plan_create(descs, k)
+    assert plan.num_chunks == chunks
+    m = torch.empty(n, device="cuda").normal_(0, 1e-3, generator=torch.Generator(device="cuda").manual_seed(k))
+    m[-4096:] = 0.0
+    m[-8192:-4096] = -2e-3
+    want = m.cpu().numpy()
+    sl.sl_sub_topk(plan, m)
+    oracle.sub_topk(descs, k, want)
+    np.testing.assert_array_equal(m.cpu().numpy().view(np.uint32), want.view(np.uint32))
