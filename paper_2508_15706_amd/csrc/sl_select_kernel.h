@@ -535,28 +535,33 @@ __global__ void SL_SELECT_BOUNDS k_select(SelectArgs A)
         } else if constexpr (PARAMS) {
             // pseudo-gradient delta = theta_outer - theta_local (one fp32 subtraction).
             // Three input streams: the chunk is taken in four quarters (four 16-byte
-            // accesses per lane and stream each), finished one after the other, so that
-            // only a quarter of each stream sits in registers next to the result.
+            // accesses per lane and stream each), one requested ahead of the one that is being
+            // finished: two quarters of each stream in registers next to the result.
             const float *lc_ = A.theta_local + d.base;
+            sl_f4 dq[2][4], tq[2][4], eq[2][4];
+            auto request = [&](int q) __attribute__((always_inline)) {
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                sl_f4 dq[4], tq[4], eq[4];
+                for (int u = 0; u < 4; ++u) dq[q & 1][u] = sl_load_stream_at<KEEP>(dc, (4 * q + u) * step, o0);
 #pragma unroll
-                for (int u = 0; u < 4; ++u) dq[u] = sl_load_stream_at<KEEP>(dc, (4 * q + u) * step, o0);
-#pragma unroll
-                for (int u = 0; u < 4; ++u) tq[u] = sl_load_stream_at<KEEP>(lc_, (4 * q + u) * step, o0);
+                for (int u = 0; u < 4; ++u) tq[q & 1][u] = sl_load_stream_at<KEEP>(lc_, (4 * q + u) * step, o0);
                 if (!A.frozen) {
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) eq[u] = sl_load_stream_at<KEEP>(ec, (4 * q + u) * step, o0);
+                    for (int u = 0; u < 4; ++u) eq[q & 1][u] = sl_load_stream_at<KEEP>(ec, (4 * q + u) * step, o0);
                 }
+            };
+            request(0);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                if (q < 3) request(q + 1);
+                __builtin_amdgcn_sched_barrier(0);   // (the requests stay ahead of what waits for the quarter before)
                 if (pend && (q & 1) == 0) pend_half(q >> 1);
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
                     const int i = 4 * q + u;
-                    const sl_f4 g = dq[u] - tq[u];
+                    const sl_f4 g = dq[q & 1][u] - tq[q & 1][u];
                     sl_f4 v = g;
                     if (!A.frozen) {
-                        sl_f4 ee = eq[u];
+                        sl_f4 ee = eq[q & 1][u];
                         if (pend) ee = pend_sub(ee, i);
                         v.x = fmaf(A.beta, ee.x, g.x);
                         v.y = fmaf(A.beta, ee.y, g.y);
@@ -566,7 +571,7 @@ __global__ void SL_SELECT_BOUNDS k_select(SelectArgs A)
                     }
                     a[4 * i + 0] = v.x, a[4 * i + 1] = v.y, a[4 * i + 2] = v.z, a[4 * i + 3] = v.w;
                 }
-                __builtin_amdgcn_sched_barrier(0);   // keep the quarters apart: no hoisting of the next loads
+                __builtin_amdgcn_sched_barrier(0);   // keep the quarters apart: no hoisting of the loads after next
             }
         } else {
             if (!A.frozen) {
