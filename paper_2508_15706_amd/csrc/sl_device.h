@@ -121,31 +121,10 @@ SL_DEV void sl_store_edge(float *p, int n, sl_f4 v)
     }
 }
 
-// Accesses i0 .. i0 + N - 1 of a lane to a partial chunk of `arena` (access i: elements lc .. lc + 3 of row 4 i + lr); what
-// does not exist comes as +0.0f (ZERO) or as any value.  Every lane issues one 16-byte load per row, and all are under way
-// together; with them under the conditions the compiler waits for memory once per row (aggregate of three plain / coded
-// payloads, k = 32, us: 1155 chunks of a 67-column matrix 12.2 -> 10.0 / 12.8 -> 13.0, 900 of 530 columns 20.4 -> 10.6 / 17.4 -> 13.9,
-// 12,000 of 67 columns 112 -> 66 / 89 -> 80, 24,000 of 1000 columns 257 -> 189 / 235 -> 187, the last also by the order of the
-// chunks; with momentum 2000 chunks of 100 columns are 4 % slower, all others faster).
-// Where the edge cuts through a lane's columns, the load ends with the row's last element (sl_partial_load_at) and its elements are
-// moved into place afterwards.
-template <bool KEEP = false, int N>
-SL_DEV void sl_partial_request(const float *arena, const SlChunkDesc &d, int i0, int lane, sl_f4 (&v)[N])
+// Moves the elements of such loads into place: `exist` and `place` of access u (sl_partial_exist, sl_partial_origin).
+template <bool ZERO, int N, class Exist, class Place>
+SL_DEV void sl_partial_settle(const SlChunkDesc &d, int lc, int room, Exist exist, Place place, sl_f4 (&v)[N])
 {
-    const int lr = lane >> 4, lc = (lane & 15) * 4, room = sl_partial_room(d);
-    const float *p = arena + (d.base - room);
-    const unsigned o0 = sl_partial_origin(d, lr, lc, room), step = 16u * (unsigned)d.stride;
-#pragma unroll
-    for (int u = 0; u < N; ++u)
-        v[u] = sl_load_stream_at<KEEP>(p, 0u, sl_partial_load_at(sl_partial_exist(d, lr, lc, i0 + u), o0 + (unsigned)(i0 + u) * step, room));
-}
-template <bool ZERO = false, int N>
-SL_DEV void sl_partial_place(const SlChunkDesc &d, int i0, int lane, sl_f4 (&v)[N])
-{
-    const int lr = lane >> 4, lc = (lane & 15) * 4, room = sl_partial_room(d);
-    const unsigned o0 = sl_partial_origin(d, lr, lc, room), step = 16u * (unsigned)d.stride;
-    auto exist = [&](int u) -> int { return sl_partial_exist(d, lr, lc, i0 + u); };
-    auto place = [&](int u) -> unsigned { return o0 + (unsigned)(i0 + u) * step; };
     // the four elements from the one that lies `by` places into a load on
     auto moved = [&](sl_f4 w, bool one, bool two) -> sl_f4 {
         const float x0 = one ? w.y : w.x, x1 = one ? w.z : w.y, x2 = one ? w.w : w.z;
@@ -176,11 +155,48 @@ SL_DEV void sl_partial_place(const SlChunkDesc &d, int i0, int lane, sl_f4 (&v)[
         }
     }
 }
+
+// Accesses i0 .. i0 + N - 1 of a lane to a partial chunk of `arena` (access i: elements lc .. lc + 3 of row 4 i + lr); what
+// does not exist comes as +0.0f (ZERO) or as any value.  Every lane issues one 16-byte load per row, and all are under way
+// together; with them under the conditions the compiler waits for memory once per row (aggregate of three plain / coded
+// payloads, k = 32, us: 1155 chunks of a 67-column matrix 12.2 -> 10.0 / 12.8 -> 13.0, 900 of 530 columns 20.4 -> 10.6 / 17.4 -> 13.9,
+// 12,000 of 67 columns 112 -> 66 / 89 -> 80, 24,000 of 1000 columns 257 -> 189 / 235 -> 187, the last also by the order of the
+// chunks; with momentum 2000 chunks of 100 columns are 4 % slower, all others faster).
+// Where the edge cuts through a lane's columns, the load ends with the row's last element (sl_partial_load_at) and its elements are
+// moved into place afterwards.
+// (One function, not the two below: with them the aggregates' full chunks take 11 to 15 registers more; 178M list, momentum, fp32
+// values 488 / 506.)
 template <int N, bool ZERO = false, bool KEEP = false>
 SL_DEV void sl_load_partial(const float *arena, const SlChunkDesc &d, int i0, int lane, sl_f4 (&v)[N])
 {
-    sl_partial_request<KEEP>(arena, d, i0, lane, v);
-    sl_partial_place<ZERO>(d, i0, lane, v);
+    const int lr = lane >> 4, lc = (lane & 15) * 4, room = sl_partial_room(d);
+    const float *p = arena + (d.base - room);
+    const unsigned o0 = sl_partial_origin(d, lr, lc, room), step = 16u * (unsigned)d.stride;
+    auto exist = [&](int u) -> int { return sl_partial_exist(d, lr, lc, i0 + u); };
+    auto place = [&](int u) -> unsigned { return o0 + (unsigned)(i0 + u) * step; };
+#pragma unroll
+    for (int u = 0; u < N; ++u) v[u] = sl_load_stream_at<KEEP>(p, 0u, sl_partial_load_at(exist(u), place(u), room));
+    sl_partial_settle<ZERO>(d, lc, room, exist, place, v);
+}
+
+// The same in two steps, for several streams: all requested before the first is moved into place.  What does not exist comes as any value.
+template <bool KEEP = false, int N>
+SL_DEV void sl_partial_request(const float *arena, const SlChunkDesc &d, int i0, int lane, sl_f4 (&v)[N])
+{
+    const int lr = lane >> 4, lc = (lane & 15) * 4, room = sl_partial_room(d);
+    const float *p = arena + (d.base - room);
+    const unsigned o0 = sl_partial_origin(d, lr, lc, room), step = 16u * (unsigned)d.stride;
+#pragma unroll
+    for (int u = 0; u < N; ++u)
+        v[u] = sl_load_stream_at<KEEP>(p, 0u, sl_partial_load_at(sl_partial_exist(d, lr, lc, i0 + u), o0 + (unsigned)(i0 + u) * step, room));
+}
+template <int N>
+SL_DEV void sl_partial_place(const SlChunkDesc &d, int i0, int lane, sl_f4 (&v)[N])
+{
+    const int lr = lane >> 4, lc = (lane & 15) * 4, room = sl_partial_room(d);
+    const unsigned o0 = sl_partial_origin(d, lr, lc, room), step = 16u * (unsigned)d.stride;
+    sl_partial_settle<false>(d, lc, room, [&](int u) -> int { return sl_partial_exist(d, lr, lc, i0 + u); },
+                             [&](int u) -> unsigned { return o0 + (unsigned)(i0 + u) * step; }, v);
 }
 
 SL_DEV int sl_popc(unsigned long long m) { return __builtin_popcountll(m); }
