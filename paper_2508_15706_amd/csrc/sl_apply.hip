@@ -90,6 +90,9 @@ struct ApplyArgs {
 // ROUTE: how a staged record's entries reach the accumulators.
 //   0 (k <= 128, one pass): the entries of several workers are decoded ahead of the additions;
 //   1: entry by entry, one worker at a time;
+//   3: as 0, half as many workers ahead: with the momentum and values of any width that leaves registers for a second wave per SIMD,
+//      which pays from more than eight workers (46,080 chunks, fp32 values, with momentum: k = 32, R = 16 577 -> 515 us, k = 64, R = 8 513 -> 512, R = 4 499 ->
+//      506);
 //   2 (k >= 256, a multiple of 8): a lane decodes eight consecutive entries from whole words; with 2-bit
 //      codes ("direct", also below k = 256 with many workers) it loads those words from the payload itself, a
 //      batch of eight steps ahead, and no record passes through LDS.  Bound by instruction issue and, at two
@@ -101,7 +104,7 @@ struct ApplyArgs {
 template <bool TWO_BIT, bool NESTEROV, int NH, int ROUTE, bool KEEP>
 __global__ void __launch_bounds__(256) k_apply(ApplyArgs A)
 {
-    constexpr bool SMALLK = ROUTE == 0, OCTETS = ROUTE == 2, DIRECT = OCTETS && TWO_BIT;
+    constexpr bool SMALLK = ROUTE == 0 || ROUTE == 3, OCTETS = ROUTE == 2, DIRECT = OCTETS && TWO_BIT;
     static_assert(ROUTE == 1 || NH == 1, "two halves go entry by entry");
     constexpr int ACC_FLOATS = SL_CHUNK / NH, ROWS4 = 16 / NH;   // accumulators, 16-byte accesses per lane
     extern __shared__ __align__(16) unsigned char smem_all[];
@@ -348,12 +351,13 @@ __global__ void __launch_bounds__(256) k_apply(ApplyArgs A)
             if constexpr (SMALLK) {
                 // The entries of up to eight workers are decoded first (independent LDS reads,
                 // all in flight together), then added worker by worker: the additions form a
-                // chain of LDS round trips, the decoding no longer sits inside it.
-                for (int rb = 0; rb < nb; rb += 8) {
-                    unsigned jj[8][2];
-                    float qq[8][2];
+                // chain of LDS round trips, the decoding no longer sits inside it.  (Route 3: four.)
+                constexpr int DW = ROUTE == 3 ? 4 : 8;
+                for (int rb = 0; rb < nb; rb += DW) {
+                    unsigned jj[DW][2];
+                    float qq[DW][2];
 #pragma unroll
-                    for (int u = 0; u < 8; ++u)
+                    for (int u = 0; u < DW; ++u)
 #pragma unroll
                         for (int s2 = 0; s2 < 2; ++s2) {
                             const int m = lane + 64 * s2;
@@ -362,7 +366,7 @@ __global__ void __launch_bounds__(256) k_apply(ApplyArgs A)
                             if (rb + u < nb && m < k) decode(rb + u, m, jj[u][s2], qq[u][s2]);
                         }
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) {
+                    for (int u = 0; u < DW; ++u) {
                         if (rb + u < nb) {
 #pragma unroll
                             for (int s2 = 0; s2 < 2; ++s2) {
@@ -729,15 +733,15 @@ int slk_apply(const sl_plan *p, float *theta, float *mom, float mu, const void *
     const size_t lds = (size_t)A.lds_per_wave * wpb;
     const bool two = p->bits == 2;
     typedef void (*kernel_t)(ApplyArgs);
-    const int route = octets ? 2 : (!halves && p->k <= 128) ? 0 : 1;
+    const int route = octets ? 2 : (!halves && p->k <= 128) ? (mom && !two && R > 8 ? 3 : 0) : 1;
 #define SL_APPLY_ROUTES(TWO, NEST, KEEP) \
-    {k_apply<TWO, NEST, 1, 0, KEEP>, k_apply<TWO, NEST, 1, 1, KEEP>, k_apply<TWO, NEST, 1, 2, KEEP>, k_apply<TWO, NEST, 2, 1, KEEP>}
+    {k_apply<TWO, NEST, 1, 0, KEEP>, k_apply<TWO, NEST, 1, 1, KEEP>, k_apply<TWO, NEST, 1, 2, KEEP>, k_apply<TWO, NEST, 1, NEST && !TWO ? 3 : 0, KEEP>, k_apply<TWO, NEST, 2, 1, KEEP>}
 #define SL_APPLY_KINDS(KEEP) \
     {{SL_APPLY_ROUTES(false, false, KEEP), SL_APPLY_ROUTES(false, true, KEEP)}, {SL_APPLY_ROUTES(true, false, KEEP), SL_APPLY_ROUTES(true, true, KEEP)}}
-    static const kernel_t table[2][2][2][4] = {SL_APPLY_KINDS(false), SL_APPLY_KINDS(true)};
+    static const kernel_t table[2][2][2][5] = {SL_APPLY_KINDS(false), SL_APPLY_KINDS(true)};
 #undef SL_APPLY_KINDS
 #undef SL_APPLY_ROUTES
-    const kernel_t fn = table[sl_rows_unaligned(p) ? 1 : 0][two ? 1 : 0][mom ? 1 : 0][halves ? 3 : route];   // (two halves: entry by entry only)
+    const kernel_t fn = table[sl_rows_unaligned(p) ? 1 : 0][two ? 1 : 0][mom ? 1 : 0][halves ? 4 : route];   // (two halves: entry by entry only)
     if (lds > 65536) {
         hipError_t aerr = hipFuncSetAttribute(reinterpret_cast<const void *>(fn),
                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);

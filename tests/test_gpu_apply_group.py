@@ -9,7 +9,7 @@ pytestmark = pytest.mark.gpu
 
 # (k, value bits, chunks, workers)
 CASES = [(64, 2, 256, 8), (64, 2, 257, 8), (64, 2, 257, 4), (128, 4, 256, 5), (136, 2, 512, 8), (256, 2, 513, 8), (264, 2, 100, 3), (32, 1, 1024, 4),
-         (32, 1, 1025, 3), (8, 3, 1281, 8), (16, 2, 2048, 2), (64, 32, 300, 4), (128, 32, 40, 8), (4, 2, 200, 1), (100, 2, 700, 9), (256, 2, 60, 4), (72, 4, 30, 4)]
+         (32, 1, 1025, 3), (8, 3, 1281, 8), (16, 2, 2048, 2), (64, 32, 300, 4), (128, 32, 40, 8), (4, 2, 200, 1), (100, 2, 700, 9), (256, 2, 60, 4), (72, 4, 30, 4), (32, 32, 100, 9), (64, 4, 40, 17)]
 
 
 @pytest.mark.parametrize("k, bits, chunks, R", CASES)
