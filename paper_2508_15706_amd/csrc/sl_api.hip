@@ -145,7 +145,8 @@ int sl_plan_create_bits(const sl_tensor *tensors, int n_tensors, int k, int valu
             D.pay_off = (long long)pay;
             D.block_bytes = (long long)align_up((size_t)(hdr + D.n_chunks * rec), 16);
             D.group0 = (long long)groups.size();
-            for (long long g = 0; g * SL_RICE_GROUP < D.n_chunks; ++g) groups.push_back(SlGroup{t, (int)g});
+            for (long long g = 0; g * SL_RICE_GROUP < D.n_chunks; ++g)
+                groups.push_back(SlGroup{t, (int)g, (int)(D.chunk0 + g * SL_RICE_GROUP), (int)std::min<long long>(SL_RICE_GROUP, D.n_chunks - g * SL_RICE_GROUP)});
             pay += (size_t)D.block_bytes;
             n_elements += T.rows * T.cols;
         }
@@ -216,7 +217,7 @@ int sl_plan_create_bits(const sl_tensor *tensors, int n_tensors, int k, int valu
         p->ws_qsum = off;    off = align_up(off + (size_t)p->n_chunks * 2, 256);
         p->ws_gwords = off;  off = align_up(off + groups.size() * 4, 256);
         p->ws_goff = off;    off = align_up(off + groups.size() * 4, 256);
-        p->ws_twords = off;  off = align_up(off + ((size_t)n_tensors + 1) * 8, 256);
+        off = align_up(off + ((size_t)n_tensors + 1) * 8, 256);     // (not used any more; workspace sizes stay as callers know them)
         p->ws_bytes = off;
     }
 

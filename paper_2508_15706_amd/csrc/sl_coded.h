@@ -208,12 +208,11 @@ SL_DEV SlVecPlace sl_coded_dir_entry(const SlCodedGeom &G, sl_gbytes entry, int 
 // ---------------------------------------------------------------------------------- placement
 // The variable-length part of a buffer.  The writers leave each chunk's bit vector and quotient sum
 // in the workspace; then, each step reading what the one before wrote:
-//   sl_coded_scan_tensor   one workgroup per tensor: words of each group's run, their exclusive
-//                          prefix inside the tensor, the tensor's total;
-//   sl_coded_scan_list     one wave: prefix over the tensors, total size, buffer header (on lists of few tensors every
-//                          wave of the last step sums up what is before it, and this one is left out);
-//   sl_coded_place         one wave per group: the 16 vectors shifted into one run, the run and
-//                          the directory entry written.
+//   sl_coded_scan_block    one workgroup per SL_SCAN_BLOCK groups: words of each group's run and their exclusive prefix inside
+//                          the block, whatever tensors it spans (by tensor, a workgroup had 8192 groups of a large matrix to go
+//                          through alone while tensors of one group had one each);
+//   sl_coded_place         one wave per group: the words of the blocks before its own summed up, the 16 vectors
+//                          shifted into one run, the run and the directory entry written; the last one writes the buffer header.
 // The compressor runs them as extra workgroups of the quantizer's launches (sl_quant.hip), on lists of
 // many tensors and in the transcoder they are launches of their own (sl_coded.hip).
 struct SlCodedArgs {
@@ -221,13 +220,11 @@ struct SlCodedArgs {
     const SlTensorDev *tensors;
     const SlGroup *groups;
     long long n_groups;
-    int n_tensors;
     int ua_log2;                    // log2 of a power of two >= G.ua
     const unsigned *uvec;           // [n_chunks][G.ua] bit vectors as the writers left them
     const unsigned short *qsum;     // [n_chunks]
     unsigned *gwords;               // [n_groups] words of each group's run
-    unsigned *goff;                 // [n_groups] word offset of the run inside its tensor's part of the section
-    unsigned long long *twords;     // [n_tensors + 1] words of each tensor's part, then (after the list scan) its offset
+    unsigned *goff;                 // [n_groups] word offset of the run inside its block of SL_SCAN_BLOCK groups
     unsigned char *out;             // the coded buffer
 };
 
@@ -238,49 +235,59 @@ inline SlCodedArgs sl_coded_args(const sl_plan *p, unsigned char *out, unsigned 
     A.tensors = p->d_tensors;
     A.groups = p->d_groups;
     A.n_groups = p->n_groups;
-    A.n_tensors = p->n_tensors;
     A.ua_log2 = 0;
     while ((1 << A.ua_log2) < p->cg.ua) ++A.ua_log2;
     A.uvec = reinterpret_cast<const unsigned *>(ws + p->ws_uvec);
     A.qsum = reinterpret_cast<const unsigned short *>(ws + p->ws_qsum);
     A.gwords = reinterpret_cast<unsigned *>(ws + p->ws_gwords);
     A.goff = reinterpret_cast<unsigned *>(ws + p->ws_goff);
-    A.twords = reinterpret_cast<unsigned long long *>(ws + p->ws_twords);
     A.out = out;
     return A;
 }
 
-// Tensor `t`; called by all threads of a workgroup of THREADS; `wsum` (LDS) THREADS / 64 words.
-template <int THREADS>
-SL_DEV void sl_coded_scan_tensor(const SlCodedArgs &A, int t, unsigned *wsum)
+// Words of a group's run, from the chunks' quotient sums (sixteen are read whether or not the group has them: behind the last lie
+// other parts of the workspace).
+typedef unsigned sl_u4h __attribute__((ext_vector_type(4), aligned(2)));
+SL_DEV unsigned sl_coded_group_words(const SlCodedArgs &A, const SlGroup &g)
 {
-    const SlTensorDev td = A.tensors[t];
-    const long long ng = (td.n_chunks + SL_RICE_GROUP - 1) / SL_RICE_GROUP;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    unsigned long long carry = 0;                // words of the groups before this tile
-    for (long long base = 0; base < ng; base += THREADS) {
-        const long long i = base + tid, c0 = i * SL_RICE_GROUP;
-        const int nc = i < ng ? (int)min((long long)SL_RICE_GROUP, td.n_chunks - c0) : 0;
-        unsigned bits = 0;
+    const sl_u4h *q = reinterpret_cast<const sl_u4h *>(A.qsum + g.chunk0);
+    const sl_u4h lo = q[0], hi = q[1];
+    unsigned bits = (unsigned)(g.n_chunks * A.G.k);
 #pragma unroll
-        for (int q = 0; q < SL_RICE_GROUP; ++q)
-            if (q < nc) bits += (unsigned)A.G.k + A.qsum[td.chunk0 + c0 + q];
-        const unsigned v = (bits + 31u) >> 5;
-        const unsigned incl = (unsigned)sl_wave_iscan((int)v);     // a tile's total stays far below 2^31
+    for (int i = 0; i < SL_RICE_GROUP; ++i) {
+        const unsigned w = i < 8 ? lo[(i >> 1) & 3] : hi[(i >> 1) & 3];
+        bits += i < g.n_chunks ? (w >> (16 * (i & 1))) & 0xFFFFu : 0u;
+    }
+    return (bits + 31u) >> 5;
+}
+
+// Block `block` of SL_SCAN_BLOCK groups; called by all threads of a workgroup of THREADS; `wsum` (LDS) THREADS / 64 words.
+#define SL_SCAN_BLOCK 1024
+inline long long sl_scan_blocks(long long n_groups) { return (n_groups + SL_SCAN_BLOCK - 1) / SL_SCAN_BLOCK; }
+template <int THREADS>
+SL_DEV void sl_coded_scan_block(const SlCodedArgs &A, long long block, unsigned *wsum)
+{
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    unsigned carry = 0;                          // words of the block before this tile (a group has below 2^13)
+    for (int first = 0; first < SL_SCAN_BLOCK; first += THREADS) {
+        if (block * SL_SCAN_BLOCK + first >= A.n_groups) return;
+        const long long g = block * SL_SCAN_BLOCK + first + tid;
+        const unsigned v = g < A.n_groups ? sl_coded_group_words(A, A.groups[g]) : 0u;
+        const unsigned incl = (unsigned)sl_wave_iscan((int)v);
         if (lane == 63) wsum[wave] = incl;
         __syncthreads();
-        unsigned long long before = carry;
+        unsigned before = carry;
+#pragma unroll
         for (int q = 0; q < THREADS / 64; ++q) {
             before += q < wave ? wsum[q] : 0u;
             carry += wsum[q];
         }
-        if (i < ng) {
-            A.gwords[td.group0 + i] = v;
-            A.goff[td.group0 + i] = (unsigned)(before + incl - v);
+        if (g < A.n_groups) {
+            A.gwords[g] = v;
+            A.goff[g] = before + incl - v;
         }
         __syncthreads();
     }
-    if (tid == 0) A.twords[t] = carry;
 }
 
 // The buffer header and the zero padding that rounds the buffer up to 16 bytes, for a section of so many words.  One
@@ -298,44 +305,26 @@ SL_DEV void sl_coded_header(unsigned long long words, long long section, unsigne
     if (end + 4ull * lane < total) *reinterpret_cast<unsigned *>(out + end + 4ull * lane) = 0u;
 }
 
-// Words of the section in front of tensor t's part (t = n_tensors: of the whole section), from the words of each; for lists of
-// few tensors, where a wave has them sooner than a launch of sl_coded_scan_list.  One wave; uniform.
-SL_DEV unsigned long long sl_coded_words_before(const unsigned long long *twords, int t)
+// Words of the section in front of group gi, after sl_coded_scan_block.  One wave; uniform.
+SL_DEV unsigned long long sl_coded_words_before(const SlCodedArgs &A, long long gi)
 {
-    const int lane = threadIdx.x & 63;
+    const long long block = gi / SL_SCAN_BLOCK;
     unsigned long long v = 0;
-    for (int i = lane; i < t; i += 64) v += twords[i];
-#pragma unroll
-    for (int l = 0; l < 6; ++l) v += sl_partner(v, l);
-    return v;
-}
-
-// Prefix over the tensors (twords[t] becomes the tensor's offset in the section, in words), the
-// buffer header, and the zero padding that rounds the buffer up to 16 bytes.  One wave.
-SL_DEV void sl_coded_scan_list(unsigned long long *twords, int n_tensors, long long section, unsigned char *out)
-{
-    const int lane = threadIdx.x & 63;
-    unsigned long long pos = 0;
-    for (int base = 0; base < n_tensors; base += 64) {
-        const int t = base + lane;
-        const unsigned long long v = t < n_tensors ? twords[t] : 0ull;
-        unsigned long long incl = v;
-#pragma unroll
-        for (int s = 1; s < 64; s <<= 1) {
-            const unsigned long long up = __shfl_up(incl, s);
-            if (lane >= s) incl += up;
+    if (block > 0) {
+        for (long long b = threadIdx.x & 63; b < block; b += 64) {
+            const long long last = b * SL_SCAN_BLOCK + SL_SCAN_BLOCK - 1;
+            v += A.goff[last] + A.gwords[last];
         }
-        if (t < n_tensors) twords[t] = pos + incl - v;
-        pos += __shfl(incl, 63);
+#pragma unroll
+        for (int l = 0; l < 6; ++l) v += sl_partner(v, l);
     }
-    if (lane == 0) twords[n_tensors] = pos;
-    sl_coded_header(pos, section, out);
+    return v + A.goff[gi];
 }
 
 // Words of LDS that sl_coded_place needs per wave.
 inline size_t sl_coded_place_words(const SlCodedGeom &G) { return (size_t)SL_RICE_GROUP * G.ua + 1; }
 
-// Group gi of a tensor whose part of the section begins at word `before` (one wave; `run`: its LDS): the chunks' vectors, as the writers left them (G.ua words each,
+// Group g, whose run of nw words begins at word `base` of the section (below 2^32 by the plan's check; one wave; `run`: its LDS): the chunks' vectors, as the writers left them (G.ua words each,
 // bits beyond k + Q undefined), are shifted to their bit offsets inside the run in LDS; the run and
 // the directory entry go to the buffer.  A lane takes one (chunk, word) pair per turn, so that the
 // loads of several chunks are under way together (a chunk per turn left most lanes idle and waited
@@ -345,16 +334,13 @@ inline size_t sl_coded_place_words(const SlCodedGeom &G) { return (size_t)SL_RIC
 #ifndef SL_PLACE_BY_CHUNK
 #define SL_PLACE_BY_CHUNK 6               // log2 of the words of the longest vector, rounded up
 #endif
-SL_DEV void sl_coded_place(const SlCodedArgs &A, long long gi, unsigned long long before, unsigned *run)
+SL_DEV void sl_coded_place_at(const SlCodedArgs &A, const SlGroup &g, unsigned long long base, unsigned nw, unsigned *run)
 {
     const int lane = threadIdx.x & 63;
     const SlCodedGeom &G = A.G;
-    const SlGroup g = A.groups[gi];
     const SlTensorDev td = A.tensors[g.tensor];
-    const long long c0 = td.chunk0 + (long long)g.local_group * SL_RICE_GROUP;
-    const int nc = (int)min((long long)SL_RICE_GROUP, td.n_chunks - (long long)g.local_group * SL_RICE_GROUP);
-    const unsigned nw = A.gwords[gi];
-    const unsigned long long base = before + A.goff[gi];    // below 2^32 by the plan's check
+    const long long c0 = g.chunk0;
+    const int nc = g.n_chunks;
 
     const int q = lane < nc ? (int)A.qsum[c0 + lane] : 0;
     const int nbits = lane < nc ? G.k + q : 0;
@@ -403,4 +389,13 @@ SL_DEV void sl_coded_place(const SlCodedArgs &A, long long gi, unsigned long lon
         if (G.qf == 1) entry[4 + lane] = (unsigned char)q;
         else reinterpret_cast<unsigned short *>(entry + 4)[lane] = (unsigned short)q;
     }
+}
+
+// Group gi (one wave; `run`: its LDS), after sl_coded_scan_block.  The wave of the last group writes the buffer header too.
+SL_DEV void sl_coded_place(const SlCodedArgs &A, long long gi, unsigned *run)
+{
+    const unsigned long long base = sl_coded_words_before(A, gi);
+    const unsigned nw = A.gwords[gi];
+    if (gi == A.n_groups - 1) sl_coded_header(base + nw, A.G.section, A.out);
+    sl_coded_place_at(A, A.groups[gi], base, nw, run);
 }

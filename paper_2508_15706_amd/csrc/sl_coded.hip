@@ -7,6 +7,8 @@
 // payload that already exists) put everything whose place follows from the tensor list - table
 // headers, remainder and value fields - straight into the buffer, and leave each chunk's bit
 // vector and quotient sum Q in the workspace, from where the placement steps of sl_coded.h take them.
+#include <algorithm>
+
 #include "sl_coded.h"
 
 int sl_rice_param(int k)
@@ -19,37 +21,51 @@ int sl_rice_param(int k)
 
 namespace {
 
-// Threads per tensor: 1024 read the groups of a large tensor in few turns (one of 24,000 chunks, k = 64, whole
-// transcode: 29.1 us, with 256 threads 30.5); with more tensors than such workgroups fit the chip together (two per
-// compute unit) they only take each other's places (tensors of 3 chunks: 700 19.0 / 16.8 us, 3000 50.3 / 40.4).
-#ifndef SL_SCAN_WIDE_UPTO
-#define SL_SCAN_WIDE_UPTO 512
-#endif
-template <int THREADS>
-__global__ void __launch_bounds__(THREADS) k_coded_scan_tensor(SlCodedArgs A)
+__global__ void __launch_bounds__(SL_SCAN_BLOCK) k_coded_scan(SlCodedArgs A)
 {
-    __shared__ unsigned wsum[THREADS / 64];
-    sl_coded_scan_tensor<THREADS>(A, (int)blockIdx.x, wsum);
+    __shared__ unsigned wsum[SL_SCAN_BLOCK / 64];
+    sl_coded_scan_block<SL_SCAN_BLOCK>(A, (long long)blockIdx.x, wsum);
 }
 
-__global__ void __launch_bounds__(64) k_coded_scan_list(SlCodedArgs A)
-{
-    sl_coded_scan_list(A.twords, A.n_tensors, A.G.section, A.out);
-}
-
-// SCANNED: sl_coded_scan_list has run; else every wave sums up the words of the tensors before its own, and one
-// more wave writes the buffer header (up to SL_PLACE_SUMS_UPTO tensors: the launch of the list scan takes 4 us).
-template <bool SCANNED>
 __global__ void __launch_bounds__(256) k_coded_place(SlCodedArgs A)
 {
     extern __shared__ __align__(16) unsigned place_lds[];
     const int wave = sl_uniform((int)(threadIdx.x >> 6));
     const long long gi = (long long)blockIdx.x * (blockDim.x >> 6) + wave;
-    if (!SCANNED && gi == A.n_groups) sl_coded_header(sl_coded_words_before(A.twords, A.n_tensors), A.G.section, A.out);
-    if (gi >= A.n_groups) return;
-    const int t = A.groups[gi].tensor;
-    const unsigned long long before = SCANNED ? A.twords[t] : sl_coded_words_before(A.twords, t);
-    sl_coded_place(A, gi, before, place_lds + (size_t)wave * (SL_RICE_GROUP * A.G.ua + 1));
+    if (gi < A.n_groups) sl_coded_place(A, gi, place_lds + (size_t)wave * (SL_RICE_GROUP * A.G.ua + 1));
+}
+
+// The header of a buffer without groups.
+__global__ void __launch_bounds__(64) k_coded_empty(SlCodedArgs A) { sl_coded_header(0, A.G.section, A.out); }
+
+// Both placement steps in one: every workgroup sums up the words of the groups before its own.  That is quadratic in the groups, but up
+// to SL_PLACE_FUSED_UPTO it takes two turns of 1024 threads, less than a launch of the scan (sl_rice_encode at k = 64, scan and placement /
+// this, us: 16 groups 8.6 / 7.7, 1024 9.9 / 8.9, 2048 11.65 / 10.95, 4096 14.7 / 14.75, 8192 20.7 / 25.3; 9.7, 16.3, 25.5, 44.0 and 80.6 us
+// when one workgroup went through all groups of a tensor).  The waves behind the first `placing` only help to sum up.
+__global__ void __launch_bounds__(1024) k_coded_place_fused(SlCodedArgs A, int placing)
+{
+    extern __shared__ __align__(16) unsigned place_lds[];
+    __shared__ unsigned long long part[16];
+    const int tid = threadIdx.x, lane = tid & 63, wave = sl_uniform(tid >> 6);
+    const long long first = (long long)blockIdx.x * placing;
+    unsigned long long sum = 0;
+    for (long long g = tid; g < first; g += 1024) sum += sl_coded_group_words(A, A.groups[g]);
+#pragma unroll
+    for (int l = 0; l < 6; ++l) sum += sl_partner(sum, l);
+    if (lane == 0) part[wave] = sum;
+    // (meanwhile: the words of the workgroup's own groups, by lane)
+    const unsigned own = lane < placing && first + lane < A.n_groups ? sl_coded_group_words(A, A.groups[first + lane]) : 0u;
+    const unsigned upto = (unsigned)sl_wave_iscan((int)own);
+    __syncthreads();
+    const long long gi = first + wave;
+    if (wave >= placing || gi >= A.n_groups) return;
+    unsigned long long base = 0;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) base += part[w];
+    const unsigned nw = (unsigned)__builtin_amdgcn_readlane((int)own, wave);
+    base += (unsigned)__builtin_amdgcn_readlane((int)upto, wave) - nw;
+    if (gi == A.n_groups - 1) sl_coded_header(base + nw, A.G.section, A.out);
+    sl_coded_place_at(A, A.groups[gi], base, nw, place_lds + (size_t)wave * (SL_RICE_GROUP * A.G.ua + 1));
 }
 
 // ------------------------------------------------------------------ transcoders
@@ -434,42 +450,40 @@ int launched()
 
 int slk_coded_scan(const sl_plan *p, unsigned char *out, unsigned char *ws, hipStream_t st)
 {
-    if (p->n_tensors <= SL_SCAN_WIDE_UPTO)
-        hipLaunchKernelGGL(k_coded_scan_tensor<1024>, dim3(p->n_tensors), dim3(1024), 0, st, sl_coded_args(p, out, ws));
-    else
-        hipLaunchKernelGGL(k_coded_scan_tensor<256>, dim3(p->n_tensors), dim3(256), 0, st, sl_coded_args(p, out, ws));
+    hipLaunchKernelGGL(k_coded_scan, dim3((unsigned)sl_scan_blocks(p->n_groups)), dim3(SL_SCAN_BLOCK), 0, st, sl_coded_args(p, out, ws));
     return launched();
 }
 
-#ifndef SL_PLACE_SUMS_UPTO
-#define SL_PLACE_SUMS_UPTO 1024
-#endif
-// The placement steps behind sl_coded_scan_tensor; `scanned`: the list scan has run as well.
-int slk_coded_place(const sl_plan *p, unsigned char *out, unsigned char *ws, bool scanned, hipStream_t st)
+int slk_coded_place(const sl_plan *p, unsigned char *out, unsigned char *ws, hipStream_t st)
 {
-    const SlCodedArgs A = sl_coded_args(p, out, ws);
-    if (!scanned && (p->n_tensors > SL_PLACE_SUMS_UPTO || p->n_groups == 0)) {
-        hipLaunchKernelGGL(k_coded_scan_list, dim3(1), dim3(64), 0, st, A);
-        const int rc = launched();
-        if (rc) return rc;
-        scanned = true;
-    }
-    if (p->n_groups == 0) return SL_OK;
     int wpb = 4;
     const size_t per_wave = sl_coded_place_words(p->cg) * sizeof(unsigned);
     while (wpb > 1 && per_wave * wpb > 65536) wpb >>= 1;
-    const long long waves = p->n_groups + (scanned ? 0 : 1);
-    hipLaunchKernelGGL(scanned ? k_coded_place<true> : k_coded_place<false>, dim3((unsigned)((waves + wpb - 1) / wpb)), dim3(64 * wpb),
-                       per_wave * wpb, st, A);
+    hipLaunchKernelGGL(k_coded_place, dim3((unsigned)((p->n_groups + wpb - 1) / wpb)), dim3(64 * wpb), per_wave * wpb, st,
+                       sl_coded_args(p, out, ws));
     return launched();
 }
 
+#ifndef SL_PLACE_FUSED_UPTO
+#define SL_PLACE_FUSED_UPTO 2048
+#endif
 // The steps that finish a coded buffer once its writers have run, as launches of their own.
 int slk_coded_finish(const sl_plan *p, unsigned char *out, unsigned char *ws, hipStream_t st)
 {
     int rc;
-    if (p->n_groups > 0 && (rc = slk_coded_scan(p, out, ws, st))) return rc;
-    return slk_coded_place(p, out, ws, false, st);
+    if (p->n_groups == 0) {
+        hipLaunchKernelGGL(k_coded_empty, dim3(1), dim3(64), 0, st, sl_coded_args(p, out, ws));
+        return launched();
+    }
+    if (p->n_groups <= SL_PLACE_FUSED_UPTO) {
+        const size_t per_wave = sl_coded_place_words(p->cg) * sizeof(unsigned);
+        const int placing = (int)std::max<size_t>(1, std::min<size_t>(16, 49152 / per_wave));
+        hipLaunchKernelGGL(k_coded_place_fused, dim3((unsigned)((p->n_groups + placing - 1) / placing)), dim3(1024), placing * per_wave, st,
+                           sl_coded_args(p, out, ws), placing);
+        return launched();
+    }
+    if ((rc = slk_coded_scan(p, out, ws, st))) return rc;
+    return slk_coded_place(p, out, ws, st);
 }
 
 namespace {

@@ -63,6 +63,7 @@ struct SlCodedGeom {
 struct SlGroup {            // one coding group of the index coder
     int tensor;
     int local_group;
+    int chunk0, n_chunks;   // its chunks, list order
 };
 
 // Per-tensor quantizer state produced during sl_compress.
@@ -116,7 +117,7 @@ struct sl_plan {
     SlCodedGeom cg;
     // workspace sections of the coded path: per-chunk bit vectors (cg.ua words each) and quotient
     // sums, per-group run lengths and offsets (words), per-tensor section offsets (words)
-    size_t ws_uvec, ws_qsum, ws_gwords, ws_goff, ws_twords;
+    size_t ws_uvec, ws_qsum, ws_gwords, ws_goff;
     // host copies
     SlTensorDev *h_tensors;
     // optional per-kernel timing (sl_profile_begin / sl_profile_end)
@@ -261,7 +262,7 @@ int slk_rice_decode(const sl_plan *p, const unsigned char *in, size_t in_bytes, 
 // them; the first; those behind it, or the last alone)
 int slk_coded_finish(const sl_plan *p, unsigned char *out, unsigned char *ws, hipStream_t st);
 int slk_coded_scan(const sl_plan *p, unsigned char *out, unsigned char *ws, hipStream_t st);
-int slk_coded_place(const sl_plan *p, unsigned char *out, unsigned char *ws, bool scanned, hipStream_t st);
+int slk_coded_place(const sl_plan *p, unsigned char *out, unsigned char *ws, hipStream_t st);
 // theta update from R coded payloads (mom != null: with the global momentum)
 int slk_apply_coded(const sl_plan *p, float *theta, float *mom, float mu, const void *const *payloads, const size_t *bytes,
                     int R, float lr, hipStream_t st);

@@ -174,16 +174,16 @@ SL_DEV SlTensorStat wave_stats(const SlTensorDev &td, const double *leafA, long 
 }
 
 // ------------------------------------------------------------------ kernel B
-// One workgroup per tensor: its statistics.  With the coded format, up to SL_PLACE_SHARED_UPTO, a second
-// row of workgroups takes the first placement step (independent of the statistics, and a launch of its
+// One workgroup per tensor: its statistics.  With the coded format, up to SL_PLACE_SHARED_UPTO, further
+// workgroups take the first placement step (independent of the statistics, and a launch of its
 // own would cost more than its work).
 __global__ void __launch_bounds__(RED_THREADS, 8)
-k_tensor_stats(const SlTensorDev *tensors, const double *leafA, long long n_chunks_total, int k,
+k_tensor_stats(const SlTensorDev *tensors, int n_tensors, const double *leafA, long long n_chunks_total, int k,
                SlTensorStat *tstat, SlCodedArgs C)
 {
     __shared__ RedShared sh;
-    if (blockIdx.y == 1) {
-        sl_coded_scan_tensor<RED_THREADS>(C, (int)blockIdx.x, reinterpret_cast<unsigned *>(sh.part[0]));
+    if ((int)blockIdx.x >= n_tensors) {
+        sl_coded_scan_block<RED_THREADS>(C, (int)blockIdx.x - n_tensors, reinterpret_cast<unsigned *>(sh.part[0]));
         return;
     }
     const SlTensorDev td = tensors[blockIdx.x];
@@ -209,11 +209,8 @@ struct CodeArgs {
     const SlCodedDesc *cdesc;
     int rem_bytes;
     int passes;             // passes of 512 entries over a chunk (1 up to k = 512)
-    unsigned code_blocks;   // workgroups with chunks; the placement steps in these launches: one more takes the list scan
-    unsigned long long *twords;
-    int n_tensors;
-    long long section;
-    // SHORT: what kernel B would have read; the workgroups behind the chunks' take its placement step
+    // SHORT: what kernel B would have read; the workgroups behind the chunks' `code_blocks` take its placement step
+    unsigned code_blocks;
     const double *leafA;
     const SlTensorDev *tensors;
     SlCodedArgs C;
@@ -356,13 +353,9 @@ __global__ void __launch_bounds__(256) k_codes(CodeArgs A)
     if constexpr (SHORT) {
         if (blockIdx.x >= A.code_blocks) {
             __shared__ unsigned wsum[4];
-            sl_coded_scan_tensor<256>(A.C, (int)(blockIdx.x - A.code_blocks), wsum);
+            sl_coded_scan_block<256>(A.C, (int)(blockIdx.x - A.code_blocks), wsum);
             return;
         }
-    }
-    if (blockIdx.x == A.code_blocks) {
-        if (wave == 0) sl_coded_scan_list(A.twords, A.n_tensors, A.section, A.coded);
-        return;
     }
     const long long cw = ((long long)blockIdx.x * (blockDim.x >> 6) + wave) * CPW;
     if (cw >= A.n_chunks) return;
@@ -536,13 +529,12 @@ codes_kernel codes_for(int bits, int log_lpc)
 // ------------------------------------------------------------------ kernel D
 // One workgroup per (tensor, bin): fixed-tree sum of the bin's leaves, integer count, centroid ->
 // LUT[b] in the tensor block's header.  With the placement steps in these launches (PLACE) further
-// workgroups take the last of them, `place_waves` groups each; without `scanned` they sum up the words of the tensors before
-// theirs, and the wave behind the last group writes the buffer header.
+// workgroups take the last of them, `place_waves` groups each.
 template <bool PLACE>
 __global__ void __launch_bounds__(RED_THREADS, 8)
 k_tensor_lut(const SlTensorDev *tensors, int n_tensors, const double *leafC, const unsigned *cnt,
              long long n_chunks_total, int hdr_bytes, int rec_bytes, int nbins, unsigned char *payload,
-             unsigned char *coded, int cfix, SlCodedArgs C, int place_waves, int scanned)
+             unsigned char *coded, int cfix, SlCodedArgs C, int place_waves)
 {
     __shared__ RedShared sh;
     extern __shared__ __align__(16) unsigned place_lds[];
@@ -551,13 +543,7 @@ k_tensor_lut(const SlTensorDev *tensors, int n_tensors, const double *leafC, con
     if (PLACE && (int)blockIdx.x >= n_tensors) {
         const int wave = sl_uniform(tid >> 6);
         const long long gi = ((long long)((int)blockIdx.x - n_tensors) * nbins + b) * place_waves + wave;
-        if (wave < place_waves && gi < C.n_groups) {
-            const int t = C.groups[gi].tensor;
-            sl_coded_place(C, gi, scanned ? C.twords[t] : sl_coded_words_before(C.twords, t),
-                           place_lds + (size_t)wave * (SL_RICE_GROUP * C.G.ua + 1));
-        } else if (wave < place_waves && gi == C.n_groups && !scanned) {
-            sl_coded_header(sl_coded_words_before(C.twords, C.n_tensors), C.G.section, C.out);
-        }
+        if (wave < place_waves && gi < C.n_groups) sl_coded_place(C, gi, place_lds + (size_t)wave * (SL_RICE_GROUP * C.G.ua + 1));
         return;
     }
     const SlTensorDev td = tensors[blockIdx.x];
@@ -594,16 +580,10 @@ k_tensor_lut(const SlTensorDev *tensors, int n_tensors, const double *leafC, con
     if (coded && b == 0 && tid < td.cblk_bytes - cused) coded[td.cblk_off + cused + tid] = 0;
 }
 
-// Unquantized values: there is no table, only the block padding is left to write; with the coded
-// format one more workgroup takes the list scan.
+// Unquantized values: there is no table, only the block padding is left to write.
 __global__ void __launch_bounds__(64)
-k_pad_blocks(const SlTensorDev *tensors, int n_tensors, int rec_bytes, unsigned char *payload, unsigned char *coded,
-             int cfix, SlCodedArgs C)
+k_pad_blocks(const SlTensorDev *tensors, int rec_bytes, unsigned char *payload, unsigned char *coded, int cfix)
 {
-    if ((int)blockIdx.x == n_tensors) {
-        sl_coded_scan_list(C.twords, C.n_tensors, C.G.section, C.out);
-        return;
-    }
     const SlTensorDev td = tensors[blockIdx.x];
     const long long used = td.n_chunks * (long long)rec_bytes;
     if ((long long)threadIdx.x < td.block_bytes - used) payload[td.pay_off + used + threadIdx.x] = 0;
@@ -681,13 +661,12 @@ int slk_residual(const sl_plan *p, float *e, const unsigned char *payload, hipSt
     return launch_residual(p, e, nullptr, payload, st);
 }
 
-// The coded format's placement steps share the launches of B, C and D up to so many (tensors x (bins + 4)): three
-// launches are saved, but every tensor pays for a second workgroup in B and, in each of its workgroups in D, for
-// the registers and the LDS of the placement (tensors of 3 chunks, k = 64, shared / launches of their own: 2 bits,
-// 300 tensors 37.6 / 39.8 us, 500 48.5 / 47.9, 3000 204 / 165; 1 bit, 500 41.3 / 42.2, 1000 62.8 / 56.1; 4 bits,
-// 150 47.2 / 47.3, 500 95.5 / 81.1; tensors of 40 chunks, 2 bits, 300 89.3 / 90.5, 1000 250 / 239).
+// The coded format's placement steps share the launches of B, C and D up to so many (tensors x (bins + 4)): one or two
+// launches are saved, but in D every tensor's workgroups pay for the registers and the LDS of the placement (tensors of 3
+// chunks, k = 64, shared / launches of their own: 2 bits, 100 tensors 22.0 / 23.7 us, 300 34.5 / 33.6, 3000 201 / 171; 1 bit, 100 19.4 / 22.0,
+// 300 30.6 / 30.2; 4 bits, 100 35.6 / 33.8, 500 94.6 / 76.6; tensors of 40 chunks, 2 bits, 300 130.0 / 130.5, 1000 374 / 367).
 #ifndef SL_PLACE_SHARED_UPTO
-#define SL_PLACE_SHARED_UPTO 3300
+#define SL_PLACE_SHARED_UPTO 2000
 #endif
 
 // Lists up to so many chunks whose tensors have at most SL_SHORT_TENSOR go without kernel B where no wave of the code kernel
@@ -714,9 +693,7 @@ int slk_quantize(const sl_plan *p, float *e, int skip_residual, unsigned char *p
 
     if (p->bits == 32) {
         // nothing to quantize: kernel A wrote the values into the records
-        if (coded && (rc = slk_coded_scan(p, coded, ws, st))) return rc;
-        hipLaunchKernelGGL(k_pad_blocks, dim3(p->n_tensors + (coded ? 1 : 0)), dim3(64), 0, st, p->d_tensors,
-                           p->n_tensors, p->rec_bytes, payload, coded, p->cg.cfix, placing);
+        hipLaunchKernelGGL(k_pad_blocks, dim3(p->n_tensors), dim3(64), 0, st, p->d_tensors, p->rec_bytes, payload, coded, p->cg.cfix);
         if ((rc = check_launch())) return rc;
         sl_prof_mark(p, SL_PROF_LUT, st);
         if (!skip_residual) {
@@ -724,7 +701,7 @@ int slk_quantize(const sl_plan *p, float *e, int skip_residual, unsigned char *p
             sl_prof_mark(p, SL_PROF_RESIDUAL, st);
         }
         if (coded) {
-            if ((rc = slk_coded_place(p, coded, ws, true, st))) return rc;
+            if ((rc = slk_coded_finish(p, coded, ws, st))) return rc;
             sl_prof_mark(p, SL_PROF_INDEX, st);
         }
         return SL_OK;
@@ -733,9 +710,10 @@ int slk_quantize(const sl_plan *p, float *e, int skip_residual, unsigned char *p
     const int log_lpc = sl_code_lanes_log2(k);
     const bool few = p->max_tensor_chunks <= SL_SHORT_TENSOR && p->n_chunks <= SL_SHORT_LIST &&
                      p->max_wave_tensors <= SL_SHORT_WAVE_TENSORS;
+    const unsigned scan_blocks = shared ? (unsigned)sl_scan_blocks(p->n_groups) : 0;
     if (!few) {
-        hipLaunchKernelGGL(k_tensor_stats, dim3(p->n_tensors, shared ? 2 : 1), dim3(RED_THREADS), 0, st, p->d_tensors,
-                           leafA, (long long)p->n_chunks, k, tstat, placing);
+        hipLaunchKernelGGL(k_tensor_stats, dim3(p->n_tensors + scan_blocks), dim3(RED_THREADS), 0, st, p->d_tensors, p->n_tensors, leafA,
+                            (long long)p->n_chunks, k, tstat, placing);
         if ((rc = check_launch())) return rc;
     }
     sl_prof_mark(p, SL_PROF_STATS, st);
@@ -757,13 +735,10 @@ int slk_quantize(const sl_plan *p, float *e, int skip_residual, unsigned char *p
     const codes_kernel fn = few ? codes_for<true>(p->bits, log_lpc) : codes_for<false>(p->bits, log_lpc);
     const long long per_block = 4ll * (64 >> log_lpc);
     C.code_blocks = (unsigned)((p->n_chunks + per_block - 1) / per_block);
-    C.twords = placing.twords;
-    C.n_tensors = p->n_tensors;
-    C.section = p->cg.section;
     C.leafA = leafA;
     C.tensors = p->d_tensors;
     C.C = placing;
-    hipLaunchKernelGGL(fn, dim3(C.code_blocks + (shared ? few ? p->n_tensors : 1 : 0)), dim3(256), 0, st, C);
+    hipLaunchKernelGGL(fn, dim3(C.code_blocks + (few ? scan_blocks : 0)), dim3(256), 0, st, C);
     if ((rc = check_launch())) return rc;
     sl_prof_mark(p, SL_PROF_CODES, st);
 
@@ -771,10 +746,10 @@ int slk_quantize(const sl_plan *p, float *e, int skip_residual, unsigned char *p
     const size_t per_wave_lds = sl_coded_place_words(p->cg) * sizeof(unsigned);
     const int place_waves = shared ? (int)std::max<size_t>(1, std::min<size_t>(RED_WAVES, 49152 / per_wave_lds)) : 0;
     const long long per_column = (long long)place_waves * nbins;      // groups that one column of workgroups takes
-    const long long place_columns = shared ? (p->n_groups + (few ? 1 : 0) + per_column - 1) / per_column : 0;
+    const long long place_columns = shared ? (p->n_groups + per_column - 1) / per_column : 0;
     hipLaunchKernelGGL(shared ? k_tensor_lut<true> : k_tensor_lut<false>, dim3((unsigned)(p->n_tensors + place_columns), nbins), dim3(RED_THREADS),
                        place_waves * per_wave_lds, st, p->d_tensors, p->n_tensors, leafC, cnt, (long long)p->n_chunks,
-                       p->hdr_bytes, p->rec_bytes, nbins, payload, coded, p->cg.cfix, placing, place_waves, few ? 0 : 1);
+                       p->hdr_bytes, p->rec_bytes, nbins, payload, coded, p->cg.cfix, placing, place_waves);
     if ((rc = check_launch())) return rc;
     sl_prof_mark(p, SL_PROF_LUT, st);
 
