@@ -33,6 +33,28 @@ struct RedShared {
     unsigned long long cnt;
 };
 
+// Sum w of super `su` (65536 leaves) of tree s, pushed on its binary-counter stack; the last one leaves the tree's sum.  One lane.
+SL_DEV void red_push(RedShared &sh, int s, long long su, long long supers, double w)
+{
+    auto push = [&](long long idx, double x) {
+        int lvl = 0;
+        while (idx & 1) {
+            x = sh.stack[s][lvl] + x;
+            idx >>= 1;
+            ++lvl;
+        }
+        sh.stack[s][lvl] = x;
+    };
+    push(su, w);
+    if (su == supers - 1) {
+        long long P = 1;
+        int top = 0;
+        while (P < supers) P <<= 1, ++top;
+        for (long long i = supers; i < P; ++i) push(i, 0.0);      // +0.0 padding
+        sh.result[s] = sh.stack[s][top];
+    }
+}
+
 // Adjacent-pair trees over leaf[s][0 .. n), s < NS, padded with +0.0 to a power of two (of at least
 // 65536; extra +0.0 leaves do not change a sum).  Called by all RED_THREADS threads of the block;
 // the sums come back to every thread.
@@ -47,15 +69,6 @@ __device__ void block_tree_sums(const double *const (&leaf)[NS], long long n, Re
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     constexpr long long SUPER = (long long)RED_TILE * RED_TILES;
     const long long supers = n > SUPER ? (n + SUPER - 1) / SUPER : 1;
-    auto push = [&](int s, long long idx, double w) {          // binary-counter stack over the supers
-        int lvl = 0;
-        while (idx & 1) {
-            w = sh.stack[s][lvl] + w;
-            idx >>= 1;
-            ++lvl;
-        }
-        sh.stack[s][lvl] = w;
-    };
     for (long long su = 0; su < supers; ++su) {
         const long long rest = n - su * SUPER;
         const int tiles = (int)min((long long)RED_TILES, (rest + RED_TILE - 1) / RED_TILE);
@@ -103,19 +116,97 @@ __device__ void block_tree_sums(const double *const (&leaf)[NS], long long n, Re
 #pragma unroll
             for (int q = 0; q < 4; ++q) p[q] = 4 * lane + q < have ? sh.part[wave][4 * lane + q] : 0.0;
             const double w = sl_wave_tree((p[0] + p[1]) + (p[2] + p[3]), 6);
-            if (lane == 0) {
-                push(wave, su, w);
-                if (su == supers - 1) {
-                    long long P = 1;
-                    int top = 0;
-                    while (P < supers) P <<= 1, ++top;
-                    for (long long i = supers; i < P; ++i) push(wave, i, 0.0);      // +0.0 padding
-                    sh.result[wave] = sh.stack[wave][top];
-                }
-            }
+            if (lane == 0) red_push(sh, wave, su, supers, w);
         }
         __syncthreads();
     }
+#pragma unroll
+    for (int s = 0; s < NS; ++s) sum[s] = sh.result[s];
+}
+
+// ---- large tensors
+// One workgroup reads the leaves of a tensor at the rate of one compute unit: 64 us for the statistics of 131,072 chunks, 50 for a
+// bin.  Where a tensor has more than SL_SPLIT_TENSOR chunks, a launch before B and one before D sum up pieces of 256
+// leaves, one wave each, and B and D read the pieces' sums.  Piece i of tensor t stands at (group0 >> 4) + t + i: a piece
+// begins with every sixteenth group of its tensor, and the t keeps neighbours apart.  (sl_compress of one matrix, k = 64, 2 bits, whole
+// tensors / pieces, us: 4096 chunks 53.7 / 55.5, 8192 91.3 / 90.9, 12,000 127.7 / 125.4, 16,384 159.6 / 155.1, 32,768 294 / 282, 131,072 1122 / 1061;
+// 4 bits 56.6 / 58.8, 95.0 / 94.5, 133.4 / 131.7, 164.4 / 160.8, 301 / 290, 1122 / 1072.)
+#ifndef SL_SPLIT_TENSOR
+#define SL_SPLIT_TENSOR 10240
+#endif
+struct RedPieces {
+    double *sum;            // [columns][stride]; null: no tensor of the list is split
+    unsigned *cnt;          // (D only)
+    long long stride;
+    SL_DEV bool split(long long n_chunks) const { return sum && n_chunks > SL_SPLIT_TENSOR; }
+    SL_DEV long long first(const SlTensorDev &td, int t) const { return (td.group0 >> 4) + t; }
+};
+
+__global__ void __launch_bounds__(256)
+k_piece_sums(const SlTensorDev *tensors, const SlGroup *groups, long long n_groups, const double *leaf, const unsigned *cnt,
+             long long n_chunks_total, RedPieces P)
+{
+    const int lane = threadIdx.x & 63;
+    const long long gi = 4ll * blockIdx.x + sl_uniform((int)(threadIdx.x >> 6));
+    if (gi >= n_groups) return;
+    const SlGroup g = groups[gi];
+    if (g.local_group & 15) return;
+    const SlTensorDev td = tensors[g.tensor];
+    if (!P.split(td.n_chunks)) return;
+    const int n = (int)min(256ll, td.n_chunks - 16ll * g.local_group), b = 4 * lane;
+    leaf += blockIdx.y * n_chunks_total + g.chunk0;
+    double x[4] = {0.0, 0.0, 0.0, 0.0};
+    unsigned c = 0;
+    if (b + 3 < n) {
+        const red_d2 lo = *reinterpret_cast<const red_d2 *>(leaf + b), hi = *reinterpret_cast<const red_d2 *>(leaf + b + 2);
+        x[0] = lo.x, x[1] = lo.y, x[2] = hi.x, x[3] = hi.y;
+    } else if (b < n) {
+        x[0] = leaf[b];
+        if (b + 1 < n) x[1] = leaf[b + 1];
+        if (b + 2 < n) x[2] = leaf[b + 2];
+    }
+    if (P.cnt) {
+        cnt += blockIdx.y * n_chunks_total + g.chunk0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            if (64 * q + lane < n) c += cnt[64 * q + lane];
+#pragma unroll
+        for (int l = 0; l < 6; ++l) c += (unsigned)sl_partner((int)c, l);
+    }
+    const double v = sl_wave_tree((x[0] + x[1]) + (x[2] + x[3]), 6);
+    if (lane == 0) {
+        const long long at = blockIdx.y * P.stride + (gi >> 4) + g.tensor;
+        P.sum[at] = v;
+        if (P.cnt) P.cnt[at] = c;
+    }
+}
+
+// The trees of block_tree_sums over n leaves, from the sums of their pieces; wave s takes tree s.
+template <int NS>
+__device__ void block_piece_sums(const double *const (&piece)[NS], long long n, RedShared &sh, double (&sum)[NS])
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const long long pieces = (n + 255) / 256, supers = (pieces + 255) / 256;
+    if (wave < NS) {
+        const double *const src = NS == 1 || wave == 0 ? piece[0] : piece[NS - 1];
+        double p[4], next[4];
+        auto load = [&](long long su, double (&x)[4]) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const long long i = 256 * su + 4 * lane + q;
+                x[q] = i < pieces ? src[i] : 0.0;
+            }
+        };
+        load(0, next);
+        for (long long su = 0; su < supers; ++su) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) p[q] = next[q];
+            load(su + 1, next);
+            const double w = sl_wave_tree((p[0] + p[1]) + (p[2] + p[3]), 6);
+            if (lane == 0) red_push(sh, wave, su, supers, w);
+        }
+    }
+    __syncthreads();
 #pragma unroll
     for (int s = 0; s < NS; ++s) sum[s] = sh.result[s];
 }
@@ -179,7 +270,7 @@ SL_DEV SlTensorStat wave_stats(const SlTensorDev &td, const double *leafA, long 
 // own would cost more than its work).
 __global__ void __launch_bounds__(RED_THREADS, 8)
 k_tensor_stats(const SlTensorDev *tensors, int n_tensors, const double *leafA, long long n_chunks_total, int k,
-               SlTensorStat *tstat, SlCodedArgs C)
+               SlTensorStat *tstat, SlCodedArgs C, RedPieces P)
 {
     __shared__ RedShared sh;
     if ((int)blockIdx.x >= n_tensors) {
@@ -187,9 +278,15 @@ k_tensor_stats(const SlTensorDev *tensors, int n_tensors, const double *leafA, l
         return;
     }
     const SlTensorDev td = tensors[blockIdx.x];
-    const double *const leaf[2] = {leafA + td.chunk0, leafA + n_chunks_total + td.chunk0};
     double S[2];
-    block_tree_sums<2>(leaf, td.n_chunks, sh, S);
+    if (P.split(td.n_chunks)) {
+        const double *const piece = P.sum + P.first(td, (int)blockIdx.x);
+        const double *const both[2] = {piece, piece + P.stride};
+        block_piece_sums<2>(both, td.n_chunks, sh, S);
+    } else {
+        const double *const leaf[2] = {leafA + td.chunk0, leafA + n_chunks_total + td.chunk0};
+        block_tree_sums<2>(leaf, td.n_chunks, sh, S);
+    }
     if (threadIdx.x == 0) tstat[blockIdx.x] = stat_of(td.n_chunks * (long long)k, S[0], S[1]);
 }
 
@@ -534,7 +631,7 @@ template <bool PLACE>
 __global__ void __launch_bounds__(RED_THREADS, 8)
 k_tensor_lut(const SlTensorDev *tensors, int n_tensors, const double *leafC, const unsigned *cnt,
              long long n_chunks_total, int hdr_bytes, int rec_bytes, int nbins, unsigned char *payload,
-             unsigned char *coded, int cfix, SlCodedArgs C, int place_waves)
+             unsigned char *coded, int cfix, SlCodedArgs C, int place_waves, RedPieces P)
 {
     __shared__ RedShared sh;
     extern __shared__ __align__(16) unsigned place_lds[];
@@ -550,16 +647,24 @@ k_tensor_lut(const SlTensorDev *tensors, int n_tensors, const double *leafC, con
     if (tid == 0) sh.cnt = 0ull;
     __syncthreads();
     unsigned long long part = 0;
-    const unsigned *cb = cnt + b * n_chunks_total + td.chunk0;
-    for (long long i = tid; i < td.n_chunks; i += RED_THREADS) part += cb[i];
-    if (64 * (tid >> 6) < td.n_chunks) {                        // (a wave without chunks has nothing to add)
+    const bool split = P.split(td.n_chunks);
+    const long long piece = b * P.stride + P.first(td, (int)blockIdx.x);
+    const unsigned *cb = split ? P.cnt + piece : cnt + b * n_chunks_total + td.chunk0;
+    const long long counts = split ? (td.n_chunks + 255) / 256 : td.n_chunks;
+    for (long long i = tid; i < counts; i += RED_THREADS) part += cb[i];
+    if (64 * (tid >> 6) < counts) {                        // (a wave without chunks has nothing to add)
 #pragma unroll
         for (int l = 0; l < 6; ++l) part += sl_partner(part, l);
     }
     if ((tid & 63) == 0 && part) atomicAdd(&sh.cnt, part);      // integer: order-free
-    const double *const leaf[1] = {leafC + b * n_chunks_total + td.chunk0};
     double S[1];
-    block_tree_sums<1>(leaf, td.n_chunks, sh, S);               // (its barriers are behind the additions above)
+    if (split) {                                                // (the barriers of both are behind the additions above)
+        const double *const sums[1] = {P.sum + piece};
+        block_piece_sums<1>(sums, td.n_chunks, sh, S);
+    } else {
+        const double *const leaf[1] = {leafC + b * n_chunks_total + td.chunk0};
+        block_tree_sums<1>(leaf, td.n_chunks, sh, S);
+    }
     const double Sb = S[0];
     if (tid == 0) {
         const unsigned long long nb = sh.cnt;
@@ -710,10 +815,21 @@ int slk_quantize(const sl_plan *p, float *e, int skip_residual, unsigned char *p
     const int log_lpc = sl_code_lanes_log2(k);
     const bool few = p->max_tensor_chunks <= SL_SHORT_TENSOR && p->n_chunks <= SL_SHORT_LIST &&
                      p->max_wave_tensors <= SL_SHORT_WAVE_TENSORS;
+    // Sums of pieces of large tensors: those of kernel A's leaves stand where C writes its own later, those of C's where A's have been.
+    const long long stride = p->n_groups / 16 + p->n_tensors + 1;
+    const bool split = p->max_tensor_chunks > SL_SPLIT_TENSOR && stride * (1 << p->bits) <= p->n_chunks;
+    const RedPieces PB = {split ? leafC : nullptr, nullptr, stride};
+    const RedPieces PD = {split ? leafA : nullptr, reinterpret_cast<unsigned *>(leafA + (stride << p->bits)), stride};
+    const unsigned piece_blocks = (unsigned)((p->n_groups + 3) / 4);
     const unsigned scan_blocks = shared ? (unsigned)sl_scan_blocks(p->n_groups) : 0;
+    if (split) {
+        hipLaunchKernelGGL(k_piece_sums, dim3(piece_blocks, 2), dim3(256), 0, st, p->d_tensors, p->d_groups, (long long)p->n_groups, leafA,
+                           nullptr, (long long)p->n_chunks, PB);
+        if ((rc = check_launch())) return rc;
+    }
     if (!few) {
         hipLaunchKernelGGL(k_tensor_stats, dim3(p->n_tensors + scan_blocks), dim3(RED_THREADS), 0, st, p->d_tensors, p->n_tensors, leafA,
-                            (long long)p->n_chunks, k, tstat, placing);
+                            (long long)p->n_chunks, k, tstat, placing, PB);
         if ((rc = check_launch())) return rc;
     }
     sl_prof_mark(p, SL_PROF_STATS, st);
@@ -743,13 +859,18 @@ int slk_quantize(const sl_plan *p, float *e, int skip_residual, unsigned char *p
     sl_prof_mark(p, SL_PROF_CODES, st);
 
     const int nbins = 1 << p->bits;
+    if (split) {
+        hipLaunchKernelGGL(k_piece_sums, dim3(piece_blocks, nbins), dim3(256), 0, st, p->d_tensors, p->d_groups, (long long)p->n_groups,
+                           leafC, cnt, (long long)p->n_chunks, PD);
+        if ((rc = check_launch())) return rc;
+    }
     const size_t per_wave_lds = sl_coded_place_words(p->cg) * sizeof(unsigned);
     const int place_waves = shared ? (int)std::max<size_t>(1, std::min<size_t>(RED_WAVES, 49152 / per_wave_lds)) : 0;
     const long long per_column = (long long)place_waves * nbins;      // groups that one column of workgroups takes
     const long long place_columns = shared ? (p->n_groups + per_column - 1) / per_column : 0;
     hipLaunchKernelGGL(shared ? k_tensor_lut<true> : k_tensor_lut<false>, dim3((unsigned)(p->n_tensors + place_columns), nbins), dim3(RED_THREADS),
                        place_waves * per_wave_lds, st, p->d_tensors, p->n_tensors, leafC, cnt, (long long)p->n_chunks,
-                       p->hdr_bytes, p->rec_bytes, nbins, payload, coded, p->cg.cfix, placing, place_waves);
+                       p->hdr_bytes, p->rec_bytes, nbins, payload, coded, p->cg.cfix, placing, place_waves, PD);
     if ((rc = check_launch())) return rc;
     sl_prof_mark(p, SL_PROF_LUT, st);
 

@@ -104,3 +104,22 @@ def test_lists_of_many_tensors(oracle, bits, n_tensors):
     for what, buf in (("compress", coded), ("transcoder", again)):
         size = sl.coded_size(buf)
         assert size == want.size and np.array_equal(buf[:size].cpu().numpy(), want), what
+
+
+@pytest.mark.parametrize("bits", [1, 2, 4])
+def test_pieces_of_large_tensors(oracle, bits):
+    """Tensors on both sides of 10,240 chunks, from where their sums are taken in pieces of 256: the last piece full and of one
+    leaf, pieces that begin at any group of the list, small tensors between."""
+    from paper_2508_15706_amd import binding as sl
+    descs, off, k = [], 0, 8
+    for chunks in (3, 10240, 10241, 40, 10496, 1):
+        descs.append((1, 4096 * chunks, off, sl.SL_LAYOUT_FLAT))
+        off += 4096 * chunks
+    delta = torch.randn(off, device="cuda", generator=torch.Generator(device="cuda").manual_seed(bits))
+    plan = sl.sl_plan_create_bits(descs, k, bits)
+    pay, coded, ws = sl.alloc_payload(plan), sl.alloc_coded(plan), sl.alloc_workspace(plan)
+    sl.sl_compress_coded(plan, None, delta, 0.95, pay, coded, ws, flags=sl.SL_COMPRESS_EF_FROZEN)
+    torch.cuda.synchronize()
+    want = oracle.compress_b(descs, k, bits, np.zeros(off, np.float32), delta.cpu().numpy(), 0.95, ef_frozen=True)
+    assert np.array_equal(pay[:plan.payload_bytes].cpu().numpy(), want)
+    assert np.array_equal(coded[:sl.coded_size(coded)].cpu().numpy(), oracle.rice_encode_b(descs, k, bits, want))
