@@ -30,7 +30,7 @@ struct RedShared {
     double part[2][RED_TILES * RED_WAVES];  // sums of 256 consecutive leaves
     double stack[2][40];
     double result[2];
-    unsigned long long cnt;
+    unsigned long long cnt[RED_WAVES];
 };
 
 // Sum w of super `su` (65536 leaves) of tree s, pushed on its binary-counter stack; the last one leaves the tree's sum.  One lane.
@@ -643,9 +643,7 @@ k_tensor_lut(const SlTensorDev *tensors, int n_tensors, const double *leafC, con
         if (wave < place_waves && gi < C.n_groups) sl_coded_place(C, gi, place_lds + (size_t)wave * (SL_RICE_GROUP * C.G.ua + 1));
         return;
     }
-    const SlTensorDev td = tensors[blockIdx.x];
-    if (tid == 0) sh.cnt = 0ull;
-    __syncthreads();
+    const SlTensorDev &td = tensors[blockIdx.x];             // (read again behind the sums: it would be kept in scratch memory across them)
     unsigned long long part = 0;
     const bool split = P.split(td.n_chunks);
     const long long piece = b * P.stride + P.first(td, (int)blockIdx.x);
@@ -656,7 +654,7 @@ k_tensor_lut(const SlTensorDev *tensors, int n_tensors, const double *leafC, con
 #pragma unroll
         for (int l = 0; l < 6; ++l) part += sl_partner(part, l);
     }
-    if ((tid & 63) == 0 && part) atomicAdd(&sh.cnt, part);      // integer: order-free
+    if ((tid & 63) == 0) sh.cnt[tid >> 6] = part;
     double S[1];
     if (split) {                                                // (the barriers of both are behind the additions above)
         const double *const sums[1] = {P.sum + piece};
@@ -666,8 +664,12 @@ k_tensor_lut(const SlTensorDev *tensors, int n_tensors, const double *leafC, con
         block_tree_sums<1>(leaf, td.n_chunks, sh, S);
     }
     const double Sb = S[0];
+    unsigned long long nb = tid < RED_WAVES ? sh.cnt[tid] : 0ull;
+    if (tid < 64) {
+#pragma unroll
+        for (int l = 0; l < 4; ++l) nb += sl_partner(nb, l);
+    }
     if (tid == 0) {
-        const unsigned long long nb = sh.cnt;
         float cen = nb ? (float)(Sb / (double)nb) : 0.0f;
         if (cen == 0.0f) cen = 0.0f;        // never -0.0f on the wire
         reinterpret_cast<float *>(payload + td.pay_off)[b] = cen;
