@@ -1,4 +1,4 @@
-// Arguments of kernel A of sl_compress, shared by its two forms: a wavefront per chunk (sl_select.hip) and, on short
+// Arguments of kernel A of sl_compress, shared by its two forms: a wavefront per chunk (sl_select_kernel.h) and, on short
 // lists, a workgroup per chunk (sl_select_group.hip).
 #pragma once
 #include "sl_device.h"

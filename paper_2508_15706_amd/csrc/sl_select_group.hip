@@ -1,4 +1,4 @@
-// Kernel A of sl_compress on short lists: error-feedback accumulate and chunk-wise Top-k as in sl_select.hip (Eq. (2)
+// Kernel A of sl_compress on short lists: error-feedback accumulate and chunk-wise Top-k as in sl_select_kernel.h (Eq. (2)
 // lines 1 and 2; Section 3.3 last paragraph), with all waves of a workgroup on ONE chunk.
 //
 // What bounds a short list is the chain of instructions of one wave, not memory: alone on its SIMD a wave issues a dependent
@@ -65,7 +65,7 @@ __global__ void __launch_bounds__(64 * WAVES, M > 0 ? 1 : 4) k_select_group(Sele
     float *sel_val = reinterpret_cast<float *>(smem + sel_off);
     unsigned short *sel_idx = reinterpret_cast<unsigned short *>(sel_val + k);
 
-    // what needs no input: the pending values' array (+0.0f where nothing is pending, see pend_half in sl_select.hip) and the
+    // what needs no input: the pending values' array (+0.0f where nothing is pending, see pend_half in sl_select_kernel.h) and the
     // coded form's words
     if (pend) {
 #pragma unroll
