@@ -154,6 +154,29 @@ inline int sl_chunks_per_group(const sl_plan *p)
 // without: from a quarter of the chunks on.  (Arenas that do not begin on 64 bytes are not looked at.)
 inline bool sl_rows_unaligned(const sl_plan *p) { return 4 * p->n_unaligned >= p->n_chunks; }
 
+// Waves per chunk of kernel A: several (sl_select_group.hip) on lists so short that the chain of a wave's instructions is longer than the
+// stream, one where the compute units are full without.  The work that each wave of a chunk repeats grows with k, and the less a call moves
+// the sooner one wave is enough: `streams` is 1 where it reads one arena and writes none or single entries (error feedback frozen, Sub-k), 2 for the
+// accumulate with the error update deferred, 3 where the update follows or the pseudo-gradient is formed from parameters.  One wave and the number
+// taken here, us, full chunks, each call on buffers that no cache holds (which length gains depends on the rows' stride: matrices of 64 rows, others
+// named): deferred, k = 64 256 chunks 21.1 -> 16.7, 512 22.4 -> 19.0, 1024 25.1 -> 24.1, 2048 34.0 -> 34.7, 6144 70.4 -> 69.0 (1024 columns 2048 41.2 ->
+// 36.3, 6144 77.6 -> 72.9; runs 74.1 -> 69.7), k = 256 1024 28.7 -> 29.0 (32.4 -> 29.2), k = 1024 1024 44.3 -> 36.8, 2048 55.8 -> 55.2; with the update k = 64 512 26.6 ->
+// 23.1, 2048 44.6 -> 41.5, 6144 94.4 -> 88.7, k = 256 2048 55.2 -> 54.1, k = 512 768 41.5 -> 41.1, k = 1024 2048 82.1 -> 77.2, 3072 100.1 -> 99.1; frozen k = 64 512 18.5 -> 17.0,
+// 1024 20.0 -> 19.4, k = 256 512 22.1 -> 20.8, k = 1024 1024 39.1 -> 31.7; Sub-k, k = 64 512 10.9 -> 9.4, 1024 13.3 -> 12.6, k = 1024 1024 32.2 -> 26.1.  Beyond the lines:
+// deferred k = 256 2048 38.6 -> 42.1, k = 512 1024 33.0 -> 34.3, k = 1024 3072 69.3 -> 73.5, coded 86.2 -> 94.0; with the update k = 512 1536 54.7 -> 58.0; frozen k = 64 2048 23.4 -> 26.2,
+// 6144 37.6 -> 47.8, k = 256 1024 23.6 -> 24.5, k = 1024 2048 44.5 -> 49.0; Sub-k, k = 64 1536 16.6 -> 17.4, 4096 28.2 -> 33.0, k = 4 4096 18.3 -> 24.0, k = 512 768
+// 21.5 -> 22.1.  Eight waves against four (deferred, k = 64): 256 chunks 16.9 -> 16.1, 512 18.8 -> 19.0, 768 20.8 -> 21.3.  Partial chunks gain more: 900 of 530 columns,
+// k = 32 37.4 -> 27.3; 1155 of 67, k = 64 55.4 -> 30.3.
+inline int sl_select_waves(int64_t n_chunks, int k, int streams)
+{
+    if (n_chunks <= 512) return 8;
+    const int64_t upto = k <= 128 ? (streams == 1 ? 1024 : 6144)
+                         : k <= 256 ? (streams == 1 ? 512 : streams == 2 ? 1024 : 2048)
+                         : k <= 512 ? (streams == 1 ? 512 : 768)
+                                    : streams == 1 ? 1024 : streams == 2 && k < 2048 ? 2048 : 3072;
+    return n_chunks <= upto ? 4 : 1;
+}
+
 // Waves per chunk of the aggregates: several (sl_apply_group.hip) on short lists with few workers, one else.  With a wave per worker
 // and a list of entries for each the work grows with R, and with k, where the other routes' does less.  One wave and the number taken
 // here, us (in a graph, lr update of full chunks): plain, k = 64, R = 4: 64 chunks 4.4 -> 3.7, 512 5.1 -> 4.5, 1024 9.0 -> 5.8, 2048 16.9 ->

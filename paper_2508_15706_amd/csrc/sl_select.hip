@@ -68,7 +68,8 @@ static int launch_select(const sl_plan *p, float *e, const float *delta, const f
     A.G = p->cg;
     A.uvec = (sub_only || !coded) ? nullptr : reinterpret_cast<unsigned *>(ws + p->ws_uvec);
     A.qsum = (sub_only || !coded) ? nullptr : reinterpret_cast<unsigned short *>(ws + p->ws_qsum);
-    const int waves = random ? 1 : sl_select_waves(p->n_chunks, k);
+    const int streams = sub_only || frozen ? 1 : update_follows || theta_local ? 3 : 2;
+    const int waves = random ? 1 : sl_select_waves(p->n_chunks, k, streams);
     // Without the streaming hint: unaligned rows, and error buffers that the caches still hold when step E writes at the selected places
     // (sl_compress, with the hint / without, us: 1500 chunks, k = 128 37.6 / 38.4, 2048 43.8 / 43.1, 4096 67.1 / 60.6, 8192 118.8 / 106.6, 12,288 165.7 / 165.6,
     // 16,384 210 / 235).  With several waves per chunk unaligned rows gain from it on longer lists only (deferred, k = 32: 4000 chunks of 1001 columns 70.3 /

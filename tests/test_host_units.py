@@ -9,7 +9,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 
 
-@pytest.mark.parametrize("name", ["chunk_groups", "edge_bounds", "threshold_search"])
+@pytest.mark.parametrize("name", ["chunk_groups", "edge_bounds", "list_rules", "threshold_search"])
 def test_host_unit(tmp_path, name):
     exe = str(tmp_path / name)
     # (signed overflow ends the program instead of wrapping)
