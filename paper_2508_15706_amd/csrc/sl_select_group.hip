@@ -384,23 +384,30 @@ __global__ void __launch_bounds__(64 * WAVES, M > 0 ? 1 : 4) k_select_group(Sele
             n_gt += n_above;
         }
     } else {
-        // ties without number: the waves count their own registers
+        // Ties without number: the waves count their own registers.  Mostly the keys that are too many are those at `from` itself (zeros,
+        // values of few levels): where k keys reach it and fewer lie above, it is the threshold (chunks of eight values among zeros, k = 64, us: 2048
+        // deferred 37.5, with a wave per chunk 66.6; 512 frozen 18.1 and 50.5, searched here too 63.1).
         auto reach = [&](int x) { return count_all([&](int y) { return y >= x; }); };
-        int lmax = key[0];
-#pragma unroll
-        for (int r = 1; r < NR; ++r) lmax = max(lmax, key[r]);
-        gather(sl_wave_max(lmax), all);
-        int hi = all[0];
-#pragma unroll
-        for (int w = 1; w < WAVES; ++w) hi = max(hi, all[w]);
-        if (sl_sample_serves(hi)) {
-            int n_lo = reach(0), beyond = hi + 1;
-            T = sl_find_kth(0, beyond, n_lo, n_gt, k, reach, exact);
+        const int above = n_above + ncand >= k ? count_all([&](int y) { return y > from; }) : k;
+        if (above < k) {
+            T = from, n_gt = above, exact = n_above + ncand == k;
         } else {
-            T = sl_bisect_kth(0, hi, k, reach, exact);
-            if (!exact) {
-                exact = reach(T) == k;
-                n_gt = count_all([&](int y) { return y > T; });
+            int lmax = key[0];
+#pragma unroll
+            for (int r = 1; r < NR; ++r) lmax = max(lmax, key[r]);
+            gather(sl_wave_max(lmax), all);
+            int hi = all[0];
+#pragma unroll
+            for (int w = 1; w < WAVES; ++w) hi = max(hi, all[w]);
+            if (sl_sample_serves(hi)) {
+                int n_lo = reach(0), beyond = hi + 1;
+                T = sl_find_kth(0, beyond, n_lo, n_gt, k, reach, exact);
+            } else {
+                T = sl_bisect_kth(0, hi, k, reach, exact);
+                if (!exact) {
+                    exact = reach(T) == k;
+                    n_gt = count_all([&](int y) { return y > T; });
+                }
             }
         }
     }

@@ -72,3 +72,38 @@ def test_both_forms(oracle, k, bits, chunks):
     sl.sl_sub_topk(plan, m)
     oracle.sub_topk(descs, k, want_m)
     same(m, want_m)
+
+
+@pytest.mark.parametrize("k, chunks", [(64, 500), (1500, 40), (256, 600), (1500, 600)])
+def test_ties_without_number(oracle, k, chunks):
+    """More keys than the list of candidates holds share the threshold, or the lower end of the bracket is not the threshold."""
+    from paper_2508_15706_amd import binding as sl
+    rng, n = np.random.default_rng(k), 4096 * chunks
+    x = rng.normal(0, 1e-3, (chunks, 4096)).astype(np.float32)
+    sign = np.where(rng.random((7, 4096)) < 0.5, -1, 1).astype(np.float32)
+    x[0] = 0.0
+    x[0, rng.permutation(4096)[:8]] = 1e-3       # few values among zeros
+    x[1] = np.float32(1e-3) * sign[1]            # one magnitude
+    x[2] = 0.0
+    order = rng.permutation(4096)
+    x[2, order[:3000]], x[2, order[:k + 10]] = 1e-3, 2e-3    # the upper level holds a few more than k
+    x[2] *= sign[2]
+    x[3] = 0.0
+    # exactly k keys of one magnitude, the sample's positions (those of eight waves) all among them
+    wave, lane = np.divmod(np.arange(512), 64)
+    sample = 256 * (2 * wave + ((lane & 7) >> 2)) + 4 * lane + (lane & 3)
+    rest = np.setdiff1d(rng.permutation(4096), sample)
+    x[3, np.concatenate([sample, rest])[:k]] = 1e-3
+    x[4] = 0.0
+    x[5] = np.float32(3e38) * sign[5]
+    x[6] = np.round(x[6] * 2e3) / 2e3            # levels
+    x = x.reshape(-1)
+    descs = [(64 * chunks, 64, 0, 0)]
+    plan = sl.sl_plan_create(descs, k)
+    ws, pay = sl.alloc_workspace(plan), sl.alloc_payload(plan)
+    sl.sl_compress(plan, None, torch.from_numpy(x).cuda(), 0.95, pay, ws, flags=sl.SL_COMPRESS_EF_FROZEN)
+    assert np.array_equal(pay[:plan.payload_bytes].cpu().numpy(), oracle.compress_b(descs, k, 2, np.zeros(n, np.float32), x, 0.95, ef_frozen=True))
+    m, want = torch.from_numpy(x.copy()).cuda(), x.copy()
+    sl.sl_sub_topk(plan, m)
+    oracle.sub_topk(descs, k, want)
+    np.testing.assert_array_equal(m.cpu().numpy().view(np.uint32), want.view(np.uint32))
