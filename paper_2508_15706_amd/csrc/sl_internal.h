@@ -177,6 +177,17 @@ inline int sl_select_waves(int64_t n_chunks, int k, int streams)
     return n_chunks <= upto ? 4 : 1;
 }
 
+// Does the accumulate leave the streaming hint out because the error update follows, which writes at the selected places?  It pays where
+// those are many and the buffer is still in the caches then, and fits them beside the pseudo-gradient; it costs the accumulate what the hint is worth, most where
+// little is selected.  sl_compress on buffers that no cache holds before the call, with the hint / without, us: k = 16 4096 chunks 57.9 / 63.7, k = 64 64.0 / 67.8,
+// k = 256 79.2 / 81.6, k = 512 3072 79.9 / 80.7, 4096 99.8 / 97.8, 6144 144 / 132, 9216 201 / 185, 10,240 199 / 203, k = 1024 4096 129 / 126, 9216 237 / 218, k = 1536 8192 222 / 209, k = 2048
+// 6144 206 / 208; fp32 values, k = 512 6144 131 / 113; from parameters k = 512 4096 102 / 107, k = 1024 9216 238 / 245.  (Called again on the same buffers it pays
+// at every k, as the next call then finds them in the caches: 4096, k = 64 62.0 / 53.3.  A training step between two calls leaves nothing there.)
+inline bool sl_update_kept(int64_t n_chunks, int k, bool params)
+{
+    return !params && k > 256 && k <= 1536 && n_chunks >= 4096 && n_chunks <= 9216;
+}
+
 // Waves per chunk of the aggregates: several (sl_apply_group.hip) on short lists with few workers, one else.  With a wave per worker
 // and a list of entries for each the work grows with R, and with k, where the other routes' does less.  One wave and the number taken
 // here, us (in a graph, lr update of full chunks): plain, k = 64, R = 4: 64 chunks 4.4 -> 3.7, 512 5.1 -> 4.5, 1024 9.0 -> 5.8, 2048 16.9 ->

@@ -14,9 +14,7 @@ static unsigned host_fmix32(unsigned h)
     return h;
 }
 
-#define SL_UPDATE_KEPT_FROM 2048
 #define SL_PIECES_FROM 16384
-#define SL_UPDATE_KEPT_UPTO 9216
 static int launch_select(const sl_plan *p, float *e, const float *delta, const float *theta_local, float beta,
                          int frozen, const unsigned char *pending, unsigned char *payload, unsigned char *coded,
                          unsigned char *ws, bool update_follows, bool sub_only, bool random, unsigned seed, hipStream_t st)
@@ -70,12 +68,10 @@ static int launch_select(const sl_plan *p, float *e, const float *delta, const f
     A.qsum = (sub_only || !coded) ? nullptr : reinterpret_cast<unsigned short *>(ws + p->ws_qsum);
     const int streams = sub_only || frozen ? 1 : update_follows || theta_local ? 3 : 2;
     const int waves = random ? 1 : sl_select_waves(p->n_chunks, k, streams);
-    // Without the streaming hint: unaligned rows, and error buffers that the caches still hold when step E writes at the selected places
-    // (sl_compress, with the hint / without, us: 1500 chunks, k = 128 37.6 / 38.4, 2048 43.8 / 43.1, 4096 67.1 / 60.6, 8192 118.8 / 106.6, 12,288 165.7 / 165.6,
-    // 16,384 210 / 235).  With several waves per chunk unaligned rows gain from it on longer lists only (deferred, k = 32: 4000 chunks of 1001 columns 70.3 /
-    // 60.2, 900 of 530 29.4 / 30.7).
-    const bool keep = update_follows && p->n_chunks >= SL_UPDATE_KEPT_FROM && p->n_chunks <= SL_UPDATE_KEPT_UPTO;
-    if (waves > 1) return slk_select_group(A, sub_only, waves, keep || (sl_rows_unaligned(p) && p->n_chunks > 2048 && !sub_only), st);
+    // Without the streaming hint: unaligned rows, and error buffers that the caches still hold when the update follows (sl_update_kept).  With several
+    // waves per chunk unaligned rows gain from it on longer lists only (deferred, k = 32: 4000 chunks of 1001 columns 70.3 / 60.2, 900 of 530 29.4 / 30.7).
+    const bool keep = update_follows && sl_update_kept(p->n_chunks, k, theta_local != nullptr);
+    if (waves > 1) return slk_select_group(A, sub_only, waves, sl_rows_unaligned(p) && p->n_chunks > 2048 && !sub_only, st);
     // (one chunk per workgroup where the LDS of four does not fit)
     const int wpb = 4 * (size_t)A.lds_per_wave > 65536 ? 1 : random && k <= 128 ? sl_chunks_per_group(p) : 4;
     const dim3 grid((unsigned)((p->n_chunks + wpb - 1) / wpb)), block(64 * wpb);

@@ -25,9 +25,20 @@ static void selection()
     for (const auto &r : rows) expect("selection", r.n, r.k, sl_select_waves(r.n, r.k, r.streams), r.want);
 }
 
+// the eager accumulate without the streaming hint
+static void kept()
+{
+    const struct { int n, k, params, want; } rows[] = {
+        {2048, 64, 0, 0}, {4096, 16, 0, 0}, {4096, 256, 0, 0}, {8192, 128, 0, 0}, {9216, 4, 0, 0}, {3072, 512, 0, 0}, {4096, 512, 0, 1}, {9216, 1024, 0, 1},
+        {9217, 1024, 0, 0}, {8192, 1536, 0, 1}, {6144, 2048, 0, 0}, {4096, 512, 1, 0}, {9216, 1024, 1, 0}, {6144, 64, 1, 0},
+    };
+    for (const auto &r : rows) expect(r.params ? "kept, parameters" : "kept", r.n, r.k, sl_update_kept(r.n, r.k, r.params), r.want);
+}
+
 int main()
 {
     selection();
+    kept();
     if (failures) return 1;
     std::puts("ok");
     return 0;
