@@ -741,7 +741,7 @@ int slk_apply(const sl_plan *p, float *theta, float *mom, float mu, const void *
     static const kernel_t table[2][2][2][5] = {SL_APPLY_KINDS(false), SL_APPLY_KINDS(true)};
 #undef SL_APPLY_KINDS
 #undef SL_APPLY_ROUTES
-    const kernel_t fn = table[sl_rows_unaligned(p) ? 1 : 0][two ? 1 : 0][mom ? 1 : 0][halves ? 4 : route];   // (two halves: entry by entry only)
+    const kernel_t fn = table[sl_rows_unaligned(p, sl_apply_kept_from(p, mom != nullptr)) ? 1 : 0][two ? 1 : 0][mom ? 1 : 0][halves ? 4 : route];   // (two halves: entry by entry only)
     if (lds > 65536) {
         hipError_t aerr = hipFuncSetAttribute(reinterpret_cast<const void *>(fn),
                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);

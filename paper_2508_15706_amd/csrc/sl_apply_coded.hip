@@ -859,7 +859,7 @@ int slk_apply_coded(const sl_plan *p, float *theta, float *mom, float mu, const 
       {k_apply_coded<true, false, true, KEEP>, k_apply_coded<true, true, true, KEEP>}}}
     static const kernel_t table[2][2][2][2] = {SL_CAPPLY_KINDS(false), SL_CAPPLY_KINDS(true)};
 #undef SL_CAPPLY_KINDS
-    const kernel_t fn = table[sl_rows_unaligned(p) ? 1 : 0][p->bits == 2 ? 1 : 0][lists ? 1 : 0][mom ? 1 : 0];
+    const kernel_t fn = table[sl_rows_unaligned(p, sl_apply_kept_from(p, mom != nullptr)) ? 1 : 0][p->bits == 2 ? 1 : 0][lists ? 1 : 0][mom ? 1 : 0];
     if (lds > 65536) {
         hipError_t aerr = hipFuncSetAttribute(reinterpret_cast<const void *>(fn),
                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);

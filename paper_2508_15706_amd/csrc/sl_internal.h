@@ -150,9 +150,29 @@ inline int sl_chunks_per_group(const sl_plan *p)
     return turns <= 2 && 3 * groups <= 2 * SL_COMPUTE_UNITS * turns && p->n_partial * 32 < p->n_chunks ? 1 : 4;
 }
 
+#define SL_DENSE_SHORT_BELOW 5120         // see k_dense_avg_apply
+
 // Do the accesses of this list go without the streaming hint (sl_access_load)?  Unaligned rows lose up to half with it, aligned ones a tenth
-// without: from a quarter of the chunks on.  (Arenas that do not begin on 64 bytes are not looked at.)
-inline bool sl_rows_unaligned(const sl_plan *p) { return 4 * p->n_unaligned >= p->n_chunks; }
+// without, so it is a matter of their share, `percent` of the chunks at least.  On buffers that no cache holds, rows of 1001 columns among aligned ones, with
+// the hint / without, us: aggregates (k = 64, R = 4) 1920 chunks, 25 % 18.4 / 20.1, 50 % 19.7 / 20.3, 75 % 20.7 / 20.3; 9600, 15 % 62.8 / 65.3, 25 % 66.5 / 66.5, 35 %
+// 69.7 / 66.9, 25,600, 25 % 171 / 160; with momentum 1920, 35 % 32.9 / 34.2, 50 % 34.6 / 34.3, 5120, 25 % 76.4 / 76.2, 35 % 79.8 / 76.8.  Dense streams: direction 5120, 25 % 76.7 / 79.8, 35 % 79.9 / 80.7, 50 % 84.3 /
+// 82.6; average of four 9600, 25 % 185 / 192, 35 % 188 / 190, 50 % 194 / 188.  (Arenas that do not begin on 64 bytes are not looked at.)
+inline bool sl_rows_unaligned(const sl_plan *p, int percent) { return 100 * p->n_unaligned >= percent * p->n_chunks; }
+inline int sl_apply_kept_from(const sl_plan *p, bool mom) { return p->n_chunks > (mom ? 4096 : 8192) ? 25 : 50; }     // aggregates
+inline int sl_dense_kept_from(const sl_plan *p) { return p->n_chunks < SL_DENSE_SHORT_BELOW ? 25 : 40; }              // dense average
+#define SL_DIRECTION_KEPT_FROM 40
+
+// The same for the accumulate (`streams` as for sl_select_waves; none gains that only reads: frozen, 25,600 chunks, all unaligned, k = 32 136 / 140, 12,800 79.2 / 78.4):
+// deferred, k = 128 2560 chunks, 25 % 48.5 / 50.9, 50 % 50.9 / 51.4, 75 % 51.9 / 51.4; 9600, 25 % 120 / 122, 50 % 124 / 123, 75 % 133 / 127; k = 64 25,600, 25 % 272 / 283,
+// 50 % 289 / 277, 75 % 307 / 283.  Where the update follows, k = 64 9600, 25 % 140 / 147, 75 % 155 / 146, 25,600, 25 % 330 / 371, 75 % 361 / 363, all 374 / 362; k = 512 5120, 25 % 132 /
+// 120, 9600, 25 % 225 / 197, 12,160, 25 % 265 / 251, 16,000, 75 % 384 / 358, 25,600, 25 % 551 / 580, 50 % 520 / 583, 75 % 609 / 591, all 643 / 628; from parameters k = 64 25,600, 25 %
+// 405 / 459, 75 % 465 / 457; k = 512 9600, 25 % 231 / 235, 75 % 252 / 242.
+inline bool sl_select_unaligned(const sl_plan *p, int streams, bool update_follows, bool params)
+{
+    if (streams == 1) return false;
+    if (update_follows && p->n_chunks > 12288) return sl_rows_unaligned(p, 75);
+    return sl_rows_unaligned(p, update_follows && !params && p->k > 256 && p->k <= 1536 ? 25 : 50);
+}
 
 // Waves per chunk of kernel A: several (sl_select_group.hip) on lists so short that the chain of a wave's instructions is longer than the
 // stream, one where the compute units are full without.  The work that each wave of a chunk repeats grows with k, and the less a call moves

@@ -121,7 +121,6 @@ struct DenseArgs {
 // with fewer loads open at a time (6144 98.6 / 99.5, 16384 260 / 273, 1.8B list 7362 / 7454), and so are ragged ones at every length (32,000 x
 // 100 19.0 / 20.0, 200 x 530 15.4 / 16.2): the loads of their partial chunks come one by one, and neighbours that share lines should
 // meet.  The line lies between the two.
-#define SL_DENSE_SHORT_BELOW 5120
 template <bool NESTEROV, bool SHORT, bool KEEP>
 __global__ void __launch_bounds__(256) k_dense_avg_apply(DenseArgs A)
 {
@@ -220,7 +219,7 @@ int slk_lom_direction(const sl_plan *p, float *m, const float *delta, float mu, 
     A.n_chunks = p->n_chunks;
     const dim3 grid((unsigned)((p->n_chunks + 3) / 4)), block(256);
     A.order = sl_order(p, grid.x);
-    hipLaunchKernelGGL(sl_rows_unaligned(p) ? k_lom_direction<true> : k_lom_direction<false>, grid, block, SL_STREAM_LDS, st, A);
+    hipLaunchKernelGGL(sl_rows_unaligned(p, SL_DIRECTION_KEPT_FROM) ? k_lom_direction<true> : k_lom_direction<false>, grid, block, SL_STREAM_LDS, st, A);
     return check_launch();
 }
 
@@ -246,6 +245,6 @@ int slk_dense_avg_apply(const sl_plan *p, float *theta, float *mom, const float 
                               {k_dense_avg_apply<true, false, KEEP>, k_dense_avg_apply<true, true, KEEP>}}
     static const kernel_t table[2][2][2] = {SL_DENSE_KINDS(false), SL_DENSE_KINDS(true)};
 #undef SL_DENSE_KINDS
-    hipLaunchKernelGGL(table[sl_rows_unaligned(p) ? 1 : 0][mom ? 1 : 0][is_short ? 1 : 0], grid, block, SL_STREAM_LDS, st, A);
+    hipLaunchKernelGGL(table[sl_rows_unaligned(p, sl_dense_kept_from(p)) ? 1 : 0][mom ? 1 : 0][is_short ? 1 : 0], grid, block, SL_STREAM_LDS, st, A);
     return check_launch();
 }

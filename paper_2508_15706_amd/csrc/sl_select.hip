@@ -71,7 +71,8 @@ static int launch_select(const sl_plan *p, float *e, const float *delta, const f
     // Without the streaming hint: unaligned rows, and error buffers that the caches still hold when the update follows (sl_update_kept).  With several
     // waves per chunk unaligned rows gain from it on longer lists only (deferred, k = 32: 4000 chunks of 1001 columns 70.3 / 60.2, 900 of 530 29.4 / 30.7).
     const bool keep = update_follows && sl_update_kept(p->n_chunks, k, theta_local != nullptr);
-    if (waves > 1) return slk_select_group(A, sub_only, waves, sl_rows_unaligned(p) && p->n_chunks > 2048 && !sub_only, st);
+    const bool unaligned = sl_select_unaligned(p, streams, update_follows, theta_local != nullptr);
+    if (waves > 1) return slk_select_group(A, sub_only, waves, unaligned && p->n_chunks > 2048, st);
     // (one chunk per workgroup where the LDS of four does not fit)
     const int wpb = 4 * (size_t)A.lds_per_wave > 65536 ? 1 : random && k <= 128 ? sl_chunks_per_group(p) : 4;
     const dim3 grid((unsigned)((p->n_chunks + wpb - 1) / wpb)), block(64 * wpb);
@@ -81,7 +82,7 @@ static int launch_select(const sl_plan *p, float *e, const float *delta, const f
     select_kernel fn;
     if (sub_only) fn = select_for<2, false, false>(k);
     else if (random) fn = two ? k_select<0, 0, true, false, true> : k_select<0, 0, false, false, true>;
-    else fn = keep || sl_rows_unaligned(p) ? sl_select_kept(k, two, theta_local != nullptr) : select_for<false>(k, two, theta_local != nullptr);
+    else fn = keep || unaligned ? sl_select_kept(k, two, theta_local != nullptr) : select_for<false>(k, two, theta_local != nullptr);
     hipLaunchKernelGGL(fn, grid, block, lds, st, A);
     hipError_t err = hipGetLastError();
     if (err != hipSuccess) {

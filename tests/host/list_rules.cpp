@@ -35,10 +35,32 @@ static void kept()
     for (const auto &r : rows) expect(r.params ? "kept, parameters" : "kept", r.n, r.k, sl_update_kept(r.n, r.k, r.params), r.want);
 }
 
+// shares of unaligned chunks from which the streaming hint is left out
+static void unaligned()
+{
+    const struct { int n, percent, k, streams, update, params, select, apply, mom, direction, dense; } rows[] = {
+        {1920, 24, 64, 2, 0, 0, 0, 0, 0, 0, 0}, {1920, 35, 64, 2, 0, 0, 0, 0, 0, 0, 1}, {1920, 50, 64, 2, 0, 0, 1, 1, 1, 1, 1},
+        {5120, 25, 64, 2, 0, 0, 0, 0, 1, 0, 0}, {5120, 39, 128, 3, 1, 0, 0, 0, 1, 0, 0}, {5120, 40, 128, 3, 1, 0, 0, 0, 1, 1, 1},
+        {9600, 24, 512, 3, 1, 0, 0, 0, 0, 0, 0}, {9600, 25, 512, 3, 1, 0, 1, 1, 1, 0, 0}, {9600, 25, 512, 3, 1, 1, 0, 1, 1, 0, 0}, {9600, 25, 256, 3, 1, 0, 0, 1, 1, 0, 0},
+        {9600, 50, 1024, 3, 1, 1, 1, 1, 1, 1, 1}, {9600, 100, 64, 1, 0, 0, 0, 1, 1, 1, 1}, {25600, 25, 64, 2, 0, 0, 0, 1, 1, 0, 0}, {25600, 50, 64, 2, 0, 0, 1, 1, 1, 1, 1},
+        {25600, 50, 256, 3, 0, 1, 1, 1, 1, 1, 1}, {12288, 50, 512, 3, 1, 0, 1, 1, 1, 1, 1}, {25600, 50, 512, 3, 1, 0, 0, 1, 1, 1, 1}, {25600, 75, 512, 3, 1, 1, 1, 1, 1, 1, 1},
+    };
+    for (const auto &r : rows) {
+        sl_plan p{};
+        p.k = r.k, p.n_chunks = r.n, p.n_unaligned = (int64_t)r.n * r.percent / 100;
+        expect("unaligned, selection", r.n, r.k, sl_select_unaligned(&p, r.streams, r.update != 0, r.params != 0), r.select);
+        expect("unaligned, aggregate", r.n, r.k, sl_rows_unaligned(&p, sl_apply_kept_from(&p, false)), r.apply);
+        expect("unaligned, momentum", r.n, r.k, sl_rows_unaligned(&p, sl_apply_kept_from(&p, true)), r.mom);
+        expect("unaligned, direction", r.n, r.k, sl_rows_unaligned(&p, SL_DIRECTION_KEPT_FROM), r.direction);
+        expect("unaligned, dense", r.n, r.k, sl_rows_unaligned(&p, sl_dense_kept_from(&p)), r.dense);
+    }
+}
+
 int main()
 {
     selection();
     kept();
+    unaligned();
     if (failures) return 1;
     std::puts("ok");
     return 0;

@@ -1,5 +1,5 @@
 """Long lists of matrices whose rows begin anywhere (their kernels go without the streaming hint, one wave per chunk), with
-last columns of every remainder, and lists in which a quarter of the chunks, or one chunk less, are such: accumulate (eager, deferred
+last columns of every remainder, and lists in which a quarter, two fifths or a half of the chunks, or one chunk less, are such: accumulate (eager, deferred
 with a pending record, from parameters), both aggregates with and without momentum, the dense steps, against the oracle."""
 import numpy as np
 import pytest
@@ -12,6 +12,9 @@ CASES = [(16, 2, 3, [(64 * 100, 64 * 63 + 1, 1)]), (64, 4, 2, [(64 * 99 + 30, 64
          (32, 2, 9, [(64 * 3100, 67, 1), (66, 131, 1)]), (128, 32, 2, [(64 * 98 + 5, 64 * 63 + 30, 1)]), (200, 2, 12, [(64 * 40, 64 * 63 + 5, 1)]),
          (264, 1, 2, [(64 * 30, 64 * 31 + 10, 1)]), (520, 2, 8, [(64 * 55, 64 * 63 + 9, 1)]), (256, 3, 2, [(64 * 45, 64 * 63 + 20, 1)]),
          (64, 2, 2, [(64, 64 * 1575 + 1, 1), (64 * 4728, 64, 1)]), (64, 2, 2, [(64, 64 * 1575 + 1, 1), (64 * 4729, 64, 1)])]
+# the shares from which the kernels go without the hint: two fifths, a half; a quarter of longer lists
+CASES += [(64, 2, 9, [(64, 64 * 1575 + 1, 1), (64 * rest, 64, 1)]) for rest in (1576, 1577, 2364, 2365)]
+CASES += [(32, 2, 9, [(64, 64 * 2048 + 1, 1), (64 * rest, 64, 1)]) for rest in (6147, 6148)]
 
 
 @pytest.mark.parametrize("case", range(len(CASES)))
