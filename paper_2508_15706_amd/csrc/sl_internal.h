@@ -208,6 +208,12 @@ inline bool sl_update_kept(int64_t n_chunks, int k, bool params)
     return !params && k > 256 && k <= 1536 && n_chunks >= 4096 && n_chunks <= 9216;
 }
 
+// Does Sub-k write whole 64-byte pieces back?  Where the caches do not hold the buffer, a write of four bytes costs the memory a read and a write of its piece;
+// with few of them looking at every piece costs more.  Single entries / pieces, us, buffers that no cache holds: k = 4 16,384 chunks 51.8 / 55.3, 49,152 147 / 152, k = 8 16,384 56.9 / 58.8,
+// 49,152 159 / 162, k = 16 16,384 64.1 / 63.4, 49,152 177 / 172, k = 64 12,288 64.7 / 58.5, 16,384 84.1 / 74.2, 49,152 258 / 195, k = 128 49,152 348 / 220, k = 512 16,384 167 / 117, 49,152 496 / 311.
+// (Just written before the call: k = 64 12,288 54.6 / 60.4, 16,384 73.8 / 76.2, 20,480 94.7 / 91.6.)
+inline bool sl_subk_pieces(int64_t n_chunks, int k) { return k >= 16 && n_chunks >= 16384; }
+
 // Waves per chunk of the aggregates: several (sl_apply_group.hip) on short lists with few workers, one else.  With a wave per worker
 // and a list of entries for each the work grows with R, and with k, where the other routes' does less.  One wave and the number taken
 // here, us (in a graph, lr update of full chunks): plain, k = 64, R = 4: 64 chunks 4.4 -> 3.7, 512 5.1 -> 4.5, 1024 9.0 -> 5.8, 2048 16.9 ->

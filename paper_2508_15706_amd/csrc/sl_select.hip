@@ -14,7 +14,6 @@ static unsigned host_fmix32(unsigned h)
     return h;
 }
 
-#define SL_PIECES_FROM 16384
 static int launch_select(const sl_plan *p, float *e, const float *delta, const float *theta_local, float beta,
                          int frozen, const unsigned char *pending, unsigned char *payload, unsigned char *coded,
                          unsigned char *ws, bool update_follows, bool sub_only, bool random, unsigned seed, hipStream_t st)
@@ -56,7 +55,7 @@ static int launch_select(const sl_plan *p, float *e, const float *delta, const f
         }
         A.lds_per_wave = (int)((b + 15) & ~(size_t)15);
     }
-    A.pieces = sub_only && p->n_chunks >= SL_PIECES_FROM;
+    A.pieces = sub_only && sl_subk_pieces(p->n_chunks, k);
     A.vals = sub_only ? nullptr : reinterpret_cast<float *>(ws + p->ws_vals);
     A.leafA = sub_only ? nullptr : reinterpret_cast<double *>(ws + p->ws_leafA);
     A.payload = payload;

@@ -773,11 +773,9 @@ __global__ void SL_SELECT_BOUNDS k_select(SelectArgs A)
     sl_wave_sync();
 
     if constexpr (SUBK) {
-        // m - Top-k(m): x - x = +0.0 at the selected positions, the rest stays as it is.  On long lists a full chunk of aligned rows writes back the
-        // 64-byte pieces that hold a selected position, from the registers: where the caches do not hold the buffer, a write of four bytes costs
-        // the memory a read and a write of its piece (49,152 chunks, us, k = 64 255 -> 190, k = 128 355 -> 210, k = 512 500 -> 300; 24,576, k = 64
-        // 115 -> 95; 12,288, k = 64 49 -> 55, so not there).  The selected positions go to LDS as bits, of which a lane looks at its own
-        // four and its piece's sixteen per access.
+        // m - Top-k(m): x - x = +0.0 at the selected positions, the rest stays as it is.  On long lists (sl_subk_pieces) a full chunk of aligned rows writes
+        // back the 64-byte pieces that hold a selected position, from the registers.  The selected positions go to LDS as bits, of which a lane
+        // looks at its own four and its piece's sixteen per access.
         if (A.pieces && full && ((d.base | stride) & 15) == 0) {
             unsigned *marks = reinterpret_cast<unsigned *>(smem);       // (in the place of the candidates, 2 KB at least)
 #pragma unroll

@@ -56,11 +56,19 @@ static void unaligned()
     }
 }
 
+// whole pieces written back by Sub-k
+static void pieces()
+{
+    const struct { int n, k, want; } rows[] = {{16383, 64, 0}, {16384, 64, 1}, {16384, 4, 0}, {98304, 8, 0}, {49152, 14, 0}, {16384, 16, 1}, {98304, 4096, 1}};
+    for (const auto &r : rows) expect("pieces", r.n, r.k, sl_subk_pieces(r.n, r.k), r.want);
+}
+
 int main()
 {
     selection();
     kept();
     unaligned();
+    pieces();
     if (failures) return 1;
     std::puts("ok");
     return 0;

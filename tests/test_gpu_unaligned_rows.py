@@ -84,7 +84,7 @@ def test_unaligned_rows(oracle, case):
         same(m, m_ref, "momentum")
 
 
-@pytest.mark.parametrize("k, chunks", [(4, 16384), (64, 16383), (128, 16385), (264, 16384), (600, 16384), (4096, 16384)])
+@pytest.mark.parametrize("k, chunks", [(4, 16384), (12, 16385), (16, 16384), (64, 16383), (128, 16385), (264, 16384), (600, 16384), (4096, 16384)])
 def test_subk_of_long_lists(oracle, k, chunks):
     """Sub-k on both sides of the length from which whole pieces are written back; aligned matrices, one whose rows are not, a run with a
     tail, chunks of zeros and of one value."""
