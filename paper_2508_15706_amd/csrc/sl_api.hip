@@ -70,6 +70,7 @@ int sl_plan_create_bits(const sl_tensor *tensors, int n_tensors, int k, int valu
     std::vector<SlChunkDesc> desc;
     std::vector<SlTensorDev> tdev;
     std::vector<SlGroup> groups;
+    std::vector<SlPiece> pieces;
     int64_t n_elements = 0, n_partial = 0, n_unaligned = 0;
     size_t pay = 0;
 
@@ -150,6 +151,7 @@ int sl_plan_create_bits(const sl_tensor *tensors, int n_tensors, int k, int valu
             pay += (size_t)D.block_bytes;
             n_elements += T.rows * T.cols;
         }
+        sl_make_pieces(tdev, pieces);
     } catch (const std::bad_alloc &) {
         return SL_ERR_NOMEM;
     }
@@ -185,6 +187,7 @@ int sl_plan_create_bits(const sl_tensor *tensors, int n_tensors, int k, int valu
     p->ws_tstat = off;  off = align_up(off + (size_t)n_tensors * sizeof(SlTensorStat), 256);
     p->ws_bytes = off ? off : 256;
     p->n_groups = (int64_t)groups.size();
+    p->n_pieces = (int64_t)pieces.size();
     {
         // the coded format's sizes, its upper bound and the scratch its writers need
         SlCodedGeom &g = p->cg;
@@ -272,6 +275,9 @@ int sl_plan_create_bits(const sl_tensor *tensors, int n_tensors, int k, int valu
             (err = hipMalloc((void **)&p->d_groups, groups.size() * sizeof(SlGroup))) != hipSuccess ||
             (err = hipMemcpy(p->d_groups, groups.data(), groups.size() * sizeof(SlGroup),
                              hipMemcpyHostToDevice)) != hipSuccess ||
+            (!pieces.empty() && ((err = hipMalloc((void **)&p->d_pieces, pieces.size() * sizeof(SlPiece))) != hipSuccess ||
+                                 (err = hipMemcpy(p->d_pieces, pieces.data(), pieces.size() * sizeof(SlPiece),
+                                                  hipMemcpyHostToDevice)) != hipSuccess)) ||
             (err = hipMemcpy(p->d_desc, desc.data(), b_desc, hipMemcpyHostToDevice)) != hipSuccess ||
             (err = hipMemcpy(p->d_tensors, tdev.data(), b_t, hipMemcpyHostToDevice)) != hipSuccess) {
             const int rc = err == hipErrorOutOfMemory ? SL_ERR_NOMEM : hip_fail(err);
@@ -290,6 +296,7 @@ int sl_plan_destroy(sl_plan *p)
     if (p->d_cdesc) (void)hipFree(p->d_cdesc);
     if (p->d_tensors) (void)hipFree(p->d_tensors);
     if (p->d_groups) (void)hipFree(p->d_groups);
+    if (p->d_pieces) (void)hipFree(p->d_pieces);
     std::free(p->h_tensors);
     if (p->prof) {
         double ms[SL_PROF_PHASES];

@@ -30,6 +30,7 @@ struct SlTensorDev {
     // coded format: byte offsets inside a coded buffer of the tensor's block (table header first),
     // of its directory and of its first fixed record; size of the block
     long long cblk_off, cdir_off, cfix_off, cblk_bytes;
+    long long piece0;       // first of its pieces (SlPiece), -1 where its leaves are summed without
 };
 
 enum { SL_RICE_GROUP = 16 };  // chunks per directory entry of the coded format
@@ -65,6 +66,23 @@ struct SlGroup {            // one coding group of the index coder
     int local_group;
     int chunk0, n_chunks;   // its chunks, list order
 };
+
+struct SlPiece {            // so many leaves of a tensor that are summed up by a wave of their own (k_piece_sums)
+    int chunk0, n_chunks;   // its chunks, list order
+};
+enum { SL_PIECE = 256 };
+// The pieces of the tensors of more than SL_SPLIT_TENSOR chunks, and each tensor's first one.
+#define SL_SPLIT_TENSOR 10240
+template <class Tensors, class Pieces>
+inline void sl_make_pieces(Tensors &tensors, Pieces &pieces)
+{
+    for (SlTensorDev &t : tensors) {
+        const bool split = t.n_chunks > SL_SPLIT_TENSOR;
+        t.piece0 = split ? (long long)pieces.size() : -1;
+        for (long long c = 0; split && c < t.n_chunks; c += SL_PIECE)
+            pieces.push_back(SlPiece{(int)(t.chunk0 + c), (int)(t.n_chunks - c < SL_PIECE ? t.n_chunks - c : SL_PIECE)});
+    }
+}
 
 // Per-tensor quantizer state produced during sl_compress.
 struct SlTensorStat {
@@ -113,6 +131,8 @@ struct sl_plan {
     SlTensorDev *d_tensors;
     SlGroup *d_groups;
     int64_t n_groups;
+    SlPiece *d_pieces;
+    int64_t n_pieces;
     size_t rice_max_bytes;      // upper bound of a coded buffer, 0 when the list is beyond the coded format
     SlCodedGeom cg;
     // workspace sections of the coded path: per-chunk bit vectors (cg.ua words each) and quotient

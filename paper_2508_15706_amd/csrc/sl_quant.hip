@@ -127,33 +127,26 @@ __device__ void block_tree_sums(const double *const (&leaf)[NS], long long n, Re
 // ---- large tensors
 // One workgroup reads the leaves of a tensor at the rate of one compute unit: 64 us for the statistics of 131,072 chunks, 50 for a
 // bin.  Where a tensor has more than SL_SPLIT_TENSOR chunks, a launch before B and one before D sum up pieces of 256
-// leaves, one wave each, and B and D read the pieces' sums.  Piece i of tensor t stands at (group0 >> 4) + t + i: a piece
-// begins with every sixteenth group of its tensor, and the t keeps neighbours apart.  (sl_compress of one matrix, k = 64, 2 bits, whole
-// tensors / pieces, us: 4096 chunks 53.7 / 55.5, 8192 91.3 / 90.9, 12,000 127.7 / 125.4, 16,384 159.6 / 155.1, 32,768 294 / 282, 131,072 1122 / 1061;
-// 4 bits 56.6 / 58.8, 95.0 / 94.5, 133.4 / 131.7, 164.4 / 160.8, 301 / 290, 1122 / 1072.)
-#ifndef SL_SPLIT_TENSOR
-#define SL_SPLIT_TENSOR 10240
-#endif
+// leaves, one wave each, and B and D read the pieces' sums; the plan has a table of the pieces, as other tensors' leaves are not looked at.
+// (sl_compress, error feedback frozen, k = 64, whole tensors / pieces, us: one matrix of 10,496 chunks, 2 bits 66.4 / 65.1, 4 bits 74.2 / 73.6, 16,384 89.2 / 85.5,
+// 98.4 / 94.0, 25,600 127.2 / 117.3, 140.3 / 132.1; one of 12,288 beside 60 of 768 233.4 / 232.8, 262.2 / 261.9, one of 25,600 beside 60 of 512
+// 234.8 / 226.4, 260.9 / 253.9; 1.8B list, two of 25,152 chunks, 1600 / 1596, 1775 / 1771, 1605 and 1796 where the launch went over all groups
+// of the list; MoE list, one of 12,576, 605.4 / 606.5, 693.5 / 691.9.)
 struct RedPieces {
     double *sum;            // [columns][stride]; null: no tensor of the list is split
     unsigned *cnt;          // (D only)
-    long long stride;
-    SL_DEV bool split(long long n_chunks) const { return sum && n_chunks > SL_SPLIT_TENSOR; }
-    SL_DEV long long first(const SlTensorDev &td, int t) const { return (td.group0 >> 4) + t; }
+    long long stride;       // (the number of pieces)
+    SL_DEV bool split(const SlTensorDev &td) const { return sum && td.piece0 >= 0; }
 };
 
 __global__ void __launch_bounds__(256)
-k_piece_sums(const SlTensorDev *tensors, const SlGroup *groups, long long n_groups, const double *leaf, const unsigned *cnt,
-             long long n_chunks_total, RedPieces P)
+k_piece_sums(const SlPiece *pieces, const double *leaf, const unsigned *cnt, long long n_chunks_total, RedPieces P)
 {
     const int lane = threadIdx.x & 63;
-    const long long gi = 4ll * blockIdx.x + sl_uniform((int)(threadIdx.x >> 6));
-    if (gi >= n_groups) return;
-    const SlGroup g = groups[gi];
-    if (g.local_group & 15) return;
-    const SlTensorDev td = tensors[g.tensor];
-    if (!P.split(td.n_chunks)) return;
-    const int n = (int)min(256ll, td.n_chunks - 16ll * g.local_group), b = 4 * lane;
+    const long long pi = 4ll * blockIdx.x + sl_uniform((int)(threadIdx.x >> 6));
+    if (pi >= P.stride) return;
+    const SlPiece g = pieces[pi];
+    const int n = g.n_chunks, b = 4 * lane;
     leaf += blockIdx.y * n_chunks_total + g.chunk0;
     double x[4] = {0.0, 0.0, 0.0, 0.0};
     unsigned c = 0;
@@ -175,7 +168,7 @@ k_piece_sums(const SlTensorDev *tensors, const SlGroup *groups, long long n_grou
     }
     const double v = sl_wave_tree((x[0] + x[1]) + (x[2] + x[3]), 6);
     if (lane == 0) {
-        const long long at = blockIdx.y * P.stride + (gi >> 4) + g.tensor;
+        const long long at = blockIdx.y * P.stride + pi;
         P.sum[at] = v;
         if (P.cnt) P.cnt[at] = c;
     }
@@ -186,7 +179,7 @@ template <int NS>
 __device__ void block_piece_sums(const double *const (&piece)[NS], long long n, RedShared &sh, double (&sum)[NS])
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const long long pieces = (n + 255) / 256, supers = (pieces + 255) / 256;
+    const long long pieces = (n + SL_PIECE - 1) / SL_PIECE, supers = (pieces + 255) / 256;
     if (wave < NS) {
         const double *const src = NS == 1 || wave == 0 ? piece[0] : piece[NS - 1];
         double p[4], next[4];
@@ -279,8 +272,8 @@ k_tensor_stats(const SlTensorDev *tensors, int n_tensors, const double *leafA, l
     }
     const SlTensorDev td = tensors[blockIdx.x];
     double S[2];
-    if (P.split(td.n_chunks)) {
-        const double *const piece = P.sum + P.first(td, (int)blockIdx.x);
+    if (P.split(td)) {
+        const double *const piece = P.sum + td.piece0;
         const double *const both[2] = {piece, piece + P.stride};
         block_piece_sums<2>(both, td.n_chunks, sh, S);
     } else {
@@ -645,10 +638,10 @@ k_tensor_lut(const SlTensorDev *tensors, int n_tensors, const double *leafC, con
     }
     const SlTensorDev &td = tensors[blockIdx.x];             // (read again behind the sums: it would be kept in scratch memory across them)
     unsigned long long part = 0;
-    const bool split = P.split(td.n_chunks);
-    const long long piece = b * P.stride + P.first(td, (int)blockIdx.x);
+    const bool split = P.split(td);
+    const long long piece = b * P.stride + td.piece0;
     const unsigned *cb = split ? P.cnt + piece : cnt + b * n_chunks_total + td.chunk0;
-    const long long counts = split ? (td.n_chunks + 255) / 256 : td.n_chunks;
+    const long long counts = split ? (td.n_chunks + SL_PIECE - 1) / SL_PIECE : td.n_chunks;
     for (long long i = tid; i < counts; i += RED_THREADS) part += cb[i];
     if (64 * (tid >> 6) < counts) {                        // (a wave without chunks has nothing to add)
 #pragma unroll
@@ -818,15 +811,15 @@ int slk_quantize(const sl_plan *p, float *e, int skip_residual, unsigned char *p
     const bool few = p->max_tensor_chunks <= SL_SHORT_TENSOR && p->n_chunks <= SL_SHORT_LIST &&
                      p->max_wave_tensors <= SL_SHORT_WAVE_TENSORS;
     // Sums of pieces of large tensors: those of kernel A's leaves stand where C writes its own later, those of C's where A's have been.
-    const long long stride = p->n_groups / 16 + p->n_tensors + 1;
-    const bool split = p->max_tensor_chunks > SL_SPLIT_TENSOR && stride * (1 << p->bits) <= p->n_chunks;
+    // (They fit: a split tensor has two hundred times as many chunks as pieces.)
+    const bool split = p->n_pieces > 0;
+    const long long stride = p->n_pieces;
     const RedPieces PB = {split ? leafC : nullptr, nullptr, stride};
     const RedPieces PD = {split ? leafA : nullptr, reinterpret_cast<unsigned *>(leafA + (stride << p->bits)), stride};
-    const unsigned piece_blocks = (unsigned)((p->n_groups + 3) / 4);
+    const unsigned piece_blocks = (unsigned)((p->n_pieces + 3) / 4);
     const unsigned scan_blocks = shared ? (unsigned)sl_scan_blocks(p->n_groups) : 0;
     if (split) {
-        hipLaunchKernelGGL(k_piece_sums, dim3(piece_blocks, 2), dim3(256), 0, st, p->d_tensors, p->d_groups, (long long)p->n_groups, leafA,
-                           nullptr, (long long)p->n_chunks, PB);
+        hipLaunchKernelGGL(k_piece_sums, dim3(piece_blocks, 2), dim3(256), 0, st, p->d_pieces, leafA, nullptr, (long long)p->n_chunks, PB);
         if ((rc = check_launch())) return rc;
     }
     if (!few) {
@@ -862,8 +855,7 @@ int slk_quantize(const sl_plan *p, float *e, int skip_residual, unsigned char *p
 
     const int nbins = 1 << p->bits;
     if (split) {
-        hipLaunchKernelGGL(k_piece_sums, dim3(piece_blocks, nbins), dim3(256), 0, st, p->d_tensors, p->d_groups, (long long)p->n_groups,
-                           leafC, cnt, (long long)p->n_chunks, PD);
+        hipLaunchKernelGGL(k_piece_sums, dim3(piece_blocks, nbins), dim3(256), 0, st, p->d_pieces, leafC, cnt, (long long)p->n_chunks, PD);
         if ((rc = check_launch())) return rc;
     }
     const size_t per_wave_lds = sl_coded_place_words(p->cg) * sizeof(unsigned);

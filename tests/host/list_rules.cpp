@@ -1,6 +1,7 @@
 // The rules on a list's length that choose between the forms of a kernel, at calls that were measured on both sides of every line: a
 // call that a form is slower for keeps the other one.  Prints the first row that goes the wrong way.
 #include <cstdio>
+#include <vector>
 
 #include "sl_internal.h"
 
@@ -63,12 +64,39 @@ static void pieces()
     for (const auto &r : rows) expect("pieces", r.n, r.k, sl_subk_pieces(r.n, r.k), r.want);
 }
 
+// pieces whose sums a launch of their own takes: those of the large tensors, and no others
+static void tensor_pieces()
+{
+    std::vector<SlTensorDev> list;
+    long long chunk0 = 0;
+    for (long long n : {3ll, 25152ll, 4096ll, 10240ll, 10241ll, 10496ll, 1ll}) {
+        SlTensorDev t{};
+        t.chunk0 = chunk0, t.n_chunks = n;
+        list.push_back(t);
+        chunk0 += n;
+    }
+    std::vector<SlPiece> got;
+    sl_make_pieces(list, got);
+    size_t at = 0;
+    for (const SlTensorDev &t : list) {
+        const bool split = t.n_chunks > 10240;
+        expect("first piece", t.n_chunks, 0, (int)t.piece0, split ? (int)at : -1);
+        for (long long c = 0; split && c < t.n_chunks; c += 256, ++at) {
+            const bool there = at < got.size();
+            expect("piece begins", t.n_chunks, 0, there ? got[at].chunk0 : -1, (int)(t.chunk0 + c));
+            expect("piece holds", t.n_chunks, 0, there ? got[at].n_chunks : -1, (int)(t.n_chunks - c < 256 ? t.n_chunks - c : 256));
+        }
+    }
+    expect("pieces", chunk0, 0, (int)got.size(), 99 + 41 + 41);
+}
+
 int main()
 {
     selection();
     kept();
     unaligned();
     pieces();
+    tensor_pieces();
     if (failures) return 1;
     std::puts("ok");
     return 0;
