@@ -807,7 +807,13 @@ __global__ void SL_SELECT_BOUNDS k_select(SelectArgs A)
     }
 
     // ---------------------------------------------------------------- outputs
-    unsigned char *rec = A.payload + d.rec_off;
+    // (What only they need of the arguments is read here: read at the start it costs scalar registers all along, and full chunks reload what
+    // was spilled for it.  Error feedback frozen, 25,600 chunks, this kernel, us: fp32 values, k = 64 108.9 -> 103.1, 4 bits 107.5 -> 102.2, k = 256 139.4 -> 134.6; 2 bits, k =
+    // 128 112.1 -> 109.6.  The struct is the kernel's only parameter.)
+    typedef const SelectArgs __attribute__((address_space(4))) *ArgsPtr;
+    ArgsPtr late = (ArgsPtr)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(late));
+    unsigned char *rec = late->payload + d.rec_off;
 
     // the selected values, four LDS reads in flight per round of stores
     float *recv = bits == 32 ? reinterpret_cast<float *>(rec + 3 * k / 2) : nullptr;   // unquantized: the values
@@ -819,7 +825,7 @@ __global__ void SL_SELECT_BOUNDS k_select(SelectArgs A)
 #pragma unroll
         for (int u = 0; u < 4; ++u)
             if (p0 + 64 * u < k) {
-                A.vals[c * k + p0 + 64 * u] = t[u];
+                late->vals[c * k + p0 + 64 * u] = t[u];
                 if (recv) recv[p0 + 64 * u] = t[u];
             }
     }
@@ -855,12 +861,14 @@ __global__ void SL_SELECT_BOUNDS k_select(SelectArgs A)
     }
 
     // the coded form of the index list (the candidate list's LDS is free by now)
-    if (A.coded) {
-        const SlCodedGeom &G = A.G;
+    if (late->coded) {
+        SlCodedGeom G;                       // (what the coder uses of it)
+        G.k = k, G.b = late->G.b, G.qmax = late->G.qmax, G.ua = late->G.ua;
+        G.rem_bytes = late->G.rem_bytes, G.val_bytes = late->G.val_bytes, G.cfix = late->G.cfix;
         unsigned *uv = reinterpret_cast<unsigned *>(smem), *rw = uv + G.ua;
         const int nrw = G.rem_bytes >> 2;
         const int Q = sl_coded_emit(G, lane, sel_idx, uv, rw);
-        unsigned char *fix = A.coded + A.cdesc[c].fix_off;
+        unsigned char *fix = late->coded + late->cdesc[c].fix_off;
         for (int w = lane; w < nrw; w += 64) reinterpret_cast<unsigned *>(fix)[w] = rw[w];
         if (bits == 32) {
             // unquantized: the values follow the remainders as they follow the indices of a plain record
@@ -869,10 +877,10 @@ __global__ void SL_SELECT_BOUNDS k_select(SelectArgs A)
             // the record's last word holds value fields and padding: cleared here, the codes come later
             *reinterpret_cast<unsigned *>(fix + G.cfix - 4) = 0u;
         }
-        unsigned *uvo = A.uvec + (size_t)c * G.ua;
+        unsigned *uvo = late->uvec + (size_t)c * G.ua;
         const int words = (k + Q + 31) >> 5;
         for (int w = lane; w < words; w += 64) uvo[w] = uv[w];
-        if (lane == 0) A.qsum[c] = (unsigned short)Q;
+        if (lane == 0) late->qsum[c] = (unsigned short)Q;
     }
 
     // per-chunk leaves of the quantizer's mean / variance sums
@@ -880,8 +888,8 @@ __global__ void SL_SELECT_BOUNDS k_select(SelectArgs A)
     constexpr int MAXE = GPL == 0 ? 64 : GPL <= 2 ? 1 : GPL / 2;      // pow2ceil(largest k served) / 64
     sl_chunk_trees<MAXE>(k, lane, sel_val, s1, s2);
     if (lane == 0) {
-        A.leafA[c] = s1;
-        A.leafA[A.n_chunks + c] = s2;
+        late->leafA[c] = s1;
+        late->leafA[late->n_chunks + c] = s2;
     }
 }
 
