@@ -687,7 +687,7 @@ int slk_apply(const sl_plan *p, float *theta, float *mom, float mu, const void *
               float lr, hipStream_t st)
 {
     if (p->n_chunks == 0) return SL_OK;
-    if (const int waves = sl_apply_waves(p, R, false); waves > 1) return slk_apply_group(p, theta, mom, mu, payloads, nullptr, R, lr, waves, st);
+    if (const int waves = sl_apply_waves(p, R, false, mom != nullptr); waves > 1) return slk_apply_group(p, theta, mom, mu, payloads, nullptr, R, lr, waves, st);
     ApplyArgs A;
     A.desc = p->d_desc;
     A.theta = theta;

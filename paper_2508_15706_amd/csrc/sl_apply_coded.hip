@@ -790,7 +790,7 @@ int slk_apply_coded(const sl_plan *p, float *theta, float *mom, float mu, const 
                     int R, float lr, hipStream_t st)
 {
     if (p->n_chunks == 0) return SL_OK;
-    if (const int waves = sl_apply_waves(p, R, true); waves > 1) return slk_apply_group(p, theta, mom, mu, payloads, bytes, R, lr, waves, st);
+    if (const int waves = sl_apply_waves(p, R, true, mom != nullptr); waves > 1) return slk_apply_group(p, theta, mom, mu, payloads, bytes, R, lr, waves, st);
     CodedApplyArgs A;
     A.G = p->cg;
     A.desc = p->d_desc;

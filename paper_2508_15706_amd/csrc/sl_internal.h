@@ -158,11 +158,13 @@ __host__ __device__ inline long long sl_lut_off(const SlChunkDesc &d, int hdr_by
     return d.rec_off - hdr_bytes - (long long)d.local_chunk * rec_bytes;
 }
 
-// Chunks (waves) per workgroup of the aggregates: four adjacent ones, so that a workgroup streams
+// Chunks (waves) per workgroup of the aggregates with a wave per chunk: four adjacent ones, so that a workgroup streams
 // 1 KB of every matrix row it touches; but one on lists so short that workgroups of four, dealt to the compute units in one turn or two,
-// would leave a third of the places without any.  Four / one, us (matrices, R = 4, k = 64): plain aggregate
-// 512 chunks 8.5 / 8.4, 1280 8.9 / 8.4, 2048 11.1 / 11.8, 3072 20.0 / 21.1; coded 1280 9.8 / 9.4, 3072 19.4 / 21.2.  Not where one chunk in 32 or more is partial: rows then begin anywhere in a line of memory, and the neighbours
-// that share a line should share an L2 (1155 chunks of a 67-column matrix, aggregate of three: 12.6 / 19.7).
+// would leave a third of the places without any.  Four / one, us, one call on buffers that no cache holds (768-column matrices): plain, k = 512, R = 4
+// 504 chunks 11.7 / 11.1, 1020 13.2 / 13.0, 1536 15.0 / 15.6, 2040 17.3 / 18.1, 4092 33.2 / 34.4; k = 64, R = 16 504 12.2 / 11.9, 2040 16.8 / 17.3, 4092 32.4 / 34.2; coded, k =
+// 256, R = 4 504 12.3 / 11.6, 1272 15.2 / 15.0, 3072 25.5 / 25.6.  (Rows of 1024 columns want one up to 3072 chunks, plain, k = 64, R = 16 1024 16.7 / 13.7, 2048 22.1 /
+// 17.2; those of 64, 1088 and 2048 do not.)  Not where one chunk in 32 or more is partial: rows then begin anywhere in a line of memory, and the neighbours
+// that share a line should share an L2 (coded, k = 64, R = 8, 594 chunks of a 530-column matrix 17.5 / 18.7; plain, k = 256, 1024 of 1001 columns 19.3 / 21.3).
 #define SL_COMPUTE_UNITS 256
 inline int sl_chunks_per_group(const sl_plan *p)
 {
@@ -236,18 +238,21 @@ inline bool sl_subk_pieces(int64_t n_chunks, int k) { return k >= 16 && n_chunks
 
 // Waves per chunk of the aggregates: several (sl_apply_group.hip) on short lists with few workers, one else.  With a wave per worker
 // and a list of entries for each the work grows with R, and with k, where the other routes' does less.  One wave and the number taken
-// here, us (in a graph, lr update of full chunks): plain, k = 64, R = 4: 64 chunks 4.4 -> 3.7, 512 5.1 -> 4.5, 1024 9.0 -> 5.8, 2048 16.9 ->
-// 13.6; R = 8 256 5.2 -> 4.5, 1024 9.7 -> 7.1, 2048 17.2 -> 16.1; k = 256, R = 4 512 5.9 -> 5.9, 1024 9.8 -> 7.9; fp32 values, k = 64, R = 3 1024
-// 9.6 -> 5.6; coded, k = 64, R = 4 256 6.9 -> 5.7, 1024 10.5 -> 8.4; R = 8 256 7.1 -> 6.3.  Beyond the lines: plain, k = 512, R = 3 256 5.7 -> 7.1; k =
-// 16, R = 16 512 7.1 -> 7.4; 4096, k = 64, R = 4 24.2 -> 24.8; 1155 chunks of 67 columns 9.0 -> 9.1 (900 of 530 columns 10.7 -> 9.5); coded, k = 64, R =
-// 8 1024 11.0 -> 11.1; k = 256, R = 4 256 7.0 -> 8.3; 2048, R = 4 16.5 -> 16.2, k = 128 16.5 -> 18.3.
-inline int sl_apply_waves(const sl_plan *p, int R, bool coded)
+// here, us, one call on buffers that no cache holds, full chunks of 1024-column matrices, lr update: plain, k = 64, R = 4 64 chunks 8.6 -> 7.2, 512 9.7 -> 8.7,
+// 1024 14.4 -> 10.6, 2048 21.8 -> 17.6; R = 8 256 9.1 -> 8.8, 1024 15.1 -> 12.1, 2048 22.0 -> 20.5; k = 200, R = 8 512 22.3 -> 11.1; k = 256, R = 4 256 9.9 -> 10.0, 512 11.0 ->
+// 10.8, 1024 15.4 -> 12.9, R = 8 512 11.9 -> 11.8, with momentum 1024 25.1 -> 21.8, 4 bits 19.6 -> 17.1, fp32 values 23.5 -> 15.6; coded, k = 64, R = 4 256 11.6 -> 10.2, 1024
+// 16.2 -> 13.6, R = 8 256 12.1 -> 10.9; k = 128, R = 4 1024 16.5 -> 14.5.  Beyond the lines: plain, k = 256, two bits (one wave decodes eight entries a lane), R =
+// 5 768 14.0 -> 14.8, R = 8 1024 16.3 -> 17.0 (1001 columns 19.2 -> 21.3); k = 512, R = 3 256 10.0 -> 12.9; k = 16, R = 16 512 11.5 -> 12.0; k = 64, R = 8 4096 30.6 -> 32.9; coded, k = 64, R = 8
+// 1280 15.4 -> 17.4, k = 128, R = 8 512 12.2 -> 13.3; k = 256, R = 4 256 11.0 -> 12.8.  (Called again and again in a graph, everything in the caches, k = 64, R = 4: 512 chunks 5.1 -> 4.5,
+// 1024 9.0 -> 5.8, 2048 16.9 -> 13.6.)
+inline int sl_apply_waves(const sl_plan *p, int R, bool coded, bool mom)
 {
     const int64_t n = p->n_chunks;
     const int k = p->k;
     if (coded) return k > 128 ? 1 : n <= 256 && R <= 8 ? 8 : n <= 1024 && R <= 4 ? 4 : 1;
     if (k > 256 || R > 8) return 1;
     if (n <= 512) return 8;
+    if (k == 256 && p->bits == 2 && R > 4 && !mom) return 1;
     if (n <= 1024) return 4;
     return R * k <= 1024 && n <= (p->n_partial * 32 >= n ? 1280 : 2048) ? 4 : 1;
 }

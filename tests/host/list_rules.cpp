@@ -64,6 +64,21 @@ static void pieces()
     for (const auto &r : rows) expect("pieces", r.n, r.k, sl_subk_pieces(r.n, r.k), r.want);
 }
 
+// waves per chunk of the aggregates
+static void aggregates()
+{
+    const struct { int n, k, bits, R, coded, mom, want; } rows[] = {
+        {64, 64, 2, 4, 0, 0, 8}, {512, 256, 2, 8, 0, 0, 8}, {513, 256, 2, 5, 0, 0, 1}, {1024, 256, 2, 8, 0, 0, 1}, {1024, 256, 2, 4, 0, 0, 4}, {1024, 256, 2, 8, 0, 1, 4},
+        {1024, 256, 4, 8, 0, 0, 4}, {1024, 256, 32, 8, 0, 0, 4}, {1024, 248, 2, 8, 0, 0, 4}, {1025, 256, 2, 4, 0, 0, 4}, {1025, 256, 2, 5, 0, 1, 1}, {2048, 64, 2, 8, 0, 0, 4},
+        {2049, 64, 2, 1, 0, 0, 1}, {64, 264, 2, 1, 0, 0, 1}, {64, 16, 2, 9, 0, 0, 1}, {256, 128, 2, 8, 1, 0, 8}, {257, 64, 2, 8, 1, 0, 1}, {1024, 64, 2, 4, 1, 1, 4}, {1025, 64, 2, 1, 1, 0, 1},
+    };
+    for (const auto &r : rows) {
+        sl_plan p{};
+        p.k = r.k, p.bits = r.bits, p.n_chunks = r.n;
+        expect(r.coded ? "aggregate, coded" : "aggregate, plain", r.n, r.k, sl_apply_waves(&p, r.R, r.coded != 0, r.mom != 0), r.want);
+    }
+}
+
 // pieces whose sums a launch of their own takes: those of the large tensors, and no others
 static void tensor_pieces()
 {
@@ -97,6 +112,7 @@ int main()
     unaligned();
     pieces();
     tensor_pieces();
+    aggregates();
     if (failures) return 1;
     std::puts("ok");
     return 0;
