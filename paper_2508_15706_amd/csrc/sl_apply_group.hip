@@ -6,8 +6,6 @@
 // of (position, value) in LDS; behind one barrier every wave adds the entries of its own positions, worker after
 // worker in the order r = 0 .. R - 1 - a part of each list, as the indices of a record ascend (where they do not, the whole list is
 // looked through).  Same order of additions, same bits.
-#include <algorithm>
-
 #include "sl_coded.h"
 
 namespace {
@@ -18,10 +16,8 @@ struct GroupApplyArgs {
     float *theta;
     float *mom;              // global outer momentum buffer (Nesterov variant), else null
     float mu, neg_lr, inv_R;
-    int R, batch;            // workers; of them decoded at a time
+    int R;
     int k, bits, hdr_bytes, rec_bytes;
-    int b, qmax, ua, rem_bytes;      // of the coded format (SlCodedGeom)
-    long long section;
     SlCodedGeom G;
     int stage_bytes;         // coded: LDS of a wave's words and running sums
     int off_list, off_bounds;        // LDS offsets of the lists and of each worker's parts
@@ -52,6 +48,8 @@ __global__ void __launch_bounds__(64 * WAVES) k_apply_group(GroupApplyArgs A)
     const bool full = d.flags & SLC_FULL;
     float *tc = A.theta + d.base, *mc = NESTEROV ? A.mom + d.base : nullptr;
     sl_f4 th[NA], mo[NA];
+    // (The streaming hint stays on unaligned rows too: with / without it, us, 1001 columns, k = 64, R = 4, plain 256 chunks 8.4 / 9.1, 512 10.3 / 11.4, 1024 14.9 / 15.3, coded 1024
+    // 16.6 / 17.6; with the momentum 256 10.3 / 11.4, 512 15.4 / 15.1, 1024 23.9 / 19.7, the one form that would gain.)
     if (full) {
 #pragma unroll
         for (int u = 0; u < NA; ++u) th[u] = sl_load_stream_at(tc, u * step, o0);
@@ -77,15 +75,15 @@ __global__ void __launch_bounds__(64 * WAVES) k_apply_group(GroupApplyArgs A)
     }
 
     // ---- decoding
-    // Entries m = m0 + lane of the worker at place `slot` of the batch: to its list, and which entries lie in which part.
+    // Entry m of worker r: to its list, and which entries lie in which part.
     int prev, last_part;     // index of the entry before, and its part
     bool ascending;
-    auto put = [&](int slot, int m, bool live, unsigned j, float v) __attribute__((always_inline)) {
+    auto put = [&](int r, int m, bool live, unsigned j, float v) __attribute__((always_inline)) {
         const int before = sl_lane_read((int)j, lane - 1), up = lane ? before : prev, part = (int)(j >> PART_LOG2);
         const int from = m == 0 ? -1 : lane ? before >> PART_LOG2 : last_part;
         if (live) {
-            list[slot * k + m] = make_uint2(4u * j, __float_as_uint(v));
-            unsigned short *first = bounds + 2 * WAVES * slot, *end = first + WAVES;
+            list[r * k + m] = make_uint2(4u * j, __float_as_uint(v));
+            unsigned short *first = bounds + 2 * WAVES * r, *end = first + WAVES;
             for (int q = from + 1; q <= part; ++q) {
                 first[q] = (unsigned short)m;
                 if (q) end[q - 1] = (unsigned short)m;
@@ -96,8 +94,8 @@ __global__ void __launch_bounds__(64 * WAVES) k_apply_group(GroupApplyArgs A)
         last_part = prev >> PART_LOG2;
     };
     auto begin = [&]() __attribute__((always_inline)) { prev = -1, last_part = -1, ascending = true; };
-    auto finish = [&](int slot, int last) __attribute__((always_inline)) {     // last: the part of entry k - 1
-        unsigned short *first = bounds + 2 * WAVES * slot, *end = first + WAVES;
+    auto finish = [&](int r, int last) __attribute__((always_inline)) {     // last: the part of entry k - 1
+        unsigned short *first = bounds + 2 * WAVES * r, *end = first + WAVES;
         sl_wave_sync();
         if (lane < WAVES) {
             if (lane > last || !ascending) first[lane] = (unsigned short)(ascending ? k : 0);
@@ -124,19 +122,19 @@ __global__ void __launch_bounds__(64 * WAVES) k_apply_group(GroupApplyArgs A)
         const unsigned code = ((h.b0 | (unsigned)h.b1 << 8) >> ((m * bits) & 7)) & ((1u << (bits & 31)) - 1u);
         return __int_as_float(sl_lane_read(__float_as_int(table), (int)code));
     };
-    const int n_fields = bits == 32 ? 0 : 1 << bits, nrw = A.rem_bytes >> 2, b = A.b;
+    const int n_fields = bits == 32 ? 0 : 1 << bits, nrw = A.G.rem_bytes >> 2, b = A.G.b;
     auto vector_word = [&](const unsigned char *p, int r, int w) __attribute__((always_inline)) {
         const unsigned long long at = (unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)v_word, r) + (unsigned)w;
-        return at < A.sec_words[r] ? reinterpret_cast<const unsigned *>(p + A.section)[at] : 0xFFFFFFFFu;   // (beyond the end: no entries)
+        return at < A.sec_words[r] ? reinterpret_cast<const unsigned *>(p + A.G.section)[at] : 0xFFFFFFFFu;   // (beyond the end: no entries)
     };
     auto request = [&](int r, Ahead &h) __attribute__((always_inline)) {
         const unsigned char *p = A.payload[r];
         const int m = min(lane, k - 1);
         h.table = 0.f;
         if constexpr (CODED) {
-            h.w0 = vector_word(p, r, min(lane, A.ua));
+            h.w0 = vector_word(p, r, min(lane, A.G.ua));
             h.w1 = reinterpret_cast<const unsigned *>(p + cd.fix_off)[min(lane, max(nrw - 1, 0))];
-            load_field(p + cd.fix_off + A.rem_bytes, m, h);
+            load_field(p + cd.fix_off + A.G.rem_bytes, m, h);
             if (n_fields) h.table = reinterpret_cast<const float *>(p + cd.lut_off)[min(lane, n_fields - 1)];
         } else {
             h.w0 = *reinterpret_cast<const u16_any *>(p + d.rec_off + ((3 * m) >> 1));
@@ -144,12 +142,12 @@ __global__ void __launch_bounds__(64 * WAVES) k_apply_group(GroupApplyArgs A)
             if (n_fields) h.table = reinterpret_cast<const float *>(p + sl_lut_off(d, A.hdr_bytes, A.rec_bytes))[min(lane, n_fields - 1)];
         }
     };
-    auto decode_plain = [&](int r, int slot, const Ahead &h) __attribute__((always_inline)) {
+    auto decode_plain = [&](int r, const Ahead &h) __attribute__((always_inline)) {
         const unsigned char *rec = A.payload[r] + d.rec_off, *fields = rec + 3 * k / 2;
         begin();
         auto entry = [&](int m, const Ahead &x) __attribute__((always_inline)) {
             const int mm = min(m, k - 1);    // (lanes beyond the last entry repeat it)
-            put(slot, m, m < k, (mm & 1) ? x.w0 >> 4 : x.w0 & 0xFFFu, value_of(x, h.table, mm));
+            put(r, m, m < k, (mm & 1) ? x.w0 >> 4 : x.w0 & 0xFFFu, value_of(x, h.table, mm));
         };
         entry(lane, h);
         constexpr int U = 4;                 // further passes whose loads are under way together
@@ -166,18 +164,18 @@ __global__ void __launch_bounds__(64 * WAVES) k_apply_group(GroupApplyArgs A)
             for (int u = 0; u < U; ++u)
                 if (m0 + 64 * u < k) entry(m0 + 64 * u + lane, x[u]);
         }
-        finish(slot, last_part);
+        finish(r, last_part);
     };
-    auto decode_coded = [&](int r, int slot, const Ahead &h) __attribute__((always_inline)) {
+    auto decode_coded = [&](int r, const Ahead &h) __attribute__((always_inline)) {
         // the bit vector and the remainders in LDS, value fields straight from the payload
         unsigned *raw = reinterpret_cast<unsigned *>(smem + SL_CHUNK * sizeof(float) + (size_t)wave * A.stage_bytes);
-        unsigned *rem = raw + A.ua + 1;
+        unsigned *rem = raw + A.G.ua + 1;
         unsigned short *sums = reinterpret_cast<unsigned short *>(rem + nrw + 1);
         const unsigned char *p = A.payload[r], *fix = p + cd.fix_off;
         const int meta = __builtin_amdgcn_readlane(v_meta, r), sh = meta & 31, n = meta >> 5;
         sl_wave_sync();
-        if (lane <= A.ua) raw[lane] = h.w0;
-        for (int w = lane + 64; w <= A.ua; w += 64) raw[w] = vector_word(p, r, w);
+        if (lane <= A.G.ua) raw[lane] = h.w0;
+        for (int w = lane + 64; w <= A.G.ua; w += 64) raw[w] = vector_word(p, r, w);
         if (lane <= nrw) rem[lane] = lane < nrw ? h.w1 : 0u;
         if (lane == 0 && nrw >= 64) rem[64] = 0u;                // (64 words at most)
         for (int m = lane; m < k; m += 64) sums[m] = 0;          // (a vector with too few zeros)
@@ -185,7 +183,7 @@ __global__ void __launch_bounds__(64 * WAVES) k_apply_group(GroupApplyArgs A)
         // bit by bit: the i-th zero, at bit z, ends entry i, whose quotients so far sum to z - i
         for (int z0 = 0, i0 = 0; z0 < n; z0 += 64) {
             const int z = z0 + lane, at = sh + z;
-            const bool zero = z < n && !((raw[min(at >> 5, A.ua)] >> (at & 31)) & 1u);
+            const bool zero = z < n && !((raw[min(at >> 5, A.G.ua)] >> (at & 31)) & 1u);
             const unsigned long long mask = sl_ballot(zero);
             const int i = i0 + sl_mbcnt(mask);
             if (zero && i < k) sums[i] = (unsigned short)(z - i);
@@ -197,56 +195,52 @@ __global__ void __launch_bounds__(64 * WAVES) k_apply_group(GroupApplyArgs A)
         Ahead x = h;
         for (int m0 = 0; m0 < k; m0 += 64) {
             const int m = m0 + lane, mm = min(m, k - 1), bit = mm * b, wi = bit >> 5;
-            if (m0) load_field(fix + A.rem_bytes, mm, x);
+            if (m0) load_field(fix + A.G.rem_bytes, mm, x);
             const unsigned f = __builtin_amdgcn_alignbit(rem[wi + (b ? 1 : 0)], rem[wi], (unsigned)(bit & 31)) & ((1u << b) - 1u);
             const int incl = sl_wave_iscan(m < k ? (int)f : 0) + carry;
             carry = __builtin_amdgcn_readlane(incl, 63);
             // index of entry m, cut to 12 bits: a malformed payload stays inside the chunk
-            put(slot, m, m < k, (unsigned)(mm + ((int)sums[mm] << b) + incl) & 0xFFFu, value_of(x, h.table, mm));
+            put(r, m, m < k, (unsigned)(mm + ((int)sums[mm] << b) + incl) & 0xFFFu, value_of(x, h.table, mm));
         }
-        finish(slot, last_part);
+        finish(r, last_part);
     };
 
-    // ---- the workers, a batch at a time
-    for (int r0 = 0; r0 < A.R; r0 += A.batch) {
-        const int nb = min(A.batch, A.R - r0);
-        Ahead next;
-        if (wave < nb) request(r0 + wave, next);
-        for (int i = wave; i < nb; i += WAVES) {
-            const Ahead h = next;
-            if (i + WAVES < nb) request(r0 + i + WAVES, next);
-            if constexpr (CODED) decode_coded(r0 + i, i, h);
-            else decode_plain(r0 + i, i, h);
+    // ---- the workers
+    Ahead next;
+    if (wave < A.R) request(wave, next);
+    for (int r = wave; r < A.R; r += WAVES) {
+        const Ahead h = next;
+        if (r + WAVES < A.R) request(r + WAVES, next);
+        if constexpr (CODED) decode_coded(r, h);
+        else decode_plain(r, h);
+    }
+    __syncthreads();
+    // this wave's part of the list of worker `lane`
+    int lo = 0, hi = 0;
+    if (lane < A.R) lo = bounds[2 * WAVES * lane + wave], hi = bounds[2 * WAVES * lane + WAVES + wave];
+    auto add = [&](int m, int end, uint2 e) __attribute__((always_inline)) {
+        if (m < end && (int)(e.x >> (PART_LOG2 + 2)) == wave) {
+            float *at = reinterpret_cast<float *>(smem + e.x);
+            *at = *at + __uint_as_float(e.y);
         }
-        __syncthreads();
-        // this wave's part of the list of worker r0 + lane
-        int lo = 0, hi = 0;
-        if (lane < nb) lo = bounds[2 * WAVES * lane + wave], hi = bounds[2 * WAVES * lane + WAVES + wave];
-        auto add = [&](int m, int end, uint2 e) __attribute__((always_inline)) {
-            if (m < end && (int)(e.x >> (PART_LOG2 + 2)) == wave) {
-                float *at = reinterpret_cast<float *>(smem + e.x);
-                *at = *at + __uint_as_float(e.y);
-            }
-            sl_wave_sync();                  // worker r is complete before worker r + 1 is added
-        };
-        constexpr int U = 4;                 // workers whose first entries are read together
-        for (int i0 = 0; i0 < nb; i0 += U) {
-            uint2 e[U];
-            int first[U], end[U];
+        sl_wave_sync();                      // worker r is complete before worker r + 1 is added
+    };
+    constexpr int U = 4;                     // workers whose first entries are read together
+    for (int r0 = 0; r0 < A.R; r0 += U) {
+        uint2 e[U];
+        int first[U], end[U];
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int i = min(i0 + u, nb - 1);
-                first[u] = __builtin_amdgcn_readlane(lo, i), end[u] = __builtin_amdgcn_readlane(hi, i);
-                e[u] = list[i * k + min(first[u] + lane, k - 1)];
-            }
-#pragma unroll
-            for (int u = 0; u < U; ++u)
-                if (i0 + u < nb) {
-                    add(first[u] + lane, end[u], e[u]);
-                    for (int m = first[u] + 64; m < end[u]; m += 64) add(m + lane, end[u], list[(i0 + u) * k + min(m + lane, k - 1)]);
-                }
+        for (int u = 0; u < U; ++u) {
+            const int r = min(r0 + u, A.R - 1);
+            first[u] = __builtin_amdgcn_readlane(lo, r), end[u] = __builtin_amdgcn_readlane(hi, r);
+            e[u] = list[r * k + min(first[u] + lane, k - 1)];
         }
-        if (r0 + A.batch < A.R) __syncthreads();         // the lists are written again
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (r0 + u < A.R) {
+                add(first[u] + lane, end[u], e[u]);
+                for (int m = first[u] + 64; m < end[u]; m += 64) add(m + lane, end[u], list[(r0 + u) * k + min(m + lane, k - 1)]);
+            }
     }
 
     // ---- theta <- theta - lr * average
@@ -298,35 +292,28 @@ int slk_apply_group(const sl_plan *p, float *theta, float *mom, float mu, const 
     A.bits = p->bits;
     A.hdr_bytes = p->hdr_bytes;
     A.rec_bytes = p->rec_bytes;
-    A.b = G.b, A.qmax = G.qmax, A.ua = G.ua, A.rem_bytes = G.rem_bytes;
-    A.section = G.section;
     A.G = G;
     for (int r = 0; r < SL_MAX_WORKERS; ++r) {
         A.payload[r] = r < R ? static_cast<const unsigned char *>(payloads[r]) : nullptr;
         const size_t sec = bytes && r < R && bytes[r] > (size_t)G.section ? (bytes[r] - (size_t)G.section) >> 2 : 0;
         A.sec_words[r] = sec > 0xFFFFFFFFull ? 0xFFFFFFFFu : (unsigned)sec;
     }
-    // lists of 4096 entries together, or of one worker
-    A.batch = std::min(R, std::max(1, SL_CHUNK / p->k));
     auto up16 = [](size_t v) { return (v + 15) & ~(size_t)15; };
     A.stage_bytes = bytes ? (int)up16(4 * (size_t)(G.ua + 1 + (G.rem_bytes >> 2) + 1) + 2 * (size_t)p->k) : 0;
     size_t at = SL_CHUNK * sizeof(float) + (size_t)waves * A.stage_bytes;
     A.off_list = (int)at;
-    at += sizeof(uint2) * (size_t)A.batch * p->k;
+    at += sizeof(uint2) * (size_t)R * p->k;
     A.off_bounds = (int)at;
-    at = up16(at + 2 * 2 * (size_t)waves * A.batch);
+    at = up16(at + 2 * 2 * (size_t)waves * R);
     typedef void (*kernel_t)(GroupApplyArgs);
     static const kernel_t table[2][2][2] = {{{k_apply_group<4, false, false>, k_apply_group<4, false, true>},
                                              {k_apply_group<4, true, false>, k_apply_group<4, true, true>}},
                                             {{k_apply_group<8, false, false>, k_apply_group<8, false, true>},
                                              {k_apply_group<8, true, false>, k_apply_group<8, true, true>}}};
     const kernel_t fn = table[waves == 8 ? 1 : 0][bytes ? 1 : 0][mom ? 1 : 0];
-    hipError_t err = hipSuccess;
-    if (at > 65536) err = hipFuncSetAttribute(reinterpret_cast<const void *>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)at);
-    if (err == hipSuccess) {
-        hipLaunchKernelGGL(fn, dim3((unsigned)p->n_chunks), dim3(64 * waves), at, st, A);
-        err = hipGetLastError();
-    }
+    if (at > 65536) return SL_ERR_INVALID_ARG;           // (sl_apply_waves sends no such call)
+    hipLaunchKernelGGL(fn, dim3((unsigned)p->n_chunks), dim3(64 * waves), at, st, A);
+    const hipError_t err = hipGetLastError();
     if (err != hipSuccess) {
         sl_note_hip_error(err);
         return SL_ERR_HIP;
