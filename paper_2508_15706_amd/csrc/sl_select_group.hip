@@ -550,7 +550,7 @@ __global__ void __launch_bounds__(64 * WAVES, M > 0 ? 1 : 4) k_select_group(Sele
     }
     const int last = 64 * share - 1 - me;    // (the index stream from the other end: with few entries other waves take it)
     if ((k & 15) == 0) {
-        // 12-bit index stream, one 32-bit word per lane (records are 4-byte aligned)
+        // 12-bit index stream, one 32-bit word per lane (see sl_select_kernel.h for records on 2 bytes)
         for (int w = last; w < 3 * k / 8; w += 64 * share) {
             const int bit0 = 32 * w;
             int m = bit0 / 12;
@@ -563,7 +563,7 @@ __global__ void __launch_bounds__(64 * WAVES, M > 0 ? 1 : 4) k_select_group(Sele
                     word |= sh >= 0 ? v << sh : v >> (-sh);
                 }
             }
-            reinterpret_cast<unsigned *>(rec)[w] = word;
+            reinterpret_cast<u32_any *>(rec)[w] = word;
         }
     } else {
         for (int b = last; b < 3 * k / 2; b += 64 * share) {

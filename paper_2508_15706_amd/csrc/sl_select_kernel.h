@@ -831,8 +831,8 @@ __global__ void SL_SELECT_BOUNDS k_select(SelectArgs A)
     }
 
     if ((k & 15) == 0) {
-        // 12-bit index stream, one 32-bit word per lane (records are 4-byte aligned)
-        unsigned *rw = reinterpret_cast<unsigned *>(rec);
+        // 12-bit index stream, one 32-bit word per lane (a record of k = 16 with 1-bit or 3-bit codes begins on 2 bytes only)
+        u32_any *rw = reinterpret_cast<u32_any *>(rec);
         const int nwords = 3 * k / 8;
         for (int w = lane; w < nwords; w += 64) {
             const int bit0 = 32 * w;
