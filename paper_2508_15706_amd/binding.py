@@ -142,7 +142,8 @@ def _stream_ptr(stream) -> Optional[int]:
     if stream is None:
         # (the handle itself: the Stream object that torch.cuda.current_stream() makes costs 2.7 us a call, as much
         # as a third of a kernel launch, and a round on a short list makes several calls)
-        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()) or None
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)      # (not a public name: it may go)
+        return (raw(torch.cuda.current_device()) if raw else torch.cuda.current_stream().cuda_stream) or None
     if isinstance(stream, torch.cuda.Stream):
         return stream.cuda_stream or None
     return int(stream) or None
