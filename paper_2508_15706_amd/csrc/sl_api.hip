@@ -220,7 +220,8 @@ int sl_plan_create_bits(const sl_tensor *tensors, int n_tensors, int k, int valu
         p->ws_qsum = off;    off = align_up(off + (size_t)p->n_chunks * 2, 256);
         p->ws_gwords = off;  off = align_up(off + groups.size() * 4, 256);
         p->ws_goff = off;    off = align_up(off + groups.size() * 4, 256);
-        off = align_up(off + ((size_t)n_tensors + 1) * 8, 256);     // (not used any more; workspace sizes stay as callers know them)
+        off = align_up(off + ((size_t)n_tensors + 1) * 8, 256);     // (not used: sl_compress_noalloc refuses lists by this
+                                                                    // size, and what it refuses or takes does not change)
         p->ws_bytes = off;
     }
 

@@ -448,42 +448,30 @@ int launched()
 
 }  // namespace
 
-int slk_coded_scan(const sl_plan *p, unsigned char *out, unsigned char *ws, hipStream_t st)
-{
-    hipLaunchKernelGGL(k_coded_scan, dim3((unsigned)sl_scan_blocks(p->n_groups)), dim3(SL_SCAN_BLOCK), 0, st, sl_coded_args(p, out, ws));
-    return launched();
-}
-
-int slk_coded_place(const sl_plan *p, unsigned char *out, unsigned char *ws, hipStream_t st)
-{
-    int wpb = 4;
-    const size_t per_wave = sl_coded_place_words(p->cg) * sizeof(unsigned);
-    while (wpb > 1 && per_wave * wpb > 65536) wpb >>= 1;
-    hipLaunchKernelGGL(k_coded_place, dim3((unsigned)((p->n_groups + wpb - 1) / wpb)), dim3(64 * wpb), per_wave * wpb, st,
-                       sl_coded_args(p, out, ws));
-    return launched();
-}
-
 #ifndef SL_PLACE_FUSED_UPTO
 #define SL_PLACE_FUSED_UPTO 2048
 #endif
 // The steps that finish a coded buffer once its writers have run, as launches of their own.
 int slk_coded_finish(const sl_plan *p, unsigned char *out, unsigned char *ws, hipStream_t st)
 {
-    int rc;
+    const SlCodedArgs A = sl_coded_args(p, out, ws);
+    const size_t per_wave = sl_coded_place_words(p->cg) * sizeof(unsigned);
     if (p->n_groups == 0) {
-        hipLaunchKernelGGL(k_coded_empty, dim3(1), dim3(64), 0, st, sl_coded_args(p, out, ws));
+        hipLaunchKernelGGL(k_coded_empty, dim3(1), dim3(64), 0, st, A);
         return launched();
     }
     if (p->n_groups <= SL_PLACE_FUSED_UPTO) {
-        const size_t per_wave = sl_coded_place_words(p->cg) * sizeof(unsigned);
         const int placing = (int)std::max<size_t>(1, std::min<size_t>(16, 49152 / per_wave));
-        hipLaunchKernelGGL(k_coded_place_fused, dim3((unsigned)((p->n_groups + placing - 1) / placing)), dim3(1024), placing * per_wave, st,
-                           sl_coded_args(p, out, ws), placing);
+        hipLaunchKernelGGL(k_coded_place_fused, dim3((unsigned)((p->n_groups + placing - 1) / placing)), dim3(1024), placing * per_wave, st, A,
+                           placing);
         return launched();
     }
-    if ((rc = slk_coded_scan(p, out, ws, st))) return rc;
-    return slk_coded_place(p, out, ws, st);
+    hipLaunchKernelGGL(k_coded_scan, dim3((unsigned)sl_scan_blocks(p->n_groups)), dim3(SL_SCAN_BLOCK), 0, st, A);
+    if (const int rc = launched()) return rc;
+    int wpb = 4;
+    while (wpb > 1 && per_wave * wpb > 65536) wpb >>= 1;
+    hipLaunchKernelGGL(k_coded_place, dim3((unsigned)((p->n_groups + wpb - 1) / wpb)), dim3(64 * wpb), per_wave * wpb, st, A);
+    return launched();
 }
 
 namespace {

@@ -16,10 +16,10 @@ SL_DEV int sl_mbcnt(unsigned long long m)
     return __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
 }
 
-// Orders this wavefront's LDS accesses: the hardware executes one wave's LDS
+// Orders this wavefront's own LDS accesses: the hardware executes one wave's LDS
 // instructions in order, so only the compiler has to be kept from moving
-// memory operations across this point.  (Waves of a block never share LDS
-// data in these kernels, so no s_barrier is needed.)
+// memory operations across this point.  What waves of a workgroup share needs
+// __syncthreads().
 SL_DEV void sl_wave_sync()
 {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");

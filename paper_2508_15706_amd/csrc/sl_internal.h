@@ -136,7 +136,7 @@ struct sl_plan {
     size_t rice_max_bytes;      // upper bound of a coded buffer, 0 when the list is beyond the coded format
     SlCodedGeom cg;
     // workspace sections of the coded path: per-chunk bit vectors (cg.ua words each) and quotient
-    // sums, per-group run lengths and offsets (words), per-tensor section offsets (words)
+    // sums, per-group run lengths (words) and offsets in a block of groups (words)
     size_t ws_uvec, ws_qsum, ws_gwords, ws_goff;
     // host copies
     SlTensorDev *h_tensors;
@@ -343,11 +343,8 @@ int slk_pack_bits(const uint16_t *idx, const uint8_t *codes, const float *values
 int slk_rice_encode(const sl_plan *p, const unsigned char *payload, unsigned char *out,
                     unsigned char *ws, hipStream_t st);
 int slk_rice_decode(const sl_plan *p, const unsigned char *in, size_t in_bytes, unsigned char *payload, hipStream_t st);
-// coded wire format: the steps that place the quotient bit vectors once a buffer's writers have run (all of
-// them; the first; those behind it, or the last alone)
+// coded wire format: the steps that place the quotient bit vectors once a buffer's writers have run
 int slk_coded_finish(const sl_plan *p, unsigned char *out, unsigned char *ws, hipStream_t st);
-int slk_coded_scan(const sl_plan *p, unsigned char *out, unsigned char *ws, hipStream_t st);
-int slk_coded_place(const sl_plan *p, unsigned char *out, unsigned char *ws, hipStream_t st);
 // theta update from R coded payloads (mom != null: with the global momentum)
 int slk_apply_coded(const sl_plan *p, float *theta, float *mom, float mu, const void *const *payloads, const size_t *bytes,
                     int R, float lr, hipStream_t st);

@@ -46,7 +46,7 @@ __global__ void __launch_bounds__(64 * WAVES, M > 0 ? 1 : 4) k_select_group(Sele
     const int wave = sl_uniform(tid >> 6);
     const long long c = blockIdx.x;
     // (what only the outputs need of the arguments is read when they are written: read at the start it costs scalar registers
-    // all along, and the searches spill theirs)
+    // all along, and the searches spill theirs; A is the first parameter, so the kernel's arguments begin with it)
     typedef const SelectArgs __attribute__((address_space(4))) *ArgsPtr;
     ArgsPtr late = (ArgsPtr)__builtin_amdgcn_kernarg_segment_ptr();
     const SlChunkDesc d = A.desc[c];

@@ -155,3 +155,38 @@ def test_non_finite(oracle, k):
     for (d, i), idx in zip(chunks, at):          # (+0.0 at every selected position, also where x - x is NaN)
         want_m[[oracle.element_of(d, i, int(j)) for j in idx]] = 0.0
     L.same(m, want_m)
+
+
+@pytest.mark.parametrize("k, R", [(264, 3), (64, 9)])
+@pytest.mark.parametrize("sizes", [[679, 1], [681], [1025, 339], [1365]])
+def test_chunks_per_workgroup(oracle, k, R, sizes):
+    """Aggregates of lists on both sides of where workgroups change between one chunk and four, at a density and a worker count that several
+    waves per chunk do not serve."""
+    from paper_2508_15706_amd import binding as sl
+    descs, n = [], 0
+    for c in sizes:
+        descs.append((64, 64 * c, n, 1))
+        n += 4096 * c
+    rng = np.random.default_rng(n + k)
+    plan = sl.sl_plan_create(descs, k)
+    pays = [oracle.compress(descs, k, np.zeros(n, np.float32), rng.normal(0, 1e-3, n).astype(np.float32), 0.0, ef_frozen=True) for _ in range(3)]
+    theta0, m0 = rng.normal(0, 0.02, n).astype(np.float32), rng.normal(0, 1e-3, n).astype(np.float32)
+    cuda = lambda x: torch.from_numpy(x.copy()).cuda()  # noqa: E731
+    coded = [oracle.rice_encode(descs, k, p) for p in pays]
+    gp, gc, sizes_ = [cuda(p) for p in pays] * 3, [cuda(p) for p in coded] * 3, [p.size for p in coded] * 3
+    same = lambda got, want: np.testing.assert_array_equal(got.cpu().numpy().view(np.uint32), want.view(np.uint32))  # noqa: E731
+    want, want_n, want_m = theta0.copy(), theta0.copy(), m0.copy()
+    oracle.decompress_avg_apply(descs, k, want, (pays * 3)[:R], 0.8)
+    oracle.decompress_avg_apply_nesterov_b(descs, k, 2, want_n, want_m, (pays * 3)[:R], 0.8, 0.9)
+    t = cuda(theta0)
+    sl.sl_decompress_avg_apply(plan, t, gp[:R], 0.8)
+    same(t, want)
+    t = cuda(theta0)
+    sl.sl_decompress_avg_apply_coded(plan, t, gc[:R], sizes_[:R], 0.8)
+    same(t, want)
+    t, m = cuda(theta0), cuda(m0)
+    sl.sl_decompress_avg_apply_nesterov(plan, t, m, gp[:R], 0.8, 0.9)
+    same(t, want_n), same(m, want_m)
+    t, m = cuda(theta0), cuda(m0)
+    sl.sl_decompress_avg_apply_nesterov_coded(plan, t, m, gc[:R], sizes_[:R], 0.8, 0.9)
+    same(t, want_n), same(m, want_m)
