@@ -1,6 +1,6 @@
 """Partial chunks - rows that end at every place inside a lane's four columns, narrow matrices with few lanes
-that hold elements (the selection's pruning then needs more groups per lane), run tails of many lengths,
-all-zero chunks - against the oracle: compress (eager, deferred, from
+that hold elements (the selection's bound is then poor), run tails of many lengths,
+all-zero chunks - on short lists, which take several waves per chunk (test_gpu_wave_per_chunk.py has the other form), against the oracle: compress (eager, deferred, from
 parameters), Sub-k and the plain aggregate with and without momentum."""
 import numpy as np
 import pytest
@@ -80,9 +80,8 @@ def test_partial_chunks(oracle, k, zero):
 
 @pytest.mark.parametrize("k", [4, 12, 32, 48, 64, 100, 128, 200, 256, 300, 512])
 def test_pruning_groups_of_partial_chunks(oracle, k):
-    """Widths and tail lengths on both sides of every place where the number of groups per lane of a partial
-    chunk changes: as many lanes with elements as give just under and just over 3k/2 maxima, one element per
-    group, fewer elements than 16 groups per lane can spread."""
+    """Widths and tail lengths around the numbers of maxima that bound the threshold of a partial chunk: as many lanes with elements as
+    give just under and just over 3k/2 maxima, one element per group, fewer elements than 16 groups per lane can spread."""
     from paper_2508_15706_amd import binding as sl
     descs, off = [], 0
     shapes = [(r, c, 1) for r in (64, 66, 67, 80, 96, 192) for c in (4, 8, 12, 20, 24, 28, 36, 44, 52, 60, 63, 100)]

@@ -1,4 +1,5 @@
-"""Selections of more than 512 of a chunk's elements, whose threshold is bracketed by a sample on lists of 3328 chunks and more: values for which the bracket holds,
+"""Selections of more than 512 of a chunk's elements, whose threshold is bracketed by a sample on lists of 3328 chunks and more, and with several
+waves per chunk on short ones: values for which the bracket holds,
 misses (elements outside the sample's registers differ from those in it) or overflows (uneven columns, ties), partial chunks, the first and the last densities.
 Top-k removed in place and the payload, against the oracle."""
 import numpy as np

@@ -1,5 +1,6 @@
 """Lists on both sides of the rules for short ones: statistics found by the code kernel itself (tensors of up to 1024 chunks,
-lists of up to 8192, at most two tensors in any code wave), one chunk per workgroup up to 680 chunks and from 1025 to 1364.  Payload, coded bytes, e and both
+lists of up to 8192, at most two tensors in any code wave), and the lengths where workgroups of a wave-per-chunk aggregate change between one chunk and four (680, 1025, 1364;
+those aggregates themselves: test_gpu_wave_per_chunk.py).  Payload, coded bytes, e and both
 aggregates against the oracle."""
 import numpy as np
 import pytest
