@@ -612,19 +612,24 @@ __global__ void SL_SELECT_BOUNDS k_select(SelectArgs A)
         // as much as the registers hold next to the results.
         constexpr int PA = SUBK ? 8 : 4;
         const bool need_e = SUBK || !A.frozen;
+        // (A lane of its own for the compiler: what the loads' places need is then formed here and not ahead of the branch, where it costs full chunks
+        // scalar registers.  Together with the outputs' arguments, below: 10,240 full chunks, k = 128, deferred 115.6 us without, 114.9 with it, 178M list, pending
+        // 380.2 / 377.3.)
+        int part_lane = lane;
+        asm volatile("" : "+v"(part_lane));
 #pragma unroll
         for (int h = 0; h < 16 / PA; ++h) {
             sl_f4 pe[PA], pd[PA], pt[PARAMS ? PA : 1];
-            if (need_e) sl_partial_request<KEEP>(A.e, d, PA * h, lane, pe);
-            if constexpr (!SUBK) sl_partial_request<KEEP>(A.delta, d, PA * h, lane, pd);
-            if constexpr (PARAMS) sl_partial_request<KEEP>(A.theta_local, d, PA * h, lane, pt);
+            if (need_e) sl_partial_request<KEEP>(A.e, d, PA * h, part_lane, pe);
+            if constexpr (!SUBK) sl_partial_request<KEEP>(A.delta, d, PA * h, part_lane, pd);
+            if constexpr (PARAMS) sl_partial_request<KEEP>(A.theta_local, d, PA * h, part_lane, pt);
             if constexpr (!SUBK) {
                 if (pend && (PA * h) % 8 == 0) pend_half(PA * h / 8);
             }
-            if (need_e) sl_partial_place(d, PA * h, lane, pe);
-            if constexpr (!SUBK) sl_partial_place(d, PA * h, lane, pd);
+            if (need_e) sl_partial_place(d, PA * h, part_lane, pe);
+            if constexpr (!SUBK) sl_partial_place(d, PA * h, part_lane, pd);
             if constexpr (PARAMS) {
-                sl_partial_place(d, PA * h, lane, pt);
+                sl_partial_place(d, PA * h, part_lane, pt);
 #pragma unroll
                 for (int u = 0; u < PA; ++u) pd[u] = pd[u] - pt[u];
             }
@@ -810,8 +815,7 @@ __global__ void SL_SELECT_BOUNDS k_select(SelectArgs A)
 
     // ---------------------------------------------------------------- outputs
     // (What only they need of the arguments is read here: read at the start it costs scalar registers all along, and full chunks reload what
-    // was spilled for it.  Error feedback frozen, 25,600 chunks, this kernel, us: fp32 values, k = 64 108.9 -> 103.1, 4 bits 107.5 -> 102.2, k = 256 139.4 -> 134.6; 2 bits, k =
-    // 128 112.1 -> 109.6.  The struct is the kernel's only parameter.)
+    // was spilled for it.  Error feedback frozen, 25,600 chunks, this kernel, us: fp32 values, k = 64 108.9 -> 103.2, 4 bits 107.5 -> 101.7, k = 256 139.4 -> 132.9.  The struct is the kernel's only parameter.)
     typedef const SelectArgs __attribute__((address_space(4))) *ArgsPtr;
     ArgsPtr late = (ArgsPtr)__builtin_amdgcn_kernarg_segment_ptr();
     asm volatile("" : "+s"(late));
