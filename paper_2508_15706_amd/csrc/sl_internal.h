@@ -158,11 +158,11 @@ __host__ __device__ inline long long sl_lut_off(const SlChunkDesc &d, int hdr_by
     return d.rec_off - hdr_bytes - (long long)d.local_chunk * rec_bytes;
 }
 
-// Chunks (waves) per workgroup of the aggregates with a wave per chunk: four adjacent ones, so that a workgroup streams
+// Chunks (waves) per workgroup of the aggregates, and of the selection up to k = 128, with a wave per chunk: four adjacent ones, so that a workgroup streams
 // 1 KB of every matrix row it touches; but one on lists so short that workgroups of four, dealt to the compute units in one turn or two,
 // would leave a third of the places without any.  Four / one, us, one call on buffers that no cache holds (768-column matrices): plain, k = 512, R = 4
 // 504 chunks 11.7 / 11.1, 1020 13.2 / 13.0, 1536 15.0 / 15.6, 2040 17.3 / 18.1, 4092 33.2 / 34.4; k = 64, R = 16 504 12.2 / 11.9, 2040 16.8 / 17.3, 4092 32.4 / 34.2; coded, k =
-// 256, R = 4 504 12.3 / 11.6, 1272 15.2 / 15.0, 3072 25.5 / 25.6.  (Rows of 1024 columns want one up to 3072 chunks, plain, k = 64, R = 16 1024 16.7 / 13.7, 2048 22.1 /
+// 256, R = 4 504 12.3 / 11.6, 1272 15.2 / 15.0, 3072 25.5 / 25.6.  Sub-k, k = 64 1360 18.4 / 18.0, k = 16 15.7 / 15.5 (1024 columns 19.7 / 18.3, 17.0 / 15.5).  (Rows of 1024 columns want one up to 3072 chunks, plain, k = 64, R = 16 1024 16.7 / 13.7, 2048 22.1 /
 // 17.2; those of 64, 1088 and 2048 do not.)  Not where one chunk in 32 or more is partial: rows then begin anywhere in a line of memory, and the neighbours
 // that share a line should share an L2 (coded, k = 64, R = 8, 594 chunks of a 530-column matrix 17.5 / 18.7; plain, k = 256, 1024 of 1001 columns 19.3 / 21.3).
 #define SL_COMPUTE_UNITS 256
@@ -199,23 +199,24 @@ inline bool sl_select_unaligned(const sl_plan *p, int streams, bool update_follo
 // Waves per chunk of kernel A: several (sl_select_group.hip) on lists so short that the chain of a wave's instructions is longer than the
 // stream, one where the compute units are full without.  The work that each wave of a chunk repeats grows with k, and the less a call moves
 // the sooner one wave is enough: `streams` is 1 where it reads one arena and writes none or single entries (error feedback frozen, Sub-k), 2 for the
-// accumulate with the error update deferred, 3 where the update follows or the pseudo-gradient is formed from parameters.  One wave and the number
-// taken here, us, full chunks, each call on buffers that no cache holds (which length gains depends on the rows' stride: matrices of 64 rows, others
-// named): deferred, k = 64 256 chunks 21.1 -> 16.7, 512 22.4 -> 19.0, 1024 25.1 -> 24.1, 2048 34.0 -> 34.7, 6144 70.4 -> 69.0 (1024 columns 2048 41.2 ->
-// 36.3, 6144 77.6 -> 72.9; runs 74.1 -> 69.7), k = 256 1024 28.7 -> 29.0 (32.4 -> 29.2), k = 1024 1024 44.3 -> 36.8, 2048 55.8 -> 55.2; with the update k = 64 512 26.6 ->
-// 23.1, 2048 44.6 -> 41.5, 6144 94.4 -> 88.7, k = 256 2048 55.2 -> 54.1, k = 512 768 41.5 -> 41.1, k = 1024 2048 82.1 -> 77.2, 3072 100.1 -> 99.1; frozen k = 64 512 18.5 -> 17.0,
-// 1024 20.0 -> 19.4, k = 256 512 22.1 -> 20.8, k = 1024 1024 39.1 -> 31.7; Sub-k, k = 64 512 10.9 -> 9.4, 1024 13.3 -> 12.6, k = 1024 1024 32.2 -> 26.1.  Beyond the lines:
-// deferred k = 256 2048 38.6 -> 42.1, k = 512 1024 33.0 -> 34.3, k = 1024 3072 69.3 -> 73.5, coded 86.2 -> 94.0; with the update k = 512 1536 54.7 -> 58.0; frozen k = 64 2048 23.4 -> 26.2,
-// 6144 37.6 -> 47.8, k = 256 1024 23.6 -> 24.5, k = 1024 2048 44.5 -> 49.0; Sub-k, k = 64 1536 16.6 -> 17.4, 4096 28.2 -> 33.0, k = 4 4096 18.3 -> 24.0, k = 512 768
-// 21.5 -> 22.1.  Eight waves against four (deferred, k = 64): 256 chunks 16.9 -> 16.1, 512 18.8 -> 19.0, 768 20.8 -> 21.3.  Partial chunks gain more: 900 of 530 columns,
-// k = 32 37.4 -> 27.3; 1155 of 67, k = 64 55.4 -> 30.3.
+// accumulate with the error update deferred, 3 where the update follows or the pseudo-gradient is formed from parameters.  A workgroup per chunk goes in turns over
+// the compute units, so the lines lie at multiples of 256.  One wave / several, us, one call on buffers that no cache holds, full chunks of 1024 columns, of 768:
+// frozen k = 64 512 18.5 / 17.0, 1280 32.9 / 30.2, 32.4 / 30.3, 1360 32.9 / 34.0, 32.8 / 34.0; k = 136 1280 35.8 / 33.7, 34.8 / 33.7; k = 256 768 31.0 / 29.4, 31.4 / 29.4; k = 264 768
+// 35.7 / 31.7, 35.2 / 31.6; k = 1024 1280 54.2 / 51.8, 53.2 / 51.8, 1536 55.0 / 54.3, 54.0 / 54.1, 1792 56.6 / 57.6, 55.8 / 57.0; Sub-k k = 64 1280 19.4 / 16.1, 18.2 / 16.1, 1360
+// 19.7 / 19.3, 18.4 / 18.3, 2048 22.2 / 22.6, 21.0 / 22.1; k = 256 768 20.1 / 18.8, 19.4 / 18.9, 896 20.6 / 20.6, 20.0 / 20.8; k = 512 768 25.3 / 23.8, 24.8 / 24.2; k = 1024 1280 37.1 / 36.2,
+// 37.4 / 36.1, 1536 38.4 / 38.5.  Deferred k = 136 1536 45.5 / 42.8, 43.8 / 42.7, 1792 48.0 / 45.7, 44.8 / 46.2; k = 256 1280 46.4 / 39.8, 43.4 / 40.0, 1536 46.8 / 45.4, 44.2 / 45.6;
+// k = 1024 2304 79.5 / 70.8, 73.7 / 71.2, 2560 80.3 / 75.0, 74.6 / 74.1, 2816 83.7 / 77.9, 76.1 / 77.7.  Matrices of 64 rows: deferred, k = 64 256 21.1 / 16.7, 1024 25.1 / 24.1, 2048 34.0 / 34.7,
+// 6144 70.4 / 69.0 (1024 columns 2048 41.2 / 36.3, 6144 77.6 / 72.9); k = 512 1024 33.0 / 34.3; with the update k = 64 512 26.6 / 23.1, 2048 44.6 / 41.5, 6144 94.4 / 88.7, k = 256 2048 55.2 / 54.1, k = 512 768
+// 41.5 / 41.1, 1536 54.7 / 58.0, k = 1024 2048 82.1 / 77.2, 3072 100.1 / 99.1.  Eight waves against four (deferred, k = 64): 256 chunks 16.9 -> 16.1, 512 18.8 -> 19.0, 768 20.8 -> 21.3.
+// Partial chunks gain more: 900 of 530 columns, k = 32 37.4 / 27.3; 1155 of 67, k = 64 55.4 / 30.3.
 inline int sl_select_waves(int64_t n_chunks, int k, int streams)
 {
     if (n_chunks <= 512) return 8;
-    const int64_t upto = k <= 128 ? (streams == 1 ? 1024 : 6144)
-                         : k <= 256 ? (streams == 1 ? 512 : streams == 2 ? 1024 : 2048)
-                         : k <= 512 ? (streams == 1 ? 512 : 768)
-                                    : streams == 1 ? 1024 : streams == 2 && k < 2048 ? 2048 : 3072;
+    const int64_t upto = streams == 1 ? (k <= 160 || k > 512 ? 1280 : 768)
+                         : k <= 128   ? 6144
+                         : k <= 256   ? (streams == 3 ? 2048 : k <= 160 ? 1536 : 1280)
+                         : k <= 512   ? 768
+                                      : streams == 2 && k < 2048 ? 2560 : 3072;
     return n_chunks <= upto ? 4 : 1;
 }
 

@@ -73,7 +73,7 @@ static int launch_select(const sl_plan *p, float *e, const float *delta, const f
     const bool unaligned = sl_select_unaligned(p, streams, update_follows, theta_local != nullptr);
     if (waves > 1) return slk_select_group(A, sub_only, waves, unaligned && p->n_chunks > 2048, st);
     // (one chunk per workgroup where the LDS of four does not fit)
-    const int wpb = 4 * (size_t)A.lds_per_wave > 65536 ? 1 : random && k <= 128 ? sl_chunks_per_group(p) : 4;
+    const int wpb = 4 * (size_t)A.lds_per_wave > 65536 ? 1 : k <= 128 ? sl_chunks_per_group(p) : 4;
     const dim3 grid((unsigned)((p->n_chunks + wpb - 1) / wpb)), block(64 * wpb);
     A.order = sl_order(p, grid.x);
     const size_t lds = (size_t)A.lds_per_wave * wpb;

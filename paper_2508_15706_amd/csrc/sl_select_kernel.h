@@ -73,7 +73,7 @@ SL_DEV unsigned fmix32(unsigned h)
 // counts the keys above the bracket and lets every lane put its own keys inside it (six on average) into a column of `list`;
 // T is found among those.  A dozen passes over the registers, which this replaces, are half of the instructions (24,000 chunks, sl_compress: k = 520 405 -> 354 us, 1024 368 -> 322, 2048 591 -> 518, 4000 954 -> 903; 123,505 chunks with heavy tails, k = 1024, this kernel 1505 -> 1240).
 // Not on lists below SL_SAMPLE_FROM chunks, where a wave has its SIMD almost to itself and the sample's chain of steps is
-// longer than the passes it saves.  (The lists that come here and not to sl_select_group.hip: from 1025 chunks where error feedback is frozen, and Sub-k, from 2049 or
+// longer than the passes it saves.  (The lists that come here and not to sl_select_group.hip: from 1281 chunks where error feedback is frozen, and Sub-k, from 2561 or
 // 3073 otherwise.  Two stages / sample, us, calls on buffers that no cache holds: frozen, k = 520 1280 chunks 52.1 / 56.0, 2048 55.1 / 59.1, 3072 65.1 / 64.9; k = 1024 1280
 // 53.7 / 56.8, 2048 57.2 / 60.3, 3072 66.2 / 69.9; k = 2048 2048 63.6 / 67.1, 2560 91.4 / 86.6; deferred, k = 1024 2560 77.6 / 80.7, 3072 82.1 / 85.2; eager 3840 118.0 / 114.6,
 // 8192 201 / 190.  From 3073 to the line the sample is ahead already: frozen, k = 1024 3200 83.7 / 70.0, deferred 99.3 / 96.5.)
