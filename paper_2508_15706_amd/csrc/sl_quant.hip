@@ -132,6 +132,8 @@ __device__ void block_tree_sums(const double *const (&leaf)[NS], long long n, Re
 // 98.4 / 94.0, 25,600 127.2 / 117.3, 140.3 / 132.1; one of 12,288 beside 60 of 768 233.4 / 232.8, 262.2 / 261.9, one of 25,600 beside 60 of 512
 // 234.8 / 226.4, 260.9 / 253.9; 1.8B list, two of 25,152 chunks, 1600 / 1596, 1775 / 1771, 1605 and 1796 where the launch went over all groups
 // of the list; MoE list, one of 12,576, 605.4 / 606.5, 693.5 / 691.9.)
+// B and D are instantiations of their own where a list has pieces (PIECES): with the choice made in one kernel lists without any were up to a microsecond slower
+// (sl_compress, frozen, us, one kernel / two: 10,240 chunks 61.6 / 60.9, 178M list, 4 bits 192.2 / 191.3, 700 tensors of 3 chunks, 4 bits 84.3 / 79.5).
 struct RedPieces {
     double *sum;            // [columns][stride]; null: no tensor of the list is split
     unsigned *cnt;          // (D only)
@@ -261,6 +263,7 @@ SL_DEV SlTensorStat wave_stats(const SlTensorDev &td, const double *leafA, long 
 // One workgroup per tensor: its statistics.  With the coded format, up to SL_PLACE_SHARED_UPTO, further
 // workgroups take the first placement step (independent of the statistics, and a launch of its
 // own would cost more than its work).
+template <bool PIECES>
 __global__ void __launch_bounds__(RED_THREADS, 8)
 k_tensor_stats(const SlTensorDev *tensors, int n_tensors, const double *leafA, long long n_chunks_total, int k,
                SlTensorStat *tstat, SlCodedArgs C, RedPieces P)
@@ -272,7 +275,7 @@ k_tensor_stats(const SlTensorDev *tensors, int n_tensors, const double *leafA, l
     }
     const SlTensorDev td = tensors[blockIdx.x];
     double S[2];
-    if (P.split(td)) {
+    if (PIECES && P.split(td)) {
         const double *const piece = P.sum + td.piece0;
         const double *const both[2] = {piece, piece + P.stride};
         block_piece_sums<2>(both, td.n_chunks, sh, S);
@@ -620,7 +623,7 @@ codes_kernel codes_for(int bits, int log_lpc)
 // One workgroup per (tensor, bin): fixed-tree sum of the bin's leaves, integer count, centroid ->
 // LUT[b] in the tensor block's header.  With the placement steps in these launches (PLACE) further
 // workgroups take the last of them, `place_waves` groups each.
-template <bool PLACE>
+template <bool PLACE, bool PIECES>
 __global__ void __launch_bounds__(RED_THREADS, 8)
 k_tensor_lut(const SlTensorDev *tensors, int n_tensors, const double *leafC, const unsigned *cnt,
              long long n_chunks_total, int hdr_bytes, int rec_bytes, int nbins, unsigned char *payload,
@@ -638,7 +641,7 @@ k_tensor_lut(const SlTensorDev *tensors, int n_tensors, const double *leafC, con
     }
     const SlTensorDev &td = tensors[blockIdx.x];             // (read again behind the sums: it would be kept in scratch memory across them)
     unsigned long long part = 0;
-    const bool split = P.split(td);
+    const bool split = PIECES && P.split(td);
     const long long piece = b * P.stride + td.piece0;
     const unsigned *cb = split ? P.cnt + piece : cnt + b * n_chunks_total + td.chunk0;
     const long long counts = split ? (td.n_chunks + SL_PIECE - 1) / SL_PIECE : td.n_chunks;
@@ -823,7 +826,7 @@ int slk_quantize(const sl_plan *p, float *e, int skip_residual, unsigned char *p
         if ((rc = check_launch())) return rc;
     }
     if (!few) {
-        hipLaunchKernelGGL(k_tensor_stats, dim3(p->n_tensors + scan_blocks), dim3(RED_THREADS), 0, st, p->d_tensors, p->n_tensors, leafA,
+        hipLaunchKernelGGL(split ? k_tensor_stats<true> : k_tensor_stats<false>, dim3(p->n_tensors + scan_blocks), dim3(RED_THREADS), 0, st, p->d_tensors, p->n_tensors, leafA,
                             (long long)p->n_chunks, k, tstat, placing, PB);
         if ((rc = check_launch())) return rc;
     }
@@ -862,7 +865,8 @@ int slk_quantize(const sl_plan *p, float *e, int skip_residual, unsigned char *p
     const int place_waves = shared ? (int)std::max<size_t>(1, std::min<size_t>(RED_WAVES, 49152 / per_wave_lds)) : 0;
     const long long per_column = (long long)place_waves * nbins;      // groups that one column of workgroups takes
     const long long place_columns = shared ? (p->n_groups + per_column - 1) / per_column : 0;
-    hipLaunchKernelGGL(shared ? k_tensor_lut<true> : k_tensor_lut<false>, dim3((unsigned)(p->n_tensors + place_columns), nbins), dim3(RED_THREADS),
+    const auto lut = split ? (shared ? k_tensor_lut<true, true> : k_tensor_lut<false, true>) : (shared ? k_tensor_lut<true, false> : k_tensor_lut<false, false>);
+    hipLaunchKernelGGL(lut, dim3((unsigned)(p->n_tensors + place_columns), nbins), dim3(RED_THREADS),
                        place_waves * per_wave_lds, st, p->d_tensors, p->n_tensors, leafC, cnt, (long long)p->n_chunks,
                        p->hdr_bytes, p->rec_bytes, nbins, payload, coded, p->cg.cfix, placing, place_waves, PD);
     if ((rc = check_launch())) return rc;
