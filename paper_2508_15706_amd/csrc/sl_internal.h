@@ -208,15 +208,17 @@ inline bool sl_select_unaligned(const sl_plan *p, int streams, bool update_follo
 // k = 1024 2304 79.5 / 70.8, 73.7 / 71.2, 2560 80.3 / 75.0, 74.6 / 74.1, 2816 83.7 / 77.9, 76.1 / 77.7.  Matrices of 64 rows: deferred, k = 64 256 21.1 / 16.7, 1024 25.1 / 24.1, 2048 34.0 / 34.7,
 // 6144 70.4 / 69.0 (1024 columns 2048 41.2 / 36.3, 6144 77.6 / 72.9); k = 512 1024 33.0 / 34.3; with the update k = 64 512 26.6 / 23.1, 2048 44.6 / 41.5, 6144 94.4 / 88.7, k = 256 2048 55.2 / 54.1, k = 512 768
 // 41.5 / 41.1, 1536 54.7 / 58.0, k = 1024 2048 82.1 / 77.2, 3072 100.1 / 99.1.  Eight waves against four (deferred, k = 64): 256 chunks 16.9 -> 16.1, 512 18.8 -> 19.0, 768 20.8 -> 21.3.
-// Partial chunks gain more: 900 of 530 columns, k = 32 37.4 / 27.3; 1155 of 67, k = 64 55.4 / 30.3.
-inline int sl_select_waves(int64_t n_chunks, int k, int streams)
+// Above k = 1928 the LDS of a compute unit holds two workgroups of the one-wave form, not three, which a list of 2049 chunks and more feels: frozen, k = 2048 2048 chunks
+// 64.2 / 66.6, 2220 87.1 / 74.9, Sub-k 2880 62.2 / 56.3.  Lists with partial chunks (`ragged`: one chunk in 32 or more) gain whatever the call reads, narrow tiles most: columns 200, frozen, k = 256 780 49.6 / 30.6, Sub-k
+// 916 37.2 / 20.7, deferred, k = 200 1360 61.0 / 45.5; columns 1001, frozen, k = 32 3120 40.5 / 37.5; 900 of 530 columns, k = 32 37.4 / 27.3; 1155 of 67, k = 64 55.4 / 30.3.
+inline int sl_select_waves(int64_t n_chunks, int k, int streams, bool ragged)
 {
     if (n_chunks <= 512) return 8;
-    const int64_t upto = streams == 1 ? (k <= 160 || k > 512 ? 1280 : 768)
-                         : k <= 128   ? 6144
-                         : k <= 256   ? (streams == 3 ? 2048 : k <= 160 ? 1536 : 1280)
-                         : k <= 512   ? 768
-                                      : streams == 2 && k < 2048 ? 2560 : 3072;
+    int64_t upto = k <= 128 ? 6144 : k <= 256 ? 2048 : k <= 512 ? 768 : 3072;
+    if (!ragged && k <= 1928) {
+        if (streams == 1) upto = k <= 160 || k > 512 ? 1280 : 768;
+        else if (streams == 2) upto = k <= 128 ? 6144 : k <= 256 ? 1536 : k <= 512 ? 768 : 2560;
+    }
     return n_chunks <= upto ? 4 : 1;
 }
 

@@ -66,7 +66,7 @@ static int launch_select(const sl_plan *p, float *e, const float *delta, const f
     A.uvec = (sub_only || !coded) ? nullptr : reinterpret_cast<unsigned *>(ws + p->ws_uvec);
     A.qsum = (sub_only || !coded) ? nullptr : reinterpret_cast<unsigned short *>(ws + p->ws_qsum);
     const int streams = sub_only || frozen ? 1 : update_follows || theta_local ? 3 : 2;
-    const int waves = random ? 1 : sl_select_waves(p->n_chunks, k, streams);
+    const int waves = random ? 1 : sl_select_waves(p->n_chunks, k, streams, p->n_partial * 32 >= p->n_chunks);
     // Without the streaming hint: unaligned rows, and error buffers that the caches still hold when the update follows (sl_update_kept).  With several
     // waves per chunk unaligned rows gain from it on longer lists only (deferred, k = 32: 4000 chunks of 1001 columns 70.3 / 60.2, 900 of 530 29.4 / 30.7).
     const bool keep = update_follows && sl_update_kept(p->n_chunks, k, theta_local != nullptr);

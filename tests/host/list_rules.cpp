@@ -16,15 +16,16 @@ static void expect(const char *what, long long n, int k, int got, int want)
 // waves per chunk of the selection; streams: 1 frozen or Sub-k, 2 deferred, 3 with the update or from parameters
 static void selection()
 {
-    const struct { int n, k, streams, want; } rows[] = {
-        {64, 64, 1, 8}, {512, 4096, 1, 8}, {512, 64, 2, 8}, {512, 256, 3, 8},
-        {1280, 64, 1, 4}, {1281, 64, 1, 1}, {1280, 16, 1, 4}, {2048, 16, 1, 1}, {1280, 136, 1, 4}, {768, 256, 1, 4}, {769, 256, 1, 1}, {768, 512, 1, 4}, {1024, 512, 1, 1},
-        {1280, 1024, 1, 4}, {1281, 1024, 1, 1}, {2048, 4096, 1, 1},
-        {6144, 64, 2, 4}, {6145, 64, 2, 1}, {1536, 136, 2, 4}, {1537, 136, 2, 1}, {1280, 256, 2, 4}, {1281, 256, 2, 1}, {768, 512, 2, 4}, {1024, 512, 2, 1},
-        {2560, 1024, 2, 4}, {2561, 520, 2, 1}, {3072, 2048, 2, 4}, {3073, 4096, 2, 1},
-        {6144, 128, 3, 4}, {6145, 4, 3, 1}, {2048, 256, 3, 4}, {2049, 136, 3, 1}, {768, 264, 3, 4}, {769, 512, 3, 1}, {3072, 1024, 3, 4}, {3073, 1024, 3, 1},
+    const struct { int n, k, streams, ragged, want; } rows[] = {
+        {64, 64, 1, 0, 8}, {512, 4096, 1, 0, 8}, {512, 64, 2, 0, 8}, {512, 256, 3, 0, 8}, {512, 256, 1, 1, 8},
+        {1280, 64, 1, 0, 4}, {1281, 64, 1, 0, 1}, {1280, 16, 1, 0, 4}, {2048, 16, 1, 0, 1}, {1280, 136, 1, 0, 4}, {768, 256, 1, 0, 4}, {769, 256, 1, 0, 1}, {768, 512, 1, 0, 4}, {1024, 512, 1, 0, 1},
+        {1280, 1024, 1, 0, 4}, {1281, 1024, 1, 0, 1}, {2220, 2048, 1, 0, 4}, {3073, 4096, 1, 0, 1},
+        {6144, 64, 2, 0, 4}, {6145, 64, 2, 0, 1}, {1536, 136, 2, 0, 4}, {1537, 136, 2, 0, 1}, {1536, 256, 2, 0, 4}, {1537, 256, 2, 0, 1}, {768, 512, 2, 0, 4}, {1024, 512, 2, 0, 1},
+        {2560, 1024, 2, 0, 4}, {2561, 520, 2, 0, 1}, {3072, 2048, 2, 0, 4}, {3073, 4096, 2, 0, 1},
+        {6144, 128, 3, 0, 4}, {6145, 4, 3, 0, 1}, {2048, 256, 3, 0, 4}, {2049, 136, 3, 0, 1}, {768, 264, 3, 0, 4}, {769, 512, 3, 0, 1}, {3072, 1024, 3, 0, 4}, {3073, 1024, 3, 0, 1},
+        {3120, 32, 1, 1, 4}, {6145, 32, 1, 1, 1}, {1360, 200, 2, 1, 4}, {916, 256, 1, 1, 4}, {2049, 256, 2, 1, 1}, {769, 512, 1, 1, 1}, {3072, 1024, 2, 1, 4},
     };
-    for (const auto &r : rows) expect("selection", r.n, r.k, sl_select_waves(r.n, r.k, r.streams), r.want);
+    for (const auto &r : rows) expect(r.ragged ? "selection, ragged" : "selection", r.n, r.k, sl_select_waves(r.n, r.k, r.streams, r.ragged != 0), r.want);
 }
 
 // the eager accumulate without the streaming hint
